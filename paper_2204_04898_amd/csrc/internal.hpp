@@ -171,29 +171,29 @@ hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t
 
 // ---- variants (variants.hip) ----
 struct VarWs {
-    uint64_t* hash;      // [C] sequence hash per case, then sorted (ping-pong with hash2)
+    uint64_t* hash;      // claim words of the sequence table, two per case: on into hash2
     uint64_t* hash2;
-    uint32_t* idx;       // [C] case index carried through the hash sort (ping-pong with idx2)
-    uint32_t* idx2;
-    uint32_t* hist;      // radix histograms
+    uint32_t* idx;       // [C] representative of each case's variant
+    uint32_t* idx2;      // [C] cases of a representative's variant, 0 for other cases
+    uint32_t* hist;      // [256][tiles] count digits of the representatives
     uint32_t* rowsum;    // [256]
-    uint32_t* flag;      // [C] group start flags in hash order
-    uint32_t* sid;       // [C] exclusive count of group starts
-    uint32_t* sstart;    // [V+1] group start positions
-    uint32_t* repflag;   // [C] 1 for representative cases
-    uint32_t* rrank;     // [C] representative-order index of representative cases
-    uint2* vcr;          // [V] (cases, representative case index), representative order
-    uint32_t* cvar;      // [C] representative-order variant of each case
-    uint32_t* vkey;      // [V] ordering keys (ping-pong with vkey2)
-    uint32_t* vkey2;
-    uint32_t* vidx;      // [V] representative-order ids (ping-pong with vidx2)
+    uint32_t* flag;      // (spare)
+    uint32_t* sid;       // (spare)
+    uint32_t* sstart;    // [V] representative case in final order
+    uint32_t* repflag;   // [C] by claiming case: members besides it
+    uint32_t* rrank;     // [C] by claiming case: smallest member, if smaller than it
+    uint2* vcr;          // [V] (cases, representative) by count digit, then case
+    uint32_t* cvar;      // [C] claiming case of each case's table slot
+    uint32_t* vkey;      // the variants of 255 cases or more in final order: representative,
+    uint32_t* vkey2;     //   cases
+    uint32_t* vidx;      // their other buffers while they are sorted in byte passes
     uint32_t* vidx2;
-    uint32_t* fid;       // [V] final id of each representative-order variant
+    uint32_t* fid;       // [C] by representative: final id of its variant
     uint32_t* lens;      // [V] sequence lengths in final order
-    uint32_t* part32;    // scan partials
-    int64_t* part64;
-    int64_t* scal;       // [0] C, [1] V, [2] total sequence length
-    uint32_t* u32scal;   // [0] collision flag, [1] V
+    uint32_t* part32;    // (spare)
+    int64_t* part64;     // [dev::kScanGrid] total length of each block's variants
+    int64_t* scal;       // [0] C, [1] V, [2] variants of 255 cases or more
+    uint32_t* u32scal;   // (spare)
 };
 VarWs var_ws_layout(Bump& b, int64_t n);
 struct VarOutDev {

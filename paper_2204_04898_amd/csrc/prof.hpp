@@ -19,8 +19,8 @@ enum ProfId {
     P_DFG_AGG,
     P_DFG_REDUCE,
     P_VAR_HASH,
-    P_VAR_SORT,
-    P_VAR_GROUP,
+    P_VAR_SORT,    // no longer timed: kept so that stage numbers stay
+    P_VAR_GROUP,   // likewise
     P_VAR_ORDER,
     P_VAR_EMIT,
     P_VIEW_PLAN,

@@ -2,22 +2,29 @@
 // their activity sequence, an aggregation of the per-case aggregation; the
 // cases dataframe carries numbers from which each case's variant follows).
 //
-// Grouping is exact: a 64-bit hash of each case's sequence (the numeric
-// feature) only brings candidates together; every equal-hash neighbour pair
-// is compared element by element, and a run of equal hashes holding more
-// than one sequence is regrouped exactly.  Variant ids follow (count desc,
+// Grouping is exact: cases enter an open-addressing table keyed by a 64-bit
+// hash of their sequence, and a case joins a slot only if its sequence equals
+// that of the case that claimed it, element by element (the sequences are
+// input, so nothing has to be published with the claim); different sequences
+// with one hash take different slots.  Variant ids follow (count desc,
 // representative asc) with the representative the smallest case id.
 //
-//   k_var_hash       per case: sum over positions of mix(position, activity), mixed
-//                    with the length (wave-cooperative, coalesced)
-//   radix (64 bits)  cases by hash; stable, so equal hashes keep case order
-//   k_var_verify     neighbour sequences compared exactly -> group starts
-//   k_var_fix        only after a true collision: exact regrouping of a run
-//   scans            group ids; representatives (first member = smallest id)
-//                    enumerated in case order = representative order
-//   radix (count)    stable sort by descending count -> final ids
-//   k_var_emit       counts, lengths, representatives, CSR sequences, ids
-// All sizes (cases, variants) stay on the device; nothing synchronises.
+//   k_var_clear    the table and the per-case counters
+//   k_var_group    per case: sum over positions of mix(position, activity), mixed
+//                  with the length (wave-cooperative, coalesced); equal hashes
+//                  of a wave's 64 cases meet in LDS, one lane of each enters
+//                  the table: claiming case, further members, smallest member
+//   k_var_reps     representatives and their counts, in case order; histogram
+//                  of the count digit (255 - min(count, 255)) per tile
+//   scan           of the digit rows
+//   k_var_order    representatives to their place by (digit, case): the final
+//                  order, except among the variants of 255 cases or more
+//   k_var_top      those by descending count
+//   k_var_ids      counts, lengths, representatives in final order
+//   k_var_emit     CSR sequences, ids of the cases
+// 8 launches (sorting the cases by hash, then the variants by count, took 46,
+// which was most of a call on a small log).  All sizes (cases, variants) stay
+// on the device; nothing synchronises.
 #include "common.hpp"
 #include "devsort.hpp"
 #include "internal.hpp"
@@ -75,13 +82,27 @@ __device__ bool same_seq(const int32_t* act_s, const int64_t* case_off, uint32_t
     return true;
 }
 
-__global__ void k_var_init(VarWs w, const int64_t* n_cases) {
-    if (threadIdx.x == 0) {
-        w.scal[0] = *n_cases;   // C
-        w.scal[1] = 0;          // V (filled later)
-        w.u32scal[0] = 0;       // collisions
-        w.u32scal[1] = 0;       // V (u32)
+// Scalars: scal[0] C, [1] V, [2] variants of 255 cases or more.
+// Counters per claiming case (more: members besides it, low: its smallest
+// member if smaller); claim words: hash's low half << 32 | case + 1, 0 empty.
+__device__ __forceinline__ int64_t var_slots(int64_t C) { return 2 * C; }
+
+__global__ __launch_bounds__(kBlk) void k_var_clear(VarWs w, const int64_t* n_cases) {
+    const int64_t C = *n_cases, stride = (int64_t)gridDim.x * kBlk;
+    uint64_t* claim = w.hash;   // runs on into hash2
+    for (int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x; i < C; i += stride) {
+        *reinterpret_cast<ulonglong2*>(claim + 2 * i) = make_ulonglong2(0, 0);
+        w.repflag[i] = 0;
+        w.rrank[i] = 0xFFFFFFFFu;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.scal[0] = C;
+}
+
+// Orders this wave's LDS accesses before it and after it (the lanes run
+// together; only the compiler has to keep the order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Wave-cooperative walk over 64 consecutive segments: lane m holds the
@@ -110,16 +131,54 @@ __device__ __forceinline__ int seg_of32(int32_t vstart, int64_t p) {
     return lo;
 }
 
-// Sequence hash of every case: a sum over positions of mix(position, activity)
-// (order-sensitive, computable in any order), mixed with the length.  A wave
-// takes 64 consecutive cases; their events are read in 1024-event windows
-// with coalesced 16-byte loads into LDS, then each lane sums 16 consecutive
-// events, adding a case's partial sum to its LDS total when it leaves the case
-// (so a case costs one or two LDS additions, not one per event).
+// The table slot of case c's sequence (hash h): the case that claimed it, c
+// itself if it is the first.  A slot is read without a device-scope access
+// first: a claim never changes, so a stale read can only show it empty, and
+// the compare-and-swap then tells.
+__device__ __forceinline__ uint32_t enter(uint64_t* claim, int64_t slots, uint64_t h, uint32_t c,
+                                          const int32_t* act_s, const int64_t* case_off) {
+    const uint64_t mine = (h << 32) | (uint64_t)(c + 1u);
+    uint64_t p = __umul64hi(h, (uint64_t)slots);
+    for (;;) {   // ends: the table has twice as many slots as cases
+        uint64_t cur = __hip_atomic_load(&claim[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        if (cur == 0) {
+            uint64_t want = 0;
+            if (__hip_atomic_compare_exchange_strong(&claim[p], &want, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return c;
+            cur = want;
+        }
+        const uint32_t lead = (uint32_t)cur - 1u;
+        if ((uint32_t)(cur >> 32) == (uint32_t)h && same_seq(act_s, case_off, c, lead)) return lead;
+        p = p + 1 == (uint64_t)slots ? 0 : p + 1;
+    }
+}
+
+// Sequence hash of every case, and its variant's slot.  The hash is a sum over
+// positions of mix(position, activity) (order-sensitive, computable in any
+// order), mixed with the length.  A wave takes 64 consecutive cases; their
+// events are read in 1024-event windows with coalesced 16-byte loads into LDS,
+// then each lane sums 16 consecutive events, adding a case's partial sum to
+// its LDS total when it leaves the case (so a case costs one or two LDS
+// additions, not one per event).
+// Then the wave's equal hashes meet in a 128-slot LDS table, one lane of each
+// enters the global table for all of them, and the further members of a
+// variant are counted in a block-wide LDS cache by claiming case, written out
+// at the end: a variant that holds a third of the cases costs a global atomic
+// per block, not one per case (they queue on one address at about 8 ns each).
+// Bound by the latency of the scattered claims beside the hash's arithmetic:
+// 0.45 ms on 5M cases of 99M events (the hash alone 0.21 ms; sorting by hash
+// and regrouping took 0.80 ms after it).
 constexpr int kHashWin = 1024;
-__global__ __launch_bounds__(kBlk) void k_var_hash(const int32_t* __restrict__ act_s,
-                                                   const int64_t* __restrict__ case_off, VarWs w,
-                                                   uint64_t mask, int64_t n) {
+constexpr int kMeet = 2 * kWave;   // LDS slots for a wave's hashes
+constexpr int kMore = 512;         // cached member counts per block
+__global__ __launch_bounds__(kBlk) void k_var_group(const int32_t* __restrict__ act_s,
+                                                    const int64_t* __restrict__ case_off, VarWs w,
+                                                    uint64_t mask, int64_t n) {
+    __shared__ uint32_t meet[kBlk / kWave][kMeet];       // lane + 1 of a hash's first lane
+    __shared__ uint32_t members[kBlk / kWave][kWave];    // its lanes
+    __shared__ uint32_t lead_of[kBlk / kWave][kWave];    // its claiming case
+    __shared__ uint32_t mtag[kMore], mcnt[kMore];        // claiming case + 1, further members
     __shared__ unsigned long long hsum[kBlk / kWave][kWave];
     __shared__ int64_t sst[kBlk / kWave][kWave + 1];
     __shared__ int32_t sact[kBlk / kWave][kHashWin];
@@ -128,6 +187,14 @@ __global__ __launch_bounds__(kBlk) void k_var_hash(const int32_t* __restrict__ a
     const int64_t wv = ((int64_t)blockIdx.x * kBlk + threadIdx.x) / kWave;
     const int64_t nw = (int64_t)gridDim.x * kBlk / kWave;
     const bool aligned = (reinterpret_cast<uintptr_t>(act_s) & 15) == 0;
+    for (int i = threadIdx.x; i < kMore; i += kBlk) mtag[i] = mcnt[i] = 0;
+    __syncthreads();
+    auto more = [&](uint32_t lead, uint32_t k) {
+        const uint32_t at = (lead * 0x9E3779B1u) >> 23;   // 9 bits: kMore
+        const uint32_t old = atomicCAS(&mtag[at], 0u, lead + 1u);
+        if (old == 0u || old == lead + 1u) atomicAdd(&mcnt[at], k);
+        else atomicAdd(&w.repflag[lead], k);
+    };
     constexpr int kPer = kHashWin / kWave;   // 16 events per lane and window
     for (int64_t c0 = wv * kWave; c0 < C; c0 += nw * kWave) {
         const int64_t c = c0 + lane();
@@ -189,158 +256,327 @@ __global__ __launch_bounds__(kBlk) void k_var_hash(const int32_t* __restrict__ a
             }
             if (lo < hi) atomicAdd(&hsum[wl][m], (unsigned long long)acc);
         }
+        uint64_t h = mix64((uint64_t)hsum[wl][lane()] ^ mix64((uint64_t)(en - st) + 0x9e3779b97f4a7c15ull));
+        if (mask) h &= mask;
+        // meet: every lane finds the first lane with its hash (itself perhaps)
+        meet[wl][lane()] = 0;
+        meet[wl][lane() + kWave] = 0;
+        members[wl][lane()] = 0;
+        hsum[wl][lane()] = h;
+        wave_sync();
+        int first = lane();
         if (has) {
-            uint64_t h = mix64((uint64_t)hsum[wl][lane()] ^ mix64((uint64_t)(en - st) + 0x9e3779b97f4a7c15ull));
-            if (mask) h &= mask;
-            w.hash[c] = h;
-            w.idx[c] = (uint32_t)c;
-            w.repflag[c] = 0;
-        }
-    }
-}
-
-__global__ __launch_bounds__(kBlk) void k_var_verify(const uint64_t* __restrict__ hs,
-                                                     const uint32_t* __restrict__ is,
-                                                     const int32_t* __restrict__ act_s,
-                                                     const int64_t* __restrict__ case_off, VarWs w) {
-    const int64_t C = w.scal[0];
-    for (int64_t p = (int64_t)blockIdx.x * kBlk + threadIdx.x; p < C; p += (int64_t)gridDim.x * kBlk) {
-        uint32_t f = 1;
-        if (p > 0 && hs[p] == hs[p - 1]) {
-            if (same_seq(act_s, case_off, is[p], is[p - 1])) f = 0;
-            else atomicOr(&w.u32scal[0], 1u);
-        }
-        w.flag[p] = f;
-    }
-}
-
-// Exact regrouping of equal-hash runs that hold several sequences.  Only does
-// work after a true hash collision; one thread per affected run.
-__global__ __launch_bounds__(kBlk) void k_var_fix(const uint64_t* __restrict__ hs, uint32_t* is,
-                                                  const int32_t* __restrict__ act_s,
-                                                  const int64_t* __restrict__ case_off, VarWs w) {
-    if (w.u32scal[0] == 0) return;
-    const int64_t C = w.scal[0];
-    uint32_t* out = w.vidx2;     // scratch
-    uint32_t* mark = w.vkey2;    // scratch
-    for (int64_t p = (int64_t)blockIdx.x * kBlk + threadIdx.x; p < C; p += (int64_t)gridDim.x * kBlk) {
-        if (p > 0 && hs[p] == hs[p - 1]) continue;   // not a run start
-        int64_t q = p + 1;
-        bool mixed = false;
-        while (q < C && hs[q] == hs[p]) {
-            mixed |= w.flag[q] != 0;
-            ++q;
-        }
-        if (!mixed) continue;
-        for (int64_t a = p; a < q; ++a) mark[a] = 0;
-        int64_t o = p;
-        for (int64_t a = p; a < q; ++a) {
-            if (mark[a]) continue;
-            const uint32_t lead = is[a];
-            mark[a] = 1;
-            out[o] = lead;
-            w.flag[o] = 1;
-            ++o;
-            for (int64_t b = a + 1; b < q; ++b) {
-                if (!mark[b] && same_seq(act_s, case_off, is[b], lead)) {
-                    mark[b] = 1;
-                    out[o] = is[b];
-                    w.flag[o] = 0;
-                    ++o;
+            for (uint32_t p = (uint32_t)h & (kMeet - 1);; p = (p + 1) & (kMeet - 1)) {   // 64 lanes, 128 slots
+                const uint32_t old = atomicCAS(&meet[wl][p], 0u, (uint32_t)lane() + 1u);
+                if (old == 0u) break;
+                if ((uint64_t)hsum[wl][old - 1u] == h) {
+                    first = (int)old - 1;
+                    break;
                 }
             }
+            // one hash, another sequence: the lane enters the table by itself
+            if (first != lane() && !same_seq(act_s, case_off, (uint32_t)c, (uint32_t)(c0 + first))) first = lane();
+            atomicAdd(&members[wl][first], 1u);
         }
-        for (int64_t a = p; a < q; ++a) is[a] = out[a];
+        wave_sync();
+        if (has && first == lane()) {
+            const uint32_t lead = enter(w.hash, var_slots(C), h, (uint32_t)c, act_s, case_off);
+            lead_of[wl][lane()] = lead;
+            const uint32_t k = members[wl][lane()] - (lead == (uint32_t)c ? 1u : 0u);
+            if (k) more(lead, k);
+        }
+        wave_sync();
+        if (has) {
+            const uint32_t lead = lead_of[wl][first];
+            w.cvar[c] = lead;
+            if ((uint32_t)c < lead) atomicMin(&w.rrank[lead], (uint32_t)c);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kMore; i += kBlk)
+        if (mcnt[i]) atomicAdd(&w.repflag[mtag[i] - 1u], mcnt[i]);
+}
+
+// Representative of every case (w.idx), and the count of a representative's
+// variant (w.idx2; 0 for the other cases); per tile the histogram of the
+// representatives' count digits.
+__device__ __forceinline__ uint32_t count_digit(uint32_t count) { return 255u - (count < 255u ? count : 255u); }
+
+__global__ __launch_bounds__(dev::kB) void k_var_reps(VarWs w, int64_t nb) {
+    __shared__ uint32_t h[256];
+    const int64_t C = w.scal[0], tiles_n = (C + dev::kTile - 1) / dev::kTile;
+    for (int64_t tile = blockIdx.x; tile < tiles_n; tile += gridDim.x) {
+        if (threadIdx.x < 256) h[threadIdx.x] = 0;
+        __syncthreads();
+        uint32_t lead[dev::kI], low[dev::kI], cnt[dev::kI];
+#pragma unroll
+        for (int k = 0; k < dev::kI; ++k) {
+            const int64_t c = tile * dev::kTile + k * dev::kB + threadIdx.x;
+            lead[k] = w.cvar[c < C ? c : C - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < dev::kI; ++k) {
+            low[k] = w.rrank[lead[k]];
+            cnt[k] = w.repflag[lead[k]] + 1u;
+        }
+#pragma unroll
+        for (int k = 0; k < dev::kI; ++k) {
+            const int64_t c = tile * dev::kTile + k * dev::kB + threadIdx.x;
+            if (c >= C) continue;
+            const uint32_t rep = low[k] < lead[k] ? low[k] : lead[k];
+            const bool is = rep == (uint32_t)c;
+            w.idx[c] = rep;
+            w.idx2[c] = is ? cnt[k] : 0u;
+            if (is) atomicAdd(&h[count_digit(cnt[k])], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) w.hist[(int64_t)threadIdx.x * nb + tile] = h[threadIdx.x];
+        __syncthreads();
     }
 }
 
-// sid = inclusive group index (after the exclusive scan of flags + flag - 1).
-__global__ __launch_bounds__(kBlk) void k_var_groups(const uint32_t* __restrict__ is, VarWs w) {
-    const int64_t C = w.scal[0];
-    for (int64_t p = (int64_t)blockIdx.x * kBlk + threadIdx.x; p < C; p += (int64_t)gridDim.x * kBlk) {
-        if (w.flag[p]) {
-            const uint32_t g = w.sid[p];       // exclusive count of starts before p
-            w.sstart[g] = (uint32_t)p;
-            w.repflag[is[p]] = 1;              // first member: smallest case index
-        }
-    }
+// Representatives (count, case) to their place by (digit, case), in vcr: one
+// stable digit pass over the cases, as dev::k_scatter, where only the
+// representatives take part.
+__global__ __launch_bounds__(dev::kB) void k_var_order(VarWs w, int64_t nb) {
+    using namespace dev;
+    __shared__ uint32_t cnt[kW * 256];
+    __shared__ uint32_t tstart[256];
+    __shared__ int64_t gshift[256];
+    __shared__ uint32_t scnt[kTile];
+    __shared__ uint32_t scase[kTile];
+    __shared__ uint32_t tmp[kB / kWave + 1];
+
+    const int64_t C = w.scal[0], tiles_n = (C + kTile - 1) / kTile;
+    const int wv = threadIdx.x / kWave;
+    uint32_t all;
+    const uint32_t rs = threadIdx.x < 256 ? w.rowsum[threadIdx.x] : 0u;
+    const uint32_t digit_base = block_excl_sum<kB>(rs, tmp, &all);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint32_t V = w.u32scal[1];
-        w.sstart[V] = (uint32_t)C;
-        w.scal[1] = V;
+        w.scal[1] = all;   // V
+        w.scal[2] = rs;    // digit 0: 255 cases or more
+    }
+    const XcdSplit xs = xcd_split(tiles_n);
+    for (int64_t tile = xs.first; tile < xs.end; tile += xs.stride) {
+        const int64_t wbase = tile * kTile + (int64_t)wv * (kWave * kI);
+        for (int i = threadIdx.x; i < kW * 256; i += kB) cnt[i] = 0;
+        uint32_t key[kI], rk[kI];
+#pragma unroll
+        for (int k = 0; k < kI; ++k) {
+            const int64_t i = wbase + k * kWave + lane();
+            key[k] = i < C ? w.idx2[i] : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kI; ++k) {
+            const bool valid = key[k] != 0u;
+            const uint32_t d = count_digit(key[k]);
+            const uint64_t peers = match_digit8(d, __ballot(valid));
+            const uint32_t below = __popcll(peers & lanes_below());
+            uint32_t c = 0;
+            if (valid) c = cnt[wv * 256 + d];
+            rk[k] = c + below;
+            if (valid && below == 0) cnt[wv * 256 + d] = c + __popcll(peers);
+        }
+        __syncthreads();
+        uint32_t tot = 0;
+        if (threadIdx.x < 256) {
+            uint32_t run = 0;
+            for (int ww = 0; ww < kW; ++ww) {
+                const uint32_t x = cnt[ww * 256 + threadIdx.x];
+                cnt[ww * 256 + threadIdx.x] = run;
+                run += x;
+            }
+            tot = run;
+        }
+        uint32_t reps;
+        const uint32_t ex = block_excl_sum<kB>(tot, tmp, &reps);
+        if (threadIdx.x < 256) {
+            tstart[threadIdx.x] = ex;
+            gshift[threadIdx.x] = (int64_t)digit_base + (int64_t)w.hist[(int64_t)threadIdx.x * nb + tile] - (int64_t)ex;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kI; ++k) {
+            if (key[k] == 0u) continue;
+            const uint32_t d = count_digit(key[k]);
+            const uint32_t pos = tstart[d] + cnt[wv * 256 + d] + rk[k];
+            scnt[pos] = key[k];
+            scase[pos] = (uint32_t)(wbase + k * kWave + lane());
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < reps; i += kB)
+            w.vcr[gshift[count_digit(scnt[i])] + i] = make_uint2(scnt[i], scase[i]);
+        __syncthreads();
     }
 }
 
-// Per group (hash order): count and representative, stored at the group's
-// representative-order index v (one 8-byte scattered write); the group's v
-// is kept in hash order (gv, coalesced) for the per-case pass.
-__global__ __launch_bounds__(kBlk) void k_var_segments(const uint32_t* __restrict__ is, VarWs w) {
-    const int64_t V = w.scal[1];
-    uint32_t* gv = w.repflag;   // free again after the representative scan
-    for (int64_t g = (int64_t)blockIdx.x * kBlk + threadIdx.x; g < V; g += (int64_t)gridDim.x * kBlk) {
-        const uint32_t s0 = w.sstart[g], s1 = w.sstart[g + 1];
-        const uint32_t rep = is[s0];
-        const uint32_t v = w.rrank[rep];
-        w.vcr[v] = make_uint2(s1 - s0, rep);
-        gv[g] = v;
+// The variants of 255 cases or more (the first scal[2] of vcr, in case order)
+// by descending count, case order kept among equals.  At most 16384 of them:
+// an element's place is the number of elements before it, counted over all of
+// them (64 elements per block, its waves sharing the others in 64-element
+// chunks, lane by lane through a scalar register; hundreds in the logs seen),
+// into vkey (case) and vkey2 (count).  More: one block, stable byte passes
+// between (vkey, vkey2) and (vidx, vidx2) -- there are at most C / 255, so a
+// block's few ns per element and pass stay far below the rest of the call.
+constexpr int kTopThreads = 1024;
+constexpr int64_t kTopPairs = 16384;
+__global__ __launch_bounds__(kTopThreads) void k_var_top(VarWs w) {
+    __shared__ uint32_t cnt[kTopThreads / kWave * 256];
+    __shared__ uint32_t base[256];
+    __shared__ uint32_t tmp[kTopThreads / kWave + 1];
+    const int64_t M = w.scal[2];
+    if (M <= kTopPairs) {
+        __shared__ uint32_t place[kWave];
+        if ((int64_t)blockIdx.x * kWave >= M) return;
+        if (threadIdx.x < kWave) place[threadIdx.x] = 0;
+        __syncthreads();
+        const int64_t i = (int64_t)blockIdx.x * kWave + lane();
+        const uint2 me = i < M ? w.vcr[i] : make_uint2(0, 0);
+        uint32_t before = 0;
+        for (int64_t ch = threadIdx.x / kWave; ch * kWave < M; ch += kTopThreads / kWave) {   // wave-uniform
+            const int64_t j0 = ch * kWave;
+            const uint32_t o = j0 + lane() < M ? w.vcr[j0 + lane()].x : 0u;   // 0: before nobody
+            // an equal count of an earlier element comes first: in earlier chunks
+            // all of them do, in later ones none, in this one the lower lanes
+            const uint32_t lim = ch < (int64_t)blockIdx.x ? me.x : me.x + 1u;
+#pragma unroll 16
+            for (int j = 0; j < kWave; ++j) {
+                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)o, j);
+                before += v >= lim ? 1u : 0u;
+                if (ch == (int64_t)blockIdx.x) before += (v == me.x && j < lane()) ? 1u : 0u;
+            }
+        }
+        atomicAdd(&place[lane()], before);
+        __syncthreads();
+        if (threadIdx.x < kWave && i < M) {
+            w.vkey[place[threadIdx.x]] = me.y;
+            w.vkey2[place[threadIdx.x]] = me.x;
+        }
+        return;
+    }
+    if (blockIdx.x != 0) return;
+    const int wv = threadIdx.x / kWave;
+    uint32_t *ck = w.vidx, *cv = w.vidx2, *ok = w.vkey, *ov = w.vkey2;   // (case, count), 4 passes: ends in (vkey, vkey2)
+    for (int64_t i = threadIdx.x; i < M; i += kTopThreads) {
+        ok[i] = w.vcr[i].y;
+        ov[i] = w.vcr[i].x;
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        uint32_t* t = ck; ck = ok; ok = t;
+        t = cv; cv = ov; ov = t;
+        __threadfence_block();
+        __syncthreads();
+        if (threadIdx.x < 256) base[threadIdx.x] = 0;
+        __syncthreads();
+        for (int64_t i = threadIdx.x; i < M; i += kTopThreads) atomicAdd(&base[(~cv[i] >> shift) & 255u], 1u);
+        __syncthreads();
+        uint32_t all;
+        const uint32_t v = threadIdx.x < 256 ? base[threadIdx.x] : 0u;
+        const uint32_t ex = block_excl_sum<kTopThreads>(v, tmp, &all);
+        if (threadIdx.x < 256) base[threadIdx.x] = ex;
+        for (int64_t t0 = 0; t0 < M; t0 += kTopThreads) {
+            for (int i = threadIdx.x; i < kTopThreads / kWave * 256; i += kTopThreads) cnt[i] = 0;
+            __syncthreads();
+            const int64_t i = t0 + threadIdx.x;
+            const bool valid = i < M;
+            const uint32_t c = valid ? ck[i] : 0u, k = valid ? cv[i] : 0u;
+            const uint32_t d = (~k >> shift) & 255u;
+            const uint64_t peers = match_digit8(d, __ballot(valid));
+            const uint32_t below = __popcll(peers & lanes_below());
+            if (valid && below == 0) cnt[wv * 256 + d] = __popcll(peers);
+            __syncthreads();
+            if (threadIdx.x < 256) {
+                uint32_t run = base[threadIdx.x];
+                for (int ww = 0; ww < kTopThreads / kWave; ++ww) {
+                    const uint32_t x = cnt[ww * 256 + threadIdx.x];
+                    cnt[ww * 256 + threadIdx.x] = run;
+                    run += x;
+                }
+                base[threadIdx.x] = run;
+            }
+            __syncthreads();
+            if (valid) {
+                const uint32_t g = cnt[wv * 256 + d] + below;
+                ok[g] = c;
+                ov[g] = k;
+            }
+            __syncthreads();
+        }
     }
 }
 
-// Sort input of the final order (ascending key = descending count, stable on
-// the representative order), and every case's representative-order variant.
-__global__ __launch_bounds__(kBlk) void k_var_keys(const uint32_t* __restrict__ is, VarWs w) {
-    const int64_t C = w.scal[0];
-    const int64_t V = w.scal[1];
-    const uint32_t* gv = w.repflag;
-    for (int64_t v = (int64_t)blockIdx.x * kBlk + threadIdx.x; v < V; v += (int64_t)gridDim.x * kBlk) {
-        w.vkey[v] = (uint32_t)C - w.vcr[v].x;
-        w.vidx[v] = (uint32_t)v;
-    }
-    for (int64_t p = (int64_t)blockIdx.x * kBlk + threadIdx.x; p < C; p += (int64_t)gridDim.x * kBlk) {
-        // group of p: flags up to p, minus one
-        const uint32_t g = w.sid[p] + w.flag[p] - 1;
-        w.cvar[is[p]] = gv[g];
-    }
-}
+// The final order in ranges of variants, one per block (k_var_emit walks the
+// same ranges): counts, representatives, lengths; the range's total length in
+// part64, the variant of each representative in fid (by case).
+constexpr int kEmitBlk = 512;
+__device__ __forceinline__ int64_t emit_chunk(int64_t V) { return (V + gridDim.x - 1) / gridDim.x; }
 
-__global__ __launch_bounds__(kBlk) void k_var_ids(const uint32_t* __restrict__ order, VarWs w,
-                                                  const int64_t* __restrict__ case_off,
-                                                  const int32_t* __restrict__ case_code, VarOutDev out) {
-    const int64_t V = w.scal[1];
-    for (int64_t k = (int64_t)blockIdx.x * kBlk + threadIdx.x; k < V; k += (int64_t)gridDim.x * kBlk) {
-        const uint32_t v = order[k];
-        w.fid[v] = (uint32_t)k;
-        const uint2 cr = w.vcr[v];
+__global__ __launch_bounds__(kEmitBlk) void k_var_ids(VarWs w, const int64_t* __restrict__ case_off,
+                                                      const int32_t* __restrict__ case_code, VarOutDev out) {
+    __shared__ int64_t red[kEmitBlk / kWave];
+    const int64_t V = w.scal[1], M = w.scal[2], chunk = emit_chunk(V);
+    const int64_t b0 = blockIdx.x * chunk, b1 = b0 + chunk < V ? b0 + chunk : V;
+    int64_t sum = 0;
+    for (int64_t k = b0 + threadIdx.x; k < b1; k += kEmitBlk) {
+        const uint2 cr = k < M ? make_uint2(w.vkey2[k], w.vkey[k]) : w.vcr[k];
         const uint32_t r = cr.y;
         const uint32_t L = (uint32_t)(case_off[r + 1] - case_off[r]);
+        w.fid[r] = (uint32_t)k;
+        w.sstart[k] = r;
         out.var_count[k] = cr.x;
         out.var_rep[k] = case_code[r];
         out.var_len[k] = (int32_t)L;
         w.lens[k] = L;
+        sum += L;
+    }
+    sum = wave_sum(sum);
+    if (lane() == 0) red[threadIdx.x / kWave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t t = 0;
+        for (int k = 0; k < kEmitBlk / kWave; ++k) t += red[k];
+        w.part64[blockIdx.x] = t;
     }
 }
 
-// Sequences in final order: a wave takes 64 consecutive variants and copies
-// their representatives' activities, writes coalesced over the output range.
-__global__ __launch_bounds__(kBlk) void k_var_emit(const uint32_t* __restrict__ order,
-                                                   const int32_t* __restrict__ act_s,
-                                                   const int64_t* __restrict__ case_off, VarWs w,
-                                                   const int32_t* status_in, VarOutDev out) {
+// Sequences in final order: a block takes its range in steps of 512 variants
+// (offsets from the ranges' totals and a block scan), a wave 64 consecutive
+// variants of a step, copying their representatives' activities, writes
+// coalesced over the output range.
+__global__ __launch_bounds__(kEmitBlk) void k_var_emit(const int32_t* __restrict__ act_s,
+                                                       const int64_t* __restrict__ case_off, VarWs w,
+                                                       const int32_t* status_in, VarOutDev out) {
+    __shared__ int64_t tmp[kEmitBlk / kWave + 1];
     const int64_t C = w.scal[0];
-    const int64_t V = w.scal[1];
-    const int64_t wv = ((int64_t)blockIdx.x * kBlk + threadIdx.x) / kWave;
-    const int64_t nw = (int64_t)gridDim.x * kBlk / kWave;
-    for (int64_t k0 = wv * kWave; k0 < V; k0 += nw * kWave) {
+    const int64_t V = w.scal[1], chunk = emit_chunk(V);
+    const int64_t b0 = blockIdx.x * chunk, b1 = b0 + chunk < V ? b0 + chunk : V;
+    int64_t run;
+    {
+        int64_t before = 0;
+        for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kEmitBlk) before += w.part64[i];
+        block_excl_sum<kEmitBlk>(before, tmp, &run);
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        out.var_off[V] = run + w.part64[blockIdx.x];
+        *out.n_variants = V;
+        *out.status = status_in ? *status_in : 0;
+    }
+    for (int64_t s0 = b0; s0 < b1; s0 += kEmitBlk) {   // block-uniform
+        const int64_t k0 = s0 + threadIdx.x / kWave * kWave;
         const int64_t k = k0 + lane();
-        const bool has = k < V;
-        int64_t src = 0, dst = INT64_MAX, len = 0;
+        const bool has = k < b1;
+        int64_t src = 0, len = 0;
         if (has) {
-            const uint32_t r = w.vcr[order[k]].y;
-            src = case_off[r];
-            len = case_off[r + 1] - src;
-            dst = out.var_off[k];
+            src = case_off[w.sstart[k]];
+            len = w.lens[k];
         }
-        const int last = (V - 1 - k0) < (kWave - 1) ? (int)(V - 1 - k0) : (kWave - 1);
+        int64_t total;
+        const int64_t dst = run + block_excl_sum<kEmitBlk>(len, tmp, &total);
+        run += total;
+        if (has) out.var_off[k] = dst;
+        if (k0 >= b1) continue;   // wave-uniform; the block scan above is every wave's
+        const int last = (b1 - 1 - k0) < (kWave - 1) ? (int)(b1 - 1 - k0) : (kWave - 1);
         const int64_t base = __shfl(dst, 0);
         const int64_t end = __shfl(dst + len, last);
         // event positions are below 2^31 (the log's size limit), so output
@@ -368,20 +604,9 @@ __global__ __launch_bounds__(kBlk) void k_var_emit(const uint32_t* __restrict__ 
         }
     }
     if (out.case_variant) {
-        for (int64_t c = (int64_t)blockIdx.x * kBlk + threadIdx.x; c < C; c += (int64_t)gridDim.x * kBlk)
-            out.case_variant[c] = (int32_t)w.fid[w.cvar[c]];
+        for (int64_t c = (int64_t)blockIdx.x * kEmitBlk + threadIdx.x; c < C; c += (int64_t)gridDim.x * kEmitBlk)
+            out.case_variant[c] = (int32_t)w.fid[w.idx[c]];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        out.var_off[V] = w.scal[2];
-        *out.n_variants = V;
-        *out.status = status_in ? *status_in : 0;
-    }
-}
-
-int bits_for(int64_t n) {
-    int b = 0;
-    while (b < 63 && (int64_t(1) << b) <= n) ++b;
-    return b;
 }
 
 }  // namespace
@@ -392,42 +617,26 @@ hipError_t launch_variants(const int32_t* act_s, const int64_t* case_off, const 
     const uint64_t mask = (debug_hash_bits == 0 || debug_hash_bits >= 64)
                               ? 0ull
                               : ((uint64_t(1) << debug_hash_bits) - 1);
-    k_var_init<<<1, 1, 0, s>>>(w, n_cases);
+    const int64_t nb = dev::tiles(n);
+    // the case count is on the device; n bounds it, and with it every grid
+    const auto grid = [](int64_t want, int64_t most) { return (unsigned)(want < 1 ? 1 : (want < most ? want : most)); };
     {
         ProfScope p(P_VAR_HASH, s);
-        k_var_hash<<<kGrid, kBlk, 0, s>>>(act_s, case_off, w, mask, n);
+        k_var_clear<<<grid((n + kBlk - 1) / kBlk, kGrid), kBlk, 0, s>>>(w, n_cases);
+        k_var_group<<<grid((n + kBlk - 1) / kBlk, kGrid), kBlk, 0, s>>>(act_s, case_off, w, mask, n);
     }
-    bool in2;
-    {
-        ProfScope p(P_VAR_SORT, s);
-        in2 = dev::sort_pairs<uint64_t>(w.hash, w.idx, w.hash2, w.idx2, &w.scal[0], n, 64, w.hist,
-                                        w.rowsum, s);
-    }
-    const uint64_t* hs = in2 ? w.hash2 : w.hash;
-    uint32_t* is = in2 ? w.idx2 : w.idx;
-    {
-        ProfScope p(P_VAR_GROUP, s);
-        k_var_verify<<<kGrid, kBlk, 0, s>>>(hs, is, act_s, case_off, w);
-        k_var_fix<<<kGrid, kBlk, 0, s>>>(hs, is, act_s, case_off, w);
-        // group index of every group start; V
-        dev::excl_scan<uint32_t>(w.flag, &w.scal[0], w.sid, w.part32, &w.u32scal[1], s);
-        k_var_groups<<<kGrid, kBlk, 0, s>>>(is, w);
-        // representative-order index of every representative case
-        dev::excl_scan<uint32_t>(w.repflag, &w.scal[0], w.rrank, w.part32, (uint32_t*)nullptr, s);
-        k_var_segments<<<kGrid, kBlk, 0, s>>>(is, w);
-        k_var_keys<<<kGrid, kBlk, 0, s>>>(is, w);
-    }
-    bool o2;
     {
         ProfScope p(P_VAR_ORDER, s);
-        o2 = dev::sort_pairs<uint32_t>(w.vkey, w.vidx, w.vkey2, w.vidx2, &w.scal[1], n, bits_for(n),
-                                       w.hist, w.rowsum, s);
+        k_var_reps<<<dev::grid_for(nb), dev::kB, 0, s>>>(w, nb);
+        dev::k_hist_scan<<<256, 256, 0, s>>>(w.hist, &w.scal[0], nb, w.rowsum);
+        k_var_order<<<dev::grid_for(nb), dev::kB, 0, s>>>(w, nb);
+        // at most n / 255 variants have 255 cases
+        k_var_top<<<grid((n / 255 + kWave - 1) / kWave, kTopPairs / kWave), kTopThreads, 0, s>>>(w);
     }
-    const uint32_t* order = o2 ? w.vidx2 : w.vidx;
     ProfScope p(P_VAR_EMIT, s);
-    k_var_ids<<<kGrid, kBlk, 0, s>>>(order, w, case_off, case_code, out);
-    dev::excl_scan<int64_t>(w.lens, &w.scal[1], out.var_off, w.part64, &w.scal[2], s);
-    k_var_emit<<<kGrid, kBlk, 0, s>>>(order, act_s, case_off, w, status_in, out);
+    const unsigned ge = grid((n + kEmitBlk - 1) / kEmitBlk, dev::kScanGrid);
+    k_var_ids<<<ge, kEmitBlk, 0, s>>>(w, case_off, case_code, out);
+    k_var_emit<<<ge, kEmitBlk, 0, s>>>(act_s, case_off, w, status_in, out);
     return hipGetLastError();
 }
 
