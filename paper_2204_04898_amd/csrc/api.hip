@@ -173,15 +173,12 @@ int run_prepare(const pm4g_log* log, const pm4g_prepared* out, bool case_table, 
     PrepWs w = prep_ws_layout(bp, n, ws_rows);
     int32_t* const row_s = ws_rows ? out->row : nullptr;
     if (!row_s) w.a.row = w.b.row = nullptr;   // the row order is carried only when asked for
-    k_set_status<<<1, 1, 0, s>>>(out->status, 0);
-    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, presorted, false,
-                               w.info, w.rpart, presorted ? nullptr : w.hist_raw, s));
+    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, presorted, w.info, w.rpart,
+                               w.hist_raw, out->status, s));
     RangeInfo h{};
     PM4G_HIP(hipMemcpyAsync(&h, w.info, sizeof(h), hipMemcpyDeviceToHost, s));
     PM4G_HIP(hipStreamSynchronize(s));
-    if (h.status != 0) {
-        k_set_status<<<1, 1, 0, s>>>(out->status, h.status);
-        PM4G_HIP(hipGetLastError());
+    if (h.status != 0) {   // out->status holds it
         set_err("%s", h.status == PM4G_E_RANGE ? "activity outside [0, n_activities)"
                                                : "rows are not in (case, timestamp, row) order");
         return h.status;

@@ -3,11 +3,13 @@
 // distinct case id in order and case_off[j] the position of its first event.
 // Reduce-then-scan compaction of the boundary flags
 // flag(i) = (i == 0) || case_s[i] != case_s[i-1]:
-//   k_case_count  per-tile flag counts (or k_case_tiles: from the per-window
-//                 case counts the per-case sort already produced)
+//   k_case_count  per-tile flag counts (not needed where the per-case sort
+//                 already counted the cases of each of its windows)
 //   k_case_scan   exclusive scan of the tile counts, n_cases, case_off[C] = N
+//                 (not needed up to kCaseDirect tiles: each tile of k_case_emit
+//                 sums the counts before it itself, a few loads per thread)
 //   k_case_emit   per-tile ranks -> case_off / case_code
-// Bytes per event: 4 + 4 read (the column is read twice).
+// Bytes per event: 4 read after the per-case sort, else 4 + 4.
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -42,16 +44,41 @@ __global__ __launch_bounds__(kCB) void k_case_count(const int32_t* __restrict__ 
     if (threadIdx.x == 0) blockcnt[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(1024) void k_case_scan(uint32_t* blockcnt, int64_t nb, int64_t n,
-                                                    int64_t* case_off, int64_t* n_cases) {
+// Counts of tile t: per_tile counts [t * per_tile, ...) of the nc given (1: one
+// count per tile; 4: one per sort window).
+constexpr int kPerTile = kCaseTile / kSegWindow;
+static_assert(kCaseTile % kSegWindow == 0 && kPerTile == 4, "a case tile holds four sort windows (one 16-byte load)");
+__device__ __forceinline__ uint32_t tile_count(const uint32_t* cnt, int64_t nc, int per_tile, int64_t t) {
+    if (per_tile == 1) return t < nc ? cnt[t] : 0u;
+    if (4 * t + 3 < nc) {
+        const uint4 v = *reinterpret_cast<const uint4*>(cnt + 4 * t);
+        return v.x + v.y + v.z + v.w;
+    }
+    uint32_t c = 0;
+    for (int64_t k = 4 * t; k < nc; ++k) c += cnt[k];   // the last tile's windows, or none
+    return c;
+}
+
+__global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t nc, int per_tile, uint32_t* blockoff,
+                                                    int64_t nb, int64_t n, int64_t* case_off, int64_t* n_cases) {
     __shared__ uint32_t tmp[1024 / kWave + 1];
+    constexpr int kT = 4;   // tiles per thread and step
     uint32_t run = 0;
-    for (int64_t c0 = 0; c0 < nb; c0 += 1024) {
-        const int64_t i = c0 + threadIdx.x;
-        const uint32_t v = i < nb ? blockcnt[i] : 0u;
+    for (int64_t c0 = 0; c0 < nb; c0 += 1024 * kT) {
+        const int64_t t0 = c0 + (int64_t)threadIdx.x * kT;
+        uint32_t v[kT], sum = 0;
+#pragma unroll
+        for (int q = 0; q < kT; ++q) {
+            v[q] = tile_count(cnt, nc, per_tile, t0 + q);
+            sum += v[q];
+        }
         uint32_t total;
-        const uint32_t ex = block_excl_sum<1024>(v, tmp, &total);
-        if (i < nb) blockcnt[i] = run + ex;
+        uint32_t r = run + block_excl_sum<1024>(sum, tmp, &total);
+#pragma unroll
+        for (int q = 0; q < kT; ++q) {
+            if (t0 + q < nb) blockoff[t0 + q] = r;
+            r += v[q];
+        }
         run += total;
     }
     if (threadIdx.x == 0) {
@@ -60,25 +87,10 @@ __global__ __launch_bounds__(1024) void k_case_scan(uint32_t* blockcnt, int64_t 
     }
 }
 
-// Tile counts from per-window counts (kCaseTile / kSegWindow windows per tile),
-// written by the per-case sort.
-__global__ __launch_bounds__(1024) void k_case_tiles(const uint32_t* wincnt, int64_t nwin, uint32_t* blockcnt,
-                                                     int64_t nb) {
-    constexpr int kPerTile = kCaseTile / kSegWindow;
-    for (int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x; t < nb; t += (int64_t)gridDim.x * 1024) {
-        uint32_t c = 0;
-#pragma unroll
-        for (int k = 0; k < kPerTile; ++k) {
-            const int64_t w = t * kPerTile + k;
-            if (w < nwin) c += wincnt[w];
-        }
-        blockcnt[t] = c;
-    }
-}
-
 __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ case_s, int64_t n,
-                                                   const uint32_t* blockoff, int64_t* case_off,
-                                                   int32_t* case_code) {
+                                                   const uint32_t* blockoff, const uint32_t* cnt, int64_t nc,
+                                                   int per_tile, int64_t* case_off, int32_t* case_code,
+                                                   int64_t* n_cases) {
     // striped layout (coalesced loads): item k of thread t is position base + k*256 + t,
     // so position order is (k, wave, lane) order; ranks from ballots + one small scan
     constexpr int kNW = kCB / kWave;
@@ -111,7 +123,18 @@ __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ c
     const uint32_t ex = block_excl_sum<kCB>(v, tmp, &total);
     if (threadIdx.x < kCI * kNW) wcnt[threadIdx.x] = ex;
     __syncthreads();
-    const uint32_t b0 = blockoff[blockIdx.x];
+    uint32_t b0;
+    if (blockoff) {
+        b0 = blockoff[blockIdx.x];
+    } else {   // no scan: the cases of the tiles before this one
+        uint32_t before = 0;
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kCB) before += tile_count(cnt, nc, per_tile, t);
+        block_excl_sum<kCB>(before, tmp, &b0);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+            *n_cases = b0 + total;
+            case_off[b0 + total] = n;
+        }
+    }
 #pragma unroll
     for (int k = 0; k < kCI; ++k) {
         if ((masks[k] >> lane()) & 1ull) {
@@ -124,19 +147,25 @@ __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ c
 
 hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcnt, int64_t* case_off,
                              int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, hipStream_t s) {
-    static_assert(kCaseTile % kSegWindow == 0, "case tiles hold whole sort windows");
     ProfScope p(P_CASE_TABLE, s);
     const int64_t nb = case_blocks(n);
-    if (nb > 0) {
-        if (wincnt) {
-            const int64_t g = (nb + 1023) / 1024;
-            k_case_tiles<<<(unsigned)(g < 1024 ? g : 1024), 1024, 0, s>>>(wincnt, segsort_blocks(n), blockcnt, nb);
-        } else {
-            k_case_count<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, blockcnt);
-        }
+    // nb partial sums of the tiles before: nb^2 / 2 cached loads against a launch
+    // of 4.5 us and a one-block scan (22 us for 24k tiles)
+    constexpr int64_t kCaseDirect = 1024;
+    const uint32_t* cnt = wincnt;
+    int64_t nc = segsort_blocks(n);
+    int per_tile = kPerTile;
+    if (!wincnt) {
+        if (nb > 0) k_case_count<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, blockcnt);
+        cnt = blockcnt;
+        nc = nb;
+        per_tile = 1;
     }
-    k_case_scan<<<1, 1024, 0, s>>>(blockcnt, nb, n, case_off, n_cases);
-    if (nb > 0) k_case_emit<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, blockcnt, case_off, case_code);
+    const bool scan = nb == 0 || nb > kCaseDirect;
+    if (scan) k_case_scan<<<1, 1024, 0, s>>>(cnt, nc, per_tile, blockcnt, nb, n, case_off, n_cases);
+    if (nb > 0)
+        k_case_emit<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, scan ? blockcnt : nullptr, cnt, nc, per_tile, case_off,
+                                                 case_code, n_cases);
     return hipGetLastError();
 }
 

@@ -47,12 +47,12 @@ struct Bump {
 };
 
 // ---- range scan (range.hip) ----
-// hist_raw (may be NULL): [256][radix tiles] histograms of the raw case id's
-// low byte, for the first radix pass (raw logs only; the partials then need
-// one entry per radix tile).
+// hist_raw: [256][radix tiles] histograms of the raw case id's low byte, for
+// the first radix pass (raw logs only; the partials then have one entry per
+// radix tile).  status: the call's status word, set to the scan's.
 hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const int64_t* ts, int64_t n,
-                             int32_t A, bool presorted, bool want_ts, RangeInfo* info, RangePart* part,
-                             uint32_t* hist_raw, hipStream_t s);
+                             int32_t A, bool presorted, RangeInfo* info, RangePart* part,
+                             uint32_t* hist_raw, int32_t* status, hipStream_t s);
 hipError_t launch_ts_range(const int64_t* ts, int64_t n, RangeInfo* info, hipStream_t s);
 
 // ---- LSD radix passes over (case key u32, ts i64, act u32) elements (radix.hip) ----

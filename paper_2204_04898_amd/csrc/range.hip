@@ -12,94 +12,48 @@
 
 namespace pm4g {
 
-__global__ void k_range_init(RangeInfo* info) {
-    info->case_min = INT32_MAX;
-    info->case_max = INT32_MIN;
-    info->status = 0;
-    info->long_case = 0;
-    info->ts_min = INT64_MAX;
-    info->ts_max = INT64_MIN;
-}
-
-template <bool PRESORTED, bool WANT_TS>
+// A log that claims to be ordered: activities in range, and every event not
+// before its predecessor.  Four events per thread and step (16-byte loads where
+// the columns allow them), the event before them from its own cache lines.
 __global__ __launch_bounds__(256) void k_range_scan(const int32_t* __restrict__ case_id,
                                                     const int32_t* __restrict__ act,
                                                     const int64_t* __restrict__ ts, int64_t n,
                                                     int32_t A, RangePart* part) {
-    __shared__ RangePart red[256 / kWave];
-    int32_t cmin = INT32_MAX, cmax = INT32_MIN;
-    int64_t tmin = INT64_MAX, tmax = INT64_MIN;
-    bool bad_act = false, unsorted = false;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    auto visit = [&](int64_t i, int32_t c, int32_t a) {
-        bad_act |= (uint32_t)a >= (uint32_t)A;
-        cmin = c < cmin ? c : cmin;
-        cmax = c > cmax ? c : cmax;
-        if (WANT_TS || PRESORTED) {
-            const int64_t t = ts[i];
-            tmin = t < tmin ? t : tmin;
-            tmax = t > tmax ? t : tmax;
-            if (PRESORTED && i > 0) {
-                const int32_t c0 = case_id[i - 1];
-                const int64_t t0 = ts[i - 1];
-                unsorted |= (c0 > c) || (c0 == c && t0 > t);
+    bool bad = false, unsorted = false;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(case_id) | reinterpret_cast<uintptr_t>(act) |
+                           reinterpret_cast<uintptr_t>(ts)) & 15) == 0;
+    const int64_t stride = 4 * (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); i < n; i += stride) {
+        const int32_t cp = i > 0 ? case_id[i - 1] : INT32_MIN;
+        const int64_t tp = i > 0 ? ts[i - 1] : INT64_MIN;
+        if (aligned && i + 3 < n) {
+            const int4 c = *reinterpret_cast<const int4*>(case_id + i);
+            const int4 a = *reinterpret_cast<const int4*>(act + i);
+            const longlong2 t0 = *reinterpret_cast<const longlong2*>(ts + i);
+            const longlong2 t1 = *reinterpret_cast<const longlong2*>(ts + i + 2);
+            bad |= (uint32_t)a.x >= (uint32_t)A || (uint32_t)a.y >= (uint32_t)A || (uint32_t)a.z >= (uint32_t)A ||
+                   (uint32_t)a.w >= (uint32_t)A;
+            unsorted |= cp > c.x || (cp == c.x && tp > t0.x);
+            unsorted |= c.x > c.y || (c.x == c.y && t0.x > t0.y);
+            unsorted |= c.y > c.z || (c.y == c.z && t0.y > t1.x);
+            unsorted |= c.z > c.w || (c.z == c.w && t1.x > t1.y);
+        } else {
+            int32_t c0 = cp;
+            int64_t t0 = tp;
+            for (int64_t k = i; k < n && k < i + 4; ++k) {
+                const int32_t c = case_id[k];
+                const int64_t t = ts[k];
+                bad |= (uint32_t)act[k] >= (uint32_t)A;
+                unsorted |= c0 > c || (c0 == c && t0 > t);
+                c0 = c;
+                t0 = t;
             }
         }
-    };
-    if (!WANT_TS && !PRESORTED) {
-        // 16-byte loads of four ids and four activities (the columns are 16-byte aligned
-        // torch/hip allocations; a misaligned start falls back to the scalar loop)
-        const bool aligned = ((reinterpret_cast<uintptr_t>(case_id) | reinterpret_cast<uintptr_t>(act)) & 15) == 0;
-        const int64_t n4 = aligned ? n / 4 : 0;
-        const int4* c4 = reinterpret_cast<const int4*>(case_id);
-        const int4* a4 = reinterpret_cast<const int4*>(act);
-        int64_t q = tid;
-        for (; q + stride < n4; q += 2 * stride) {   // two loads of each column in flight
-            const int4 c = c4[q], cb = c4[q + stride];
-            const int4 a = a4[q], ab = a4[q + stride];
-            visit(4 * q, c.x, a.x);
-            visit(4 * q + 1, c.y, a.y);
-            visit(4 * q + 2, c.z, a.z);
-            visit(4 * q + 3, c.w, a.w);
-            visit(4 * (q + stride), cb.x, ab.x);
-            visit(4 * (q + stride) + 1, cb.y, ab.y);
-            visit(4 * (q + stride) + 2, cb.z, ab.z);
-            visit(4 * (q + stride) + 3, cb.w, ab.w);
-        }
-        for (; q < n4; q += stride) {
-            const int4 c = c4[q];
-            const int4 a = a4[q];
-            visit(4 * q, c.x, a.x);
-            visit(4 * q + 1, c.y, a.y);
-            visit(4 * q + 2, c.z, a.z);
-            visit(4 * q + 3, c.w, a.w);
-        }
-        for (int64_t i = 4 * n4 + tid; i < n; i += stride) visit(i, case_id[i], act[i]);
-    } else {
-        for (int64_t i = tid; i < n; i += stride) visit(i, case_id[i], act[i]);
     }
-    RangePart r;
-    r.cmin = wave_min(cmin);
-    r.cmax = wave_max(cmax);
-    r.tmin = wave_min(tmin);
-    r.tmax = wave_max(tmax);
-    r.bad = __ballot(bad_act) != 0;
-    r.unsorted = __ballot(unsorted) != 0;
-    if (lane() == 0) red[threadIdx.x / kWave] = r;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < 256 / kWave; ++k) {
-            const RangePart& o = red[k];
-            r.cmin = o.cmin < r.cmin ? o.cmin : r.cmin;
-            r.cmax = o.cmax > r.cmax ? o.cmax : r.cmax;
-            r.tmin = o.tmin < r.tmin ? o.tmin : r.tmin;
-            r.tmax = o.tmax > r.tmax ? o.tmax : r.tmax;
-            r.bad |= o.bad;
-            r.unsorted |= o.unsorted;
-        }
-        part[blockIdx.x] = r;
-    }
+    const int any_bad = __syncthreads_or(bad);
+    const int any_unsorted = __syncthreads_or(unsorted);
+    if (threadIdx.x == 0)
+        part[blockIdx.x] = RangePart{INT32_MAX, INT32_MIN, any_bad ? 1 : 0, any_unsorted ? 1 : 0, INT64_MAX, INT64_MIN};
 }
 
 // The formatting step's range scan over radix tiles (kRadixTile events per
@@ -156,8 +110,10 @@ __global__ __launch_bounds__(kRangeTileThreads) void k_range_tiles(const int32_t
     if (threadIdx.x < 256) hist_raw[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// One block folds the per-block partials into the RangeInfo.
-__global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int nparts, RangeInfo* info) {
+// One block folds the per-block partials into the RangeInfo (no partials: an
+// empty log) and starts the call's status word.
+__global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int nparts, RangeInfo* info,
+                                                      int32_t* status) {
     __shared__ RangePart red[1024 / kWave];
     RangePart r{INT32_MAX, INT32_MIN, 0, 0, INT64_MAX, INT64_MIN};
     for (int k = threadIdx.x; k < nparts; k += 1024) {
@@ -192,6 +148,8 @@ __global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int
         info->ts_min = r.tmin;
         info->ts_max = r.tmax;
         info->status = r.bad ? PM4G_E_RANGE : (r.unsorted ? PM4G_E_NOT_SORTED : 0);
+        info->long_case = 0;
+        *status = info->status;
     }
 }
 
@@ -219,26 +177,18 @@ static int range_grid(int64_t n) {
 }
 
 hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const int64_t* ts, int64_t n,
-                             int32_t A, bool presorted, bool want_ts, RangeInfo* info, RangePart* part,
-                             uint32_t* hist_raw, hipStream_t s) {
+                             int32_t A, bool presorted, RangeInfo* info, RangePart* part,
+                             uint32_t* hist_raw, int32_t* status, hipStream_t s) {
     ProfScope p(P_RANGE, s);
-    k_range_init<<<1, 1, 0, s>>>(info);
-    if (n > 0) {
-        if (hist_raw && !presorted && !want_ts) {
-            const int64_t nb = radix_blocks(n);
-            k_range_tiles<<<(unsigned)nb, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, nb);
-            k_range_final<<<1, 1024, 0, s>>>(part, (int)nb, info);
-            return hipGetLastError();
-        }
-        const int g = range_grid(n);
-        if (presorted)
-            k_range_scan<true, true><<<g, 256, 0, s>>>(case_id, act, ts, n, A, part);
-        else if (want_ts)
-            k_range_scan<false, true><<<g, 256, 0, s>>>(case_id, act, ts, n, A, part);
-        else
-            k_range_scan<false, false><<<g, 256, 0, s>>>(case_id, act, ts, n, A, part);
-        k_range_final<<<1, 1024, 0, s>>>(part, g, info);
+    int parts = 0;
+    if (n > 0 && presorted) {
+        parts = range_grid(n);
+        k_range_scan<<<parts, 256, 0, s>>>(case_id, act, ts, n, A, part);
+    } else if (n > 0) {
+        parts = (int)radix_blocks(n);
+        k_range_tiles<<<parts, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, parts);
     }
+    k_range_final<<<1, 1024, 0, s>>>(part, parts, info, status);
     return hipGetLastError();
 }
 
