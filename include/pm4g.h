@@ -20,11 +20,13 @@
  *   - Every array argument is DEVICE memory allocated by the caller, unless the
  *     comment says "host".  The library never allocates or frees device memory;
  *     scratch space is the caller's workspace `ws` of at least
- *     pm4g_workspace_bytes(...) bytes (256-byte aligned).
+ *     pm4g_workspace_bytes(...) bytes (256-byte aligned).  For the words it
+ *     waits for it keeps one pinned host page of 16 KB per process.
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL is the
- *     default stream).  Functions taking a raw (unsorted) log synchronise the
- *     stream once or twice to read a few bytes (key ranges, a long-case flag);
- *     functions taking a prepared log do not synchronise.
+ *     default stream).  Functions taking a raw (unsorted) log wait once or
+ *     twice for a few bytes (key ranges, a long-case flag; their later work
+ *     may still be running when they return, in stream order); functions
+ *     taking a prepared log do not wait.
  *   - Host-detectable errors (NULL pointer, negative size, A outside
  *     [1, PM4G_MAX_ACTIVITIES], n_events >= 2^31, unknown flags, workspace too
  *     small) are returned before anything is enqueued.
@@ -264,8 +266,8 @@ size_t pm4g_workspace_bytes(int op, int64_t n_events, int32_t n_activities, int3
  * Formats a raw log (Sec. 3, first formatting step and the cases table):
  * writes `out`'s arrays and device scalars.  With PM4G_PRESORTED the order is
  * verified instead of computed (status PM4G_E_NOT_SORTED if it does not
- * hold).  Synchronises `stream` once (twice if a case has more than 2049
- * events).  out->n_events and out->n_activities must equal the log's.
+ * hold).  Waits for work on `stream` once or twice (a third time if a case has
+ * more than 2049 events).  out->n_events and out->n_activities must equal the log's.
  */
 int pm4g_prepare(const pm4g_log *log, const pm4g_prepared *out, void *ws, size_t ws_bytes,
                  void *stream);

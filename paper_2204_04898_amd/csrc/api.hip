@@ -162,81 +162,117 @@ int bits_of(uint64_t range) {
     return b;
 }
 
-// Formatting step into `out` (caller's arrays or workspace arrays).  With
-// ws_rows the workspace has room for the row order, and out->row (if not
-// NULL) receives the original row of each position.
-int run_prepare(const pm4g_log* log, const pm4g_prepared* out, bool case_table, Bump& bp,
-                hipStream_t s, bool ws_rows = false) {
+// Formatting step into `out` (caller's arrays or workspace arrays), then what
+// the call does with the formatted log (`after`, enqueues only).  With ws_rows
+// the workspace has room for the row order, and out->row (if not NULL) receives
+// the original row of each position.  With own, `out`'s arrays are the
+// workspace's: a log given as ordered is then used where it is, not copied.
+//
+// The host waits for two things: the range scan's header (the key range decides
+// the passes) and whether the per-case sort met a case beyond its window.  The
+// second answer is almost always no, so `after` is queued before it is known
+// and the GPU goes on; if it is yes, the fallback sorts again and `after` runs
+// again on its result.  Until then the arrays may hold anything where the sort
+// left windows out: the case table is empty in that case (launch_case_table) and
+// the DFG's kernels check every activity they index with.
+template <class After>
+int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& bp, hipStream_t s, bool ws_rows,
+                bool own, const After& after) {
     const int64_t n = log->n_events;
     const int32_t A = log->n_activities;
     const bool presorted = (log->flags & PM4G_PRESORTED) != 0;
     PrepWs w = prep_ws_layout(bp, n, ws_rows);
     int32_t* const row_s = ws_rows ? out->row : nullptr;
     if (!row_s) w.a.row = w.b.row = nullptr;   // the row order is carried only when asked for
-    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, presorted, w.info, w.rpart,
-                               w.hist_raw, out->status, s));
+    HostBack back;
     RangeInfo h{};
+    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, presorted, w.info, w.rpart,
+                               w.hist_raw, out->status, back.dst(), s));
+    const auto table = [&](const uint32_t* wincnt) {
+        return case_table ? launch_case_table(out->case_s, n, w.caseblk, out->case_off, out->case_code, out->n_cases,
+                                              wincnt, w.info, s)
+                          : hipSuccess;
+    };
+    const auto status = [&]() -> int {   // out->status holds it too
+        PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
+        if (h.status != 0)
+            set_err("%s", h.status == PM4G_E_RANGE ? "activity outside [0, n_activities)"
+                                                   : "rows are not in (case, timestamp, row) order");
+        return h.status;
+    };
+    if (presorted || n == 0) {
+        // nothing depends on the scan but the status: everything is queued first
+        if (own && presorted) {
+            out->case_s = const_cast<int32_t*>(log->case_id);
+            out->act_s = const_cast<int32_t*>(log->activity);
+            out->ts_s = const_cast<int64_t*>(log->timestamp);
+        } else {
+            PM4G_HIP(launch_copy_log(log->case_id, log->activity, log->timestamp, n, out->case_s, out->act_s, out->ts_s,
+                                     row_s, s));
+        }
+        PM4G_HIP(table(nullptr));
+        if (back.live()) {
+            if (int rc = after()) return rc;
+            return status();
+        }
+        if (int rc = status()) return rc;   // copied from the workspace, which `after` may use again
+        return after();
+    }
+    if (int rc = status()) return rc;
+    const SortBufs raw{(uint32_t*)log->case_id, (int64_t*)log->timestamp, (uint32_t*)log->activity, nullptr};
+    const int case_bits = bits_of((uint64_t)(uint32_t)(h.case_max - h.case_min));
+    const int act_bits = bits_of((uint64_t)(A - 1));
+    // packed keys (activity above the case bits) when both fit in 32 bits
+    const int act_shift = (case_bits > 0 && case_bits < 32 && case_bits + act_bits <= 32) ? case_bits : 0;
+    int passes = (case_bits + 7) / 8;
+    if (passes == 0) passes = 1;   // a single case: one pass still biases the keys
+    SortBufs bufs[2] = {w.a, w.b};
+    SortBufs in = raw;
+    int cur = 0;
+    for (int p = 0; p < passes; ++p) {
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, p == 0, w.info, w.hist, w.rowsum, act_shift,
+                                   p == 0 ? w.hist_raw : nullptr, s));
+        in = bufs[cur];
+        cur ^= 1;
+    }
+    PM4G_HIP(launch_segsort(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, w.wincnt, row_s, s));
+    const bool may_be_long = n > kSegCap;   // a log that fits one window has no longer case
+    if (may_be_long) PM4G_HIP(launch_publish(w.info, back.dst(), s));
+    PM4G_HIP(table(w.wincnt));
+    if (may_be_long && !back.live()) PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
+    if (!h.long_case) {
+        if (int rc = after()) return rc;
+        if (!may_be_long || !back.live()) return PM4G_OK;
+        PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
+        if (!h.long_case) return PM4G_OK;
+    }
+    // Full-key fallback: stable passes on the timestamp bits, then the case bits.
+    // `after` may use the sort's workspace again (the raw-log entry points do):
+    // it is done before the passes, in stream order, but the header has to be
+    // put back.
+    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, false, w.info, w.rpart, w.hist_raw,
+                               out->status, BackDst{nullptr, nullptr, 0}, s));
+    PM4G_HIP(launch_ts_range(log->timestamp, n, w.info, s));
     PM4G_HIP(hipMemcpyAsync(&h, w.info, sizeof(h), hipMemcpyDeviceToHost, s));
     PM4G_HIP(hipStreamSynchronize(s));
-    if (h.status != 0) {   // out->status holds it
-        set_err("%s", h.status == PM4G_E_RANGE ? "activity outside [0, n_activities)"
-                                               : "rows are not in (case, timestamp, row) order");
-        return h.status;
+    const int ts_bits = bits_of((uint64_t)h.ts_max - (uint64_t)h.ts_min);
+    const int ts_passes = (ts_bits + 7) / 8;
+    in = raw;
+    cur = 0;
+    bool first = true;
+    for (int p = 0; p < ts_passes; ++p, first = false) {
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 1, 8 * p, first, w.info, w.hist, w.rowsum, act_shift, nullptr, s));
+        in = bufs[cur];
+        cur ^= 1;
     }
-    bool have_wincnt = false;   // the per-case sort counted the cases of each window
-    if (presorted) {
-        PM4G_HIP(launch_copy_log(log->case_id, log->activity, log->timestamp, n, out->case_s,
-                                 out->act_s, out->ts_s, row_s, s));
-    } else if (n > 0) {
-        const SortBufs raw{(uint32_t*)log->case_id, (int64_t*)log->timestamp, (uint32_t*)log->activity, nullptr};
-        const int case_bits = bits_of((uint64_t)(uint32_t)(h.case_max - h.case_min));
-        const int act_bits = bits_of((uint64_t)(A - 1));
-        // packed keys (activity above the case bits) when both fit in 32 bits
-        const int act_shift = (case_bits > 0 && case_bits < 32 && case_bits + act_bits <= 32) ? case_bits : 0;
-        int passes = (case_bits + 7) / 8;
-        if (passes == 0) passes = 1;   // a single case: one pass still biases the keys
-        SortBufs bufs[2] = {w.a, w.b};
-        SortBufs in = raw;
-        int cur = 0;
-        for (int p = 0; p < passes; ++p) {
-            PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, p == 0, w.info, w.hist, w.rowsum, act_shift,
-                                       p == 0 ? w.hist_raw : nullptr, s));
-            in = bufs[cur];
-            cur ^= 1;
-        }
-        PM4G_HIP(launch_segsort(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, w.wincnt, row_s, s));
-        PM4G_HIP(hipMemcpyAsync(&h, w.info, sizeof(h), hipMemcpyDeviceToHost, s));
-        PM4G_HIP(hipStreamSynchronize(s));
-        have_wincnt = !h.long_case;
-        if (h.long_case) {
-            // Full-key fallback: stable passes on the timestamp bits, then the case bits.
-            PM4G_HIP(launch_ts_range(log->timestamp, n, w.info, s));
-            PM4G_HIP(hipMemcpyAsync(&h, w.info, sizeof(h), hipMemcpyDeviceToHost, s));
-            PM4G_HIP(hipStreamSynchronize(s));
-            const int ts_bits = bits_of((uint64_t)h.ts_max - (uint64_t)h.ts_min);
-            const int ts_passes = (ts_bits + 7) / 8;
-            in = raw;
-            cur = 0;
-            bool first = true;
-            for (int p = 0; p < ts_passes; ++p, first = false) {
-                PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 1, 8 * p, first, w.info, w.hist, w.rowsum,
-                                           act_shift, nullptr, s));
-                in = bufs[cur];
-                cur ^= 1;
-            }
-            for (int p = 0; p < passes; ++p, first = false) {
-                PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, first, w.info, w.hist, w.rowsum,
-                                           act_shift, nullptr, s));
-                in = bufs[cur];
-                cur ^= 1;
-            }
-            PM4G_HIP(launch_unbias_copy(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, row_s, s));
-        }
+    for (int p = 0; p < passes; ++p, first = false) {
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, first, w.info, w.hist, w.rowsum, act_shift, nullptr, s));
+        in = bufs[cur];
+        cur ^= 1;
     }
-    if (case_table)
-        PM4G_HIP(launch_case_table(out->case_s, n, w.caseblk, out->case_off, out->case_code,
-                                   out->n_cases, have_wincnt ? w.wincnt : nullptr, s));
-    return PM4G_OK;
+    PM4G_HIP(launch_unbias_copy(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, row_s, s));
+    PM4G_HIP(table(nullptr));
+    return after();
 }
 
 // Library-owned workspace of pm4g_dfg_prepared_noalloc: one copy per GPU,
@@ -275,6 +311,15 @@ int scratch_of_current_device(void** ptr) {
 DfgOutDev dev_out(const pm4g_dfg_out* o) {
     return DfgOutDev{o->count, o->dt_sum, o->dt_min, o->dt_max, o->dt_mean, o->start_count,
                      o->end_count, o->act_count, o->n_cases, o->overflow, o->status};
+}
+
+// A raw-log call's data error, in its own status word too.
+int raw_status(int rc, int32_t* status, hipStream_t s) {
+    if (rc == PM4G_E_RANGE || rc == PM4G_E_NOT_SORTED) {
+        k_set_status<<<1, 1, 0, s>>>(status, rc);
+        PM4G_HIP(hipGetLastError());
+    }
+    return rc;
 }
 
 int check_dfg_out(const pm4g_dfg_out* o) {
@@ -538,14 +583,14 @@ int pm4g_ingest_csv(const uint8_t* text, int64_t n_bytes, const pm4g_csv_schema*
     // values are matched by 64-bit hash, then checked byte by byte; the code
     // kernels do nothing after a parse or capacity error or a collision (two
     // values, one hash), and a collision repeats the call with the next seed
-    int64_t sc_host[16];
+    int64_t sc_host[kBackWords];
+    HostBack back;
     for (uint64_t attempt = 0;; ++attempt) {
         PM4G_HIP(launch_csv_parse(text, n_bytes, *sc, 0x5851F42D4C957F2Dull * (attempt + 1),
                                   attempt == 0 ? g_csv_hash_bits : 0, out->capacity, w, *out, s));
         PM4G_HIP(launch_csv_codes(w, out->capacity, *out, s));
-        PM4G_HIP(launch_csv_finish(w, *out, s));
-        PM4G_HIP(hipMemcpyAsync(sc_host, w.scal, sizeof(sc_host), hipMemcpyDeviceToHost, s));
-        PM4G_HIP(hipStreamSynchronize(s));
+        PM4G_HIP(launch_csv_finish(w, *out, back.dst(), s));
+        PM4G_HIP(back.wait(w.scal, sc_host, kBackWords, s));
         if (sc_host[6] || sc_host[3] != INT64_MAX || !sc_host[4]) break;
         PM4G_CHECK(attempt < 8, "value hashes kept colliding");
     }
@@ -667,10 +712,10 @@ int pm4g_ingest_parquet(const uint8_t* file, int64_t n_bytes, const pm4g_parquet
     // kernels do nothing after a decode error or a null
     PM4G_HIP(launch_pq_match(file, w, rows, 0x2545F4914F6CDD1Dull, g_csv_hash_bits, s));
     PM4G_HIP(launch_pq_codes(w, rows, *out, s));
-    PM4G_HIP(launch_pq_finish(w, *out, s));
-    int64_t sc_host[16];
-    PM4G_HIP(hipMemcpyAsync(sc_host, w.scal, sizeof(sc_host), hipMemcpyDeviceToHost, s));
-    PM4G_HIP(hipStreamSynchronize(s));
+    HostBack back;
+    PM4G_HIP(launch_pq_finish(w, *out, back.dst(), s));
+    int64_t sc_host[kBackWords];
+    PM4G_HIP(back.wait(w.scal, sc_host, kBackWords, s));
     if (sc_host[0] != 0) {
         set_err("%s", sc_host[0] == PM4G_E_UNSUPPORTED ? "a page encoding outside the covered subset"
                                                        : "malformed Parquet page");
@@ -774,7 +819,8 @@ int pm4g_prepare(const pm4g_log* log, const pm4g_prepared* out, void* ws, size_t
         return PM4G_E_WORKSPACE;
     }
     Bump bp(ws);
-    return run_prepare(log, out, true, bp, (hipStream_t)stream, true);
+    pm4g_prepared p = *out;
+    return run_prepare(log, &p, true, bp, (hipStream_t)stream, true, false, [] { return (int)PM4G_OK; });
 }
 
 int pm4g_dfg_prepared(const pm4g_prepared* log, const pm4g_dfg_out* out, void* ws, size_t ws_size,
@@ -831,22 +877,14 @@ int pm4g_dfg(const pm4g_log* log, const pm4g_dfg_out* out, void* ws, size_t ws_s
     Bump bp(ws);
     pm4g_prepared p = prepared_in_ws(bp, log->n_events, log->n_activities);
     const size_t rest = bp.off;
-    {
-        Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-        int rc = run_prepare(log, &p, false, b2, s);
-        if (rc != PM4G_OK) {
-            if (rc != PM4G_E_DEVICE) {
-                k_set_status<<<1, 1, 0, s>>>(out->status, rc);
-                PM4G_HIP(hipGetLastError());
-            }
-            return rc;
-        }
-    }
-    Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-    DfgWs w = dfg_ws_layout(b3, log->n_events, log->n_activities);
-    PM4G_HIP(launch_dfg(p.case_s, p.act_s, p.ts_s, p.n_events, p.n_activities, p.status, w,
-                        dev_out(out), s));
-    return PM4G_OK;
+    Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
+    const int rc = run_prepare(log, &p, false, b2, s, false, true, [&]() -> int {
+        Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
+        DfgWs w = dfg_ws_layout(b3, log->n_events, log->n_activities);
+        PM4G_HIP(launch_dfg(p.case_s, p.act_s, p.ts_s, p.n_events, p.n_activities, p.status, w, dev_out(out), s));
+        return PM4G_OK;
+    });
+    return raw_status(rc, out->status, s);
 }
 
 int pm4g_variants_prepared(const pm4g_prepared* log, const pm4g_variants_out* out, void* ws,
@@ -881,24 +919,17 @@ int pm4g_variants(const pm4g_log* log, const pm4g_variants_out* out, void* ws, s
     Bump bp(ws);
     pm4g_prepared p = prepared_in_ws(bp, log->n_events, log->n_activities);
     const size_t rest = bp.off;
-    {
-        Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-        int rc = run_prepare(log, &p, true, b2, s);
-        if (rc != PM4G_OK) {
-            if (rc != PM4G_E_DEVICE) {
-                k_set_status<<<1, 1, 0, s>>>(out->status, rc);
-                PM4G_HIP(hipGetLastError());
-            }
-            return rc;
-        }
-    }
-    Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-    VarWs w = var_ws_layout(b3, log->n_events);
-    const VarOutDev o{out->n_variants, out->var_count, out->var_len, out->var_rep,
-                      out->var_off,    out->var_acts,  out->case_variant, out->status};
-    PM4G_HIP(launch_variants(p.act_s, p.case_off, p.case_code, p.n_cases, p.status, p.n_events, w, o,
-                             (uint32_t)g_variant_hash_bits, s));
-    return PM4G_OK;
+    Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
+    const int rc = run_prepare(log, &p, true, b2, s, false, true, [&]() -> int {
+        Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
+        VarWs w = var_ws_layout(b3, log->n_events);
+        const VarOutDev o{out->n_variants, out->var_count, out->var_len, out->var_rep,
+                          out->var_off,    out->var_acts,  out->case_variant, out->status};
+        PM4G_HIP(launch_variants(p.act_s, p.case_off, p.case_code, p.n_cases, p.status, p.n_events, w, o,
+                                 (uint32_t)g_variant_hash_bits, s));
+        return PM4G_OK;
+    });
+    return raw_status(rc, out->status, s);
 }
 
 }  // extern "C"

@@ -60,7 +60,12 @@ __device__ __forceinline__ uint32_t tile_count(const uint32_t* cnt, int64_t nc, 
 }
 
 __global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t nc, int per_tile, uint32_t* blockoff,
-                                                    int64_t nb, int64_t n, int64_t* case_off, int64_t* n_cases) {
+                                                    int64_t nb, int64_t n, int64_t* case_off, int64_t* n_cases,
+                                                    const RangeInfo* info) {
+    if (info && info->long_case) {   // uncounted windows
+        if (threadIdx.x == 0) *n_cases = case_off[0] = 0;
+        return;
+    }
     __shared__ uint32_t tmp[1024 / kWave + 1];
     constexpr int kT = 4;   // tiles per thread and step
     uint32_t run = 0;
@@ -90,7 +95,11 @@ __global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t
 __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ case_s, int64_t n,
                                                    const uint32_t* blockoff, const uint32_t* cnt, int64_t nc,
                                                    int per_tile, int64_t* case_off, int32_t* case_code,
-                                                   int64_t* n_cases) {
+                                                   int64_t* n_cases, const RangeInfo* info) {
+    if (info && info->long_case) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *n_cases = case_off[0] = 0;
+        return;
+    }
     // striped layout (coalesced loads): item k of thread t is position base + k*256 + t,
     // so position order is (k, wave, lane) order; ranks from ballots + one small scan
     constexpr int kNW = kCB / kWave;
@@ -146,7 +155,8 @@ __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ c
 }
 
 hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcnt, int64_t* case_off,
-                             int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, hipStream_t s) {
+                             int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, const RangeInfo* info,
+                             hipStream_t s) {
     ProfScope p(P_CASE_TABLE, s);
     const int64_t nb = case_blocks(n);
     // nb partial sums of the tiles before: nb^2 / 2 cached loads against a launch
@@ -156,16 +166,17 @@ hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcn
     int64_t nc = segsort_blocks(n);
     int per_tile = kPerTile;
     if (!wincnt) {
+        info = nullptr;
         if (nb > 0) k_case_count<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, blockcnt);
         cnt = blockcnt;
         nc = nb;
         per_tile = 1;
     }
     const bool scan = nb == 0 || nb > kCaseDirect;
-    if (scan) k_case_scan<<<1, 1024, 0, s>>>(cnt, nc, per_tile, blockcnt, nb, n, case_off, n_cases);
+    if (scan) k_case_scan<<<1, 1024, 0, s>>>(cnt, nc, per_tile, blockcnt, nb, n, case_off, n_cases, info);
     if (nb > 0)
         k_case_emit<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, scan ? blockcnt : nullptr, cnt, nc, per_tile, case_off,
-                                                 case_code, n_cases);
+                                                 case_code, n_cases, info);
     return hipGetLastError();
 }
 

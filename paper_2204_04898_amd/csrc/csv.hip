@@ -949,11 +949,12 @@ __global__ __launch_bounds__(256) void k_csv_emit(CsvWs w, int32_t* __restrict__
     }
 }
 
-__global__ void k_csv_finish(CsvWs w, int64_t* n_rows, int32_t* status, int64_t* bad_row) {
+__global__ void k_csv_finish(CsvWs w, int64_t* n_rows, int32_t* status, int64_t* bad_row, BackDst back) {
     const bool over = w.scal[6] != 0, bad = w.scal[3] != INT64_MAX;
     *n_rows = (over || bad) ? 0 : w.scal[2];
     *bad_row = bad ? w.scal[3] : -1;
     *status = over ? PM4G_E_CAPACITY : (bad ? PM4G_E_PARSE : 0);
+    publish(back, w.scal, kBackWords);
 }
 
 unsigned grid_rows(int64_t rows) {
@@ -1005,8 +1006,8 @@ hipError_t launch_csv_codes(CsvWs w, int64_t max_rows, const pm4g_csv_out& o, hi
     return hipGetLastError();
 }
 
-hipError_t launch_csv_finish(CsvWs w, const pm4g_csv_out& o, hipStream_t s) {
-    k_csv_finish<<<1, 1, 0, s>>>(w, o.n_rows, o.status, o.bad_row);
+hipError_t launch_csv_finish(CsvWs w, const pm4g_csv_out& o, BackDst back, hipStream_t s) {
+    k_csv_finish<<<1, 1, 0, s>>>(w, o.n_rows, o.status, o.bad_row, back);
     return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "../../include/pm4g.h"
+#include "hostback.hpp"
 
 namespace pm4g {
 
@@ -49,10 +50,15 @@ struct Bump {
 // ---- range scan (range.hip) ----
 // hist_raw: [256][radix tiles] histograms of the raw case id's low byte, for
 // the first radix pass (raw logs only; the partials then have one entry per
-// radix tile).  status: the call's status word, set to the scan's.
+// radix tile).  status: the call's status word, set to the scan's.  back: the
+// header, as kInfoWords words.
+constexpr int kInfoWords = sizeof(RangeInfo) / sizeof(int64_t);
+static_assert(kInfoWords <= kBackWords, "the header fits a slot");
 hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const int64_t* ts, int64_t n,
                              int32_t A, bool presorted, RangeInfo* info, RangePart* part,
-                             uint32_t* hist_raw, int32_t* status, hipStream_t s);
+                             uint32_t* hist_raw, int32_t* status, BackDst back, hipStream_t s);
+// The header to the host, once the stream gets here.
+hipError_t launch_publish(const RangeInfo* info, BackDst back, hipStream_t s);
 hipError_t launch_ts_range(const int64_t* ts, int64_t n, RangeInfo* info, hipStream_t s);
 
 // ---- LSD radix passes over (case key u32, ts i64, act u32) elements (radix.hip) ----
@@ -110,9 +116,12 @@ hipError_t launch_copy_log(const int32_t* c, const int32_t* a, const int64_t* t,
 // ---- case table (cases.hip) ----
 constexpr int kCaseTile = 4096;
 inline int64_t case_blocks(int64_t n) { return (n + kCaseTile - 1) / kCaseTile; }
-// wincnt (may be NULL): cases starting in each kSegWindow window, from k_segsort.
+// wincnt (may be NULL): cases starting in each kSegWindow window, from k_segsort;
+// info then tells whether k_segsort met a long case, whose windows are not
+// counted: the table is left empty (no cases).
 hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcnt, int64_t* case_off,
-                             int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, hipStream_t s);
+                             int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, const RangeInfo* info,
+                             hipStream_t s);
 
 // ---- DFG aggregation (dfg.hip) ----
 constexpr int kCellsPerTable = 4096;     // one LDS table of cells
@@ -419,7 +428,7 @@ hipError_t launch_csv_lines(const uint8_t* text, int64_t n_bytes, int has_header
 hipError_t launch_csv_parse(const uint8_t* text, int64_t n_bytes, const pm4g_csv_schema& sc, uint64_t seed,
                             int hash_bits, int64_t max_rows, CsvWs w, const pm4g_csv_out& o, hipStream_t s);
 hipError_t launch_csv_codes(CsvWs w, int64_t max_rows, const pm4g_csv_out& o, hipStream_t s);
-hipError_t launch_csv_finish(CsvWs w, const pm4g_csv_out& o, hipStream_t s);
+hipError_t launch_csv_finish(CsvWs w, const pm4g_csv_out& o, BackDst back, hipStream_t s);
 
 
 // ---- Parquet ingestion (parquet.hip) ----
@@ -471,6 +480,6 @@ hipError_t launch_pq_decode(const uint8_t* file, PqWs w, int64_t n_chunks, int64
 hipError_t launch_pq_match(const uint8_t* file, PqWs w, int64_t rows, uint64_t seed, int hash_bits,
                            hipStream_t s);
 hipError_t launch_pq_codes(PqWs w, int64_t rows, const pm4g_csv_out& o, hipStream_t s);
-hipError_t launch_pq_finish(PqWs w, const pm4g_csv_out& o, hipStream_t s);
+hipError_t launch_pq_finish(PqWs w, const pm4g_csv_out& o, BackDst back, hipStream_t s);
 
 }  // namespace pm4g

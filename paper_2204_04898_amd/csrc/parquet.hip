@@ -1252,12 +1252,13 @@ __global__ void k_pq_init(PqWs w, int64_t rows) {
     }
 }
 
-__global__ void k_pq_finish(PqWs w, int64_t* n_rows, int32_t* status, int64_t* bad_row) {
+__global__ void k_pq_finish(PqWs w, int64_t* n_rows, int32_t* status, int64_t* bad_row, BackDst back) {
     const int64_t err = w.scal[0];
     const bool null = w.scal[1] != INT64_MAX;
     *n_rows = (err || null) ? 0 : w.scal[3];
     *bad_row = (!err && null) ? w.scal[1] : -1;
     *status = err ? (int32_t)err : (null ? PM4G_E_PARSE : 0);
+    publish(back, w.scal, kBackWords);
 }
 
 unsigned grid_of(int64_t rows) {
@@ -1301,8 +1302,8 @@ hipError_t launch_pq_codes(PqWs w, int64_t rows, const pm4g_csv_out& o, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_pq_finish(PqWs w, const pm4g_csv_out& o, hipStream_t s) {
-    k_pq_finish<<<1, 1, 0, s>>>(w, o.n_rows, o.status, o.bad_row);
+hipError_t launch_pq_finish(PqWs w, const pm4g_csv_out& o, BackDst back, hipStream_t s) {
+    k_pq_finish<<<1, 1, 0, s>>>(w, o.n_rows, o.status, o.bad_row, back);
     return hipGetLastError();
 }
 

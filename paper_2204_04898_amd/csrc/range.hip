@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kRangeTileThreads) void k_range_tiles(const int32_t
 // One block folds the per-block partials into the RangeInfo (no partials: an
 // empty log) and starts the call's status word.
 __global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int nparts, RangeInfo* info,
-                                                      int32_t* status) {
+                                                      int32_t* status, BackDst back) {
     __shared__ RangePart red[1024 / kWave];
     RangePart r{INT32_MAX, INT32_MIN, 0, 0, INT64_MAX, INT64_MIN};
     for (int k = threadIdx.x; k < nparts; k += 1024) {
@@ -150,6 +150,7 @@ __global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int
         info->status = r.bad ? PM4G_E_RANGE : (r.unsorted ? PM4G_E_NOT_SORTED : 0);
         info->long_case = 0;
         *status = info->status;
+        publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
     }
 }
 
@@ -170,6 +171,15 @@ __global__ __launch_bounds__(256) void k_ts_range(const int64_t* __restrict__ ts
     }
 }
 
+__global__ void k_publish(const RangeInfo* info, BackDst back) {
+    publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
+}
+
+hipError_t launch_publish(const RangeInfo* info, BackDst back, hipStream_t s) {
+    if (back.words) k_publish<<<1, 1, 0, s>>>(info, back);
+    return hipGetLastError();
+}
+
 static int range_grid(int64_t n) {
     int64_t g = (n + 255) / 256;
     if (g > kRangeParts) g = kRangeParts;
@@ -178,7 +188,7 @@ static int range_grid(int64_t n) {
 
 hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const int64_t* ts, int64_t n,
                              int32_t A, bool presorted, RangeInfo* info, RangePart* part,
-                             uint32_t* hist_raw, int32_t* status, hipStream_t s) {
+                             uint32_t* hist_raw, int32_t* status, BackDst back, hipStream_t s) {
     ProfScope p(P_RANGE, s);
     int parts = 0;
     if (n > 0 && presorted) {
@@ -188,7 +198,7 @@ hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const i
         parts = (int)radix_blocks(n);
         k_range_tiles<<<parts, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, parts);
     }
-    k_range_final<<<1, 1024, 0, s>>>(part, parts, info, status);
+    k_range_final<<<1, 1024, 0, s>>>(part, parts, info, status, back);
     return hipGetLastError();
 }
 

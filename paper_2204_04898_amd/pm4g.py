@@ -292,13 +292,13 @@ class Prepared:
     @staticmethod
     def empty(n: int, A: int, device, rows: bool = False) -> "Prepared":
         m = max(n, 1)
+        head = torch.zeros(2, dtype=torch.int64, device=device)   # one fill for both scalars
         return Prepared(case_s=torch.empty(n, dtype=torch.int32, device=device),
                         act_s=torch.empty(n, dtype=torch.int32, device=device),
                         ts_s=torch.empty(n, dtype=torch.int64, device=device),
                         case_off=torch.empty(m + 1, dtype=torch.int64, device=device),
                         case_code=torch.empty(m, dtype=torch.int32, device=device),
-                        n_cases=torch.zeros(1, dtype=torch.int64, device=device),
-                        status=torch.zeros(1, dtype=torch.int32, device=device), n_activities=A,
+                        n_cases=head[:1], status=head[1:].view(torch.int32)[:1], n_activities=A,
                         row=torch.empty(n, dtype=torch.int32, device=device) if rows else None)
 
 
@@ -326,9 +326,9 @@ def _dfg_out(A: int, device) -> dict:
              start_count=torch.empty(A, dtype=torch.int64, device=device),
              end_count=torch.empty(A, dtype=torch.int64, device=device),
              act_count=torch.empty(A, dtype=torch.int64, device=device),
-             n_cases=torch.zeros(1, dtype=torch.int64, device=device),
-             overflow=torch.zeros(1, dtype=torch.int32, device=device),
-             status=torch.zeros(1, dtype=torch.int32, device=device))
+             n_cases=torch.empty(1, dtype=torch.int64, device=device),
+             overflow=torch.empty(1, dtype=torch.int32, device=device),
+             status=torch.empty(1, dtype=torch.int32, device=device))
     return o
 
 
@@ -377,14 +377,14 @@ def pm4g_dfg_prepared_noalloc(prep: Prepared, out: dict, stream=None) -> dict:
 
 def _var_out(n: int, device, with_cases: bool = True) -> dict:
     m = max(n, 1)
-    return dict(n_variants=torch.zeros(1, dtype=torch.int64, device=device),
+    return dict(n_variants=torch.empty(1, dtype=torch.int64, device=device),
                 var_count=torch.empty(m, dtype=torch.int64, device=device),
                 var_len=torch.empty(m, dtype=torch.int32, device=device),
                 var_rep=torch.empty(m, dtype=torch.int32, device=device),
                 var_off=torch.empty(m + 1, dtype=torch.int64, device=device),
                 var_acts=torch.empty(m, dtype=torch.int32, device=device),
                 case_variant=torch.empty(m, dtype=torch.int32, device=device) if with_cases else None,
-                status=torch.zeros(1, dtype=torch.int32, device=device))
+                status=torch.empty(1, dtype=torch.int32, device=device))
 
 
 def _var_struct(o: dict) -> _VarOut:
@@ -471,6 +471,7 @@ def views_to_device(views, device) -> tuple[torch.Tensor, torch.Tensor]:
 def _batched_out(V: int, A: int, cap_edges: int, device) -> dict:
     cap = max(int(cap_edges), 1)
     i64 = dict(dtype=torch.int64, device=device)
+    head = torch.zeros(6, **i64)   # one fill for both
     return dict(edge_off=torch.empty(V + 1, **i64),
                 src=torch.empty(cap, dtype=torch.int32, device=device),
                 dst=torch.empty(cap, dtype=torch.int32, device=device),
@@ -479,8 +480,8 @@ def _batched_out(V: int, A: int, cap_edges: int, device) -> dict:
                 dt_mean=torch.empty(cap, dtype=torch.float64, device=device),
                 start_count=torch.empty(max(V * A, 1), **i64), end_count=torch.empty(max(V * A, 1), **i64),
                 act_count=torch.empty(max(V * A, 1), **i64), n_events=torch.empty(max(V, 1), **i64),
-                n_cases=torch.empty(max(V, 1), **i64), required=torch.zeros(5, **i64),
-                status=torch.zeros(1, dtype=torch.int32, device=device), cap_edges=cap)
+                n_cases=torch.empty(max(V, 1), **i64), required=head[:5], status=head[5:].view(torch.int32)[:1],
+                cap_edges=cap)
 
 
 def _batched_struct(o: dict) -> _BatchedOut:
@@ -532,8 +533,7 @@ def pm4g_dfg_batched(prep: Prepared, views: torch.Tensor, masks: torch.Tensor, n
         rc = L.pm4g_dfg_batched(ctypes.byref(p), _ptr(views), _ptr(masks), int(n_views), ctypes.byref(s),
                                 ctypes.byref(t), _ptr(ws), need, _stream(stream))
         if rc == PM4G_OK:
-            (torch.cuda.current_stream() if stream is None else stream).synchronize()
-            status = int(o["status"].item())
+            status = int(o["status"].item())   # waits for the current stream, which is the call's
             if status == PM4G_OK:
                 return o
             if status != PM4G_E_CAPACITY or not retry:
@@ -612,6 +612,19 @@ def pm4g_sample(prep: Prepared, k: int, seed: int, by_events: bool = False, out:
     return o
 
 
+def _ingest_out(capacity: int, dev) -> tuple[dict, torch.Tensor]:
+    """Outputs of the ingestion calls, and the three counts as one tensor."""
+    cap = max(int(capacity), 1)
+    i32 = dict(dtype=torch.int32, device=dev)
+    i64 = dict(dtype=torch.int64, device=dev)
+    head = torch.zeros(5, **i64)   # one fill
+    o = dict(case_code=torch.empty(cap, **i32), act_code=torch.empty(cap, **i32), ts=torch.empty(cap, **i64),
+             n_rows=head[:1], case_dict_off=torch.empty(cap, **i64), case_dict_len=torch.empty(cap, **i32),
+             n_cases=head[1:2], act_dict_off=torch.empty(cap, **i64), act_dict_len=torch.empty(cap, **i32),
+             n_acts=head[2:3], bad_row=head[3:4], status=head[4:].view(torch.int32)[:1])
+    return o, head[:3]
+
+
 @_on_stream
 def pm4g_ingest_csv(text: torch.Tensor, case_col: int, act_col: int, ts_col: int, sep: bytes = b",",
                     has_header: bool = True, ts_iso: bool = False, ts_scale: int = 3, capacity: int | None = None,
@@ -626,13 +639,7 @@ def pm4g_ingest_csv(text: torch.Tensor, case_col: int, act_col: int, ts_col: int
     n = int(text.numel())
     if capacity is None:
         capacity = int((text == 10).sum().item()) + 1
-    cap = max(int(capacity), 1)
-    i32 = dict(dtype=torch.int32, device=dev)
-    i64 = dict(dtype=torch.int64, device=dev)
-    o = dict(case_code=torch.empty(cap, **i32), act_code=torch.empty(cap, **i32), ts=torch.empty(cap, **i64),
-             n_rows=torch.zeros(1, **i64), case_dict_off=torch.empty(cap, **i64), case_dict_len=torch.empty(cap, **i32),
-             n_cases=torch.zeros(1, **i64), act_dict_off=torch.empty(cap, **i64), act_dict_len=torch.empty(cap, **i32),
-             n_acts=torch.zeros(1, **i64), status=torch.zeros(1, **i32), bad_row=torch.zeros(1, **i64))
+    o, counts = _ingest_out(capacity, dev)
     need = int(L.pm4g_ingest_csv_workspace_bytes(n, int(capacity)))
     ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     sc = CsvSchema(int(case_col), int(act_col), int(ts_col), 1 if has_header else 0, 1 if ts_iso else 0,
@@ -641,7 +648,7 @@ def pm4g_ingest_csv(text: torch.Tensor, case_col: int, act_col: int, ts_col: int
                 _ptr(o["case_dict_off"]), _ptr(o["case_dict_len"]), _ptr(o["n_cases"]), _ptr(o["act_dict_off"]),
                 _ptr(o["act_dict_len"]), _ptr(o["n_acts"]), _ptr(o["status"]), _ptr(o["bad_row"]))
     _check(L.pm4g_ingest_csv(_ptr(text), n, ctypes.byref(sc), ctypes.byref(q), _ptr(ws), need, _stream(stream)))
-    r, c, a = int(o["n_rows"].item()), int(o["n_cases"].item()), int(o["n_acts"].item())
+    r, c, a = counts.tolist()
     res = {k: o[k][:r] for k in ("case_code", "act_code", "ts")}
     res.update(case_dict_off=o["case_dict_off"][:c], case_dict_len=o["case_dict_len"][:c],
                act_dict_off=o["act_dict_off"][:a], act_dict_len=o["act_dict_len"][:a], n_rows=r, n_cases=c,
@@ -667,13 +674,7 @@ def pm4g_ingest_parquet(data: torch.Tensor, case_col: int, act_col: int, ts_col:
         rows = ctypes.c_int64(0)
         _check(L.pm4g_parquet_rows(_ptr(data), n, ctypes.byref(rows), s))
         capacity = int(rows.value)
-    cap = max(int(capacity), 1)
-    i32 = dict(dtype=torch.int32, device=dev)
-    i64 = dict(dtype=torch.int64, device=dev)
-    o = dict(case_code=torch.empty(cap, **i32), act_code=torch.empty(cap, **i32), ts=torch.empty(cap, **i64),
-             n_rows=torch.zeros(1, **i64), case_dict_off=torch.empty(cap, **i64), case_dict_len=torch.empty(cap, **i32),
-             n_cases=torch.zeros(1, **i64), act_dict_off=torch.empty(cap, **i64), act_dict_len=torch.empty(cap, **i32),
-             n_acts=torch.zeros(1, **i64), status=torch.zeros(1, **i32), bad_row=torch.zeros(1, **i64))
+    o, counts = _ingest_out(capacity, dev)
     need = int(L.pm4g_ingest_parquet_workspace_bytes(n, int(capacity)))
     ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     sc = ParquetSchema(int(case_col), int(act_col), int(ts_col), 0)
@@ -681,7 +682,7 @@ def pm4g_ingest_parquet(data: torch.Tensor, case_col: int, act_col: int, ts_col:
                 _ptr(o["case_dict_off"]), _ptr(o["case_dict_len"]), _ptr(o["n_cases"]), _ptr(o["act_dict_off"]),
                 _ptr(o["act_dict_len"]), _ptr(o["n_acts"]), _ptr(o["status"]), _ptr(o["bad_row"]))
     _check(L.pm4g_ingest_parquet(_ptr(data), n, ctypes.byref(sc), ctypes.byref(q), _ptr(ws), need, s))
-    r, c, a = int(o["n_rows"].item()), int(o["n_cases"].item()), int(o["n_acts"].item())
+    r, c, a = counts.tolist()
     res = {k: o[k][:r] for k in ("case_code", "act_code", "ts")}
     res.update(case_dict_off=o["case_dict_off"][:c], case_dict_len=o["case_dict_len"][:c],
                act_dict_off=o["act_dict_off"][:a], act_dict_len=o["act_dict_len"][:a], n_rows=r, n_cases=c,
@@ -707,8 +708,8 @@ def pm4g_efg(prep: Prepared, out: dict | None = None, ws: torch.Tensor | None = 
         out = dict(count=torch.empty(cells, **i64), sum_lo=torch.empty(cells, **i64), sum_hi=torch.empty(cells, **i64),
                    sq_lo=torch.empty(cells, **i64), sq_hi=torch.empty(cells, **i64),
                    mean=torch.empty(cells, dtype=torch.float64, device=dev),
-                   std=torch.empty(cells, dtype=torch.float64, device=dev), n_pairs=torch.zeros(1, **i64),
-                   status=torch.zeros(1, dtype=torch.int32, device=dev))
+                   std=torch.empty(cells, dtype=torch.float64, device=dev), n_pairs=torch.empty(1, **i64),
+                   status=torch.empty(1, dtype=torch.int32, device=dev))
     need = int(L.pm4g_efg_workspace_bytes(prep.n_events, A))
     if need == 0:
         raise Pm4gError(PM4G_E_INVALID, f"no EFG workspace size for n={prep.n_events}, A={A}")
