@@ -562,6 +562,11 @@ typedef struct {
     int64_t *bad_row;
 } pm4g_csv_out;
 
+/* Newline characters of a text in device memory (host int64): one more bounds
+   its data rows, as pm4g_csv_out.capacity.  Waits for the stream's work so far. */
+size_t pm4g_csv_newlines_workspace_bytes(void);
+int pm4g_csv_newlines(const uint8_t* text, int64_t n_bytes, int64_t* newlines, void* ws, size_t ws_bytes,
+                      void* stream);
 size_t pm4g_ingest_csv_workspace_bytes(int64_t n_bytes, int64_t capacity);
 int pm4g_ingest_csv(const uint8_t *text, int64_t n_bytes, const pm4g_csv_schema *schema, const pm4g_csv_out *out,
                     void *ws, size_t ws_bytes, void *stream);

@@ -588,7 +588,7 @@ int pm4g_ingest_csv(const uint8_t* text, int64_t n_bytes, const pm4g_csv_schema*
     for (uint64_t attempt = 0;; ++attempt) {
         PM4G_HIP(launch_csv_parse(text, n_bytes, *sc, 0x5851F42D4C957F2Dull * (attempt + 1),
                                   attempt == 0 ? g_csv_hash_bits : 0, out->capacity, w, *out, s));
-        PM4G_HIP(launch_csv_codes(w, out->capacity, *out, s));
+        PM4G_HIP(launch_csv_codes(text, n_bytes, w, out->capacity, *out, s));
         PM4G_HIP(launch_csv_finish(w, *out, back.dst(), s));
         PM4G_HIP(back.wait(w.scal, sc_host, kBackWords, s));
         if (sc_host[6] || sc_host[3] != INT64_MAX || !sc_host[4]) break;
@@ -602,6 +602,21 @@ int pm4g_ingest_csv(const uint8_t* text, int64_t n_bytes, const pm4g_csv_schema*
         set_err("CSV parse error at data row %lld", (long long)sc_host[3]);
         return PM4G_E_PARSE;
     }
+    return PM4G_OK;
+}
+
+size_t pm4g_csv_newlines_workspace_bytes(void) { return csv_newlines_ws_bytes(); }
+
+int pm4g_csv_newlines(const uint8_t* text, int64_t n_bytes, int64_t* newlines, void* ws, size_t ws_size, void* stream) {
+    PM4G_CHECK(n_bytes >= 0 && (n_bytes == 0 || text) && newlines, "text or newlines is NULL or n_bytes < 0");
+    if (ws_size < csv_newlines_ws_bytes() || !ws) {
+        set_err("workspace of %zu bytes, %zu needed", ws_size, csv_newlines_ws_bytes());
+        return PM4G_E_WORKSPACE;
+    }
+    hipStream_t s = (hipStream_t)stream;
+    HostBack back;
+    PM4G_HIP(launch_csv_newlines(text, n_bytes, static_cast<int64_t*>(ws), back.dst(), s));
+    PM4G_HIP(back.wait(ws, newlines, 1, s));
     return PM4G_OK;
 }
 

@@ -23,13 +23,13 @@
 //   k_csv_close      the unterminated last line, row count, capacity
 //   k_csv_parse      a thread per data row: field ranges, value hashes, the
 //                    timestamp; values enter open-addressing tables keyed by
-//                    64-bit hash, each slot keeping its first row; the slots
-//                    claimed (one per distinct value) are listed per table
-//   k_csv_verify     every row's value against its slot's first row, byte by
-//                    byte (a hash collision is detected, and the call is
-//                    repeated with another hash seed)
-//   codes            the listed slots sorted by first row: the code is the rank
-//   k_csv_emit       codes per row
+//                    64-bit hash, each slot keeping its first row
+//   k_csv_first      per tile of rows, those that are their value's first
+//   k_csv_codes      their ranks in row order: the codes, in the slots, and
+//                    the dictionaries
+//   k_csv_emit       every row's codes; its values against the dictionary's,
+//                    byte by byte (a hash collision is detected, and the call
+//                    is repeated with another hash seed)
 // Bytes: the text is read once by the tile pass and once more by the row
 // pass (plus the first rows' values once); 16 B/row written.
 #include "common.hpp"
@@ -89,31 +89,22 @@ CsvWs csv_ws_layout(Bump& b, int64_t n_bytes, int64_t max_rows) {
 namespace {
 
 // scal: [0] tiles, [1] lines found by the tile pass, [2] data rows, [3] first
-// bad row (INT64_MAX: none), [4] hash collision seen, [5] distinct values (case
-// table, then activity table), [6] rows over capacity, [7] quote parity at
-// the end, [8] table slots, [9] line capacity, [10], [11] slots listed in the
-// case and activity tables
+// bad row (INT64_MAX: none), [4] hash collision seen, [6] rows over capacity,
+// [7] quote parity at the end, [8] table slots, [9] line capacity
 __global__ void k_csv_init(CsvWs w, int64_t n_bytes, int64_t max_lines) {
     w.scal[0] = (n_bytes + kCT - 1) / kCT;
     w.scal[1] = 0;
     w.scal[2] = 0;
     w.scal[3] = INT64_MAX;
     w.scal[4] = 0;
-    w.scal[5] = 0;
     w.scal[6] = 0;
     w.scal[7] = 0;
     w.scal[8] = w.tsize;
     w.scal[9] = max_lines;
-    w.scal[10] = 0;
-    w.scal[11] = 0;
 }
 
 __global__ __launch_bounds__(256) void k_csv_clear(CsvWs w) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // this attempt's retry flag and slot lists
-        w.scal[4] = 0;
-        w.scal[10] = 0;
-        w.scal[11] = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.scal[4] = 0;   // this attempt's retry flag
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * w.tsize; i += (int64_t)gridDim.x * 256) {
         w.table[i].hash = 0;
         w.table[i].first = 0xffffffffu;
@@ -553,17 +544,13 @@ __device__ __forceinline__ bool raw_equal(const uint8_t* __restrict__ text, int6
 // smallest row that holds the value.  A slot is read before any atomic: a
 // value already in the table (nearly every row) costs no atomic unless this
 // row is smaller than the first row seen, so hot values (few activities over
-// millions of rows) do not serialise on their slot.  Sets *claimed when this
-// row's compare-and-swap took an empty slot (the value's first insert).
-__device__ __forceinline__ uint32_t insert(CsvSlot* tab, int64_t tsize, uint64_t h, uint32_t r, bool* claimed) {
+// millions of rows) do not serialise on their slot.
+__device__ __forceinline__ uint32_t insert(CsvSlot* tab, int64_t tsize, uint64_t h, uint32_t r) {
     uint64_t i = h & (uint64_t)(tsize - 1);
     for (;;) {   // the table has more slots than rows: an empty or equal slot exists
         unsigned long long cur = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&tab[i].hash),
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == 0) {
-            cur = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[i].hash), 0ull, (unsigned long long)h);
-            *claimed = cur == 0;
-        }
+        if (cur == 0) cur = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[i].hash), 0ull, (unsigned long long)h);
         if (cur == 0 || cur == h) {
             if (r < __hip_atomic_load(&tab[i].first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
                 atomicMin(&tab[i].first, r);
@@ -577,7 +564,7 @@ __device__ __forceinline__ uint32_t insert(CsvSlot* tab, int64_t tsize, uint64_t
 // case: the tables are at least twice the rows) the two lookups share their
 // memory round trips; otherwise one insert after the other.
 __device__ __forceinline__ void insert2(CsvSlot* t0, CsvSlot* t1, int64_t tsize, uint64_t h0, uint64_t h1,
-                                        uint32_t r, bool* claimed, uint32_t* s0, uint32_t* s1) {
+                                        uint32_t r, uint32_t* s0, uint32_t* s1) {
     const uint64_t i0 = h0 & (uint64_t)(tsize - 1), i1 = h1 & (uint64_t)(tsize - 1);
     const unsigned long long c0 = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&t0[i0].hash),
                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -592,8 +579,8 @@ __device__ __forceinline__ void insert2(CsvSlot* t0, CsvSlot* t1, int64_t tsize,
         *s1 = (uint32_t)i1;
         return;
     }
-    *s0 = insert(t0, tsize, h0, r, &claimed[0]);
-    *s1 = insert(t1, tsize, h1, r, &claimed[1]);
+    *s0 = insert(t0, tsize, h0, r);
+    *s1 = insert(t1, tsize, h1, r);
 }
 
 // Bytes of the text already staged in LDS: [lo, lo + len) at stage[0..).
@@ -694,7 +681,7 @@ __device__ __forceinline__ bool split_fast(const uint8_t* stage, int64_t lo, int
 template <class Src>
 __device__ __forceinline__ void parse_row(Src B, int64_t r, int64_t a, int64_t e, const CsvWs w,
                                          const pm4g_csv_schema& sc, int32_t need, uint64_t seed, uint64_t mask,
-                                         int64_t* __restrict__ ts_out, bool* claimed) {
+                                         int64_t* __restrict__ ts_out) {
     const uint8_t sep = (uint8_t)sc.sep;
     // skip the empty lines in between ("\n" or "\r\n" each)
     while (a < e && (B.at(a) == '\n' || (B.at(a) == '\r' && a + 1 < e && B.at(a + 1) == '\n'))) ++a;
@@ -753,7 +740,7 @@ __device__ __forceinline__ void parse_row(Src B, int64_t r, int64_t a, int64_t e
     w.foff[2 * r + 1] = ab;
     w.flen[2 * r + 1] = (int32_t)(ae - ab);
     uint32_t s0, s1;
-    insert2(w.table, w.table + w.tsize, w.tsize, hc, ha, (uint32_t)r, claimed, &s0, &s1);
+    insert2(w.table, w.table + w.tsize, w.tsize, hc, ha, (uint32_t)r, &s0, &s1);
     w.slot[2 * r] = s0;
     w.slot[2 * r + 1] = s1;
     bool ok = te - tb <= kTsMax;
@@ -785,9 +772,6 @@ __global__ __launch_bounds__(256) void k_csv_parse(const uint8_t* __restrict__ t
                                                    pm4g_csv_schema sc, uint64_t seed, uint64_t mask,
                                                    int64_t* __restrict__ ts_out) {
     __shared__ uint4 stage4[kStage / 16 + 1];   // + 16 bytes of room for the word reads
-    __shared__ uint32_t s_new[2][256];   // slots this block's rows claimed, per table
-    __shared__ uint32_t s_cnt[2];
-    __shared__ int64_t s_base[2];
     uint8_t* stage = reinterpret_cast<uint8_t*>(stage4);
     const int64_t rows = w.scal[2];
     const int64_t hdr = (sc.has_header && w.scal[1] > 0) ? 1 : 0;
@@ -795,7 +779,6 @@ __global__ __launch_bounds__(256) void k_csv_parse(const uint8_t* __restrict__ t
                                                    : (sc.act_col > sc.ts_col ? sc.act_col : sc.ts_col);
     const bool vec = (reinterpret_cast<uintptr_t>(text) & 15) == 0;
     for (int64_t r0 = (int64_t)blockIdx.x * 256; r0 < rows; r0 += (int64_t)gridDim.x * 256) {
-        if (threadIdx.x < 2) s_cnt[threadIdx.x] = 0;
         const int64_t rl = (r0 + 255 < rows ? r0 + 255 : rows - 1);
         const int64_t li0 = r0 + hdr, lil = rl + hdr;
         const int64_t lo = (li0 == 0 ? 0 : w.line_end[li0 - 1] + 1) & ~(int64_t)15;
@@ -813,69 +796,179 @@ __global__ __launch_bounds__(256) void k_csv_parse(const uint8_t* __restrict__ t
         }
         __syncthreads();
         const int64_t r = r0 + threadIdx.x;
-        bool claimed[2] = {false, false};
         if (r < rows) {
             const int64_t li = r + hdr;
             const int64_t a = li == 0 ? 0 : w.line_end[li - 1] + 1;
             const int64_t e = w.line_end[li];
             if (staged) {
                 StagedBytes SB{stage, lo};
-                parse_row(SB, r, a, e, w, sc, need, seed, mask, ts_out, claimed);
+                parse_row(SB, r, a, e, w, sc, need, seed, mask, ts_out);
             } else {
                 Bytes B(text, n_bytes);
-                parse_row(B, r, a, e, w, sc, need, seed, mask, ts_out, claimed);
+                parse_row(B, r, a, e, w, sc, need, seed, mask, ts_out);
             }
         }
-        // list the claimed slots: one global reservation per table and block pass
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (claimed[k]) s_new[k][atomicAdd(&s_cnt[k], 1u)] = w.slot[2 * r + k];
-        __syncthreads();
-        if (threadIdx.x < 2)
-            s_base[threadIdx.x] = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(&w.scal[10 + threadIdx.x]),
-                                                     (unsigned long long)s_cnt[threadIdx.x]);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            for (uint32_t j = threadIdx.x; j < s_cnt[k]; j += 256) w.dlist[k * w.max_rows + s_base[k] + j] = s_new[k][j];
         __syncthreads();
     }
 }
 
-// Every row's value against its slot's first row, byte by byte: equal values,
-// or a hash collision (scal[4]: the call is repeated with another seed).  A
-// thread takes two rows per step, and the four (row, field) items go through
-// each stage together (slot, first row, field ranges, first 16 bytes) so that
-// their loads are in flight at once; longer or unequal fields take the
+// Rows that are the first of their value, per tile of kRT rows: the case
+// table's in the low half of k0[tile], the activity table's in the high half.
+constexpr int kRT = 2048;
+constexpr int kRI = kRT / 256;
+__global__ __launch_bounds__(256) void k_csv_first(CsvWs w) {
+    __shared__ uint32_t tmp[256 / kWave + 1];
+    const int64_t rows = w.scal[2], tiles = (rows + kRT - 1) / kRT;
+    if (w.scal[3] != INT64_MAX) return;
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        uint2 sl[kRI];
+#pragma unroll
+        for (int k = 0; k < kRI; ++k) {
+            const int64_t r = t * kRT + k * 256 + threadIdx.x;
+            sl[k] = reinterpret_cast<const uint2*>(w.slot)[r < rows ? r : rows - 1];
+        }
+        uint32_t c = 0;
+#pragma unroll
+        for (int k = 0; k < kRI; ++k) {
+            const int64_t r = t * kRT + k * 256 + threadIdx.x;
+            c += (r < rows && w.table[sl[k].x].first == (uint32_t)r) ? 1u : 0u;
+            c += (r < rows && w.table[w.tsize + sl[k].y].first == (uint32_t)r) ? 0x10000u : 0u;
+        }
+        uint32_t total;
+        block_excl_sum<256>(c, tmp, &total);
+        if (threadIdx.x == 0) w.k0[t] = total;
+    }
+}
+
+// Their ranks in row order: the codes, kept in the slots, and the dictionary
+// entries.  A block takes a range of tiles (the counts before it summed from
+// k0); ranks within a tile in (item, wave, lane) order from ballots.  Sorting
+// the claimed slots by first row instead took 9 launches per table.
+__global__ __launch_bounds__(256) void k_csv_codes(CsvWs w, int64_t* __restrict__ cdict_off,
+                                                   int32_t* __restrict__ cdict_len, int64_t* n_cases,
+                                                   int64_t* __restrict__ adict_off, int32_t* __restrict__ adict_len,
+                                                   int64_t* n_acts) {
+    constexpr int kNW = 256 / kWave;
+    __shared__ uint32_t wc[2][kRI * kNW];
+    __shared__ int64_t tmp[kNW + 1];
+    const bool failed = w.scal[6] != 0 || w.scal[3] != INT64_MAX;
+    const int64_t rows = failed ? 0 : w.scal[2], tiles = (rows + kRT - 1) / kRT;
+    const int64_t per = (tiles + gridDim.x - 1) / gridDim.x;
+    const int64_t t0 = blockIdx.x * per, t1 = t0 + per < tiles ? t0 + per : tiles;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (t0 >= t1 && !last) return;   // block-uniform
+    int64_t before[2];
+    {
+        int64_t b0 = 0, b1 = 0;
+        for (int64_t t = threadIdx.x; t < (t0 < tiles ? t0 : tiles); t += 256) {
+            const uint32_t c = w.k0[t];
+            b0 += c & 0xFFFFu;
+            b1 += c >> 16;
+        }
+        block_excl_sum<256>(b0, tmp, &before[0]);
+        block_excl_sum<256>(b1, tmp, &before[1]);
+    }
+    const int wv = threadIdx.x / kWave;
+    for (int64_t t = t0; t < t1; ++t) {
+        uint2 sl[kRI];
+        uint64_t m0[kRI], m1[kRI];
+#pragma unroll
+        for (int k = 0; k < kRI; ++k) {
+            const int64_t r = t * kRT + k * 256 + threadIdx.x;
+            sl[k] = reinterpret_cast<const uint2*>(w.slot)[r < rows ? r : rows - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < kRI; ++k) {
+            const int64_t r = t * kRT + k * 256 + threadIdx.x;
+            m0[k] = __ballot(r < rows && w.table[sl[k].x].first == (uint32_t)r);
+            m1[k] = __ballot(r < rows && w.table[w.tsize + sl[k].y].first == (uint32_t)r);
+            if (lane() == 0) {
+                wc[0][k * kNW + wv] = (uint32_t)__popcll(m0[k]);
+                wc[1][k * kNW + wv] = (uint32_t)__popcll(m1[k]);
+            }
+        }
+        __syncthreads();
+        static_assert(2 * kRI * kNW == kWave, "one wave scans the counts of both tables");
+        if (threadIdx.x < kWave) {
+            const int half = threadIdx.x / (kRI * kNW), i = threadIdx.x % (kRI * kNW);
+            const uint32_t v = wc[half][i];
+            const uint32_t inc = wave_incl_sum(v);
+            const uint32_t first_half = (uint32_t)__shfl((int)inc, kRI * kNW - 1);
+            wc[half][i] = inc - v - (half ? first_half : 0u);
+        }
+        __syncthreads();
+        const uint32_t c = w.k0[t];
+#pragma unroll
+        for (int k = 0; k < kRI; ++k) {
+            const int64_t r = t * kRT + k * 256 + threadIdx.x;
+            if ((m0[k] >> lane()) & 1ull) {
+                const int64_t d = before[0] + wc[0][k * kNW + wv] + __popcll(m0[k] & lanes_below());
+                w.table[sl[k].x].code = (uint32_t)d;
+                cdict_off[d] = w.foff[2 * r];
+                cdict_len[d] = w.flen[2 * r];
+            }
+            if ((m1[k] >> lane()) & 1ull) {
+                const int64_t d = before[1] + wc[1][k * kNW + wv] + __popcll(m1[k] & lanes_below());
+                w.table[w.tsize + sl[k].y].code = (uint32_t)d;
+                adict_off[d] = w.foff[2 * r + 1];
+                adict_len[d] = w.flen[2 * r + 1];
+            }
+        }
+        before[0] += c & 0xFFFFu;
+        before[1] += c >> 16;
+        __syncthreads();
+    }
+    if (last && threadIdx.x == 0) {
+        *n_cases = before[0];
+        *n_acts = before[1];
+    }
+}
+
+// Every row's codes, and its values against the dictionary's, byte by byte:
+// equal values, or a hash collision (scal[4]: the call is repeated with another
+// seed).  The dictionaries are compact (12 bytes per distinct value), so that
+// the look-ups of a frequent or a repeated value stay in the caches; checked
+// against the first row's own field range, each row cost two more scattered
+// lines.  A thread takes two rows per step, and the four (row, field) items go
+// through each stage together (slot, code, field ranges, first 16 bytes) so
+// that their loads are in flight at once; longer or unequal fields take the
 // general comparison.
-__global__ __launch_bounds__(256) void k_csv_verify(const uint8_t* __restrict__ text, int64_t n_bytes, CsvWs w) {
+__global__ __launch_bounds__(256) void k_csv_emit(const uint8_t* __restrict__ text, int64_t n_bytes, CsvWs w,
+                                                  const int64_t* __restrict__ cdict_off,
+                                                  const int32_t* __restrict__ cdict_len,
+                                                  const int64_t* __restrict__ adict_off,
+                                                  const int32_t* __restrict__ adict_len,
+                                                  int32_t* __restrict__ case_code, int32_t* __restrict__ act_code) {
     const int64_t rows = w.scal[2];
-    if (w.scal[3] != INT64_MAX) return;   // a parse error ends the call
+    if (w.scal[6] != 0 || w.scal[3] != INT64_MAX) return;   // an error ends the call
     const bool aligned = (reinterpret_cast<uintptr_t>(text) & 7) == 0;
     const int64_t stride = (int64_t)gridDim.x * 256;
     constexpr int kJ = 4;   // two rows x two fields
     for (int64_t r0 = (int64_t)blockIdx.x * 256 + threadIdx.x; r0 < rows; r0 += 2 * stride) {
         int64_t row[kJ];
-        uint32_t sl[kJ], first[kJ];
+        uint32_t sl[kJ], code[kJ];
 #pragma unroll
         for (int j = 0; j < kJ; ++j) {
             row[j] = r0 + (j >> 1) * stride;
-            sl[j] = row[j] < rows ? w.slot[2 * row[j] + (j & 1)] : 0u;
+            const int64_t r = row[j] < rows ? row[j] : r0;
+            sl[j] = w.slot[2 * r + (j & 1)];
         }
-#pragma unroll
-        for (int j = 0; j < kJ; ++j)
-            first[j] = row[j] < rows ? w.table[(j & 1) * w.tsize + sl[j]].first : (uint32_t)row[j];
         bool need[kJ];
         int64_t b1[kJ], b2[kJ];
         int32_t l1[kJ], l2[kJ];
 #pragma unroll
         for (int j = 0; j < kJ; ++j) {
-            need[j] = row[j] < rows && first[j] != (uint32_t)row[j];
-            const int64_t r = need[j] ? row[j] : 0, f = need[j] ? (int64_t)first[j] : 0;
+            const int64_t r = row[j] < rows ? row[j] : r0;
+            code[j] = w.table[(j & 1) * w.tsize + sl[j]].code;
             b1[j] = w.foff[2 * r + (j & 1)];
             l1[j] = w.flen[2 * r + (j & 1)];
-            b2[j] = w.foff[2 * f + (j & 1)];
-            l2[j] = w.flen[2 * f + (j & 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) {
+            b2[j] = (j & 1) ? adict_off[code[j]] : cdict_off[code[j]];
+            l2[j] = (j & 1) ? adict_len[code[j]] : cdict_len[code[j]];
+            need[j] = row[j] < rows && b1[j] != b2[j];
+            if (row[j] < rows) ((j & 1) ? act_code : case_code)[row[j]] = (int32_t)code[j];
         }
         // fields of at most 16 bytes whose aligned words lie inside the text
         bool quick[kJ];
@@ -906,46 +999,6 @@ __global__ __launch_bounds__(256) void k_csv_verify(const uint8_t* __restrict__ 
             Bytes B1(text, n_bytes), B2(text, n_bytes);
             if (!same_value(B1, b1[j], b1[j] + l1[j], B2, b2[j], b2[j] + l2[j])) w.scal[4] = 1;
         }
-    }
-}
-
-// The slots listed for table k with their first rows, to sort; their number
-// goes to scal[5] (none after a capacity or parse error or a collision).
-__global__ __launch_bounds__(256) void k_csv_gather(CsvWs w, int k) {
-    const bool failed = w.scal[6] != 0 || w.scal[3] != INT64_MAX || w.scal[4] != 0;
-    const int64_t D = failed ? 0 : w.scal[10 + k];
-    if (blockIdx.x == 0 && threadIdx.x == 0) w.scal[5] = D;
-    const uint32_t* dl = w.dlist + k * w.max_rows;
-    const CsvSlot* tab = w.table + k * w.tsize;
-    for (int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x; d < D; d += (int64_t)gridDim.x * 256) {
-        const uint32_t i = dl[d];
-        w.k0[d] = tab[i].first;
-        w.v0[d] = i;
-    }
-}
-
-// Sorted by first row: the code of a slot is its rank.
-__global__ __launch_bounds__(256) void k_csv_codes(CsvWs w, int k, const uint32_t* __restrict__ key,
-                                                   const uint32_t* __restrict__ val, int64_t* __restrict__ dict_off,
-                                                   int32_t* __restrict__ dict_len, int64_t* n_dict) {
-    CsvSlot* tab = w.table + k * w.tsize;
-    const int64_t D = w.scal[5];
-    for (int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x; d < D; d += (int64_t)gridDim.x * 256) {
-        tab[val[d]].code = (uint32_t)d;
-        const int64_t r = key[d];
-        dict_off[d] = w.foff[2 * r + k];
-        dict_len[d] = w.flen[2 * r + k];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *n_dict = D;
-}
-
-__global__ __launch_bounds__(256) void k_csv_emit(CsvWs w, int32_t* __restrict__ case_code,
-                                                  int32_t* __restrict__ act_code) {
-    if (w.scal[6] != 0 || w.scal[3] != INT64_MAX || w.scal[4] != 0) return;
-    const int64_t rows = w.scal[2];
-    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < rows; r += (int64_t)gridDim.x * 256) {
-        case_code[r] = (int32_t)w.table[w.slot[2 * r]].code;
-        act_code[r] = (int32_t)w.table[w.tsize + w.slot[2 * r + 1]].code;
     }
 }
 
@@ -985,24 +1038,60 @@ hipError_t launch_csv_parse(const uint8_t* text, int64_t n_bytes, const pm4g_csv
     const unsigned gr = grid_rows(max_rows);
     k_csv_clear<<<2048, 256, 0, s>>>(w);
     k_csv_parse<<<gr, 256, 0, s>>>(text, n_bytes, w, sc, seed, mask, o.ts);
-    k_csv_verify<<<gr, 256, 0, s>>>(text, n_bytes, w);
     return hipGetLastError();
 }
 
-hipError_t launch_csv_codes(CsvWs w, int64_t max_rows, const pm4g_csv_out& o, hipStream_t s) {
-    int bits = 8;   // first rows are below max_rows: sort on that many bits
-    while (bits < 32 && (int64_t(1) << bits) < max_rows) bits += 8;
-    for (int k = 0; k < 2; ++k) {
-        k_csv_gather<<<grid_rows(max_rows), 256, 0, s>>>(w, k);
-        const bool flip = dev::sort_pairs<uint32_t>(w.k0, w.v0, w.k1, w.v1, &w.scal[5], max_rows, bits, w.hist,
-                                                    w.rowsum, s);
-        const uint32_t* key = flip ? w.k1 : w.k0;
-        const uint32_t* val = flip ? w.v1 : w.v0;
-        k_csv_codes<<<grid_rows(max_rows), 256, 0, s>>>(w, k, key, val, k == 0 ? o.case_dict_off : o.act_dict_off,
-                                                        k == 0 ? o.case_dict_len : o.act_dict_len,
-                                                        k == 0 ? o.n_cases : o.n_acts);
+hipError_t launch_csv_codes(const uint8_t* text, int64_t n_bytes, CsvWs w, int64_t max_rows, const pm4g_csv_out& o,
+                            hipStream_t s) {
+    const int64_t tiles = (max_rows + kRT - 1) / kRT;
+    const unsigned g = (unsigned)(tiles < 1024 ? (tiles < 1 ? 1 : tiles) : 1024);
+    k_csv_first<<<g, 256, 0, s>>>(w);
+    k_csv_codes<<<g, 256, 0, s>>>(w, o.case_dict_off, o.case_dict_len, o.n_cases, o.act_dict_off, o.act_dict_len, o.n_acts);
+    k_csv_emit<<<grid_rows(max_rows), 256, 0, s>>>(text, n_bytes, w, o.case_dict_off, o.case_dict_len, o.act_dict_off,
+                                                   o.act_dict_len, o.case_code, o.act_code);
+    return hipGetLastError();
+}
+
+// ---- rows of a text at most ----
+
+// Newlines of 16-byte words, per block; every count below 2^32 (a block's bytes).
+constexpr int kNLBlocks = 1024;
+__global__ __launch_bounds__(256) void k_csv_newlines(const uint8_t* __restrict__ text, int64_t n, int64_t* part) {
+    __shared__ int64_t red[256 / kWave];
+    int64_t c = 0;
+    const int64_t stride = (int64_t)gridDim.x * 256 * kCPer;
+    for (int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kCPer; p < n; p += stride) {
+        uint64_t lo, hi;
+        load16w(text, n, p, &lo, &hi);
+        c += __popcll(eq_bytes(lo, kRep8 * '\n')) + __popcll(eq_bytes(hi, kRep8 * '\n'));
     }
-    k_csv_emit<<<grid_rows(max_rows), 256, 0, s>>>(w, o.case_code, o.act_code);
+    c = wave_sum(c);
+    if (lane() == 0) red[threadIdx.x / kWave] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t t = 0;
+        for (int k = 0; k < 256 / kWave; ++k) t += red[k];
+        part[blockIdx.x] = t;
+    }
+}
+
+__global__ __launch_bounds__(kNLBlocks) void k_csv_newlines_sum(int64_t* part, int blocks, BackDst back) {
+    __shared__ int64_t tmp[kNLBlocks / kWave + 1];
+    int64_t total;
+    block_excl_sum<kNLBlocks>((int)threadIdx.x < blocks ? part[threadIdx.x] : 0, tmp, &total);
+    if (threadIdx.x == 0) {
+        part[0] = total;
+        publish(back, &total, 1);
+    }
+}
+
+size_t csv_newlines_ws_bytes() { return kNLBlocks * sizeof(int64_t); }
+
+hipError_t launch_csv_newlines(const uint8_t* text, int64_t n_bytes, int64_t* part, BackDst back, hipStream_t s) {
+    const int64_t want = (n_bytes + 256 * kCPer - 1) / (256 * kCPer);
+    const int g = (int)(want < 1 ? 1 : (want < kNLBlocks ? want : kNLBlocks));
+    k_csv_newlines<<<(unsigned)g, 256, 0, s>>>(text, n_bytes, part);
+    k_csv_newlines_sum<<<1, kNLBlocks, 0, s>>>(part, g, back);
     return hipGetLastError();
 }
 

@@ -413,10 +413,9 @@ struct CsvWs {
     uint32_t* slot;       // [rows][2] table slot
     CsvSlot* table;       // [2][tsize] case table, activity table
     int64_t max_rows;
-    uint32_t* dlist;      // [2][max_rows] slots claimed in each table (the distinct values)
-    uint32_t *k0, *v0, *k1, *v1;   // [rows] (first row, slot) pairs to sort
-    uint32_t* hist;
-    uint32_t* rowsum;
+    uint32_t* dlist;      // (spare)
+    uint32_t* k0;         // per tile of rows, those that are the first of their value
+    uint32_t *v0, *k1, *v1, *hist, *rowsum;   // (spare)
     uint32_t* part32;
     int64_t* part64;
     int64_t* scal;
@@ -427,7 +426,11 @@ hipError_t launch_csv_lines(const uint8_t* text, int64_t n_bytes, int has_header
 // hash_bits: value hashes truncated to that many bits (0: all 64; a test hook)
 hipError_t launch_csv_parse(const uint8_t* text, int64_t n_bytes, const pm4g_csv_schema& sc, uint64_t seed,
                             int hash_bits, int64_t max_rows, CsvWs w, const pm4g_csv_out& o, hipStream_t s);
-hipError_t launch_csv_codes(CsvWs w, int64_t max_rows, const pm4g_csv_out& o, hipStream_t s);
+hipError_t launch_csv_codes(const uint8_t* text, int64_t n_bytes, CsvWs w, int64_t max_rows, const pm4g_csv_out& o,
+                            hipStream_t s);
+// Newlines of a text (an upper bound of its rows, less one), to `back` and part[0].
+size_t csv_newlines_ws_bytes();
+hipError_t launch_csv_newlines(const uint8_t* text, int64_t n_bytes, int64_t* part, BackDst back, hipStream_t s);
 hipError_t launch_csv_finish(CsvWs w, const pm4g_csv_out& o, BackDst back, hipStream_t s);
 
 

@@ -173,6 +173,10 @@ def load():
             L.pm4g_ingest_csv.argtypes = [_P, ctypes.c_int64, ctypes.POINTER(CsvSchema), ctypes.POINTER(_CsvOut), _P,
                                           ctypes.c_size_t, _P]
             L.pm4g_ingest_csv.restype = ctypes.c_int
+            L.pm4g_csv_newlines_workspace_bytes.argtypes = []
+            L.pm4g_csv_newlines_workspace_bytes.restype = ctypes.c_size_t
+            L.pm4g_csv_newlines.argtypes = [_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64), _P, ctypes.c_size_t, _P]
+            L.pm4g_csv_newlines.restype = ctypes.c_int
             L.pm4g_parquet_rows.argtypes = [_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64), _P]
             L.pm4g_parquet_rows.restype = ctypes.c_int
             L.pm4g_ingest_parquet_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int64]
@@ -638,7 +642,10 @@ def pm4g_ingest_csv(text: torch.Tensor, case_col: int, act_col: int, ts_col: int
     dev = text.device
     n = int(text.numel())
     if capacity is None:
-        capacity = int((text == 10).sum().item()) + 1
+        lines = ctypes.c_int64(0)
+        lws = torch.empty(int(L.pm4g_csv_newlines_workspace_bytes()), dtype=torch.uint8, device=dev)
+        _check(L.pm4g_csv_newlines(_ptr(text), n, ctypes.byref(lines), _ptr(lws), lws.numel(), _stream(stream)))
+        capacity = int(lines.value) + 1
     o, counts = _ingest_out(capacity, dev)
     need = int(L.pm4g_ingest_csv_workspace_bytes(n, int(capacity)))
     ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
