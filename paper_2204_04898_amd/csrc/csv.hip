@@ -560,29 +560,6 @@ __device__ __forceinline__ uint32_t insert(CsvSlot* tab, int64_t tsize, uint64_t
     }
 }
 
-// Both values of a row: when each is already at its home slot (the common
-// case: the tables are at least twice the rows) the two lookups share their
-// memory round trips; otherwise one insert after the other.
-__device__ __forceinline__ void insert2(CsvSlot* t0, CsvSlot* t1, int64_t tsize, uint64_t h0, uint64_t h1,
-                                        uint32_t r, uint32_t* s0, uint32_t* s1) {
-    const uint64_t i0 = h0 & (uint64_t)(tsize - 1), i1 = h1 & (uint64_t)(tsize - 1);
-    const unsigned long long c0 = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&t0[i0].hash),
-                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long c1 = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&t1[i1].hash),
-                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (c0 == h0 && c1 == h1) {
-        const uint32_t f0 = __hip_atomic_load(&t0[i0].first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t f1 = __hip_atomic_load(&t1[i1].first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (r < f0) atomicMin(&t0[i0].first, r);
-        if (r < f1) atomicMin(&t1[i1].first, r);
-        *s0 = (uint32_t)i0;
-        *s1 = (uint32_t)i1;
-        return;
-    }
-    *s0 = insert(t0, tsize, h0, r);
-    *s1 = insert(t1, tsize, h1, r);
-}
-
 // Bytes of the text already staged in LDS: [lo, lo + len) at stage[0..).
 struct StagedBytes {
     static constexpr bool kStaged = true;
@@ -610,6 +587,10 @@ struct ValueHash {
         h = (h ^ x) * kFnvPrime;
         n += 8;
     }
+    __device__ __forceinline__ void tail(uint64_t x, uint32_t k) {   // the last k < 8 bytes; n is a multiple of 8
+        acc = x & ((1ull << (8 * k)) - 1);
+        n += k;
+    }
     __device__ __forceinline__ uint64_t done(uint64_t seed, uint64_t mask) {
         if (n & 7) h = (h ^ acc) * kFnvPrime;
         return finish_hash(h ^ (uint64_t)n, seed, mask);
@@ -626,26 +607,27 @@ __device__ __forceinline__ uint64_t stage_word(const uint8_t* stage, int64_t o) 
     return sh ? ((lo >> sh) | (s64[1] << (64 - sh))) : lo;
 }
 
-// 0x80 in each byte of x equal to the byte repeated in c8, 0 elsewhere.
-
 // A staged row with no quote character, eight bytes at a time: separators
-// from byte masks, the case and activity values hashed a word at a time.
-// Fills the field ranges and hashes the byte walk would; false (nothing
-// written) when the row holds a quote.
+// from byte masks of the stage's aligned words, the case and activity values
+// hashed a word at a time.  Fills the field ranges and hashes the byte walk
+// would; false when the row holds a quote (the byte walk then fills them).
 __device__ __forceinline__ bool split_fast(const uint8_t* stage, int64_t lo, int64_t a, int64_t e,
                                            const pm4g_csv_schema& sc, int32_t need, uint64_t seed, uint64_t mask,
                                            int64_t* fr, int32_t* nf, uint64_t* hc, uint64_t* ha) {
-    const uint64_t sep8 = 0x0101010101010101ull * (uint8_t)sc.sep;
-    const uint64_t quo8 = 0x0101010101010101ull * (uint8_t)'"';
-    for (int64_t p = a; p < e; p += 8)
-        if (eq_bytes(stage_word(stage, p - lo), quo8) & (e - p >= 8 ? ~0ull : ((1ull << (8 * (e - p))) - 1)))
-            return false;
+    const uint64_t sep8 = kRep8 * (uint8_t)sc.sep;
+    const uint64_t quo8 = kRep8 * (uint8_t)'"';
     int32_t f = 0;
     int64_t fs = a;
-    for (int64_t p = a; p < e && f <= need; p += 8) {
-        uint64_t sm = eq_bytes(stage_word(stage, p - lo), sep8) & (e - p >= 8 ? ~0ull : ((1ull << (8 * (e - p))) - 1));
+    const int a0 = (int)(a - lo), e0 = (int)(e - lo);   // stage offsets
+    for (int p = a0 & ~7; p < e0; p += 8) {
+        const uint64_t x = *reinterpret_cast<const uint64_t*>(stage + p);
+        uint64_t in = ~0ull;   // the word's bytes that belong to the row
+        if (p < a0) in <<= 8 * (a0 - p);
+        if (e0 - p < 8) in &= (1ull << (8 * (e0 - p))) - 1;
+        if (eq_bytes(x, quo8) & in) return false;
+        uint64_t sm = eq_bytes(x, sep8) & in;
         while (sm && f <= need) {
-            const int64_t i = p + (__builtin_ctzll(sm) >> 3);
+            const int64_t i = lo + p + (__builtin_ctzll(sm) >> 3);
             if (f == sc.case_col) { fr[0] = fs; fr[1] = i; }
             if (f == sc.act_col) { fr[2] = fs; fr[3] = i; }
             if (f == sc.ts_col) { fr[4] = fs; fr[5] = i; }
@@ -662,14 +644,67 @@ __device__ __forceinline__ bool split_fast(const uint8_t* stage, int64_t lo, int
     }
     *nf = f;
     if (f <= need) return true;
+#pragma unroll
     for (int k = 0; k < 2; ++k) {
-        const int64_t b = fr[2 * k], en = fr[2 * k + 1];
+        int p = (int)(fr[2 * k] - lo);
+        const int en = (int)(fr[2 * k + 1] - lo);
         ValueHash hv(seed);
-        int64_t p = b;
-        for (; p + 8 <= en; p += 8) hv.word(stage_word(stage, p - lo));
-        for (; p < en; ++p) hv.byte(stage[p - lo]);
+        for (; p + 8 <= en; p += 8) hv.word(stage_word(stage, p));
+        if (p < en) hv.tail(stage_word(stage, p), (uint32_t)(en - p));
         (k == 0 ? *hc : *ha) = hv.done(seed, mask);
     }
+    return true;
+}
+
+// Bytes of x that `where` marks (0xFF each): all decimal digits?
+__device__ __forceinline__ bool all_digits(uint64_t x, uint64_t where) {
+    const uint64_t hi = 0xF0F0F0F0F0F0F0F0ull & where, three = 0x3030303030303030ull & where;
+    return (x & hi) == three && (((x & where) + (0x0606060606060606ull & where)) & hi) == three;
+}
+__device__ __forceinline__ int64_t two_digits(uint64_t x, int byte) {
+    return (int64_t)((x >> (8 * byte)) & 15u) * 10 + (int64_t)((x >> (8 * byte + 8)) & 15u);
+}
+
+// The common form of a date-time in a staged field without quotes,
+// YYYY-MM-DD(T| )HH:MM:SS[(.|,)F][Z] with 1 to 9 fraction digits, from three or
+// four words; false for any other form or value (the general cursor decides).
+__device__ __forceinline__ bool iso_common(const uint8_t* stage, int o, int len, int scale, int64_t* out) {
+    if (len < 19 || len > 30) return false;
+    const uint64_t w0 = stage_word(stage, o), w1 = stage_word(stage, o + 8), w2 = stage_word(stage, o + 16);
+    if (!all_digits(w0, 0x00FFFF00FFFFFFFFull) || (w0 & 0xFF0000FF00000000ull) != 0x2D00002D00000000ull) return false;
+    const uint32_t sep = (uint32_t)(w1 >> 16) & 0xFFu;
+    if (!all_digits(w1, 0xFFFF00FFFF00FFFFull) || ((w1 >> 40) & 0xFFu) != ':' || (sep != 'T' && sep != ' ')) return false;
+    if (!all_digits(w2, 0x0000000000FFFF00ull) || (w2 & 0xFFu) != ':') return false;
+    int64_t frac = 0;
+    int nf = 0;
+    if (len > 19) {
+        const uint32_t c = (uint32_t)(w2 >> 24) & 0xFFu;
+        if (c == '.' || c == ',') {
+            const uint64_t w3 = stage_word(stage, o + 24);
+            const uint64_t d0 = (w2 >> 32) | (w3 << 32);   // digits 1-8, then w3's fifth byte on
+            nf = len - 20;
+            const int last = nf - 1;   // 'Z', or the last digit
+            const uint32_t lc = last < 8 ? (uint32_t)(d0 >> (8 * last)) & 0xFFu : (uint32_t)(w3 >> (8 * (last - 4))) & 0xFFu;
+            if (lc == 'Z') --nf;
+            if (nf < 1 || nf > 9) return false;
+            if (!all_digits(d0, nf >= 8 ? ~0ull : ((1ull << (8 * nf)) - 1))) return false;
+            if (nf == 9 && !all_digits(w3, 0x000000FF00000000ull)) return false;
+            const int k = nf < scale ? nf : scale;   // digits below the unit are dropped
+            for (int j = 0; j < k; ++j)
+                frac = frac * 10 + (int64_t)((j < 8 ? d0 >> (8 * j) : w3 >> 32) & 15u);
+        } else if (c != 'Z' || len != 20) {
+            return false;
+        }
+    }
+    const int64_t y = two_digits(w0, 0) * 100 + two_digits(w0, 2), mo = two_digits(w0, 5), d = two_digits(w1, 0);
+    const int64_t hh = two_digits(w1, 3), mi = two_digits(w1, 6), ss = two_digits(w2, 1);
+    if (mo < 1 || mo > 12 || d < 1 || d > month_days(y, mo) || hh > 23 || mi > 59 || ss > 59) return false;
+    const int64_t secs = days_since_epoch(y, mo, d) * 86400 + hh * 3600 + mi * 60 + ss;
+    if (secs > 9000000000ll || secs < -9000000000ll) return false;   // (year 2255) may leave int64 in nanoseconds
+    for (int k = nf < scale ? nf : scale; k < scale; ++k) frac *= 10;
+    int64_t p10 = 1;
+    for (int k = 0; k < scale; ++k) p10 *= 10;
+    *out = secs * p10 + frac;
     return true;
 }
 
@@ -677,11 +712,12 @@ __device__ __forceinline__ bool split_fast(const uint8_t* stage, int64_t lo, int
 // case and activity values are hashed and the timestamp value copied as the
 // walk unwraps their runs (a doubled quote inside a run is one quote and
 // leaves the run open, as two toggles would).  A staged row without quotes
-// takes split_fast instead of the byte walk.
+// takes split_fast instead of the byte walk.  False (the row flagged) when it
+// has too few fields; else the hashes of its two values.
 template <class Src>
-__device__ __forceinline__ void parse_row(Src B, int64_t r, int64_t a, int64_t e, const CsvWs w,
+__device__ __forceinline__ bool parse_row(Src B, int64_t r, int64_t a, int64_t e, const CsvWs w,
                                          const pm4g_csv_schema& sc, int32_t need, uint64_t seed, uint64_t mask,
-                                         int64_t* __restrict__ ts_out) {
+                                         int64_t* __restrict__ ts_out, uint64_t* case_hash, uint64_t* act_hash) {
     const uint8_t sep = (uint8_t)sc.sep;
     // skip the empty lines in between ("\n" or "\r\n" each)
     while (a < e && (B.at(a) == '\n' || (B.at(a) == '\r' && a + 1 < e && B.at(a + 1) == '\n'))) ++a;
@@ -732,24 +768,22 @@ __device__ __forceinline__ void parse_row(Src B, int64_t r, int64_t a, int64_t e
     }
     if (f <= need) {
         flag_bad(w, r);
-        w.slot[2 * r] = w.slot[2 * r + 1] = 0;
-        return;
+        return false;
     }
-    w.foff[2 * r] = cb;
-    w.flen[2 * r] = (int32_t)(ce - cb);
-    w.foff[2 * r + 1] = ab;
-    w.flen[2 * r + 1] = (int32_t)(ae - ab);
-    uint32_t s0, s1;
-    insert2(w.table, w.table + w.tsize, w.tsize, hc, ha, (uint32_t)r, &s0, &s1);
-    w.slot[2 * r] = s0;
-    w.slot[2 * r + 1] = s1;
+    *case_hash = hc;
+    *act_hash = ha;
+    *reinterpret_cast<longlong2*>(w.foff + 2 * r) = make_longlong2(cb, ab);
+    *reinterpret_cast<int2*>(w.flen + 2 * r) = make_int2((int32_t)(ce - cb), (int32_t)(ae - ab));
     bool ok = te - tb <= kTsMax;
     if (ok) {
         int64_t t;
         if constexpr (Src::kStaged) {
             if (fast) {   // no quote in the row: the field's bytes are its value
-                PlainCursor pc(B.stage + (tb - B.lo), te - tb);
-                ok = sc.ts_iso ? iso_value(pc, sc.ts_scale, &t) : int_value(pc, &t);
+                ok = sc.ts_iso && iso_common(B.stage, (int)(tb - B.lo), (int)(te - tb), sc.ts_scale, &t);
+                if (!ok) {
+                    PlainCursor pc(B.stage + (tb - B.lo), te - tb);
+                    ok = sc.ts_iso ? iso_value(pc, sc.ts_scale, &t) : int_value(pc, &t);
+                }
             } else {
                 ValueCursor<Src> vc(B, tb, te);
                 ok = sc.ts_iso ? iso_value(vc, sc.ts_scale, &t) : int_value(vc, &t);
@@ -761,54 +795,102 @@ __device__ __forceinline__ void parse_row(Src B, int64_t r, int64_t a, int64_t e
         if (ok) ts_out[r] = t;
     }
     if (!ok) flag_bad(w, r);
+    return true;
 }
 
-constexpr int kStage = 32768;   // bytes of text staged per block of rows
+constexpr int kStage = 20448;   // bytes of text staged per block of rows: 8 blocks of 20 KB per CU
 
 // A block takes 256 consecutive rows; their bytes (one contiguous range) are
-// copied to LDS with coalesced 16-byte loads and walked there; a range longer
-// than the stage is walked through the chunk reader instead.
+// copied to LDS with coalesced 16-byte loads and walked there.  Rows of more
+// than 80 bytes on average are taken 128, 64 or 32 at a time; a range that is
+// still longer than the stage is walked through the chunk reader instead.
+// The activity values a block has met stay in an LDS table with their slots: a
+// log's few activities otherwise send every row to the same few addresses of
+// the global table, past the caches.  A block's rows only grow, so a value met
+// before needs no more than its slot; for a new one the block's smallest row
+// enters the global table.
 __global__ __launch_bounds__(256) void k_csv_parse(const uint8_t* __restrict__ text, int64_t n_bytes, CsvWs w,
                                                    pm4g_csv_schema sc, uint64_t seed, uint64_t mask,
                                                    int64_t* __restrict__ ts_out) {
-    __shared__ uint4 stage4[kStage / 16 + 1];   // + 16 bytes of room for the word reads
+    __shared__ uint4 stage4[kStage / 16 + 2];   // + 32 bytes of room for the word reads
+    constexpr int kMet = 256, kProbes = 8;
+    __shared__ unsigned long long met[kMet];    // activity hashes met (0: free; a value's hash is not 0)
+    __shared__ uint32_t met_row[kMet], met_slot[kMet];
+    for (int i = threadIdx.x; i < kMet; i += 256) {
+        met[i] = 0;
+        met_row[i] = 0xFFFFFFFFu;
+    }
     uint8_t* stage = reinterpret_cast<uint8_t*>(stage4);
     const int64_t rows = w.scal[2];
     const int64_t hdr = (sc.has_header && w.scal[1] > 0) ? 1 : 0;
     const int32_t need = sc.case_col > sc.act_col ? (sc.case_col > sc.ts_col ? sc.case_col : sc.ts_col)
                                                    : (sc.act_col > sc.ts_col ? sc.act_col : sc.ts_col);
     const bool vec = (reinterpret_cast<uintptr_t>(text) & 15) == 0;
+    const auto row_start = [&](int64_t r) -> int64_t { return r + hdr == 0 ? 0 : w.line_end[r + hdr - 1] + 1; };
     for (int64_t r0 = (int64_t)blockIdx.x * 256; r0 < rows; r0 += (int64_t)gridDim.x * 256) {
-        const int64_t rl = (r0 + 255 < rows ? r0 + 255 : rows - 1);
-        const int64_t li0 = r0 + hdr, lil = rl + hdr;
-        const int64_t lo = (li0 == 0 ? 0 : w.line_end[li0 - 1] + 1) & ~(int64_t)15;
-        const int64_t hi = w.line_end[lil];   // bytes [lo, hi) hold the rows
-        const bool staged = hi - lo <= kStage;   // block-uniform
-        if (staged) {
-            for (int64_t off = (int64_t)threadIdx.x * 16; off < hi - lo; off += 256 * 16) {
-                const int64_t p = lo + off;
-                if (vec && p + 16 <= n_bytes) {
-                    stage4[off >> 4] = *reinterpret_cast<const uint4*>(text + p);
-                } else {
-                    for (int k = 0; k < 16; ++k) stage[off + k] = p + k < n_bytes ? text[p + k] : 0;
+        const int64_t r1 = r0 + 256 < rows ? r0 + 256 : rows;
+        int step = 256;   // rows per stage filling (block-uniform)
+        for (; step > 32; step /= 2) {
+            const int64_t rl = r0 + step < r1 ? r0 + step : r1;
+            if (w.line_end[rl - 1 + hdr] - (row_start(r0) & ~(int64_t)15) <= kStage) break;
+        }
+        for (int64_t s0 = r0; s0 < r1; s0 += step) {
+            const int64_t rl = (s0 + step < r1 ? s0 + step : r1) - 1;
+            const int64_t lo = row_start(s0) & ~(int64_t)15;
+            const int64_t hi = w.line_end[rl + hdr];   // bytes [lo, hi) hold the rows
+            const bool staged = hi - lo <= kStage;     // block-uniform
+            if (staged) {
+                for (int64_t off = (int64_t)threadIdx.x * 16; off < hi - lo; off += 256 * 16) {
+                    const int64_t p = lo + off;
+                    if (vec && p + 16 <= n_bytes) {
+                        stage4[off >> 4] = *reinterpret_cast<const uint4*>(text + p);
+                    } else {
+                        for (int k = 0; k < 16; ++k) stage[off + k] = p + k < n_bytes ? text[p + k] : 0;
+                    }
                 }
             }
-        }
-        __syncthreads();
-        const int64_t r = r0 + threadIdx.x;
-        if (r < rows) {
-            const int64_t li = r + hdr;
-            const int64_t a = li == 0 ? 0 : w.line_end[li - 1] + 1;
-            const int64_t e = w.line_end[li];
-            if (staged) {
-                StagedBytes SB{stage, lo};
-                parse_row(SB, r, a, e, w, sc, need, seed, mask, ts_out);
-            } else {
-                Bytes B(text, n_bytes);
-                parse_row(B, r, a, e, w, sc, need, seed, mask, ts_out);
+            __syncthreads();
+            const int64_t r = s0 + threadIdx.x;
+            const bool mine = r <= rl && (int)threadIdx.x < step;
+            bool row = false;
+            uint64_t hc = 0, ha = 0;
+            if (mine) {
+                const int64_t a = row_start(r);
+                const int64_t e = w.line_end[r + hdr];
+                if (staged) {
+                    StagedBytes SB{stage, lo};
+                    row = parse_row(SB, r, a, e, w, sc, need, seed, mask, ts_out, &hc, &ha);
+                } else {
+                    Bytes B(text, n_bytes);
+                    row = parse_row(B, r, a, e, w, sc, need, seed, mask, ts_out, &hc, &ha);
+                }
             }
+            int at = -1;
+            bool fresh = false;
+            if (row) {
+                const uint32_t h0 = (uint32_t)(ha >> 40);
+                for (int k = 0; k < kProbes; ++k) {
+                    const int i = (int)((h0 + k) & (kMet - 1));
+                    const unsigned long long old = atomicCAS(&met[i], 0ull, (unsigned long long)ha);
+                    if (old == 0 || old == ha) {
+                        at = i;
+                        fresh = old == 0;
+                        atomicMin(&met_row[i], (uint32_t)r);
+                        break;
+                    }
+                }
+            }
+            __syncthreads();   // also: the stage may be filled again
+            uint2 sl = make_uint2(0, 0);
+            if (row) {
+                if (fresh) met_slot[at] = insert(w.table + w.tsize, w.tsize, ha, met_row[at]);
+                else if (at < 0) sl.y = insert(w.table + w.tsize, w.tsize, ha, (uint32_t)r);
+                sl.x = insert(w.table, w.tsize, hc, (uint32_t)r);
+            }
+            __syncthreads();
+            if (row && at >= 0) sl.y = met_slot[at];
+            if (mine) *reinterpret_cast<uint2*>(w.slot + 2 * r) = sl;
         }
-        __syncthreads();
     }
 }
 
@@ -1007,7 +1089,7 @@ __global__ void k_csv_finish(CsvWs w, int64_t* n_rows, int32_t* status, int64_t*
     *n_rows = (over || bad) ? 0 : w.scal[2];
     *bad_row = bad ? w.scal[3] : -1;
     *status = over ? PM4G_E_CAPACITY : (bad ? PM4G_E_PARSE : 0);
-    publish(back, w.scal, kBackWords);
+    publish(back, w.scal, 8);
 }
 
 unsigned grid_rows(int64_t rows) {
