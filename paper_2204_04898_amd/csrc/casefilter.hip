@@ -14,11 +14,11 @@
 //                   (range, time-window, start/end activity and variant
 //                   predicates read the case's first and last event and its
 //                   variant id)
-//   scans           output position of each kept case's events and of its row
-//                   in the output case table
-//   k_cf_emit       kept cases' events copied in order (a wave per 64 cases,
-//                   coalesced writes), case table rows
-//   k_cf_finish     case count, case_off[K], status
+//   k_cf_emit       kept cases' events copied in order (a block takes a range of
+//                   cases, the totals of the ranges before it summed by itself;
+//                   a wave per 64 cases, coalesced writes), case table rows,
+//                   case count, case_off[K], status
+// Three launches at most (two scans, a check and a finish beside them were 11).
 // Counts stay on the device; nothing synchronises.  Bytes: per case 16 read +
 // 24 written (tables), 16 per kept event read + 16 written; the containment
 // pass reads 4-8 B per event.
@@ -61,17 +61,41 @@ CaseFilterWs case_filter_ws_layout(Bump& b, int64_t n) {
 
 namespace {
 
-constexpr int kCB = 256;
-constexpr int kCGrid = 2048;
+constexpr int kCB = 512;
+constexpr int kCGrid = 1024;
 
+// Four cases per thread and step, their loads issued first: each case's first
+// and last timestamp sit in lines of their own (with few events per case, the
+// whole column is read).
 __global__ __launch_bounds__(kCB) void k_cases_df(const int64_t* __restrict__ case_off,
                                                   const int64_t* __restrict__ ts_s, const int64_t* n_cases,
                                                   int64_t* __restrict__ n_events, int64_t* __restrict__ thr) {
     const int64_t C = *n_cases;
-    for (int64_t c = (int64_t)blockIdx.x * kCB + threadIdx.x; c < C; c += (int64_t)gridDim.x * kCB) {
-        const int64_t a = case_off[c], b = case_off[c + 1];
-        if (n_events) n_events[c] = b - a;
-        if (thr) thr[c] = (int64_t)((uint64_t)ts_s[b - 1] - (uint64_t)ts_s[a]);
+    constexpr int kU = 4;
+    const int64_t stride = (int64_t)gridDim.x * kCB;
+    for (int64_t c0 = (int64_t)blockIdx.x * kCB + threadIdx.x; c0 < C; c0 += kU * stride) {
+        int64_t a[kU], b[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t c = c0 + u * stride < C ? c0 + u * stride : c0;
+            a[u] = case_off[c];
+            b[u] = case_off[c + 1];
+        }
+        int64_t t0[kU], t1[kU];
+        if (thr) {
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                t0[u] = ts_s[a[u]];
+                t1[u] = ts_s[b[u] - 1];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t c = c0 + u * stride;
+            if (c >= C) break;
+            if (n_events) n_events[c] = b[u] - a[u];
+            if (thr) thr[c] = (int64_t)((uint64_t)t1[u] - (uint64_t)t0[u]);
+        }
     }
 }
 
@@ -99,19 +123,66 @@ __global__ __launch_bounds__(kCB) void k_cf_contains(const int32_t* __restrict__
         const int64_t base = __shfl(st, 0);
         const int64_t end = __shfl(en, last);
         const int32_t st32 = has ? (int32_t)st : INT32_MAX;
-        for (int64_t p0 = base; p0 < end; p0 += kWave) {   // wave-uniform trip count
-            const int64_t p = p0 + lane();
-            const int m = seg_at32(st32, p);
-            const int64_t s_m = __shfl(st32, m);
-            if (p < end) {
-                const int32_t a = act_s[p];
-                uint32_t bits = 0;
-                if (act_mask && bit_of(act_mask, a)) bits |= 1u;
-                if (path_mask && p > s_m && bit_of(path_mask, (int64_t)act_s[p - 1] * A + a)) bits |= 2u;
-                if (bits) atomicOr(&lflag[wl][m], bits);
+        // wave-uniform trip count; four 64-event steps per trip: their activities,
+        // then their bit-set words, each group loaded before it is used
+        constexpr int kU = 4;
+        for (int64_t p0 = base; p0 < end; p0 += kU * kWave) {
+            int32_t a[kU], ap[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t p = p0 + u * kWave + lane();
+                const int64_t pc = p < end ? p : end - 1;
+                a[u] = act_s[pc];
+                ap[u] = act_s[pc > 0 ? pc - 1 : 0];
+            }
+            int m[kU];
+            bool pair[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t p = p0 + u * kWave + lane();
+                m[u] = seg_at32(st32, p);
+                pair[u] = p > (int64_t)__shfl(st32, m[u]);
+            }
+            uint64_t wa[kU], wp[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                wa[u] = act_mask ? act_mask[a[u] >> 6] : 0ull;
+                wp[u] = path_mask ? path_mask[(pair[u] ? (int64_t)ap[u] * A + a[u] : 0) >> 6] : 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                if (p0 + u * kWave + lane() >= end) continue;
+                const uint32_t bits = (uint32_t)((wa[u] >> (a[u] & 63)) & 1u) |
+                                      (pair[u] ? (uint32_t)((wp[u] >> (((int64_t)ap[u] * A + a[u]) & 63)) & 1u) << 1 : 0u);
+                if (bits) atomicOr(&lflag[wl][m[u]], bits);
             }
         }
         if (has) flags[c] = lflag[wl][lane()];
+    }
+}
+
+// Cases [first, end) of this block, in both kernels that follow: equal ranges.
+__device__ __forceinline__ int64_t range_first(int64_t C) {
+    const int64_t a = (int64_t)blockIdx.x * ((C + gridDim.x - 1) / gridDim.x);
+    return a < C ? a : C;
+}
+__device__ __forceinline__ int64_t range_end(int64_t C) {
+    const int64_t per = (C + gridDim.x - 1) / gridDim.x;
+    const int64_t e = (int64_t)blockIdx.x * per + per;
+    return e < C ? e : C;
+}
+
+// The block's kept events and cases.
+__device__ __forceinline__ void store_totals(CaseFilterWs w, int64_t ev, uint32_t cases) {
+    __shared__ int64_t tmp[kCB / kWave + 1];
+    __shared__ uint32_t tmp2[kCB / kWave + 1];
+    int64_t te;
+    uint32_t tc;
+    block_excl_sum<kCB>(ev, tmp, &te);
+    block_excl_sum<kCB>(cases, tmp2, &tc);
+    if (threadIdx.x == 0) {
+        w.part64[blockIdx.x] = te;
+        w.part32[blockIdx.x] = tc;
     }
 }
 
@@ -121,7 +192,9 @@ __global__ __launch_bounds__(kCB) void k_cf_decide(const int32_t* __restrict__ a
                                                    pm4g_case_filter f, CaseFilterWs w) {
     const int64_t C = *n_cases;
     const bool use_act = f.act_mask != nullptr, use_path = f.path_mask != nullptr;
-    for (int64_t c = (int64_t)blockIdx.x * kCB + threadIdx.x; c < C; c += (int64_t)gridDim.x * kCB) {
+    int64_t events = 0;
+    uint32_t cases = 0;
+    for (int64_t c = range_first(C) + threadIdx.x; c < range_end(C); c += kCB) {
         const int64_t a = case_off[c], b = case_off[c + 1];
         const int64_t ev = b - a;
         const int64_t t0 = ts_s[a], t1 = ts_s[b - 1];
@@ -142,41 +215,71 @@ __global__ __launch_bounds__(kCB) void k_cf_decide(const int32_t* __restrict__ a
             keep = keep && (in == (f.variant_keep != 0));
         }
         w.cnt[c] = keep ? (uint32_t)ev : 0u;
-        w.kept[c] = keep ? 1u : 0u;
+        events += keep ? ev : 0;
+        cases += keep ? 1u : 0u;
     }
+    store_totals(w, events, cases);
 }
-
-// scal[1] = kept events (scan total), uscal[0] = kept cases; scal[2] = 1 when
-// the output cannot hold them (nothing is written then).
-__global__ void k_cf_check(CaseFilterWs w, int64_t cap) { w.scal[2] = w.scal[1] > cap ? 1 : 0; }
 
 __global__ __launch_bounds__(kCB) void k_cf_emit(const int32_t* __restrict__ case_s,
                                                  const int32_t* __restrict__ act_s,
                                                  const int64_t* __restrict__ ts_s,
                                                  const int64_t* __restrict__ case_off,
                                                  const int32_t* __restrict__ case_code, const int64_t* n_cases,
-                                                 CaseFilterWs w, int32_t* __restrict__ o_case,
+                                                 CaseFilterWs w, int64_t cap, int32_t* __restrict__ o_case,
                                                  int32_t* __restrict__ o_act, int64_t* __restrict__ o_ts,
-                                                 int64_t* __restrict__ o_off, int32_t* __restrict__ o_code) {
-    if (w.scal[2]) return;   // over capacity (block-uniform)
+                                                 int64_t* __restrict__ o_off, int32_t* __restrict__ o_code,
+                                                 int64_t* o_n_cases, int32_t* o_status, const int32_t* status_in) {
+    __shared__ int64_t tmp[kCB / kWave + 1];
     const int64_t C = *n_cases;
-    const int64_t wv = ((int64_t)blockIdx.x * kCB + threadIdx.x) / kWave;
-    const int64_t nw = (int64_t)gridDim.x * kCB / kWave;
-    for (int64_t c0 = wv * kWave; c0 < C; c0 += nw * kWave) {
-        const int64_t c = c0 + lane();
-        const bool has = c < C;
-        int64_t src = 0, dst = INT64_MAX, len = 0;
-        if (has) {
-            src = case_off[c];
-            dst = w.eoff[c];
-            len = w.cnt[c];
-            if (w.kept[c]) {
-                const uint32_t k = w.koff[c];
-                o_off[k] = dst;
-                o_code[k] = case_code[c];
+    // kept events and cases of the ranges before this one, and of all
+    int64_t run, krun, total, kept;
+    {
+        int64_t e = 0, k = 0, et = 0, kt = 0;
+        for (int b = threadIdx.x; b < (int)gridDim.x; b += kCB) {
+            const int64_t x = w.part64[b], y = w.part32[b];
+            et += x;
+            kt += y;
+            if (b < (int)blockIdx.x) {
+                e += x;
+                k += y;
             }
         }
-        const int last = (C - 1 - c0) < (kWave - 1) ? (int)(C - 1 - c0) : (kWave - 1);
+        block_excl_sum<kCB>(e, tmp, &run);
+        block_excl_sum<kCB>(k, tmp, &krun);
+        block_excl_sum<kCB>(et, tmp, &total);
+        block_excl_sum<kCB>(kt, tmp, &kept);
+    }
+    const bool over = total > cap;   // the output cannot hold them: nothing is written
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        o_off[over ? 0 : kept] = over ? 0 : total;
+        *o_n_cases = over ? 0 : kept;
+        *o_status = (status_in && *status_in) ? *status_in : (over ? PM4G_E_CAPACITY : 0);
+    }
+    if (over) return;
+    const int64_t c1 = range_end(C);
+    for (int64_t s0 = range_first(C); s0 < c1; s0 += kCB) {   // block-uniform
+        const int64_t c0 = s0 + threadIdx.x / kWave * kWave;
+        const int64_t c = c0 + lane();
+        const bool has = c < c1;
+        int64_t src = 0, len = 0;
+        if (has) {
+            src = case_off[c];
+            len = w.cnt[c];
+        }
+        // kept events below 2^31 (the log's size limit), kept cases above them
+        int64_t all;
+        const int64_t before = block_excl_sum<kCB>(len + (len ? int64_t(1) << 32 : 0), tmp, &all);
+        const int64_t dst = run + (int64_t)(uint32_t)before;
+        if (len) {
+            const int64_t k = krun + (before >> 32);
+            o_off[k] = dst;
+            o_code[k] = case_code[c];
+        }
+        run += (int64_t)(uint32_t)all;
+        krun += all >> 32;
+        if (c0 >= c1) continue;   // wave-uniform; the block scan above is every wave's
+        const int last = (c1 - 1 - c0) < (kWave - 1) ? (int)(c1 - 1 - c0) : (kWave - 1);
         const int64_t base = __shfl(dst, 0);
         const int64_t end = __shfl(dst + len, last);
         // positions fit 32 bits: output starts and the source-minus-output shift
@@ -184,28 +287,35 @@ __global__ __launch_bounds__(kCB) void k_cf_emit(const int32_t* __restrict__ cas
         const int32_t dst32 = has ? (int32_t)dst : INT32_MAX;
         const int32_t shift = (int32_t)(src - (has ? dst : 0));
         // dropped cases are empty segments: the last segment starting at or before
-        // p is the kept case that holds p
-        for (int64_t p0 = base; p0 < end; p0 += kWave) {   // wave-uniform trip count
-            const int64_t p = p0 + lane();
-            const int m = seg_at32(dst32, p);
-            const int32_t sh = __shfl(shift, m);
-            if (p < end) {
-                const int64_t i = p + sh;
-                o_case[p] = case_s[i];
-                o_act[p] = act_s[i];
-                o_ts[p] = ts_s[i];
+        // p is the kept case that holds p.  Wave-uniform trip count; four 64-event
+        // steps per trip, their loads issued before the stores
+        constexpr int kU = 4;
+        for (int64_t p0 = base; p0 < end; p0 += kU * kWave) {
+            int32_t cv[kU], av[kU];
+            int64_t tv[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t p = p0 + u * kWave + lane();
+                const int m = seg_at32(dst32, p);
+                const int32_t sh = __shfl(shift, m);
+                if (p < end) {
+                    const int64_t i = p + sh;
+                    cv[u] = case_s[i];
+                    av[u] = act_s[i];
+                    tv[u] = ts_s[i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t p = p0 + u * kWave + lane();
+                if (p < end) {
+                    o_case[p] = cv[u];
+                    o_act[p] = av[u];
+                    o_ts[p] = tv[u];
+                }
             }
         }
     }
-}
-
-__global__ void k_cf_finish(CaseFilterWs w, int64_t* o_off, int64_t* o_n_cases, int32_t* o_status,
-                            const int32_t* status_in) {
-    const bool over = w.scal[2] != 0;
-    const int64_t K = over ? 0 : (int64_t)w.uscal[0];
-    o_off[K] = over ? 0 : w.scal[1];
-    *o_n_cases = K;
-    *o_status = (status_in && *status_in) ? *status_in : (over ? PM4G_E_CAPACITY : 0);
 }
 
 }  // namespace
@@ -229,21 +339,31 @@ __global__ __launch_bounds__(kCB) void k_cf_sample(const int64_t* __restrict__ c
     const int64_t C = *n_cases;
     const uint64_t T = sel->T;
     const bool none = sel->none != 0, all = sel->all != 0;
-    for (int64_t c = (int64_t)blockIdx.x * kCB + threadIdx.x; c < C; c += (int64_t)gridDim.x * kCB) {
+    int64_t events = 0;
+    uint32_t cases = 0;
+    for (int64_t c = range_first(C) + threadIdx.x; c < range_end(C); c += kCB) {
         const bool keep = !none && (all || splitmix64(seed, (uint64_t)(uint32_t)case_code[c]) <= T);
-        w.cnt[c] = keep ? (uint32_t)(case_off[c + 1] - case_off[c]) : 0u;
-        w.kept[c] = keep ? 1u : 0u;
+        const int64_t ev = keep ? case_off[c + 1] - case_off[c] : 0;
+        w.cnt[c] = (uint32_t)ev;
+        events += ev;
+        cases += keep ? 1u : 0u;
     }
+    store_totals(w, events, cases);
 }
 
-// The kept cases (w.cnt, w.kept) copied into out.
+// Blocks of the deciding and the copying kernel (the same ranges): at most the
+// partials' room; n bounds the case count, which is on the device.
+unsigned range_grid(int64_t n) {
+    const int64_t g = (n + kCB - 1) / kCB;
+    return (unsigned)(g < 1 ? 1 : (g < dev::kScanGrid ? g : dev::kScanGrid));
+}
+
+// The kept cases (w.cnt and the ranges' totals) copied into out.
 void materialise_cases(const pm4g_prepared* p, const pm4g_prepared* out, CaseFilterWs w, hipStream_t s) {
-    dev::excl_scan<int64_t>(w.cnt, p->n_cases, w.eoff, w.part64, &w.scal[1], s);
-    dev::excl_scan<uint32_t>(w.kept, p->n_cases, w.koff, w.part32, &w.uscal[0], s);
-    k_cf_check<<<1, 1, 0, s>>>(w, out->n_events);
-    k_cf_emit<<<kCGrid, kCB, 0, s>>>(p->case_s, p->act_s, p->ts_s, p->case_off, p->case_code, p->n_cases, w,
-                                     out->case_s, out->act_s, out->ts_s, out->case_off, out->case_code);
-    k_cf_finish<<<1, 1, 0, s>>>(w, out->case_off, out->n_cases, out->status, p->status);
+    k_cf_emit<<<range_grid(p->n_events), kCB, 0, s>>>(p->case_s, p->act_s, p->ts_s, p->case_off, p->case_code,
+                                                      p->n_cases, w, out->n_events, out->case_s, out->act_s, out->ts_s,
+                                                      out->case_off, out->case_code, out->n_cases, out->status,
+                                                      p->status);
 }
 
 }  // namespace
@@ -255,14 +375,14 @@ hipError_t launch_filter_cases(const pm4g_prepared* p, const pm4g_case_filter* f
     if (fv.act_mask || fv.path_mask)
         k_cf_contains<<<kCGrid, kCB, 0, s>>>(p->act_s, p->case_off, p->n_cases, p->n_activities, fv.act_mask,
                                              fv.path_mask, w.flags);
-    k_cf_decide<<<kCGrid, kCB, 0, s>>>(p->act_s, p->case_off, p->ts_s, p->n_cases, fv, w);
+    k_cf_decide<<<range_grid(p->n_events), kCB, 0, s>>>(p->act_s, p->case_off, p->ts_s, p->n_cases, fv, w);
     materialise_cases(p, out, w, s);
     return hipGetLastError();
 }
 
 hipError_t launch_sample_cases(const pm4g_prepared* p, uint64_t seed, const SelState* sel,
                                const pm4g_prepared* out, CaseFilterWs w, hipStream_t s) {
-    k_cf_sample<<<kCGrid, kCB, 0, s>>>(p->case_off, p->case_code, p->n_cases, seed, sel, w);
+    k_cf_sample<<<range_grid(p->n_events), kCB, 0, s>>>(p->case_off, p->case_code, p->n_cases, seed, sel, w);
     materialise_cases(p, out, w, s);
     return hipGetLastError();
 }

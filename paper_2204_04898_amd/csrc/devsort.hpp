@@ -215,25 +215,20 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* in, const i
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kScanGrid) void k_scan_top(T* partial, T* total_out) {
-    __shared__ T tmp[kScanGrid / kWave + 1];
-    T total;
-    const T v = partial[threadIdx.x];
-    const T ex = block_excl_sum<kScanGrid>(v, tmp, &total);
-    partial[threadIdx.x] = ex;
-    if (threadIdx.x == 0 && total_out) *total_out = total;
-}
-
+// Each block sums the partials before its own range itself (four cached loads
+// per thread at most, against a launch of 4.5 us for a block that scans them).
 template <typename T>
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* in, const int64_t* n_dev,
-                                                    const T* partial, T* out) {
+                                                    const T* partial, T* out, T* total_out) {
     __shared__ T tmp[256 / kWave + 1];
     const int64_t n = *n_dev;
     const int64_t chunk = (n + kScanGrid - 1) / kScanGrid;
     const int64_t b0 = blockIdx.x * chunk;
     const int64_t b1 = (b0 + chunk) < n ? (b0 + chunk) : n;
-    T run = partial[blockIdx.x];
+    T before = 0, run;
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) before += partial[k];
+    block_excl_sum<256>(before, tmp, &run);
+    if (total_out && blockIdx.x == kScanGrid - 1 && threadIdx.x == 0) *total_out = run + partial[kScanGrid - 1];
     for (int64_t c0 = b0; c0 < b1; c0 += 256) {
         const int64_t i = c0 + threadIdx.x;
         const T v = i < b1 ? (T)in[i] : (T)0;
@@ -250,8 +245,7 @@ template <typename T>
 inline void excl_scan(const uint32_t* in, const int64_t* n_dev, T* out, T* partial, T* total,
                       hipStream_t s) {
     k_scan_reduce<T><<<kScanGrid, 256, 0, s>>>(in, n_dev, partial);
-    k_scan_top<T><<<1, kScanGrid, 0, s>>>(partial, total);
-    k_scan_apply<T><<<kScanGrid, 256, 0, s>>>(in, n_dev, partial, out);
+    k_scan_apply<T><<<kScanGrid, 256, 0, s>>>(in, n_dev, partial, out, total);
 }
 
 }  // namespace

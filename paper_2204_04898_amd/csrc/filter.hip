@@ -8,12 +8,16 @@
 //   - a sample of events (Sec. 3 sampling module): the positions whose
 //     SplitMix64 key is at most the selected threshold.
 // Stream compaction with the predicate as a template parameter:
-//   k_filter_slice / k_filter_whole   p0, p1 on the device
-//   k_filter_count   per-tile kept counts (persistent grid over the slice)
-//   scan             tile offsets, kept total
-//   k_filter_cap     (whole-log filter) kept total against the capacity
-//   k_filter_emit    kept events written in order
-//   case table       of the kept events; case_off[C] = kept total
+//   k_filter_slice      (a view) p0, p1 on the device
+//   k_filter_count      kept events per block; a block takes a contiguous range
+//                       of tiles
+//   k_filter_emit       kept events written in order, each block from the sum of
+//                       the counts before it; the kept total against the capacity
+//   k_filter_case_count, k_filter_case_emit   the same for the case table of the
+//                       kept events; case_off[C] = kept total
+// No scan between count and emit: at most 2048 block counts, which each block
+// sums itself (8 cached loads per thread against two or three launches; the 13
+// launches of a filtered view were most of a small one's time).
 // Bytes per event: the view reads 12 (act, ts), the pair filter 8 (case, act;
 // the partner's sit in the same lines) in each of the count and emit passes;
 // the columns the predicate did not read (and 16 written) per kept event.
@@ -21,7 +25,6 @@
 // (clamped positions, no branch around a load), then the bit-set words, then
 // decides.
 #include "common.hpp"
-#include "devsort.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
 #include "../../include/pm4g.h"
@@ -34,7 +37,7 @@ FilterWs filter_ws_layout(Bump& b, int64_t n) {
     w.scal = b.take<int64_t>(8);
     w.tile_cnt = b.take<uint32_t>((size_t)tiles + 1);
     w.tile_off = b.take<int64_t>((size_t)tiles + 1);
-    w.part64 = b.take<int64_t>(dev::kScanGrid);
+    w.part64 = b.take<int64_t>(1024);
     w.caseblk = b.take<uint32_t>((size_t)case_blocks(n) + 1);
     return w;
 }
@@ -44,20 +47,27 @@ namespace {
 constexpr int kFB = 256;
 constexpr int kFI = kFilterTile / kFB;   // 16 events per thread
 
+// First position of the ascending a[0, n) not below x; a wave together, 64
+// probes a step (4 dependent loads over 16M entries, not 24).
 __device__ int64_t lb_i32(const int32_t* a, int64_t n, int32_t x) {
-    int64_t lo = 0, hi = n;
+    int64_t lo = 0, hi = n;   // the answer lies in [lo, hi]
     while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (a[mid] < x) lo = mid + 1;
-        else hi = mid;
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t p = lo + (int64_t)lane() * step;
+        const uint64_t below = __ballot(p < hi && a[p < hi ? p : lo] < x);   // the first lanes, or none
+        if (below == 0) return lo;
+        const int64_t last = lo + (63 - (int64_t)__clzll((long long)below)) * step;   // a[last] < x
+        hi = last + step < hi ? last + step : hi;
+        lo = last + 1;
     }
     return lo;
 }
 
-// scal: [0] p0, [1] p1, [2] tiles of the slice, [3] kept total, [5] kept cases,
-// [6] case-table blocks, [7] slice size when it exceeded the output capacity
-__global__ void k_filter_slice(const pm4g_view* view, const int64_t* case_off, const int32_t* case_code,
-                               const int64_t* n_cases, int64_t cap, FilterWs w) {
+// scal: [0] p0, [1] p1, [3] kept total, [7] slice size or kept total when it
+// exceeded the output capacity.  One wave.
+__global__ __launch_bounds__(kWave) void k_filter_slice(const pm4g_view* view, const int64_t* case_off,
+                                                        const int32_t* case_code, const int64_t* n_cases, int64_t cap,
+                                                        FilterWs w) {
     const pm4g_view v = *view;
     const int64_t C = *n_cases;
     int64_t p0 = 0, p1 = 0;
@@ -65,6 +75,7 @@ __global__ void k_filter_slice(const pm4g_view* view, const int64_t* case_off, c
         p0 = case_off[lb_i32(case_code, C, v.case_lo)];
         p1 = case_off[lb_i32(case_code, C, v.case_hi)];
     }
+    if (threadIdx.x != 0) return;
     w.scal[7] = 0;
     if (p1 - p0 > cap) {   // the output cannot hold the slice: keep nothing, report
         w.scal[7] = p1 - p0;
@@ -72,7 +83,32 @@ __global__ void k_filter_slice(const pm4g_view* view, const int64_t* case_off, c
     }
     w.scal[0] = p0;
     w.scal[1] = p1;
-    w.scal[2] = (p1 - p0 + kFilterTile - 1) / kFilterTile;
+}
+
+// Items [first, end) of n that this block takes: contiguous equal ranges.
+struct Range {
+    int64_t first, end;
+};
+__device__ __forceinline__ Range block_range(int64_t n) {
+    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
+    const int64_t a = (int64_t)blockIdx.x * per;
+    return Range{a < n ? a : n, a + per < n ? a + per : n};
+}
+
+// Sum of the counts of the blocks before this one, and of all blocks.  `tmp`
+// holds two more entries than block_excl_sum's.
+template <int BLOCK>
+__device__ __forceinline__ int64_t counts_before(const uint32_t* cnt, int64_t* tmp, int64_t* all) {
+    int64_t b = 0, t = 0;
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += BLOCK) {
+        const int64_t c = cnt[k];
+        t += c;
+        if (k < (int)blockIdx.x) b += c;
+    }
+    int64_t before;
+    block_excl_sum<BLOCK>(b, tmp, &before);
+    block_excl_sum<BLOCK>(t, tmp, all);
+    return before;
 }
 
 // Event predicates of the compaction.  ready() runs once per kernel (it may
@@ -221,12 +257,14 @@ __device__ __forceinline__ Row load_row(const Ready& keep, const int32_t* __rest
 template <class Pred>
 __global__ __launch_bounds__(kFB) void k_filter_count(Pred pred, const int32_t* __restrict__ case_s,
                                                       const int32_t* __restrict__ act_s,
-                                                      const int64_t* __restrict__ ts_s, FilterWs w) {
+                                                      const int64_t* __restrict__ ts_s, FilterWs w, int64_t whole) {
     __shared__ uint32_t tmp[kFB / kWave + 1];
     const auto keep = pred.ready();
-    const int64_t p0 = w.scal[0], p1 = w.scal[1], nt = w.scal[2];
+    const int64_t p0 = whole >= 0 ? 0 : w.scal[0], p1 = whole >= 0 ? whole : w.scal[1];
     const int64_t safe = p1 > p0 ? p1 - 1 : 0;
-    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    uint32_t c = 0;
+    const Range tiles = block_range((p1 - p0 + kFilterTile - 1) / kFilterTile);
+    for (int64_t t = tiles.first; t < tiles.end; ++t) {
         Row x[kFI];
 #pragma unroll
         for (int q = 0; q < kFI; ++q) {
@@ -236,13 +274,12 @@ __global__ __launch_bounds__(kFB) void k_filter_count(Pred pred, const int32_t* 
         __builtin_amdgcn_sched_barrier(0);
         bool f[kFI];
         decide_all<kFI, Pred>(keep, x, p0 + t * kFilterTile + threadIdx.x, p1, f);
-        uint32_t c = 0;
 #pragma unroll
         for (int q = 0; q < kFI; ++q) c += f[q] ? 1u : 0u;
-        uint32_t total;
-        block_excl_sum<kFB>(c, tmp, &total);
-        if (threadIdx.x == 0) w.tile_cnt[t] = total;
     }
+    uint32_t total;
+    block_excl_sum<kFB>(c, tmp, &total);
+    if (threadIdx.x == 0) w.caseblk[blockIdx.x] = total;   // the case table's counts come later
 }
 
 // Order-preserving compaction of one tile of kPer * kB positions, striped:
@@ -286,14 +323,24 @@ __global__ __launch_bounds__(kFB) void k_filter_emit(const int32_t* __restrict__
                                                      const int32_t* __restrict__ act_s,
                                                      const int64_t* __restrict__ ts_s, Pred pred, FilterWs w,
                                                      int32_t* __restrict__ o_case, int32_t* __restrict__ o_act,
-                                                     int64_t* __restrict__ o_ts) {
+                                                     int64_t* __restrict__ o_ts, int64_t cap, int64_t whole) {
     constexpr int kHalf = kFI / 2;   // stripes per half tile: all loads of a half are issued together
     __shared__ uint32_t wcnt[kHalf][kFB / kWave];
+    __shared__ int64_t tmp[kFB / kWave + 1];
     const auto keep = pred.ready();
-    const int64_t p0 = w.scal[0], p1 = w.scal[1], nt = w.scal[2];
+    const int64_t p0 = whole >= 0 ? 0 : w.scal[0], p1 = whole >= 0 ? whole : w.scal[1];
     const int64_t safe = p1 > p0 ? p1 - 1 : 0;
-    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
-        int64_t r = w.tile_off[t];
+    int64_t kept;
+    int64_t r = counts_before<kFB>(w.caseblk, tmp, &kept);
+    const bool over = kept > cap;   // nothing is emitted then
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        w.scal[3] = over ? 0 : kept;
+        if (over) w.scal[7] = kept;
+        else if (whole >= 0) w.scal[7] = 0;
+    }
+    if (over) return;
+    const Range tiles = block_range((p1 - p0 + kFilterTile - 1) / kFilterTile);
+    for (int64_t t = tiles.first; t < tiles.end; ++t) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int64_t base = p0 + t * kFilterTile + (int64_t)h * kHalf * kFB + threadIdx.x;
@@ -336,33 +383,13 @@ __global__ __launch_bounds__(kFB) void k_filter_emit(const int32_t* __restrict__
     }
 }
 
-// whole log as the slice
-__global__ void k_filter_whole(int64_t n, FilterWs w) {
-    w.scal[0] = 0;
-    w.scal[1] = n;
-    w.scal[2] = (n + kFilterTile - 1) / kFilterTile;
-    w.scal[7] = 0;
-}
-
-// after the count: a kept total above the output's capacity empties the
-// result (no tile is emitted) and is reported through scal[7]
-__global__ void k_filter_cap(int64_t cap, FilterWs w) {
-    if (w.scal[3] > cap) {
-        w.scal[7] = w.scal[3];
-        w.scal[2] = 0;
-        w.scal[3] = 0;
-    }
-}
-
-__global__ void k_filter_nblocks(FilterWs w) { w.scal[6] = (w.scal[3] + kCaseTile - 1) / kCaseTile; }
-
 // case table of the kept events (their count is on the device)
-__global__ __launch_bounds__(256) void k_filter_case_count(const int32_t* __restrict__ c, FilterWs w,
-                                                           uint32_t* blockcnt, int64_t nbmax) {
+__global__ __launch_bounds__(256) void k_filter_case_count(const int32_t* __restrict__ c, FilterWs w) {
     __shared__ uint32_t tmp[256 / kWave + 1];
     const int64_t n = w.scal[3];
-    const int64_t nb = (n + kCaseTile - 1) / kCaseTile;
-    for (int64_t b = blockIdx.x; b < nb && b < nbmax; b += gridDim.x) {
+    const Range blocks = block_range((n + kCaseTile - 1) / kCaseTile);
+    uint32_t cnt = 0;
+    for (int64_t b = blocks.first; b < blocks.end; ++b) {
         // loads at clamped positions (n >= 1 here), all issued before any is used
         constexpr int kCI = kCaseTile / 256;
         int32_t cv[kCI], pv[kCI];
@@ -374,26 +401,35 @@ __global__ __launch_bounds__(256) void k_filter_case_count(const int32_t* __rest
             pv[k] = c[ic > 0 ? ic - 1 : 0];
         }
         __builtin_amdgcn_sched_barrier(0);
-        uint32_t cnt = 0;
 #pragma unroll
         for (int k = 0; k < kCI; ++k) {
             const int64_t i = b * kCaseTile + k * 256 + threadIdx.x;
             if (i < n && (i == 0 || cv[k] != pv[k])) ++cnt;
         }
-        uint32_t total;
-        block_excl_sum<256>(cnt, tmp, &total);
-        if (threadIdx.x == 0) blockcnt[b] = total;
     }
+    uint32_t total;
+    block_excl_sum<256>(cnt, tmp, &total);
+    if (threadIdx.x == 0) w.tile_cnt[blockIdx.x] = total;
 }
 
+// Also the case count, the last offset and the status.
 __global__ __launch_bounds__(256) void k_filter_case_emit(const int32_t* __restrict__ c, FilterWs w,
-                                                          const int64_t* blockoff, int64_t* __restrict__ case_off,
-                                                          int32_t* __restrict__ case_code, int64_t* n_cases) {
+                                                          int64_t* __restrict__ case_off,
+                                                          int32_t* __restrict__ case_code, int64_t* n_cases,
+                                                          int32_t* status, const int32_t* status_in) {
     constexpr int kCI = kCaseTile / 256;
     __shared__ uint32_t wcnt[kCI][256 / kWave];
+    __shared__ int64_t tmp[256 / kWave + 1];
     const int64_t n = w.scal[3];
-    const int64_t nb = (n + kCaseTile - 1) / kCaseTile;
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+    int64_t C;
+    int64_t r = counts_before<256>(w.tile_cnt, tmp, &C);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        case_off[C] = n;
+        *n_cases = C;
+        *status = (status_in && *status_in) ? *status_in : (w.scal[7] ? PM4G_E_CAPACITY : 0);
+    }
+    const Range blocks = block_range((n + kCaseTile - 1) / kCaseTile);
+    for (int64_t b = blocks.first; b < blocks.end; ++b) {
         const int64_t base = b * kCaseTile + threadIdx.x;
         // loads at clamped positions (n >= 1 here), all issued before any is used
         int32_t cv[kCI], pv[kCI];
@@ -405,8 +441,8 @@ __global__ __launch_bounds__(256) void k_filter_case_emit(const int32_t* __restr
             pv[q] = c[ic > 0 ? ic - 1 : 0];
         }
         __builtin_amdgcn_sched_barrier(0);
-        striped_compact<256, kCI>(
-            blockoff[b], wcnt,
+        r = striped_compact<256, kCI>(
+            r, wcnt,
             [&](int q) {
                 const int64_t i = base + (int64_t)q * 256;
                 return i < n && (i == 0 || cv[q] != pv[q]);
@@ -419,32 +455,18 @@ __global__ __launch_bounds__(256) void k_filter_case_emit(const int32_t* __restr
     }
 }
 
-__global__ void k_filter_case_done(FilterWs w, const int64_t* ncase_total, int64_t* case_off, int64_t* n_cases,
-                                   int32_t* status, const int32_t* status_in) {
-    const int64_t C = *ncase_total;
-    case_off[C] = w.scal[3];
-    *n_cases = C;
-    *status = (status_in && *status_in) ? *status_in : (w.scal[7] ? PM4G_E_CAPACITY : 0);
-}
-
-// Kept events of the slice in scal[0..2] -> out (events, then their case table).
+// Kept events of the slice in scal[0..1] (whole >= 0: of the first `whole`
+// events) -> out (events, then their case table).
 template <class Pred>
-void filter_compact(const pm4g_prepared* p, Pred pred, const pm4g_prepared* out, FilterWs w, bool cap_after_count,
+void filter_compact(const pm4g_prepared* p, Pred pred, const pm4g_prepared* out, FilterWs w, int64_t whole,
                     unsigned grid, hipStream_t s) {
-    const int64_t n = p->n_events;
-    k_filter_count<<<grid, kFB, 0, s>>>(pred, p->case_s, p->act_s, p->ts_s, w);
-    // tile offsets: tile_cnt has scal[2] valid entries; total -> scal[3]
-    dev::excl_scan<int64_t>(w.tile_cnt, &w.scal[2], w.tile_off, w.part64, &w.scal[3], s);
-    if (cap_after_count) k_filter_cap<<<1, 1, 0, s>>>(out->n_events, w);
-    k_filter_emit<<<grid, kFB, 0, s>>>(p->case_s, p->act_s, p->ts_s, pred, w, out->case_s, out->act_s, out->ts_s);
-    const int64_t nbc = case_blocks(n);
-    const unsigned g2 = (unsigned)(nbc < 2048 ? (nbc < 1 ? 1 : nbc) : 2048);
-    k_filter_case_count<<<g2, 256, 0, s>>>(out->case_s, w, w.caseblk, nbc + 1);
-    // per-block case offsets into tile_off (free again after the emit); total cases -> scal[5]
-    k_filter_nblocks<<<1, 1, 0, s>>>(w);
-    dev::excl_scan<int64_t>(w.caseblk, &w.scal[6], w.tile_off, w.part64, &w.scal[5], s);
-    k_filter_case_emit<<<g2, 256, 0, s>>>(out->case_s, w, w.tile_off, out->case_off, out->case_code, out->n_cases);
-    k_filter_case_done<<<1, 1, 0, s>>>(w, &w.scal[5], out->case_off, out->n_cases, out->status, p->status);
+    k_filter_count<<<grid, kFB, 0, s>>>(pred, p->case_s, p->act_s, p->ts_s, w, whole);
+    k_filter_emit<<<grid, kFB, 0, s>>>(p->case_s, p->act_s, p->ts_s, pred, w, out->case_s, out->act_s, out->ts_s,
+                                       out->n_events, whole);
+    static_assert(kCaseTile == kFilterTile, "the counts of either grid fit tile_cnt and caseblk");
+    k_filter_case_count<<<grid, 256, 0, s>>>(out->case_s, w);
+    k_filter_case_emit<<<grid, 256, 0, s>>>(out->case_s, w, out->case_off, out->case_code, out->n_cases, out->status,
+                                            p->status);
 }
 
 unsigned filter_grid(int64_t n) {
@@ -457,24 +479,22 @@ unsigned filter_grid(int64_t n) {
 hipError_t launch_filter_view(const pm4g_prepared* p, const pm4g_view* view, const uint64_t* mask,
                               const pm4g_prepared* out, FilterWs w, hipStream_t s) {
     ProfScope ps(P_VIEW_FILTER, s);
-    k_filter_slice<<<1, 1, 0, s>>>(view, p->case_off, p->case_code, p->n_cases, out->n_events, w);
-    filter_compact(p, ViewPred{view, mask}, out, w, false, filter_grid(p->n_events), s);
+    k_filter_slice<<<1, kWave, 0, s>>>(view, p->case_off, p->case_code, p->n_cases, out->n_events, w);
+    filter_compact(p, ViewPred{view, mask}, out, w, -1, filter_grid(p->n_events), s);
     return hipGetLastError();
 }
 
 hipError_t launch_sample_events(const pm4g_prepared* p, uint64_t seed, const SelState* sel,
                                 const pm4g_prepared* out, FilterWs w, hipStream_t s) {
-    k_filter_whole<<<1, 1, 0, s>>>(p->n_events, w);
-    filter_compact(p, SamplePred{seed, sel}, out, w, true, filter_grid(p->n_events), s);
+    filter_compact(p, SamplePred{seed, sel}, out, w, p->n_events, filter_grid(p->n_events), s);
     return hipGetLastError();
 }
 
 hipError_t launch_filter_df_events(const pm4g_prepared* p, const uint64_t* pairs, int32_t side, int32_t keep,
                                    const pm4g_prepared* out, FilterWs w, hipStream_t s) {
     ProfScope ps(P_DF_FILTER, s);
-    k_filter_whole<<<1, 1, 0, s>>>(p->n_events, w);
-    filter_compact(p, PairPred{pairs, p->n_events, p->n_activities, side, keep}, out, w,
-                   true, filter_grid(p->n_events), s);
+    filter_compact(p, PairPred{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
+                   filter_grid(p->n_events), s);
     return hipGetLastError();
 }
 

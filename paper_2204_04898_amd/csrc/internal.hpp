@@ -285,10 +285,10 @@ struct BatchedOutDev {
 constexpr int kFilterTile = 4096;
 struct FilterWs {
     int64_t* scal;
-    uint32_t* tile_cnt;
-    int64_t* tile_off;
-    int64_t* part64;
-    uint32_t* caseblk;
+    uint32_t* tile_cnt;   // cases of each block's part of the kept events
+    int64_t* tile_off;    // (spare)
+    int64_t* part64;      // (spare)
+    uint32_t* caseblk;    // kept events of each block's tiles
 };
 FilterWs filter_ws_layout(Bump& b, int64_t n);
 hipError_t launch_filter_view(const pm4g_prepared* p, const pm4g_view* view, const uint64_t* mask,
@@ -299,14 +299,11 @@ hipError_t launch_filter_df_events(const pm4g_prepared* p, const uint64_t* pairs
 // Cases dataframe and case-level filters (casefilter.hip).
 struct CaseFilterWs {
     uint32_t* flags;   // [cases] containment bits
-    uint32_t* cnt;     // [cases] kept events
-    uint32_t* kept;    // [cases] kept flag
-    int64_t* eoff;     // [cases] first output event
-    uint32_t* koff;    // [cases] output case-table row
-    uint32_t* part32;
-    int64_t* part64;
-    int64_t* scal;
-    uint32_t* uscal;
+    uint32_t* cnt;     // [cases] kept events (a case has one at least: 0 is a dropped case)
+    uint32_t *kept, *koff, *uscal;   // (spare)
+    int64_t *eoff, *scal;            // (spare)
+    uint32_t* part32;  // [blocks] kept cases
+    int64_t* part64;   // [blocks] kept events
 };
 CaseFilterWs case_filter_ws_layout(Bump& b, int64_t n);
 hipError_t launch_cases_df(const pm4g_prepared* p, int64_t* n_events, int64_t* thr, hipStream_t s);
@@ -374,16 +371,19 @@ hipError_t launch_efg(const pm4g_prepared* p, EfgWs w, const EfgOutDev& o, int64
 
 // ---- sampling (sample.hip; the kept units' materialisation in filter.hip and
 // casefilter.hip) ----
-// Radix select of the k-th smallest SplitMix64 key over the units (events by
-// position, or cases by id): after the passes, a unit is kept iff none == 0
-// and (all != 0 or its key <= T).
+// Selection of the k-th smallest SplitMix64 key over the units (events by
+// position, or cases by id): after it, a unit is kept iff none == 0 and (all !=
+// 0 or its key <= T).
+constexpr int kSelPasses = 3;     // digit passes before the candidates left are listed
+constexpr int kSelList = 4096;    // candidates listed at most
 struct SelState {
-    uint64_t prefix;
-    int64_t krem;
     uint64_t T;
     int32_t none;
     int32_t all;
-    uint32_t hist[256];
+    uint32_t n_list;
+    uint32_t pad;
+    uint32_t hist[kSelPasses][256];
+    uint64_t list[kSelList];
 };
 hipError_t launch_sample_select(const pm4g_prepared* p, int64_t k, uint64_t seed, bool by_events, SelState* sel,
                                 hipStream_t s);
