@@ -195,16 +195,30 @@ inline bool sort_pairs(K* k0, uint32_t* v0, K* k1, uint32_t* v1, const int64_t* 
 // ---- exclusive prefix sum of u32 values into T (u32 or u64) ----------------
 constexpr int kScanGrid = 1024;
 
+// Entries per block: equal ranges of whole 16-byte words of the input.
+__device__ __forceinline__ int64_t scan_chunk(int64_t n) { return ((n + kScanGrid - 1) / kScanGrid + 3) & ~int64_t(3); }
+
+// Four consecutive entries from i (zeros at or past b1): one load when they are
+// aligned and inside.
+__device__ __forceinline__ uint4 scan_load(const uint32_t* in, int64_t i, int64_t b1) {
+    if (i + 3 < b1 && (reinterpret_cast<uintptr_t>(in) & 15) == 0) return *reinterpret_cast<const uint4*>(in + i);
+    return make_uint4(i < b1 ? in[i] : 0u, i + 1 < b1 ? in[i + 1] : 0u, i + 2 < b1 ? in[i + 2] : 0u,
+                      i + 3 < b1 ? in[i + 3] : 0u);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* in, const int64_t* n_dev,
                                                      T* partial) {
     __shared__ T red[256 / kWave];
     const int64_t n = *n_dev;
-    const int64_t chunk = (n + kScanGrid - 1) / kScanGrid;
+    const int64_t chunk = scan_chunk(n);
     const int64_t b0 = blockIdx.x * chunk;
     const int64_t b1 = (b0 + chunk) < n ? (b0 + chunk) : n;
     T s = 0;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += 256) s += in[i];
+    for (int64_t i = b0 + 4 * threadIdx.x; i < b1; i += 4 * 256) {
+        const uint4 v = scan_load(in, i, b1);
+        s += (T)v.x + (T)v.y + (T)v.z + (T)v.w;
+    }
     s = wave_sum(s);
     if (lane() == 0) red[threadIdx.x / kWave] = s;
     __syncthreads();
@@ -217,24 +231,29 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* in, const i
 
 // Each block sums the partials before its own range itself (four cached loads
 // per thread at most, against a launch of 4.5 us for a block that scans them).
+// Four entries per thread and step.
 template <typename T>
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* in, const int64_t* n_dev,
                                                     const T* partial, T* out, T* total_out) {
     __shared__ T tmp[256 / kWave + 1];
     const int64_t n = *n_dev;
-    const int64_t chunk = (n + kScanGrid - 1) / kScanGrid;
+    const int64_t chunk = scan_chunk(n);
     const int64_t b0 = blockIdx.x * chunk;
     const int64_t b1 = (b0 + chunk) < n ? (b0 + chunk) : n;
     T before = 0, run;
     for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) before += partial[k];
     block_excl_sum<256>(before, tmp, &run);
     if (total_out && blockIdx.x == kScanGrid - 1 && threadIdx.x == 0) *total_out = run + partial[kScanGrid - 1];
-    for (int64_t c0 = b0; c0 < b1; c0 += 256) {
-        const int64_t i = c0 + threadIdx.x;
-        const T v = i < b1 ? (T)in[i] : (T)0;
+    for (int64_t c0 = b0; c0 < b1; c0 += 4 * 256) {   // block-uniform
+        const int64_t i = c0 + 4 * threadIdx.x;
+        const uint4 v = scan_load(in, i, b1);
+        const T s1 = (T)v.x, s2 = s1 + (T)v.y, s3 = s2 + (T)v.z;
         T total;
-        const T ex = block_excl_sum<256>(v, tmp, &total);
-        if (i < b1) out[i] = run + ex;
+        const T ex = run + block_excl_sum<256>(s3 + (T)v.w, tmp, &total);
+        if (i < b1) out[i] = ex;
+        if (i + 1 < b1) out[i + 1] = ex + s1;
+        if (i + 2 < b1) out[i + 2] = ex + s2;
+        if (i + 3 < b1) out[i + 3] = ex + s3;
         run += total;
     }
 }

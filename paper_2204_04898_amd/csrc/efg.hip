@@ -18,15 +18,15 @@
 //                  each an equal range of the bucket's pairs
 //   k_efg_agg      a block per entry (LDS-bound: one per CU): each wave takes
 //                  64 source events, flattens their pairs across its lanes and
-//                  adds the gaps into the block's LDS table (count, gap sum
-//                  with carry count, 128-bit square sum); the table goes to
-//                  the entry's partial slot
+//                  adds the gaps into the block's LDS table (counts, gap sums
+//                  and square sums in words that cannot overflow in a pass);
+//                  the table goes to the entry's partial slot
 //   k_efg_reduce   per cell: the partial slots of its bucket summed exactly,
 //                  then mean and std
 // Bytes: 4 B/event tail + (buckets) 8 B/event list and 4 B/event of counting
 // pass, 8 B/list entry of offsets; per pair 12 B of (act, ts) read through the
-// caches (the later events of a case are contiguous) and 3-5 LDS atomics,
-// which bound the kernel.
+// caches (the later events of a case are contiguous) and 4 LDS atomics without
+// returns (4-5 with two returns in a log with a case of 2^44 time units or more).
 #include "common.hpp"
 #include "devsort.hpp"
 #include "internal.hpp"
@@ -40,6 +40,8 @@ namespace {
 constexpr int kEfgAggGrid = 256;         // one block per CU (128 KB of LDS each)
 constexpr int kEB = 1024;                // threads of an aggregation block
 constexpr int64_t kEfgSeg = int64_t(1) << 31;   // pairs per LDS pass (u32 counters)
+constexpr int kNarrowBits = 44;                 // gaps below 2^44: the narrow table
+constexpr int64_t kNarrowSeg = (int64_t(1) << 20) - 1;   // its pairs per pass (20-bit counts)
 
 }  // namespace
 
@@ -75,23 +77,28 @@ EfgWs efg_ws_layout(Bump& b, int64_t n, int32_t A) {
 namespace {
 
 // scal: [0] n, [1] list length, [2] total pairs, [3] plan entries, [4] bucket
-// counters (nbk * chunks)
+// counters (nbk * chunks), [5] a case lasts 2^44 time units or more
 __global__ void k_efg_setup(EfgWs w, int64_t n, int64_t ncounters) {
     w.scal[0] = n;
     w.scal[1] = n;   // the log itself unless bucketed
     w.scal[4] = ncounters;
+    w.scal[5] = 0;
 }
 
+// Tails; and whether any gap (at most its case's
+// duration) needs more than kNarrowBits.
 __global__ __launch_bounds__(256) void k_efg_tail(const int64_t* __restrict__ case_off, const int64_t* n_cases,
-                                                  uint32_t* __restrict__ tail) {
+                                                  const int64_t* __restrict__ ts_s, EfgWs w) {
     const int64_t C = *n_cases;
     const int64_t wv = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;
     const int64_t nw = (int64_t)gridDim.x * 256 / kWave;
+    bool wide = false;
     for (int64_t c0 = wv * kWave; c0 < C; c0 += nw * kWave) {
         const int64_t c = c0 + lane();
         const bool has = c < C;
         const int64_t st = has ? case_off[c] : INT64_MAX;
         const int64_t en = has ? case_off[c + 1] : 0;
+        if (has) wide |= (((uint64_t)ts_s[en - 1] - (uint64_t)ts_s[st]) >> kNarrowBits) != 0;
         const int last = (C - 1 - c0) < (kWave - 1) ? (int)(C - 1 - c0) : (kWave - 1);
         const int64_t base = __shfl(st, 0);
         const int64_t end = __shfl(en, last);
@@ -99,9 +106,10 @@ __global__ __launch_bounds__(256) void k_efg_tail(const int64_t* __restrict__ ca
             const int64_t p = p0 + lane();
             const int m = seg_at(st, p);
             const int64_t e_m = __shfl(en, m);
-            if (p < end) tail[p] = (uint32_t)(e_m - p - 1);
+            if (p < end) w.tail[p] = (uint32_t)(e_m - p - 1);
         }
     }
+    if (wide) w.scal[5] = 1;
 }
 
 // Per chunk of the log, the events with a later event per bucket of source
@@ -189,11 +197,18 @@ __device__ __forceinline__ void efg_bucket(const EfgWs& w, int64_t b, int64_t nb
 
 // One block of 1024 threads.  A bucket with pb pairs gets ceil(pb * G / P)
 // entries (so at most G + buckets in all), equal shares of its pairs; first the
-// per-bucket entry counts and their scan, then the entries in parallel.
-__global__ __launch_bounds__(1024) void k_efg_plan(EfgWs w, int64_t nbk, int64_t nch, int32_t G) {
+// per-bucket entry counts and their scan, then the entries in parallel.  G is
+// two entries per block of the aggregation, fewer when they would hold less
+// than 8192 pairs: every entry costs its table written and read again (160 KB
+// each way; 1088 of them took 90 us to fold for 105M pairs).
+constexpr int64_t kPlanPairs = 8192;
+__global__ __launch_bounds__(1024) void k_efg_plan(EfgWs w, int64_t nbk, int64_t nch) {
     __shared__ int64_t tmp[1024 / kWave + 1];
     __shared__ int64_t s_total;
     const int64_t len = w.scal[1], P = w.scal[2];
+    const int64_t most = 2 * kEfgAggGrid, want = P / kPlanPairs;
+    static_assert(2 * kEfgAggGrid <= kEfgPlanBlocks, "the plan's room");
+    const unsigned G = (unsigned)(want < 1 ? 1 : (want < most ? want : most));
     if (threadIdx.x == 0) w.poff[len] = P;
     int64_t run = 0;
     for (int64_t b0 = 0; b0 < nbk; b0 += 1024) {
@@ -203,7 +218,7 @@ __global__ __launch_bounds__(1024) void k_efg_plan(EfgWs w, int64_t nbk, int64_t
             int64_t klo, khi, q0, pb;
             efg_bucket(w, b, nbk, nch, len, P, klo, khi, q0, pb);
             if (pb > 0) {
-                const unsigned __int128 x = (unsigned __int128)pb * (unsigned)G;
+                const unsigned __int128 x = (unsigned __int128)pb * G;
                 nb = (int64_t)((x + (unsigned __int128)(P - 1)) / (unsigned __int128)P);
                 if (nb < 1) nb = 1;
             }
@@ -246,21 +261,76 @@ __global__ __launch_bounds__(1024) void k_efg_plan(EfgWs w, int64_t nbk, int64_t
     }
 }
 
-__device__ __forceinline__ int64_t shfl64(int64_t v, int src) {
-    const int lo = __shfl((int)(uint32_t)v, src);
-    const int hi = __shfl((int)(uint32_t)((uint64_t)v >> 32), src);
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+// A cell's words in the block's LDS table, 32 bytes, in four arrays so that
+// neighbouring cells sit in neighbouring banks.
+//   narrow (gaps d < 2^44, at most 2^20 - 1 pairs a pass): no word can overflow,
+//     so nothing is returned and the lanes do not wait:
+//     t0 count << 44 | sum of d's low 24 bits     t1 sum of d >> 24
+//     t2 sum of the low 44 bits of d^2            t3 sum of d^2 >> 44
+//   wide: t0 gap sum (low), t1 count | carries << 32 (two 32-bit halves),
+//     t2 and t3 the square sum's halves
+struct EfgTable {
+    uint64_t t0[kEfgCells], t1[kEfgCells], t2[kEfgCells], t3[kEfgCells];
+};
+typedef unsigned long long ull;
+constexpr uint64_t kLow24 = (1ull << 24) - 1, kLow44 = (1ull << kNarrowBits) - 1;
+
+template <bool NARROW>
+__device__ __forceinline__ void efg_add(EfgTable& t, int cell, uint64_t d) {
+    const uint64_t ql = d * d, qh = __umul64hi(d, d);
+    if (NARROW) {
+        atomicAdd((ull*)&t.t0[cell], (ull)((1ull << kNarrowBits) | (d & kLow24)));
+        if (d >> 24) atomicAdd((ull*)&t.t1[cell], (ull)(d >> 24));
+        if (ql & kLow44) atomicAdd((ull*)&t.t2[cell], (ull)(ql & kLow44));
+        const uint64_t q1 = (ql >> kNarrowBits) | (qh << (64 - kNarrowBits));
+        if (q1) atomicAdd((ull*)&t.t3[cell], (ull)q1);
+    } else {
+        uint32_t* half = reinterpret_cast<uint32_t*>(&t.t1[cell]);
+        atomicAdd(half, 1u);
+        const ull os = atomicAdd((ull*)&t.t0[cell], (ull)d);
+        if (os + d < os) atomicAdd(half + 1, 1u);
+        const ull oq = atomicAdd((ull*)&t.t2[cell], (ull)ql);
+        const uint64_t h = qh + (oq + ql < oq ? 1u : 0u);
+        if (h) atomicAdd((ull*)&t.t3[cell], (ull)h);
+    }
 }
 
-__global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act_s,
-                                                 const int64_t* __restrict__ ts_s, EfgWs w, int32_t A, int32_t R,
-                                                 int32_t bucketed, int64_t seg) {
-    __shared__ uint32_t s_cnt[kEfgCells];
-    __shared__ uint64_t s_slo[kEfgCells];
-    __shared__ uint32_t s_shi[kEfgCells];   // carries out of s_slo
-    __shared__ uint64_t s_qlo[kEfgCells];
-    __shared__ uint64_t s_qhi[kEfgCells];
-    __shared__ int64_t s_k0;
+// A cell's sums: count, gap sum and square sum (low, high).
+struct EfgSums {
+    uint64_t cn, sl, sh, ql, qh;
+};
+template <bool NARROW>
+__device__ __forceinline__ EfgSums efg_read(const EfgTable& t, int cell) {
+    const uint64_t a = t.t0[cell], b = t.t1[cell], c = t.t2[cell], d = t.t3[cell];
+    if (!NARROW) return EfgSums{b & 0xFFFFFFFFu, a, b >> 32, c, d};
+    EfgSums s;
+    s.cn = a >> kNarrowBits;
+    s.sl = (a & kLow44) + (b << 24);
+    s.sh = (b >> 40) + (s.sl < (b << 24) ? 1u : 0u);
+    s.ql = c + (d << kNarrowBits);
+    s.qh = (d >> (64 - kNarrowBits)) + (s.ql < c ? 1u : 0u);
+    return s;
+}
+
+// A source event of a wave's 64: its first pair is event jb (+ the flattened
+// index, modulo 2^32; events are below 2^31), its cells start at row.
+struct EfgSrc {
+    uint32_t jb;
+    int32_t row;
+    int64_t t;
+};
+
+// The entries of this block.  A wave flattens the pairs of 64 source events;
+// eight lane groups each walk an eighth of them, eight consecutive pairs at a
+// time: the lanes of an atomic then come from several sources, i.e. rows of the
+// table, instead of all from one (whose frequent target activities put up to
+// ten lanes on one address).  A lane keeps its source until its pairs end, and
+// has the loads of four steps in flight before it adds.
+template <bool NARROW>
+__device__ __forceinline__ void efg_entries(EfgTable& tab, uint32_t (*s_end)[kWave], EfgSrc (*s_src)[kWave],
+                                            int64_t* s_k0, const int32_t* __restrict__ act_s,
+                                            const int64_t* __restrict__ ts_s, const EfgWs& w, int32_t A, int32_t R,
+                                            int32_t bucketed, int64_t seg) {
     const int64_t nplan = w.scal[3];
     const int cells = R * A;
     const int wv = threadIdx.x / kWave;
@@ -271,13 +341,7 @@ __global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act
         bool first = true;
         for (int64_t s0 = en.q0; s0 < en.q1; s0 += seg) {
             const int64_t s1 = (en.q1 - s0) < seg ? en.q1 : s0 + seg;
-            for (int c = threadIdx.x; c < cells; c += kEB) {
-                s_cnt[c] = 0;
-                s_slo[c] = 0;
-                s_shi[c] = 0;
-                s_qlo[c] = 0;
-                s_qhi[c] = 0;
-            }
+            for (int c = threadIdx.x; c < cells; c += kEB) tab.t0[c] = tab.t1[c] = tab.t2[c] = tab.t3[c] = 0;
             if (threadIdx.x == 0) {   // the list entry whose pairs hold s0
                 int64_t lo = en.klo, hi = en.khi;
                 while (hi - lo > 1) {
@@ -285,10 +349,10 @@ __global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act
                     if (w.poff[mid] <= s0) lo = mid;
                     else hi = mid;
                 }
-                s_k0 = lo;
+                *s_k0 = lo;
             }
             __syncthreads();
-            const int64_t kstart = s_k0;
+            const int64_t kstart = *s_k0;
             for (int64_t k0 = kstart + (int64_t)kWave * wv; k0 < en.khi; k0 += (int64_t)kWave * kNW) {
                 if (w.poff[k0] >= s1) break;   // same address in every lane: wave-uniform
                 const int64_t k = k0 + lane();
@@ -303,50 +367,65 @@ __global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act
                 const uint32_t incl = wave_incl_sum(cnt);
                 const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1);
                 const int64_t src = valid ? (bucketed ? (int64_t)w.list[k] : k) : 0;
-                const int32_t row = valid ? act_s[src] - en.b * R : 0;
-                const int64_t ti = valid ? ts_s[src] : 0;
-                // the p-th flattened pair of this lane's source is its event jb + p
-                // (modulo 2^32; events are below 2^31)
-                const uint32_t jb = (uint32_t)(src + 1 + (lo - beg)) - (incl - cnt);
-                for (uint32_t p0 = 0; p0 < total; p0 += kWave) {   // wave-uniform trip count
-                    const uint32_t p = p0 + lane();
-                    int m = 0;   // lanes whose inclusive pair count is <= p
+                __builtin_amdgcn_wave_barrier();   // the wave's reads of the last 64 sources are done
+                s_end[wv][lane()] = incl;
+                s_src[wv][lane()] = EfgSrc{(uint32_t)(src + 1 + (lo - beg)) - (incl - cnt),
+                                           valid ? (act_s[src] - en.b * R) * A : 0, valid ? ts_s[src] : 0};
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t per = ((total + 63) / 64) * 8;   // pairs per group
+                const uint32_t g0 = (uint32_t)(lane() / 8) * per;
+                const uint32_t g1 = g0 + per < total ? g0 + per : total;
+                uint32_t p = g0 + (uint32_t)(lane() % 8);
+                // the source of pair p: the sources whose pairs end at or before it
+                int m = 0;
+                for (int step = 32; step > 0; step >>= 1)
+                    if (s_end[wv][m + step - 1] <= p) m += step;
+                m = p < g1 ? m : 0;
+                uint32_t mend = s_end[wv][m];
+                EfgSrc sr = s_src[wv][m];
+                constexpr int kU = 4;
+                for (uint32_t t = 0; t < per; t += 8 * kU) {   // wave-uniform trip count
+                    int32_t row[kU], a[kU];
+                    int64_t ti[kU], tj[kU];
+                    bool in[kU];
 #pragma unroll
-                    for (int step = 32; step > 0; step >>= 1)
-                        if ((uint32_t)__shfl((int)incl, m + step - 1) <= p) m += step;
-                    const int64_t jm = (int64_t)(uint32_t)((uint32_t)__shfl((int)jb, m) + p);
-                    const int32_t rm = __shfl(row, m);
-                    const int64_t tm = shfl64(ti, m);
-                    if (p < total) {
-                        const int cell = rm * A + act_s[jm];
-                        const uint64_t d = (uint64_t)ts_s[jm] - (uint64_t)tm;
-                        atomicAdd(&s_cnt[cell], 1u);
-                        const unsigned long long os = atomicAdd((unsigned long long*)&s_slo[cell], (unsigned long long)d);
-                        if (os + d < os) atomicAdd(&s_shi[cell], 1u);
-                        const uint64_t ql = d * d, qh = __umul64hi(d, d);
-                        const unsigned long long oq = atomicAdd((unsigned long long*)&s_qlo[cell], (unsigned long long)ql);
-                        const uint64_t h = qh + (oq + ql < oq ? 1u : 0u);
-                        if (h) atomicAdd((unsigned long long*)&s_qhi[cell], (unsigned long long)h);
+                    for (int u = 0; u < kU; ++u, p += 8) {
+                        in[u] = p < g1;
+                        if (in[u] && p >= mend) {
+                            do {   // ends: the last source's pairs end at total > p
+                                mend = s_end[wv][++m];
+                            } while (p >= mend);
+                            sr = s_src[wv][m];
+                        }
+                        row[u] = sr.row;
+                        ti[u] = sr.t;
+                        const int64_t j = in[u] ? (int64_t)(uint32_t)(sr.jb + p) : 0;
+                        a[u] = act_s[j];
+                        tj[u] = ts_s[j];
                     }
+#pragma unroll
+                    for (int u = 0; u < kU; ++u)
+                        if (in[u]) efg_add<NARROW>(tab, row[u] + a[u], (uint64_t)tj[u] - (uint64_t)ti[u]);
                 }
             }
             __syncthreads();
             for (int c = threadIdx.x; c < cells; c += kEB) {
-                const uint64_t cn = s_cnt[c], sl = s_slo[c], sh = s_shi[c], ql = s_qlo[c], qh = s_qhi[c];
+                const EfgSums v = efg_read<NARROW>(tab, c);
                 if (first) {
-                    slot[c] = cn;
-                    slot[kEfgCells + c] = sl;
-                    slot[2 * kEfgCells + c] = sh;
-                    slot[3 * kEfgCells + c] = ql;
-                    slot[4 * kEfgCells + c] = qh;
+                    slot[c] = v.cn;
+                    slot[kEfgCells + c] = v.sl;
+                    slot[2 * kEfgCells + c] = v.sh;
+                    slot[3 * kEfgCells + c] = v.ql;
+                    slot[4 * kEfgCells + c] = v.qh;
                 } else {
-                    slot[c] += cn;
+                    slot[c] += v.cn;
                     const uint64_t a = slot[kEfgCells + c];
-                    slot[kEfgCells + c] = a + sl;
-                    slot[2 * kEfgCells + c] += sh + (a + sl < a ? 1u : 0u);
+                    slot[kEfgCells + c] = a + v.sl;
+                    slot[2 * kEfgCells + c] += v.sh + (a + v.sl < a ? 1u : 0u);
                     const uint64_t q = slot[3 * kEfgCells + c];
-                    slot[3 * kEfgCells + c] = q + ql;
-                    slot[4 * kEfgCells + c] += qh + (q + ql < q ? 1u : 0u);
+                    slot[3 * kEfgCells + c] = q + v.ql;
+                    slot[4 * kEfgCells + c] += v.qh + (q + v.ql < q ? 1u : 0u);
                 }
             }
             first = false;
@@ -356,6 +435,20 @@ __global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act
             for (int c = threadIdx.x; c < cells; c += kEB)
                 for (int f = 0; f < 5; ++f) slot[f * kEfgCells + c] = 0;
     }
+}
+
+__global__ __launch_bounds__(kEB) void k_efg_agg(const int32_t* __restrict__ act_s,
+                                                 const int64_t* __restrict__ ts_s, EfgWs w, int32_t A, int32_t R,
+                                                 int32_t bucketed, int64_t seg) {
+    __shared__ EfgTable tab;
+    __shared__ uint32_t s_end[kEB / kWave][kWave];   // inclusive pair counts of a wave's sources
+    __shared__ EfgSrc s_src[kEB / kWave][kWave];
+    __shared__ int64_t s_k0;
+    static_assert(sizeof(tab) + sizeof(s_end) + sizeof(s_src) + 64 <= 160 * 1024, "one block's LDS");
+    if (w.scal[5])
+        efg_entries<false>(tab, s_end, s_src, &s_k0, act_s, ts_s, w, A, R, bucketed, seg);
+    else
+        efg_entries<true>(tab, s_end, s_src, &s_k0, act_s, ts_s, w, A, R, bucketed, seg < kNarrowSeg ? seg : kNarrowSeg);
 }
 
 // 256-bit unsigned arithmetic for the variance numerator n*Q - S*S.
@@ -403,9 +496,12 @@ __device__ __forceinline__ double limbs_to_double(const uint64_t* w, int n) {
     return x;
 }
 
-// 64 cells per block, 16 lanes per cell splitting its bucket's partial slots;
-// the 16 partial sums combine exactly in LDS.
-constexpr int kRC = 64, kRL = 16;
+// 64 cells per block, kRL lanes per cell splitting its bucket's partial slots;
+// the partial sums combine exactly in LDS.  A single bucket's few cells share
+// all slots: 16 lanes; with many buckets most have a few slots each: 8, so that
+// more blocks (their last step is one wave's) are on a CU at once.
+constexpr int kRC = 64;
+template <int kRL>
 __global__ __launch_bounds__(kRC * kRL) void k_efg_reduce(EfgWs w, int32_t A, int32_t R, EfgOutDev o,
                                                           const int32_t* status_in) {
     __shared__ uint64_t red[5][kRL][kRC];
@@ -419,6 +515,7 @@ __global__ __launch_bounds__(kRC * kRL) void k_efg_reduce(EfgWs w, int32_t A, in
             const int32_t b = row / R;
             const int64_t local = (int64_t)(row - b * R) * A + col;
             const int64_t e0 = w.bfirst[b], ne = w.bnum[b];
+#pragma unroll 2
             for (int64_t e = e0 + li; e < e0 + ne; e += kRL) {
                 const uint64_t* slot = w.part + e * (int64_t)kSlotWords;
                 cn += slot[local];
@@ -488,7 +585,8 @@ hipError_t launch_efg(const pm4g_prepared* p, EfgWs w, const EfgOutDev& o, int64
     const int64_t nbk = efg_buckets(A);
     const int64_t nch = (n + kEfgChunk - 1) / kEfgChunk;
     k_efg_setup<<<1, 1, 0, s>>>(w, n, nbk * nch);
-    k_efg_tail<<<2048, 256, 0, s>>>(p->case_off, p->n_cases, w.tail);
+    const int64_t gt = (n + 255) / 256;
+    k_efg_tail<<<(unsigned)(gt < 2048 ? (gt < 1 ? 1 : gt) : 2048), 256, 0, s>>>(p->case_off, p->n_cases, p->ts_s, w);
     const unsigned gch = (unsigned)(nch < 2048 ? (nch < 1 ? 1 : nch) : 2048);
     int kbits = 0;
     while ((int64_t(1) << kbits) < nbk) ++kbits;
@@ -501,12 +599,15 @@ hipError_t launch_efg(const pm4g_prepared* p, EfgWs w, const EfgOutDev& o, int64
     } else {
         dev::excl_scan<int64_t>(w.tail, &w.scal[1], w.poff, w.part64, &w.scal[2], s);
     }
-    k_efg_plan<<<1, 1024, 0, s>>>(w, nbk, nch, kEfgPlanBlocks);
+    k_efg_plan<<<1, 1024, 0, s>>>(w, nbk, nch);
     const int64_t seg = (pass_pairs > 0 && pass_pairs < kEfgSeg) ? pass_pairs : kEfgSeg;
     k_efg_agg<<<kEfgAggGrid, kEB, 0, s>>>(p->act_s, p->ts_s, w, A, R, nbk > 1 ? 1 : 0, seg);
     const int64_t cells = (int64_t)A * A;
     const int64_t gr = (cells + kRC - 1) / kRC;
-    k_efg_reduce<<<(unsigned)(gr < 2048 ? gr : 2048), kRC * kRL, 0, s>>>(w, A, R, o, p->status);
+    if (nbk > 1)
+        k_efg_reduce<8><<<(unsigned)(gr < 8192 ? gr : 8192), kRC * 8, 0, s>>>(w, A, R, o, p->status);
+    else
+        k_efg_reduce<16><<<(unsigned)gr, kRC * 16, 0, s>>>(w, A, R, o, p->status);
     return hipGetLastError();
 }
 

@@ -360,7 +360,7 @@ struct EfgOutDev {
 };
 constexpr int kEfgCells = 4096;          // cells of one LDS table
 constexpr int kEfgChunk = 4096;          // events per block pass when bucketing
-constexpr int kEfgPlanBlocks = 1024;     // plan entries spread over the pairs
+constexpr int kEfgPlanBlocks = 1024;     // plan entries spread over the pairs, at most
 constexpr int kSlotWords = 5 * kEfgCells;   // partial table words: cnt, sum lo, sum hi, sq lo, sq hi
 int efg_rows(int32_t A);
 int64_t efg_buckets(int32_t A);
