@@ -259,7 +259,10 @@ struct ViewWs {
     uint64_t* t_sum;
     int64_t* t_min;
     int64_t* t_max;
+    uint4* agg_item;        // [kViewAggItems] (segment, part, parts, the segment's first item)
+    uint32_t* agg_done;     // [kViewAggItems] parts done, at the segment's first item
 };
+constexpr int kViewAggItems = 1024;   // parts of all segments that several blocks share, at most
 int64_t view_buckets(int32_t A);
 ViewWs view_ws_layout(Bump& b, int64_t n, int32_t A, int32_t V, int32_t tile, int64_t pair_cap,
                       int64_t rec_cap, int64_t cell_cap);

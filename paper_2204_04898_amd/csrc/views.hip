@@ -127,6 +127,8 @@ ViewWs view_ws_layout(Bump& b, int64_t n, int32_t A, int32_t V, int32_t tile, in
     w.t_sum = b.take<uint64_t>(cc);
     w.t_min = b.take<int64_t>(cc);
     w.t_max = b.take<int64_t>(cc);
+    w.agg_item = b.take<uint4>(kViewAggItems);
+    w.agg_done = b.take<uint32_t>(kViewAggItems);
     return w;
 }
 
@@ -137,7 +139,8 @@ namespace {
 // #pairs, [9] records (scan total), [10] nonzero when some case lasts 2^52
 // time units or more (records then keep the cell in a separate array), [11]
 // (view, bucket) pairs, [12] the gate after the count walk: 0, or the status
-// that stops the call
+// that stops the call, [13] work taken by the aggregation's blocks, [14]
+// aggregation items (parts of split segments)
 //
 // Record places.  The count walk adds each (tile, view) pair's records per
 // bucket to the (view, bucket) counter with one atomic, whose old value is the
@@ -162,6 +165,7 @@ __device__ __forceinline__ void ph_init(Grid gd, ViewWs w, int32_t V, int32_t A,
     for (int64_t i = i0; i < V; i += stride) w.view_cells[i] = 0;
     for (int64_t i = i0; i < w.n_vb; i += stride) w.vb_cnt[i] = 0;
     for (int64_t i = i0; i < (int64_t)V * A; i += stride) out.start_count[i] = 0;
+    for (int64_t i = i0; i < kViewAggItems; i += stride) w.agg_done[i] = 0;
     if (i0 < 16) w.scal[i0] = i0 == 11 ? w.n_vb : 0;
     if (i0 == 0) {
         *out.status = (status_in && *status_in) ? *status_in : 0;
@@ -690,8 +694,27 @@ __device__ __forceinline__ void ph_vb_flags(Grid gd, ViewWs w, int32_t V) {
 
 __global__ void k_view_vb_flags(ViewWs w, int32_t V) { ph_vb_flags(hw_grid(), w, V); }
 
+// Blocks that share a segment's records.  One block takes a segment unless
+// the segment alone is a sizeable part (1/512) of the call's records: a few
+// views of a few buckets would otherwise leave the chip idle behind their
+// largest segment.  A block adds up about 3000 records per us and folds
+// another block's table in about 2.5 us, so sqrt(count) / 96 parts make the
+// two times meet, and below 65536 records (22 us) sharing gains nothing;
+// count * 1024 / records bounds the parts of all segments by kViewAggItems.
+// Parts have more than 16384 records each (a segment has 9216 parts^2 records
+// at least), so a part's table of kCellsPerTable cells (28 bytes each) fits
+// over the records it was made of.  One view of 4M events, one bucket: 1343 us
+// by one block, 137 us shared; 48 views of a 3M-event log: 193 and 68 us.
+__device__ __forceinline__ uint32_t seg_parts(int64_t count, int64_t records) {
+    if (count < 65536 || count * 512 < records) return 1;
+    const uint32_t a = (uint32_t)(sqrtf((float)count) * (1.0f / 96.0f));
+    const uint32_t b = (uint32_t)(count * 1024 / records);
+    return a < b ? a : b;
+}
+
 // Segments: the non-empty (view, bucket) pairs in increasing order, each with
-// its first record; the records' total closes the list.
+// its first record; the records' total closes the list.  A segment that
+// several blocks share is listed part by part.
 __device__ __forceinline__ void ph_segs(Grid gd, ViewWs w) {
     for (int64_t i = (int64_t)gd.bid * blockDim.x + threadIdx.x; i < w.n_vb;
          i += (int64_t)gd.nblk * blockDim.x) {
@@ -699,6 +722,12 @@ __device__ __forceinline__ void ph_segs(Grid gd, ViewWs w) {
         const uint32_t g = w.vb_seg[i];
         w.seg_key[g] = (uint32_t)i;
         w.seg_rec[g] = w.vb_base[i];
+        const uint32_t parts = seg_parts(w.vb_cnt[i], w.scal[9]);
+        if (parts > 1) {
+            const uint32_t at = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&w.scal[14]),
+                                                    (unsigned long long)parts);
+            for (uint32_t q = 0; q < parts; ++q) w.agg_item[at + q] = make_uint4(g, q, parts, at);
+        }
     }
     if (gd.bid == 0 && threadIdx.x == 0) {
         const int64_t S = (int64_t)((uint32_t*)&w.scal[8])[0];
@@ -711,11 +740,12 @@ __global__ void k_view_segs(ViewWs w) { ph_segs(hw_grid(), w); }
 
 // LDS of an aggregation block: one 4096-cell table.
 struct AggSmem {
-    uint32_t scount[kCellsPerTable];
-    uint64_t ssum[kCellsPerTable];
+    alignas(16) uint32_t scount[kCellsPerTable];
+    alignas(16) uint64_t ssum[kCellsPerTable];
     alignas(16) int64_t smm[2 * kCellsPerTable];   // min, max of each cell side by side
     uint32_t tmp[kAB2 / kWave + 1];
-    int64_t s_base;
+    uint32_t s_last;
+    int64_t s_next[2], s_base;
 };
 
 // LDS of an activity-count block.
@@ -741,46 +771,106 @@ __device__ __forceinline__ void view_agg_rec(uint32_t* scount, uint64_t* ssum, i
     if (gg > mm.y) __hip_atomic_fetch_max(&smm[2 * cell + 1], gg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Records [r, r1) of a segment, this thread's share (stride kAB2), into the
-// LDS table; WIDE: the cell sits in rec_cell, else in the top 12 bits.
+// A batch of records: kAggU per thread (stride kAB2) from r0 on, those before
+// r1; WIDE: the cell sits in rec_cell, else in the top 12 bits.
+constexpr int kAggU = 8;
+constexpr int kAggBatch = kAggU * kAB2;
 template <bool WIDE>
-__device__ __forceinline__ void agg_records(const ViewWs& w, int64_t r, int64_t r1, uint32_t* scount,
-                                            uint64_t* ssum, int64_t* smm) {
-    constexpr int kU = 4;   // records in flight per thread
-    for (; r + (kU - 1) * kAB2 < r1; r += kU * kAB2) {
-        uint64_t x[kU];
-        uint32_t cell[kU];
+struct AggRecs {
+    uint64_t x[kAggU];
+    uint32_t cell[WIDE ? kAggU : 1];
+};
+template <bool WIDE>
+__device__ __forceinline__ void agg_load(const ViewWs& w, int64_t r0, int64_t r1, AggRecs<WIDE>& a) {
+    const int left = (int)(r1 - r0 < kAggBatch ? r1 - r0 : kAggBatch);   // block-uniform, may be negative
+    const uint64_t* g = w.rec_gap + r0;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            x[u] = w.rec_gap[r + u * kAB2];
-            if (WIDE) cell[u] = w.rec_cell[r + u * kAB2];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            view_agg_rec(scount, ssum, smm, WIDE ? cell[u] : (uint32_t)(x[u] >> 52),
-                         WIDE ? x[u] : (x[u] & (kRecGapLimit - 1)));
+    for (int u = 0; u < kAggU; ++u) {
+        const int i = u * kAB2 + threadIdx.x;
+        if (left == kAggBatch || i < left) a.x[u] = g[i];
     }
-    for (; r < r1; r += kAB2) {
-        const uint64_t x = w.rec_gap[r];
-        view_agg_rec(scount, ssum, smm, WIDE ? (uint32_t)w.rec_cell[r] : (uint32_t)(x >> 52),
-                     WIDE ? x : (x & (kRecGapLimit - 1)));
+    if constexpr (WIDE) {
+        const uint16_t* c = w.rec_cell + r0;
+#pragma unroll
+        for (int u = 0; u < kAggU; ++u) {
+            const int i = u * kAB2 + threadIdx.x;
+            if (i < left) a.cell[u] = c[i];
+        }
+    }
+}
+template <bool WIDE>
+__device__ __forceinline__ void agg_add(const AggRecs<WIDE>& a, int64_t r0, int64_t r1, AggSmem& L) {
+    const int left = (int)(r1 - r0 < kAggBatch ? r1 - r0 : kAggBatch);
+#pragma unroll
+    for (int u = 0; u < kAggU; ++u) {
+        if (u * kAB2 + (int)threadIdx.x >= left) break;
+        if constexpr (WIDE) view_agg_rec(L.scount, L.ssum, L.smm, a.cell[u], a.x[u]);
+        else view_agg_rec(L.scount, L.ssum, L.smm, (uint32_t)(a.x[u] >> 52), a.x[u] & (kRecGapLimit - 1));
     }
 }
 
-// One block per (view, bucket) segment: its records are one contiguous range,
-// streamed into a 4096-cell LDS table; after compaction only the touched
-// cells are reset, so the table is cleared once per block.
-__device__ __forceinline__ void ph_agg(Grid gd, int32_t A, ViewWs w, BatchedOutDev out, AggSmem& L) {
+// One piece of work of an aggregation block: records [r0, r1) of segment g
+// (view, bucket) = key; it: the item (segment, part, parts, first item), parts
+// = 0 for a segment that is not an item.
+struct AggWork {
+    uint4 it;
+    uint32_t key;
+    int64_t r0, r1;   // the segment's records
+    bool any, end;
+};
+__device__ __forceinline__ AggWork agg_work(const ViewWs& w, int64_t t, int64_t items, int64_t S) {
+    AggWork k;
+    k.end = t >= items + S;
+    k.it = make_uint4(0, 0, 0, 0);
+    k.key = 0;
+    k.r0 = k.r1 = 0;
+    if (t < items) k.it = w.agg_item[t];
+    else if (!k.end) k.it.x = (uint32_t)(t - items);
+    if (!k.end) {
+        k.key = w.seg_key[k.it.x];
+        k.r0 = w.seg_rec[k.it.x];
+        k.r1 = w.seg_rec[k.it.x + 1];
+    }
+    return k;
+}
+__device__ __forceinline__ int64_t part_begin(int64_t r0, int64_t count, uint32_t part, uint32_t parts) {
+    return r0 + count * part / parts;
+}
+
+// Where a part's table lies: over its own records, on a cache line of its own.
+__device__ __forceinline__ uint4* part_table(const ViewWs& w, int64_t r0) {
+    return reinterpret_cast<uint4*>((reinterpret_cast<uintptr_t>(w.rec_gap + r0) + 255) & ~(uintptr_t)255);
+}
+
+// A (view, bucket) segment's records are one contiguous range, streamed by a
+// block into a 4096-cell LDS table; after compaction only the touched cells
+// are reset, so the table is cleared once per block.  The table fills a CU's
+// LDS: one block runs per CU and no other hides its waits, so the block runs
+// ahead of itself.  Segments are taken from one counter (they differ by orders
+// of magnitude in size), two segments before they are added up; the first
+// records of the next segment are on their way while this one's cells are
+// read out; and these cells wait in registers for their place (one atomic on
+// the cells' cursor) while the next segment is added up.  4096 views of a 99M
+// event log (2.2G records, 266,000 segments): 8.1 ms with the waits, 7.3 ms
+// without; what remains is LDS time (three to five operations per record).
+// A segment shared by several blocks (seg_parts): each writes its table over
+// the records it has read, and the last to arrive folds the others' in.
+template <bool WIDE>
+__device__ __forceinline__ void agg_segments(int32_t A, const ViewWs& w, const BatchedOutDev& out, AggSmem& L) {
     uint32_t* scount = L.scount;
     uint64_t* ssum = L.ssum;
     int64_t* smm = L.smm;
-    uint32_t* tmp = L.tmp;
-    int64_t& s_base = L.s_base;
-    if (w.scal[12] != 0) return;
-    const int64_t S = w.scal[2];
+    const int64_t S = w.scal[2], R = w.scal[9], items = w.scal[14];
     const int64_t AA = (int64_t)A * A;
     const int NB = w.n_buckets;
-    const bool wide = w.scal[10] != 0;
+    constexpr int kPer = kCellsPerTable / kAB2;   // 4 cells per thread, blocked
+    const int c0 = threadIdx.x * kPer;
+    unsigned long long* ticket = reinterpret_cast<unsigned long long*>(&w.scal[13]);
+    unsigned long long* cursor = reinterpret_cast<unsigned long long*>(&w.scal[3]);
+    if (threadIdx.x == 0) {
+        L.s_next[0] = (int64_t)atomicAdd(ticket, 1ull);
+        L.s_next[1] = (int64_t)atomicAdd(ticket, 1ull);
+    }
     for (int c = threadIdx.x; c < kCellsPerTable; c += kAB2) {
         scount[c] = 0;
         ssum[c] = 0;
@@ -788,63 +878,157 @@ __device__ __forceinline__ void ph_agg(Grid gd, int32_t A, ViewWs w, BatchedOutD
         smm[2 * c + 1] = INT64_MIN;
     }
     __syncthreads();
-    for (int64_t g = gd.bid; g < S; g += gd.nblk) {
-        const uint32_t key = w.seg_key[g];
-        const uint32_t v = key / (uint32_t)NB;
-        const uint32_t bk = key % (uint32_t)NB;
-        const int64_t r1 = w.seg_rec[g + 1];
-        if (wide) agg_records<true>(w, w.seg_rec[g] + threadIdx.x, r1, scount, ssum, smm);
-        else agg_records<false>(w, w.seg_rec[g] + threadIdx.x, r1, scount, ssum, smm);
-        __syncthreads();
-        // compaction in cell order; start cells go straight to the start counts
-        constexpr int kPer = kCellsPerTable / kAB2;   // 4 cells per thread, blocked
-        uint32_t flags = 0, touched = 0;
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int c = threadIdx.x * kPer + q;
-            const int64_t cell = (int64_t)bk * kCellsPerTable + c;
-            if (scount[c] == 0) continue;
-            touched |= 1u << q;
-            if (cell < AA) flags |= 1u << q;
-            else if (cell < AA + A) out.start_count[(size_t)v * A + (cell - AA)] = scount[c];
+    // trims a work's records to its part; none for a segment whose parts are items
+    auto trim = [&](AggWork& k) {
+        const int64_t a = k.r0, n = k.r1 - k.r0;
+        if (k.it.z != 0) {
+            k.r0 = part_begin(a, n, k.it.y, k.it.z);
+            k.r1 = part_begin(a, n, k.it.y + 1, k.it.z);
         }
-        uint32_t total;
-        uint32_t rr = block_excl_sum<kAB2>((uint32_t)__popc(flags), tmp, &total);
+        k.any = !k.end && (k.it.z != 0 || seg_parts(n, R) == 1);
+        if (!k.any) k.r1 = k.r0;
+    };
+    AggRecs<WIDE> recs;
+    AggWork k = agg_work(w, wave_lane(L.s_next[0], 0), items, S);
+    int64_t tn = wave_lane(L.s_next[1], 0);   // the same in every lane
+    trim(k);
+    agg_load(w, k.r0, k.r1, recs);
+    __syncthreads();
+    // cells read out, not yet written: their place (thread 0), rank, values
+    int64_t base0 = 0;
+    uint32_t rr = 0, flags = 0, cellb = 0, total = 0;
+    uint32_t cnt[kPer];
+    uint64_t sum[kPer];
+    int64_t mn[kPer], mx[kPer];
+    uint32_t done_seg = 0;
+    bool done = false;
+    for (;;) {   // block-uniform
+        AggWork kn = agg_work(w, tn, items, S);
+        int64_t nt = 0;
+        if (threadIdx.x == 0 && !k.end) nt = (int64_t)atomicAdd(ticket, 1ull);
+        agg_add(recs, k.r0, k.r1, L);
+        for (int64_t r = k.r0 + kAggBatch; r < k.r1; r += kAggBatch) {
+            agg_load(w, r, k.r1, recs);
+            agg_add(recs, r, k.r1, L);
+        }
         if (threadIdx.x == 0) {
-            s_base = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(&w.scal[3]),
-                                        (unsigned long long)total);
-            w.seg_cells[g] = total;
-            w.seg_tmp[g] = s_base;
-            atomicAdd(&w.view_cells[v], total);
+            L.s_next[0] = nt;
+            L.s_base = base0;
+            if (done) {
+                w.seg_cells[done_seg] = total;
+                w.seg_tmp[done_seg] = base0;
+            }
         }
         __syncthreads();
-        const int64_t base = s_base;
-        if (base + (int64_t)total > w.cell_cap) flags = 0;   // over capacity: counted, not written
+        trim(kn);
+        tn = wave_lane(L.s_next[0], 0);
+        agg_load(w, kn.r0, kn.r1, recs);
+        if (done) {   // the segment before this one
+            const int64_t base = wave_lane(L.s_base, 0);
+            if (base + (int64_t)total > w.cell_cap) flags = 0;   // over capacity: counted, not written
+            int64_t at = base + rr;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                if (!(flags & (1u << q))) continue;
+                w.t_cell[at] = cellb + c0 + q;
+                w.t_count[at] = cnt[q];
+                w.t_sum[at] = sum[q];
+                w.t_min[at] = mn[q];
+                w.t_max[at] = mx[q];
+                ++at;
+            }
+        }
+        if (k.end) break;
+        bool mine = k.any;
+        if (k.it.z > 1) {
+            uint4* tab = part_table(w, k.r0);
+            tab[threadIdx.x] = *reinterpret_cast<const uint4*>(&scount[c0]);
+#pragma unroll
+            for (int q = 0; q < kPer / 2; ++q)
+                tab[kAB2 + q * kAB2 + threadIdx.x] = *reinterpret_cast<const uint4*>(&ssum[c0 + 2 * q]);
+#pragma unroll
+            for (int q = 0; q < kPer; ++q)
+                tab[3 * kAB2 + q * kAB2 + threadIdx.x] = *reinterpret_cast<const uint4*>(&smm[2 * (c0 + q)]);
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __threadfence();
+                L.s_last = atomicAdd(&w.agg_done[k.it.w], 1u) == k.it.z - 1;
+                __threadfence();
+            }
+            __syncthreads();
+            mine = L.s_last != 0;
+            if (mine) {
+                const int64_t a = w.seg_rec[k.it.x], n = w.seg_rec[k.it.x + 1] - a;
+                for (uint32_t p = 0; p < k.it.z; ++p) {
+                    if (p == k.it.y) continue;
+                    const uint4* o = part_table(w, part_begin(a, n, p, k.it.z));
+                    const uint4 oc = o[threadIdx.x];
+                    uint4 os[kPer / 2], om[kPer];
+#pragma unroll
+                    for (int q = 0; q < kPer / 2; ++q) os[q] = o[kAB2 + q * kAB2 + threadIdx.x];
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) om[q] = o[3 * kAB2 + q * kAB2 + threadIdx.x];
+                    const uint32_t cc[4] = {oc.x, oc.y, oc.z, oc.w};
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) {
+                        const uint4 ov = os[q / 2];
+                        scount[c0 + q] += cc[q];
+                        ssum[c0 + q] += q % 2 ? ((uint64_t)ov.w << 32 | ov.z) : ((uint64_t)ov.y << 32 | ov.x);
+                        const int64_t on = (int64_t)((uint64_t)om[q].y << 32 | om[q].x);
+                        const int64_t ox = (int64_t)((uint64_t)om[q].w << 32 | om[q].z);
+                        if (on < smm[2 * (c0 + q)]) smm[2 * (c0 + q)] = on;
+                        if (ox > smm[2 * (c0 + q) + 1]) smm[2 * (c0 + q) + 1] = ox;
+                    }
+                }
+            }
+        }
+        // the cells, in cell order; start cells go straight to the start counts
+        const uint32_t v = k.key / (uint32_t)NB;
+        cellb = (k.key % (uint32_t)NB) * (uint32_t)kCellsPerTable;
+        const uint4 n4 = *reinterpret_cast<const uint4*>(&scount[c0]);
+        cnt[0] = n4.x;
+        cnt[1] = n4.y;
+        cnt[2] = n4.z;
+        cnt[3] = n4.w;
+        flags = 0;
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-            if (!(touched & (1u << q))) continue;
-            const int c = threadIdx.x * kPer + q;
-            if (flags & (1u << q)) {
-                const int64_t at = base + rr;
-                w.t_cell[at] = (uint32_t)((int64_t)bk * kCellsPerTable + c);
-                w.t_count[at] = scount[c];
-                w.t_sum[at] = ssum[c];
-                w.t_min[at] = smm[2 * c];
-                w.t_max[at] = smm[2 * c + 1];
-                ++rr;
-            }
+            sum[q] = 0;   // (nothing of the segment before stays live)
+            mn[q] = mx[q] = 0;
+            if (cnt[q] == 0) continue;
+            const int c = c0 + q;
+            const int64_t cell = (int64_t)cellb + c;
+            sum[q] = ssum[c];
+            mn[q] = smm[2 * c];
+            mx[q] = smm[2 * c + 1];
             scount[c] = 0;   // reset for the next segment
             ssum[c] = 0;
             smm[2 * c] = INT64_MAX;
             smm[2 * c + 1] = INT64_MIN;
+            if (!mine) continue;
+            if (cell < AA) flags |= 1u << q;
+            else if (cell < AA + A) out.start_count[(size_t)v * A + (cell - AA)] = cnt[q];
         }
-        __syncthreads();
+        rr = block_excl_sum<kAB2>((uint32_t)__popc(flags), L.tmp, &total);
+        if (mine && threadIdx.x == 0) {
+            base0 = (int64_t)atomicAdd(cursor, (unsigned long long)total);
+            atomicAdd(&w.view_cells[v], total);
+        }
+        done = mine;
+        done_seg = k.it.x;
+        k = kn;
     }
+}
+
+__device__ __forceinline__ void ph_agg(int32_t A, const ViewWs& w, const BatchedOutDev& out, AggSmem& L) {
+    if (w.scal[12] != 0) return;
+    if (w.scal[10] != 0) agg_segments<true>(A, w, out, L);
+    else agg_segments<false>(A, w, out, L);
 }
 
 __global__ __launch_bounds__(kAB2) void k_view_agg(int32_t A, ViewWs w, BatchedOutDev out) {
     __shared__ AggSmem S;
-    ph_agg(hw_grid(), A, w, out, S);
+    ph_agg(A, w, out, S);
 }
 
 __device__ __forceinline__ void ph_copy(Grid gd, int32_t A, ViewWs w, BatchedOutDev out) {
@@ -1210,7 +1394,7 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
         ph_write<TILE, kFT / kWave>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
     }
     grid_barrier(gd, bar, ++k, st);
-    ph_agg(gd, PA.A, PA.w, PA.out, sm.agg);
+    ph_agg(PA.A, PA.w, PA.out, sm.agg);
     grid_barrier(gd, bar, ++k, st);
     {
         const FusedArgs a = PA;
