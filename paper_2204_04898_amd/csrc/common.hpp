@@ -149,6 +149,22 @@ __device__ __forceinline__ T wave_sum(T v) {
     return wave_lane(wave_incl_sum(v), kWave - 1);
 }
 
+// First position of the ascending a[0, n) not below x; a wave together, 64
+// probes a step (4 dependent loads over 16M entries, not 24).
+__device__ __forceinline__ int64_t lb_i32(const int32_t* a, int64_t n, int32_t x) {
+    int64_t lo = 0, hi = n;   // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t p = lo + (int64_t)lane() * step;
+        const uint64_t below = __ballot(p < hi && a[p < hi ? p : lo] < x);   // the first lanes, or none
+        if (below == 0) return lo;
+        const int64_t last = lo + (63 - (int64_t)__clzll((long long)below)) * step;   // a[last] < x
+        hi = last + step < hi ? last + step : hi;
+        lo = last + 1;
+    }
+    return lo;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_min(T v) {
 #pragma unroll

@@ -47,22 +47,6 @@ namespace {
 constexpr int kFB = 256;
 constexpr int kFI = kFilterTile / kFB;   // 16 events per thread
 
-// First position of the ascending a[0, n) not below x; a wave together, 64
-// probes a step (4 dependent loads over 16M entries, not 24).
-__device__ int64_t lb_i32(const int32_t* a, int64_t n, int32_t x) {
-    int64_t lo = 0, hi = n;   // the answer lies in [lo, hi]
-    while (lo < hi) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t p = lo + (int64_t)lane() * step;
-        const uint64_t below = __ballot(p < hi && a[p < hi ? p : lo] < x);   // the first lanes, or none
-        if (below == 0) return lo;
-        const int64_t last = lo + (63 - (int64_t)__clzll((long long)below)) * step;   // a[last] < x
-        hi = last + step < hi ? last + step : hi;
-        lo = last + 1;
-    }
-    return lo;
-}
-
 // scal: [0] p0, [1] p1, [3] kept total, [7] slice size or kept total when it
 // exceeded the output capacity.  One wave.
 __global__ __launch_bounds__(kWave) void k_filter_slice(const pm4g_view* view, const int64_t* case_off,

@@ -246,8 +246,8 @@ struct ViewWs {
     int64_t n_vb;           // V * n_buckets (view, bucket) pairs
     uint32_t* vb_cnt;       // [n_vb] records of each (view, bucket)
     int64_t* vb_base;       // [n_vb] its segment's first record (exclusive scan)
-    uint32_t* vb_flag;      // [n_vb] non-empty
-    uint32_t* vb_seg;       // [n_vb] segment index of a non-empty pair
+    uint32_t* vb_flag;      // (spare)
+    uint32_t* vb_seg;       // [n_vb] segments before it: its own index if it is not empty
     uint32_t* seg_key;      // [segments] view * n_buckets + bucket, increasing
     int64_t* seg_rec;       // [segments + 1] first record of each segment
     uint32_t* seg_cells;    // non-empty pair cells per segment

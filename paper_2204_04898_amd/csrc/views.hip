@@ -27,13 +27,14 @@
 //                    count per cell bucket (cell >> 12) and take each run's
 //                    place in its (view, bucket) segment with one atomic (kept
 //                    per (tile, view, bucket)), then write the runs
-//   scans            (view, bucket) counters -> segment places; non-empty
-//                    pairs -> the segment list
-//   k_view_agg       one block per (view, bucket) segment: 4096-cell LDS table;
+//   k_view_place_*   (view, bucket) counters -> segment places, segment list, gate
+//   k_view_agg       a block (large segments: several) per (view, bucket)
+//                    segment: 4096-cell LDS table;
 //                    non-empty pair cells -> temporary sparse records, start
 //                    cells -> start counts
-//   scans, copy      per-view lists ordered by (src, dst), offsets, FP64 mean
-//   k_view_acts      per view: activity and end counts from the start counts
+//   k_view_out_*     places of the output cells, required sizes, status
+//   k_view_out       per-view lists ordered by (src, dst), offsets, FP64 mean;
+//                    per view: activity and end counts from the start counts
 //                    and the row / column sums
 #include <math.h>
 
@@ -134,13 +135,11 @@ ViewWs view_ws_layout(Bump& b, int64_t n, int32_t A, int32_t V, int32_t tile, in
 
 namespace {
 
-// scal: [2] #segments (u32 total written at [8] as u32 by the scan, copied
-// here), [3] temporary cell cursor, [4] total output cells, [6] #views, [7]
-// #pairs, [9] records (scan total), [10] nonzero when some case lasts 2^52
-// time units or more (records then keep the cell in a separate array), [11]
-// (view, bucket) pairs, [12] the gate after the count walk: 0, or the status
-// that stops the call, [13] work taken by the aggregation's blocks, [14]
-// aggregation items (parts of split segments)
+// scal: [2] #segments, [3] temporary cell cursor, [4] total output cells, [7]
+// #pairs, [9] records, [10] nonzero when some case lasts 2^52 time units or
+// more (records then keep the cell in a separate array), [12] the gate after
+// the count walk: 0, or the status that stops the call, [13] work taken by the
+// aggregation's blocks, [14] aggregation items (parts of split segments)
 //
 // Record places.  The count walk adds each (tile, view) pair's records per
 // bucket to the (view, bucket) counter with one atomic, whose old value is the
@@ -166,7 +165,7 @@ __device__ __forceinline__ void ph_init(Grid gd, ViewWs w, int32_t V, int32_t A,
     for (int64_t i = i0; i < w.n_vb; i += stride) w.vb_cnt[i] = 0;
     for (int64_t i = i0; i < (int64_t)V * A; i += stride) out.start_count[i] = 0;
     for (int64_t i = i0; i < kViewAggItems; i += stride) w.agg_done[i] = 0;
-    if (i0 < 16) w.scal[i0] = i0 == 11 ? w.n_vb : 0;
+    if (i0 < 16) w.scal[i0] = 0;
     if (i0 == 0) {
         *out.status = (status_in && *status_in) ? *status_in : 0;
         out.required[0] = 0;
@@ -195,33 +194,21 @@ __device__ __forceinline__ void ph_span(Grid gd, const int64_t* __restrict__ cas
     if (__ballot(wide) != 0 && lane() == 0) atomicOr(reinterpret_cast<unsigned long long*>(&w.scal[10]), 1ull);
 }
 
-__global__ void k_view_span(const int64_t* __restrict__ case_off, const int64_t* __restrict__ ts_s,
-                            const int64_t* n_cases, ViewWs w) {
-    ph_span(hw_grid(), case_off, ts_s, n_cases, w);
-}
-
-__device__ int64_t lower_bound_i32(const int32_t* a, int64_t n, int32_t x) {
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (a[mid] < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// Event slice of every view (whole cases) and the per-tile overlap differences.
+// Event slice of every view (whole cases) and the per-tile overlap differences:
+// one wave per view, whose lanes search the case table together.
 __device__ __forceinline__ void ph_slice(Grid gd, const pm4g_view* views, int32_t V, const int64_t* case_off,
                                          const int32_t* case_code, const int64_t* n_cases, ViewWs w) {
     const int64_t C = *n_cases;
-    for (int64_t v = (int64_t)gd.bid * blockDim.x + threadIdx.x; v < V;
-         v += (int64_t)gd.nblk * blockDim.x) {
+    const int64_t wv = ((int64_t)gd.bid * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nw = (int64_t)gd.nblk * blockDim.x / kWave;
+    for (int64_t v = wv; v < V; v += nw) {   // wave-uniform
         const pm4g_view vw = views[v];
         int64_t p0 = 0, p1 = 0;
         if (vw.case_lo < vw.case_hi && vw.t_lo <= vw.t_hi) {
-            p0 = case_off[lower_bound_i32(case_code, C, vw.case_lo)];
-            p1 = case_off[lower_bound_i32(case_code, C, vw.case_hi)];
+            p0 = case_off[lb_i32(case_code, C, vw.case_lo)];
+            p1 = case_off[lb_i32(case_code, C, vw.case_hi)];
         }
+        if (lane() != 0) continue;
         w.p0[v] = p0;
         w.p1[v] = p1;
         if (p1 > p0) {
@@ -231,35 +218,44 @@ __device__ __forceinline__ void ph_slice(Grid gd, const pm4g_view* views, int32_
     }
 }
 
-__global__ void k_view_slice(const pm4g_view* views, int32_t V, const int64_t* case_off,
-                             const int32_t* case_code, const int64_t* n_cases, ViewWs w) {
+// The case spans and the views' slices: both follow the zeroing of their words
+// and nothing of one depends on the other.
+__global__ void k_view_slice(const pm4g_view* views, int32_t V, const int64_t* __restrict__ case_off,
+                             const int64_t* __restrict__ ts_s, const int32_t* case_code, const int64_t* n_cases,
+                             ViewWs w) {
     ph_slice(hw_grid(), views, V, case_off, case_code, n_cases, w);
+    ph_span(hw_grid(), case_off, ts_s, n_cases, w);
 }
 
-// tcount holds differences; one block turns them into counts and offsets.
+// tcount holds differences; one block turns them into counts and offsets (each
+// thread a contiguous run of tiles: two block scans in all).
 __device__ __forceinline__ void ph_tile_scan(Grid gd, ViewWs w) {
     __shared__ uint32_t tmp[1024 / kWave + 1];
     if (gd.bid != 0) return;   // one block (of 1024 threads)
-    uint32_t run_cnt = 0, run_off = 0;
     const int64_t nt = w.n_tiles;
-    for (int64_t t0 = 0; t0 < nt; t0 += 1024) {
-        const int64_t t = t0 + threadIdx.x;
-        const uint32_t d = t < nt ? w.tcount[t] : 0u;
-        uint32_t total;
-        const uint32_t ex = block_excl_sum<1024>(d, tmp, &total);
-        const uint32_t cnt = run_cnt + ex + d;
-        uint32_t total2;
-        const uint32_t ex2 = block_excl_sum<1024>(t < nt ? cnt : 0u, tmp, &total2);
-        if (t < nt) {
-            w.tcount[t] = cnt;
-            w.toff[t] = run_off + ex2;
-        }
-        run_cnt += total;
-        run_off += total2;
+    const int64_t per = (nt + 1023) / 1024;
+    const int64_t a = per * threadIdx.x < nt ? per * threadIdx.x : nt;
+    const int64_t b = a + per < nt ? a + per : nt;
+    uint32_t d = 0, total;
+#pragma unroll 8
+    for (int64_t t = a; t < b; ++t) d += w.tcount[t];
+    uint32_t cnt = block_excl_sum<1024>(d, tmp, &total);
+    const uint32_t cnt0 = cnt;
+    uint32_t pairs = 0;
+#pragma unroll 8
+    for (int64_t t = a; t < b; ++t) pairs += (cnt += w.tcount[t]);
+    uint32_t off = block_excl_sum<1024>(pairs, tmp, &total);
+    cnt = cnt0;
+#pragma unroll 8
+    for (int64_t t = a; t < b; ++t) {
+        cnt += w.tcount[t];
+        w.tcount[t] = cnt;
+        w.toff[t] = off;
+        off += cnt;
     }
     if (threadIdx.x == 0) {
-        w.toff[nt] = run_off;
-        w.scal[7] = run_off;
+        w.toff[nt] = total;
+        w.scal[7] = total;
     }
 }
 
@@ -671,29 +667,6 @@ __global__ __launch_bounds__(kVB) void k_view_write(const int32_t* __restrict__ 
     ph_write<TILE, kVW>(hw_grid(), case_s, act_s, ts_s, n, A, views, masks, w, S);
 }
 
-// The gate after the count walk and the segment scans: every capacity the
-// later kernels write into is known now; if one is short (or the records
-// exceed 32-bit places) the call stops here, reported by k_view_finish.
-__device__ __forceinline__ void ph_gate(Grid gd, ViewWs w) {
-    if (threadIdx.x == 0 && gd.bid == 0) {
-        int64_t g = 0;
-        if (w.scal[7] > w.pair_cap || w.scal[9] > w.rec_cap) g = PM4G_E_CAPACITY;
-        if (w.scal[7] <= w.pair_cap && w.scal[9] > (int64_t)0xFFFFFFFF) g = PM4G_E_INVALID;
-        w.scal[12] = g;
-    }
-}
-
-__global__ void k_view_gate(ViewWs w) { ph_gate(hw_grid(), w); }
-
-__device__ __forceinline__ void ph_vb_flags(Grid gd, ViewWs w, int32_t V) {
-    for (int64_t i = (int64_t)gd.bid * blockDim.x + threadIdx.x; i < w.n_vb;
-         i += (int64_t)gd.nblk * blockDim.x)
-        w.vb_flag[i] = w.vb_cnt[i] != 0 ? 1u : 0u;
-    if (gd.bid == 0 && threadIdx.x == 0) w.scal[6] = V;
-}
-
-__global__ void k_view_vb_flags(ViewWs w, int32_t V) { ph_vb_flags(hw_grid(), w, V); }
-
 // Blocks that share a segment's records.  One block takes a segment unless
 // the segment alone is a sizeable part (1/512) of the call's records: a few
 // views of a few buckets would otherwise leave the chip idle behind their
@@ -712,31 +685,117 @@ __device__ __forceinline__ uint32_t seg_parts(int64_t count, int64_t records) {
     return a < b ? a : b;
 }
 
-// Segments: the non-empty (view, bucket) pairs in increasing order, each with
-// its first record; the records' total closes the list.  A segment that
-// several blocks share is listed part by part.
-__device__ __forceinline__ void ph_segs(Grid gd, ViewWs w) {
-    for (int64_t i = (int64_t)gd.bid * blockDim.x + threadIdx.x; i < w.n_vb;
-         i += (int64_t)gd.nblk * blockDim.x) {
-        if (!w.vb_flag[i]) continue;
-        const uint32_t g = w.vb_seg[i];
-        w.seg_key[g] = (uint32_t)i;
-        w.seg_rec[g] = w.vb_base[i];
-        const uint32_t parts = seg_parts(w.vb_cnt[i], w.scal[9]);
-        if (parts > 1) {
-            const uint32_t at = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&w.scal[14]),
-                                                    (unsigned long long)parts);
-            for (uint32_t q = 0; q < parts; ++q) w.agg_item[at + q] = make_uint4(g, q, parts, at);
-        }
+// Places of the segments: the non-empty (view, bucket) pairs in increasing
+// order, each with its first record.  Every block takes a contiguous range of
+// the counters: its sums first (ph_place_sum); with all blocks' sums at hand,
+// each block places its own range (ph_place), and the first one, which knows
+// the totals too, closes the lists and sets the gate: every capacity the later
+// kernels write into is known now; if one is short (or the records exceed
+// 32-bit places) the call stops here, reported at the end.  Two launches
+// where flags, two scans, gate and segment list took seven.
+constexpr int kPB = 256;   // threads per block of the placing kernels
+__device__ __forceinline__ int64_t place_chunk(Grid gd, int64_t n) {
+    return ((n + gd.nblk - 1) / gd.nblk + 3) & ~int64_t(3);
+}
+
+template <int BLOCK>
+struct PlaceSmem {
+    int64_t tmp[BLOCK / kWave + 1];
+};
+
+template <int BLOCK>
+__device__ __forceinline__ void ph_place_sum(Grid gd, ViewWs w, PlaceSmem<BLOCK>& L) {
+    const int64_t chunk = place_chunk(gd, w.n_vb);
+    const int64_t b0 = gd.bid * chunk;
+    const int64_t b1 = (b0 + chunk) < w.n_vb ? (b0 + chunk) : w.n_vb;
+    int64_t recs = 0;
+    uint32_t segs = 0;
+    for (int64_t i = b0 + 4 * threadIdx.x; i < b1; i += 4 * BLOCK) {
+        const uint4 c = dev::scan_load(w.vb_cnt, i, b1);
+        recs += (int64_t)c.x + c.y + c.z + c.w;
+        segs += (c.x != 0) + (c.y != 0) + (c.z != 0) + (c.w != 0);
     }
-    if (gd.bid == 0 && threadIdx.x == 0) {
-        const int64_t S = (int64_t)((uint32_t*)&w.scal[8])[0];
-        w.seg_rec[S] = w.scal[9];
-        w.scal[2] = S;
+    int64_t r, g;
+    block_excl_sum<BLOCK>(recs, L.tmp, &r);
+    block_excl_sum<BLOCK>((int64_t)segs, L.tmp, &g);
+    if (threadIdx.x == 0) {
+        w.part64[gd.bid] = r;
+        w.part32[gd.bid] = (uint32_t)g;
     }
 }
 
-__global__ void k_view_segs(ViewWs w) { ph_segs(hw_grid(), w); }
+__global__ __launch_bounds__(kPB) void k_view_place_sum(ViewWs w) {
+    __shared__ PlaceSmem<kPB> L;
+    ph_place_sum<kPB>(hw_grid(), w, L);
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void ph_place(Grid gd, ViewWs w, PlaceSmem<BLOCK>& L) {
+    int64_t rb = 0, rt = 0, sb = 0, st = 0;   // records, segments: before this block, of all blocks
+    for (int64_t k = threadIdx.x; k < gd.nblk; k += BLOCK) {
+        const int64_t r = w.part64[k], g = w.part32[k];
+        rt += r;
+        st += g;
+        if (k < gd.bid) {
+            rb += r;
+            sb += g;
+        }
+    }
+    int64_t run, seg, R, S;
+    block_excl_sum<BLOCK>(rb, L.tmp, &run);
+    block_excl_sum<BLOCK>(sb, L.tmp, &seg);
+    block_excl_sum<BLOCK>(rt, L.tmp, &R);
+    block_excl_sum<BLOCK>(st, L.tmp, &S);
+    if (gd.bid == 0 && threadIdx.x == 0) {
+        int64_t g = 0;
+        if (w.scal[7] > w.pair_cap || R > w.rec_cap) g = PM4G_E_CAPACITY;
+        if (w.scal[7] <= w.pair_cap && R > (int64_t)0xFFFFFFFF) g = PM4G_E_INVALID;
+        w.scal[12] = g;
+        w.scal[9] = R;
+        w.scal[2] = S;
+        w.seg_rec[S] = R;
+    }
+    const int64_t chunk = place_chunk(gd, w.n_vb);
+    const int64_t b0 = gd.bid * chunk;
+    const int64_t b1 = (b0 + chunk) < w.n_vb ? (b0 + chunk) : w.n_vb;
+    for (int64_t c0 = b0; c0 < b1; c0 += 4 * BLOCK) {   // block-uniform
+        const int64_t i0 = c0 + 4 * threadIdx.x;
+        const uint4 c = dev::scan_load(w.vb_cnt, i0, b1);
+        const uint32_t cnt[4] = {c.x, c.y, c.z, c.w};
+        // records (below 2^43) and segments of the step in one word
+        int64_t v = 0, total;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v += (int64_t)cnt[q] + (cnt[q] ? int64_t(1) << 48 : 0);
+        const int64_t ex = block_excl_sum<BLOCK>(v, L.tmp, &total);
+        int64_t rec = run + (ex & ((int64_t(1) << 48) - 1));
+        uint32_t g = (uint32_t)(seg + (ex >> 48));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = i0 + q;
+            if (i >= b1) break;
+            w.vb_base[i] = rec;
+            w.vb_seg[i] = g;
+            if (cnt[q] == 0) continue;
+            w.seg_key[g] = (uint32_t)i;
+            w.seg_rec[g] = rec;
+            const uint32_t parts = seg_parts(cnt[q], R);
+            if (parts > 1) {   // a segment that several blocks share is listed part by part
+                const uint32_t at = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&w.scal[14]),
+                                                        (unsigned long long)parts);
+                for (uint32_t p = 0; p < parts; ++p) w.agg_item[at + p] = make_uint4(g, p, parts, at);
+            }
+            rec += cnt[q];
+            ++g;
+        }
+        run += total & ((int64_t(1) << 48) - 1);
+        seg += total >> 48;
+    }
+}
+
+__global__ __launch_bounds__(kPB) void k_view_place(ViewWs w) {
+    __shared__ PlaceSmem<kPB> L;
+    ph_place<kPB>(hw_grid(), w, L);
+}
 
 // LDS of an aggregation block: one 4096-cell table.
 struct AggSmem {
@@ -1031,17 +1090,106 @@ __global__ __launch_bounds__(kAB2) void k_view_agg(int32_t A, ViewWs w, BatchedO
     ph_agg(A, w, out, S);
 }
 
+// Places of the output cells: per segment and per view, by block sums and
+// then each block's own range, as for the segments; the first block ends the
+// call's bookkeeping (totals, required sizes, status).
+template <int BLOCK>
+__device__ __forceinline__ void ph_out_sum(Grid gd, int32_t V, ViewWs w, PlaceSmem<BLOCK>& L) {
+    const int64_t S = w.scal[12] ? 0 : w.scal[2];
+    const int64_t ns[2] = {S, (int64_t)V};
+    const uint32_t* in[2] = {w.seg_cells, w.view_cells};
+    int64_t* part[2] = {w.part64, w.part64b};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int64_t chunk = place_chunk(gd, ns[k]);
+        const int64_t b0 = gd.bid * chunk;
+        const int64_t b1 = (b0 + chunk) < ns[k] ? (b0 + chunk) : ns[k];
+        int64_t c = 0, t;
+        for (int64_t i = b0 + 4 * threadIdx.x; i < b1; i += 4 * BLOCK) {
+            const uint4 x = dev::scan_load(in[k], i, b1);
+            c += (int64_t)x.x + x.y + x.z + x.w;
+        }
+        block_excl_sum<BLOCK>(c, L.tmp, &t);
+        if (threadIdx.x == 0) part[k][gd.bid] = t;
+    }
+}
+
+__global__ __launch_bounds__(kPB) void k_view_out_sum(int32_t V, ViewWs w) {
+    __shared__ PlaceSmem<kPB> L;
+    ph_out_sum<kPB>(hw_grid(), V, w, L);
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void ph_out_place(Grid gd, int32_t V, ViewWs w, BatchedOutDev out, PlaceSmem<BLOCK>& L) {
+    const int64_t gate = w.scal[12];
+    const int64_t ns[2] = {gate ? 0 : w.scal[2], (int64_t)V};
+    const uint32_t* in[2] = {w.seg_cells, w.view_cells};
+    const int64_t* part[2] = {w.part64, w.part64b};
+    int64_t* to[2] = {w.seg_out, out.edge_off};
+    int64_t cells = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        int64_t b = 0, t = 0, run, all;
+        for (int64_t j = threadIdx.x; j < gd.nblk; j += BLOCK) {
+            const int64_t x = part[k][j];
+            t += x;
+            if (j < gd.bid) b += x;
+        }
+        block_excl_sum<BLOCK>(b, L.tmp, &run);
+        block_excl_sum<BLOCK>(t, L.tmp, &all);
+        if (k == 0) cells = all;
+        const int64_t chunk = place_chunk(gd, ns[k]);
+        const int64_t b0 = gd.bid * chunk;
+        const int64_t b1 = (b0 + chunk) < ns[k] ? (b0 + chunk) : ns[k];
+        for (int64_t c0 = b0; c0 < b1; c0 += 4 * BLOCK) {   // block-uniform
+            const int64_t i0 = c0 + 4 * threadIdx.x;
+            const uint4 x = dev::scan_load(in[k], i0, b1);
+            const uint32_t c[4] = {x.x, x.y, x.z, x.w};
+            int64_t total;
+            int64_t at = run + block_excl_sum<BLOCK>((int64_t)c[0] + c[1] + c[2] + c[3], L.tmp, &total);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (i0 + q < b1) to[k][i0 + q] = at;
+                at += c[q];
+            }
+            run += total;
+        }
+    }
+    if (gd.bid == 0 && threadIdx.x == 0) {
+        const bool pairs_short = w.scal[7] > w.pair_cap;   // then the count walk did not run
+        w.scal[4] = cells;
+        out.edge_off[V] = cells;
+        out.required[0] = cells;                            // 0 (unknown) until the records are placed
+        out.required[1] = pairs_short ? 0 : w.scal[9];
+        out.required[2] = w.scal[7] * (int64_t)w.n_buckets;   // run places: pairs x buckets
+        out.required[3] = w.scal[7];
+        out.required[4] = gate ? 0 : w.scal[3];
+        if (gate) set_status(out.status, (int32_t)gate);
+        else if (cells > out.cap_edges || w.scal[3] > w.cell_cap) set_status(out.status, PM4G_E_CAPACITY);
+    }
+}
+
+__global__ __launch_bounds__(kPB) void k_view_out_place(int32_t V, ViewWs w, BatchedOutDev out) {
+    __shared__ PlaceSmem<kPB> L;
+    ph_out_place<kPB>(hw_grid(), V, w, out, L);
+}
+
 __device__ __forceinline__ void ph_copy(Grid gd, int32_t A, ViewWs w, BatchedOutDev out) {
     const int64_t S = w.scal[2];
     const bool fits = w.scal[12] == 0 && w.scal[4] <= out.cap_edges && w.scal[3] <= w.cell_cap;
     if (!fits) return;
-    const int wv = (gd.bid * blockDim.x + threadIdx.x) / kWave;
-    const int nw = gd.nblk * blockDim.x / kWave;
-    for (int64_t g = wv; g < S; g += nw) {
+    constexpr int kU = 4;                                      // all loads of kU steps issued before the stores
+    constexpr int kMost = kCellsPerTable / (kU * kWave);       // waves that a segment can use
+    const int64_t wv = ((int64_t)gd.bid * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nw = (int64_t)gd.nblk * blockDim.x / kWave;
+    // few segments: several waves per segment, so that none copies 4096 cells alone
+    const int64_t spare = S > 0 ? nw / S : 1;
+    const int64_t per = spare < 1 ? 1 : (spare < kMost ? spare : kMost);
+    for (int64_t q = wv; q < S * per; q += nw) {
+        const int64_t g = q / per;
         const int64_t src = w.seg_tmp[g], dst = w.seg_out[g];
         const uint32_t m = w.seg_cells[g];
-        constexpr int kU = 4;   // all loads of kU steps issued before the stores
-        for (uint32_t r0 = 0; r0 < m; r0 += kU * kWave) {
+        for (uint32_t r0 = (uint32_t)(q % per) * kU * kWave; r0 < m; r0 += (uint32_t)per * kU * kWave) {
             uint32_t cell[kU], cnt[kU];
             uint64_t sum[kU];
             int64_t mn[kU], mx[kU];
@@ -1085,28 +1233,17 @@ __device__ __forceinline__ void ph_acts(Grid gd, int32_t V, int32_t A, ViewWs w,
     int64_t* s_src = L.s_src;
     uint32_t* s_m = L.s_m;
     const int64_t S = w.scal[2];
-    const uint32_t NB = (uint32_t)w.n_buckets;
+    const int64_t NB = w.n_buckets;
     if (w.scal[12] != 0 || w.scal[3] > w.cell_cap) return;   // temporary cells were not all written
     for (int64_t v = gd.bid; v < V; v += gd.nblk) {
         for (int a = threadIdx.x; a < A; a += BLOCK) rows[a] = cols[a] = 0;
         __syncthreads();
-        // first segment of this view: lower bound of key v*NB over segment keys
-        int64_t lo = 0, hi = S;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (w.seg_key[mid] < (uint32_t)v * NB) lo = mid + 1;
-            else hi = mid;
-        }
         // the view's segments (at most NB): their places and cell counts to LDS
-        int ns = 0;
-        for (int k0 = 0; k0 < (int)NB; k0 += BLOCK) {
-            const int k = k0 + threadIdx.x;
-            const bool mine = k < (int)NB && lo + k < S && w.seg_key[lo + k] / NB == (uint32_t)v;
-            if (mine) {
-                s_src[k] = w.seg_tmp[lo + k];
-                s_m[k] = w.seg_cells[lo + k];
-            }
-            ns += __syncthreads_count(mine);
+        const int64_t lo = w.vb_seg[v * NB];
+        const int ns = (int)((v + 1 < V ? (int64_t)w.vb_seg[(v + 1) * NB] : S) - lo);
+        for (int k = threadIdx.x; k < ns; k += BLOCK) {
+            s_src[k] = w.seg_tmp[lo + k];
+            s_m[k] = w.seg_cells[lo + k];
         }
         __syncthreads();
         for (int g = 0; g < ns; ++g) {
@@ -1179,75 +1316,7 @@ __global__ __launch_bounds__(256) void k_view_out(int32_t V, int32_t A, ViewWs w
                      out, S);
 }
 
-__device__ __forceinline__ void ph_finish(Grid gd, int32_t V, ViewWs w, BatchedOutDev out) {
-    if (threadIdx.x == 0 && gd.bid == 0) {
-        const int64_t gate = w.scal[12];
-        const bool pairs_short = w.scal[7] > w.pair_cap;   // then the count walk did not run
-        out.edge_off[V] = gate ? 0 : w.scal[4];
-        out.required[0] = gate ? 0 : w.scal[4];             // unknown until the records are placed
-        out.required[1] = pairs_short ? 0 : w.scal[9];
-        out.required[2] = w.scal[7] * (int64_t)w.n_buckets;   // run places: pairs x buckets
-        out.required[3] = w.scal[7];
-        out.required[4] = gate ? 0 : w.scal[3];
-        if (gate) set_status(out.status, (int32_t)gate);
-        else if (w.scal[4] > out.cap_edges || w.scal[3] > w.cell_cap) set_status(out.status, PM4G_E_CAPACITY);
-    }
-}
-
-__global__ void k_view_finish(int32_t V, ViewWs w, BatchedOutDev out) { ph_finish(hw_grid(), V, w, out); }
-
-
 // ---- the single persistent launch ----
-
-// Exclusive scans over the persistent grid: per-block sums of contiguous
-// chunks, one block scans the sums (nblk <= 1024 = the block size), each block
-// applies its prefix.
-template <typename T>
-__device__ __forceinline__ void gscan_reduce(Grid gd, const uint32_t* in, int64_t n, T* partial) {
-    __shared__ T red[kFT / kWave];
-    const int64_t chunk = (n + gd.nblk - 1) / gd.nblk;
-    const int64_t b0 = gd.bid * chunk;
-    const int64_t b1 = (b0 + chunk) < n ? (b0 + chunk) : n;
-    T sum = 0;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += kFT) sum += in[i];
-    sum = wave_sum(sum);
-    if (lane() == 0) red[threadIdx.x / kWave] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        T t = 0;
-        for (int k = 0; k < kFT / kWave; ++k) t += red[k];
-        partial[gd.bid] = t;
-    }
-    __syncthreads();
-}
-
-template <typename T>
-__device__ __forceinline__ void gscan_top(Grid gd, T* partial, T* total) {
-    __shared__ T tmp[kFT / kWave + 1];
-    if (gd.bid != 0) return;
-    const T v = (int64_t)threadIdx.x < gd.nblk ? partial[threadIdx.x] : (T)0;
-    T tot;
-    const T ex = block_excl_sum<kFT>(v, tmp, &tot);
-    if ((int64_t)threadIdx.x < gd.nblk) partial[threadIdx.x] = ex;
-    if (threadIdx.x == 0 && total) *total = tot;
-}
-
-template <typename T>
-__device__ __forceinline__ void gscan_apply(Grid gd, const uint32_t* in, int64_t n, const T* partial, T* out) {
-    __shared__ T tmp[kFT / kWave + 1];
-    const int64_t chunk = (n + gd.nblk - 1) / gd.nblk;
-    const int64_t b0 = gd.bid * chunk;
-    const int64_t b1 = (b0 + chunk) < n ? (b0 + chunk) : n;
-    T run = partial[gd.bid];
-    for (int64_t c0 = b0; c0 < b1; c0 += kFT) {   // block-uniform
-        const int64_t i = c0 + threadIdx.x;
-        const T v = i < b1 ? (T)in[i] : (T)0;
-        T tot;
-        const T ex = block_excl_sum<kFT>(v, tmp, &tot);
-        if (i < b1) out[i] = run + ex;
-        run += tot;
-    }
-}
 
 // Grid barrier of the persistent launch (every block resident: a cooperative
 // launch).  Block b announces its arrival at barrier k by writing the tag
@@ -1322,6 +1391,7 @@ union FusedSmem {
     WalkSmem<TILE, kFT / kWave> walk;
     AggSmem agg;
     ActsSmem<kFT> acts;
+    PlaceSmem<kFT> place;
 };
 
 // The whole batched call in one launch: the phases of the per-phase kernels,
@@ -1364,30 +1434,9 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
         ph_count<TILE, kFT / kWave>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
     }
     grid_barrier(gd, bar, ++k, st);
-    ph_vb_flags(gd, PA.w, PA.V);
+    ph_place_sum<kFT>(gd, PA.w, sm.place);
     grid_barrier(gd, bar, ++k, st);
-    {
-        const ViewWs w = PA.w;
-        const int64_t nvb = w.scal[11];
-        gscan_reduce<int64_t>(gd, w.vb_cnt, nvb, w.part64);
-        gscan_reduce<uint32_t>(gd, w.vb_flag, nvb, w.part32);
-    }
-    grid_barrier(gd, bar, ++k, st);
-    {
-        const ViewWs w = PA.w;
-        gscan_top<int64_t>(gd, w.part64, &w.scal[9]);
-        gscan_top<uint32_t>(gd, w.part32, reinterpret_cast<uint32_t*>(&w.scal[8]));
-    }
-    grid_barrier(gd, bar, ++k, st);
-    {
-        const ViewWs w = PA.w;
-        const int64_t nvb = w.scal[11];
-        gscan_apply<int64_t>(gd, w.vb_cnt, nvb, w.part64, w.vb_base);
-        gscan_apply<uint32_t>(gd, w.vb_flag, nvb, w.part32, w.vb_seg);
-    }
-    grid_barrier(gd, bar, ++k, st);
-    ph_gate(gd, PA.w);
-    ph_segs(gd, PA.w);
+    ph_place<kFT>(gd, PA.w, sm.place);
     grid_barrier(gd, bar, ++k, st);
     {
         const FusedArgs a = PA;
@@ -1396,25 +1445,9 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
     grid_barrier(gd, bar, ++k, st);
     ph_agg(PA.A, PA.w, PA.out, sm.agg);
     grid_barrier(gd, bar, ++k, st);
-    {
-        const FusedArgs a = PA;
-        const int64_t S = a.w.scal[2];
-        gscan_reduce<int64_t>(gd, a.w.seg_cells, S, a.w.part64);
-        gscan_reduce<int64_t>(gd, a.w.view_cells, a.V, a.w.part64b);
-    }
+    ph_out_sum<kFT>(gd, PA.V, PA.w, sm.place);
     grid_barrier(gd, bar, ++k, st);
-    {
-        const FusedArgs a = PA;
-        gscan_top<int64_t>(gd, a.w.part64, &a.w.scal[4]);
-        gscan_top<int64_t>(gd, a.w.part64b, nullptr);
-    }
-    grid_barrier(gd, bar, ++k, st);
-    {
-        const FusedArgs a = PA;
-        const int64_t S = a.w.scal[2];
-        gscan_apply<int64_t>(gd, a.w.seg_cells, S, a.w.part64, a.w.seg_out);
-        gscan_apply<int64_t>(gd, a.w.view_cells, a.V, a.w.part64b, a.out.edge_off);
-    }
+    ph_out_place<kFT>(gd, PA.V, PA.w, PA.out, sm.place);
     grid_barrier(gd, bar, ++k, st);
     {   // the copy on half of the blocks, the activity counts on the other half
         const int64_t half = gd.nblk / 2 > 0 ? gd.nblk / 2 : 1;
@@ -1422,8 +1455,6 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
         if (gd.bid >= half || gd.nblk < 2)
             ph_acts<kFT>(gd.nblk < 2 ? gd : Grid{gd.bid - half, gd.nblk - half}, PA.V, PA.A, PA.w, PA.out, sm.acts);
     }
-    grid_barrier(gd, bar, ++k, st);
-    ph_finish(gd, PA.V, PA.w, PA.out);
 #undef PA
 }
 
@@ -1463,14 +1494,19 @@ hipError_t launch_views_fused(const pm4g_prepared* p, const pm4g_view* views, co
     return hipLaunchCooperativeKernel(fn, dim3((unsigned)grid), dim3(kFT), args, 0, s);
 }
 
+// Blocks of the placing kernels: a step of four entries per thread each, at
+// most one partial sum per kScanGrid.
+static unsigned place_grid(int64_t n) {
+    const int64_t g = (n + 4 * kPB - 1) / (4 * kPB);
+    return (unsigned)(g < 1 ? 1 : (g < dev::kScanGrid ? g : dev::kScanGrid));
+}
+
 hipError_t launch_views_plan(const pm4g_prepared* p, const pm4g_view* views, int32_t V, ViewWs w,
                              BatchedOutDev out, hipStream_t s) {
     ProfScope ps(P_VIEW_PLAN, s);
     const int32_t A = p->n_activities;
     k_view_init<<<1024, 256, 0, s>>>(w, V, A, p->status, out);
-    k_view_span<<<1024, 256, 0, s>>>(p->case_off, p->ts_s, p->n_cases, w);
-    if (V > 0) k_view_slice<<<(unsigned)((V + 255) / 256), 256, 0, s>>>(views, V, p->case_off, p->case_code,
-                                                                          p->n_cases, w);
+    k_view_slice<<<1024, 256, 0, s>>>(views, V, p->case_off, p->ts_s, p->case_code, p->n_cases, w);
     k_view_tile_scan<<<1, 1024, 0, s>>>(w);
     if (V > 0) k_view_fill<<<(unsigned)((V + 3) / 4), 256, 0, s>>>(V, w);
     return hipGetLastError();
@@ -1511,11 +1547,9 @@ hipError_t launch_views_reduce(const pm4g_prepared* p, const pm4g_view* views, c
     const int32_t A = p->n_activities;
     {
         ProfScope ps(P_VIEW_PLACE, s);
-        k_view_vb_flags<<<1024, 256, 0, s>>>(w, V);
-        dev::excl_scan<int64_t>(w.vb_cnt, &w.scal[11], w.vb_base, w.part64, &w.scal[9], s);
-        dev::excl_scan<uint32_t>(w.vb_flag, &w.scal[11], w.vb_seg, w.part32, (uint32_t*)&w.scal[8], s);
-        k_view_gate<<<1, 64, 0, s>>>(w);
-        k_view_segs<<<1024, 256, 0, s>>>(w);
+        const unsigned g = place_grid(w.n_vb);
+        k_view_place_sum<<<g, kPB, 0, s>>>(w);
+        k_view_place<<<g, kPB, 0, s>>>(w);
     }
     {
         const hipError_t e = launch_views_write(p, views, masks, w, emit_grid, s);
@@ -1527,10 +1561,10 @@ hipError_t launch_views_reduce(const pm4g_prepared* p, const pm4g_view* views, c
     }
     {
         ProfScope ps(P_VIEW_OUT, s);
-        dev::excl_scan<int64_t>(w.seg_cells, &w.scal[2], w.seg_out, w.part64, &w.scal[4], s);
-        dev::excl_scan<int64_t>(w.view_cells, &w.scal[6], out.edge_off, w.part64, (int64_t*)nullptr, s);
+        const unsigned g = place_grid(w.n_vb);   // segments: at most the (view, bucket) pairs
+        k_view_out_sum<<<g, kPB, 0, s>>>(V, w);
+        k_view_out_place<<<g, kPB, 0, s>>>(V, w, out);
         k_view_out<<<(unsigned)(kOutCopyBlocks + 2048), 256, 0, s>>>(V, A, w, out);
-        k_view_finish<<<1, 1, 0, s>>>(V, w, out);
     }
     return hipGetLastError();
 }

@@ -52,3 +52,23 @@ def test_split_segments(n, A, mean, span, launch):
     note(f"split segments: N={n} A={A} launch={launch}")
     res = check_views(log, views, tuning=pm4g.BatchedTuning(launch=launch))
     assert res[0]["n_events"] == n
+
+
+@pytest.mark.parametrize("launch", [0, 1])
+@pytest.mark.parametrize("n,A,V,tile,widest", [
+    (30_000, 90, 1501, 4096, 900),       # the segments' counters over several blocks, a last one cut short
+    (2_300_000, 20, 5, 2048, 200_000),   # more tiles than the tile scan has threads
+])
+def test_places_over_blocks(n, A, V, tile, widest, launch):
+    log = log_of(n, A, 12, n + V)
+    C = int(log.case.max()) + 1
+    rng = np.random.default_rng(8)
+    lo = rng.integers(0, C, V).astype(np.int32)
+    hi = (lo + rng.integers(0, widest, V)).astype(np.int32)
+    tl = rng.integers(-(1 << 40), 1 << 39, V)
+    th = tl + rng.integers(1, 1 << 41, V)
+    masks = rng.integers(0, 1 << 63, (V, (A + 63) // 64)).astype(np.uint64)
+    views = synth.Views(case_lo=lo, case_hi=hi, t_lo=tl, t_hi=th, masks=masks)
+    note(f"view places: N={n} A={A} V={V} launch={launch}")
+    sample = sorted({0, V - 1, *rng.integers(0, V, 40).tolist()})
+    check_views(log, views, tuning=pm4g.BatchedTuning(launch=launch, tile_events=tile), sample=sample)
