@@ -17,7 +17,7 @@
 //   k_view_tile_scan per-tile counts of overlapping views, offsets
 //   k_view_fill      per-tile lists of overlapping views
 //   k_view_count /   tile-major: a block stages one tile of the log in LDS;
-//   k_view_write     each wave takes one overlapping view and walks the tile:
+//   k_view_write     its waves walk the overlapping views' parts of the tile:
 //                    the view's predicate lists the kept positions (ballots),
 //                    and the kept events, 64 at a time, find the previous kept
 //                    event in the neighbouring lane, carried across groups and
@@ -51,10 +51,8 @@ namespace pm4g {
 
 namespace {
 
-constexpr int kVB = 512;                  // threads per emit block (8 waves)
-constexpr int kVW = kVB / kWave;
+constexpr int kWalkFew = 16, kWalkMany = 8;   // waves per walk block (by activities: what LDS holds)
 constexpr int kMaxBuckets = 264;          // >= ceil(1024 * 1025 / 4096) = 257
-constexpr int kMaskWords = PM4G_BATCHED_MAX_ACTIVITIES / 64;
 constexpr int kAB2 = 1024;                // threads per aggregation block
 constexpr int kFT = 1024;                 // threads per block of the persistent launch
 constexpr uint64_t kRecGapLimit = 1ull << 52;   // gaps below it share a u64 with the cell
@@ -67,15 +65,6 @@ struct Grid {
 };
 __device__ __forceinline__ Grid hw_grid() { return Grid{(int64_t)blockIdx.x, (int64_t)gridDim.x}; }
 
-
-// Value of lane l (l the same in every lane: read into a scalar register, no
-// LDS round trip as a shuffle would take).
-__device__ __forceinline__ int32_t lane_i32(int32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ __forceinline__ int64_t lane_i64(int64_t v, int l) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 }  // namespace
 
@@ -279,38 +268,35 @@ __device__ __forceinline__ void ph_fill(Grid gd, int32_t V, ViewWs w) {
 
 __global__ void k_view_fill(int32_t V, ViewWs w) { ph_fill(hw_grid(), V, w); }
 
-__device__ __forceinline__ bool kept(int32_t a, int64_t t, int64_t tlo, int64_t thi, const uint64_t* mask) {
-    return t >= tlo && t <= thi && ((mask[a >> 6] >> (a & 63)) & 1ull);
+__device__ __forceinline__ bool kept(int32_t a, int64_t t, int64_t tlo, int64_t thi, const uint8_t* mask) {
+    return t >= tlo && t <= thi && mask[a] != 0;
 }
 
 struct WalkState {
-    bool have_cur;   // the position before the window is in the slice
-    int32_t cur;     // ... and its case
-    bool cr_valid;   // a kept event of case `cur` precedes the window
+    bool cr_valid;   // a kept event before the window belongs to the case at its first event
     int32_t cr_a;
     int64_t cr_t;
 };
 
-// Initial state for a walk that starts at e0 inside slice [p0, p1): the case at
-// e0 - 1 and, if it continues at e0, its last kept event before e0.
+// Initial state for a walk that starts at e0 inside slice [p0, p1): if the case
+// at e0 - 1 continues at e0, its last kept event before e0.
 __device__ WalkState walk_init(const int32_t* case_s, const int32_t* act_s, const int64_t* ts_s,
-                               int64_t e0, int64_t p0, int64_t tlo, int64_t thi, const uint64_t* mask) {
-    WalkState st{false, 0, false, 0, 0};
+                               int64_t e0, int64_t p0, int64_t tlo, int64_t thi, int32_t A, const uint8_t* mask) {
+    WalkState st{false, 0, 0};
     if (e0 <= p0) return st;   // slices start at a case start
-    st.have_cur = true;
-    st.cur = case_s[e0 - 1];
-    if (case_s[e0] != st.cur) return st;
+    const int32_t cur = case_s[e0 - 1];
+    if (case_s[e0] != cur) return st;
     for (int64_t hi = e0; hi > p0; hi -= kWave) {
         const int64_t i = hi - 1 - lane();
         bool same = false, k = false;
         int32_t a = 0;
         int64_t t = 0;
         if (i >= p0) {
-            same = case_s[i] == st.cur;
+            same = case_s[i] == cur;
             if (same) {
                 a = act_s[i];
                 t = ts_s[i];
-                k = kept(a, t, tlo, thi, mask);
+                k = (uint32_t)a < (uint32_t)A && kept(a, t, tlo, thi, mask);
             }
         }
         const uint64_t kb = __ballot(k);
@@ -328,121 +314,181 @@ __device__ WalkState walk_init(const int32_t* case_s, const int32_t* act_s, cons
     return st;
 }
 
-// One walk over [e0, e1) of the staged tile (T0 = first position of the tile),
-// in rounds of kSub events.  Pass 1 tests the view's predicate on the round's
-// events and appends the kept positions to the wave's list; pass 2 takes the
-// listed kept events 64 at a time (a partial group waits for the next round,
-// except in the last one): lane l's previous kept event of the slice is lane
-// l - 1's (a DPP shift; lane 0 takes the carry, the last kept event before
-// the group), and the event starts its case's kept events iff that previous
-// one lies in another case or does not exist (cases are contiguous).  Every
-// kept event yields one record: WRITE=false counts per bucket in cursor[],
-// WRITE=true takes record places from cursor[] (each bucket's cursor starts
-// at its run) and writes the records.
+// LDS of a walk block: NW waves over a TILE-event tile, for logs of up to ACTS
+// activities.
+//
+// A block with many views on its tile counts a view per wave, the views taken
+// in turn.  Otherwise, and always when records are written, waves share views:
+// each wave sets one up (its slot: the activities as bytes, the window, the
+// cursors), then teams of TILE / SLICE waves walk the slots, each wave its own
+// slice of the tile, taking record places from the view's shared cursors.  So
+// a view's runs grow by a team of waves at once and the lines that a CU has
+// open in its L2 are those of a few views, where a view per wave kept more of
+// them open than the L2s hold and half-filled lines went to memory; and a tile
+// that few views overlap still occupies all waves.
+// The walks are otherwise bound by LDS and vector instructions, so a staged
+// event is one word, its case's ordinal in the tile over its activity (one
+// gather, one DPP move, one comparison of high halves), a view's activity is a
+// byte, where a bit took a shift, an address and a field extract, and 16 waves
+// of 64 registers let two blocks fill a CU.
+// 4096 views of a 99M-event log, 8.2G events tested, 2.2G kept: count walk 7.5
+// to 5.8 ms, write walk 12.9 to 9.4 ms (18 GB of records: 4 ms at copy rate);
+// 200 views of 2M events, 30 activities: 56 to 21 and 59 to 39 us.
+constexpr int kFewActs = 512;
 constexpr int kSub = 512;             // events per round (8 windows of 64)
 constexpr int kList = kSub + kWave;   // a round's kept positions plus the previous round's rest
-constexpr int kListAlloc = kList + kWave;   // and a slot per lane for the events not kept
+constexpr int kSlice = 1024;          // events of a wave's slice when writing (512: 9.75 ms, 1024: 9.45, 2048: 11.4)
+struct PairSlot {
+    int64_t tlo, thi, cr_t;   // window; the carry's timestamp
+    int32_t e0, e1;           // the view's events in the tile
+    uint32_t cr_ca;           // the carry: activity (of the tile's first case), or kNoCase
+    uint32_t pad;
+};
+constexpr uint32_t kNoCase = 0xFFFF0000u;   // an ordinal that no staged event has
+template <int TILE, int NW, int ACTS>
+struct WalkSmem {
+    static constexpr int kBuckets = (ACTS * (ACTS + 1) + kCellsPerTable - 1) / kCellsPerTable;
+    static constexpr int kMaskBytes = ACTS + 4;   // a view's activities, and one never kept
+    uint32_t s_ca[TILE];   // case ordinal in the tile << 16 | activity
+    int64_t s_ts[TILE];
+    PairSlot s_pair[NW];
+    uint32_t s_cur[NW][kBuckets];
+    uint32_t s_bnd[TILE / kWave];   // case boundaries of each 64 events
+    uint32_t s_next;
+    uint16_t s_list[NW][kList];
+    uint8_t s_mask[NW][kMaskBytes];
+};
 
-// Pass 1 over [r0, r1) (FULL: r1 = r0 + kSub): all loads issued before any
-// use; returns the list length.  mask32: the view's activity mask as 32-bit
-// words (bit a of the mask is bit a & 31 of word a >> 5).
-template <bool FULL>
-__device__ __forceinline__ int list_kept(const int16_t* __restrict__ s_act, const int64_t* __restrict__ s_ts,
+// Appends the kept positions of [r0, r1) (FULL: r1 = r0 + kSub) to the wave's
+// list (LIST; else they are only counted): all loads issued before any use;
+// returns the list length.
+template <bool FULL, bool LIST>
+__device__ __forceinline__ int list_kept(const uint32_t* __restrict__ s_ca, const int64_t* __restrict__ s_ts,
                                          int r0, int r1, int64_t tlo, int64_t thi,
-                                         const uint32_t* __restrict__ mask32, uint16_t* __restrict__ list, int n) {
+                                         const uint8_t* __restrict__ mask, uint16_t* __restrict__ list, int n) {
     constexpr int kU = kSub / kWave;
-    int32_t av[kU];
+    const int i0 = r0 + lane();
+    uint32_t av[kU];
     int64_t tv[kU];
     uint32_t mv[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-        const int i = r0 + u * kWave + lane();
-        const int ii = FULL ? i : (i < r1 ? i : r1 - 1);   // past the round: its last event, not kept
-        av[u] = s_act[ii];
+        const int i = i0 + u * kWave;
+        const int ii = FULL ? i : (i < r1 ? i : r1 - 1);   // past the end: the last event, not kept
+        av[u] = s_ca[ii] & 0xFFFFu;
         tv[u] = s_ts[ii];
     }
 #pragma unroll
-    for (int u = 0; u < kU; ++u) mv[u] = mask32[av[u] >> 5];
+    for (int u = 0; u < kU; ++u) mv[u] = mask[av[u]];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-        // one ballot per comparison (each folds to the comparison's lane
-        // mask); every lane stores, the kept ones at their list place, the
-        // others at their own slot past the list (no branch)
-        const int i = r0 + u * kWave + lane();
-        const bool ki = FULL || i < r1;
-        const bool ka = __builtin_amdgcn_ubfe(mv[u], (uint32_t)av[u], 1u) != 0;   // bit a & 31
-        const bool k1 = tv[u] >= tlo;
-        const bool k2 = tv[u] <= thi;
-        uint64_t K = __builtin_amdgcn_ballot_w64(ka) & __builtin_amdgcn_ballot_w64(k1) &
-                     __builtin_amdgcn_ballot_w64(k2);
-        if (!FULL) K &= __builtin_amdgcn_ballot_w64(ki);
-        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(K >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)K, 0u));
-        list[(ki & ka & k1 & k2) ? (uint32_t)n + at : (uint32_t)(kList + lane())] = (uint16_t)i;
+        // one ballot per comparison (each folds to the comparison's lane mask)
+        uint64_t K = __builtin_amdgcn_ballot_w64(mv[u] != 0) & __builtin_amdgcn_ballot_w64(tv[u] >= tlo) &
+                     __builtin_amdgcn_ballot_w64(tv[u] <= thi);
+        if (!FULL) K &= __builtin_amdgcn_ballot_w64(i0 + u * kWave < r1);
+        const uint32_t at =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(K >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)K, (uint32_t)n));
+        if (LIST && __builtin_amdgcn_inverse_ballot_w64(K)) list[at] = (uint16_t)(i0 + u * kWave);
         n += __popcll(K);
     }
     return n;
 }
 
-struct KeptEv {
-    int32_t c, a;
-    int64_t t;
-};
-
-__device__ __forceinline__ KeptEv kept_event(const int32_t* __restrict__ s_case, const int16_t* __restrict__ s_act,
-                                             const int64_t* __restrict__ s_ts, const uint16_t* __restrict__ list,
-                                             int j, int n) {
-    KeptEv e{0, 0, 0};
-    if (j < n) {
-        const int q = list[j];
-        e.c = s_case[q];
-        e.a = s_act[q];
-        e.t = s_ts[q];
+// The carry of a walk that starts at r0 > e0 inside a view's events [e0, ..) of
+// the staged tile: the last kept event before r0 of the case at r0; the view's
+// own carry (pca, pt as passed) if that case reaches back to e0.
+__device__ __forceinline__ void slice_carry(const uint32_t* __restrict__ s_ca, const int64_t* __restrict__ s_ts, int r0,
+                                            int e0, int64_t tlo, int64_t thi, const uint8_t* __restrict__ mask,
+                                            uint32_t& pca, int64_t& pt) {
+    const uint32_t ord = wave_lane(s_ca[r0], 0) >> 16;
+    for (int hi = r0; hi > e0; hi -= kWave) {   // wave-uniform
+        const int i = hi - 1 - lane();
+        uint32_t ca = kNoCase;
+        int64_t t = 0;
+        if (i >= e0) {
+            ca = s_ca[i];
+            t = s_ts[i];
+        }
+        const bool same = (ca >> 16) == ord;
+        const uint64_t K = __ballot(same && t >= tlo && t <= thi && mask[ca & 0xFFFFu] != 0);
+        if (K != 0) {
+            const int l = __ffsll((long long)K) - 1;   // lowest lane = latest position
+            pca = wave_lane(ca, l);
+            pt = wave_lane(t, l);
+            return;
+        }
+        if (__ballot(i >= e0 && !same) != 0) {   // the case's start
+            pca = kNoCase;
+            return;
+        }
     }
-    return e;
 }
 
-template <bool WRITE>
-__device__ __forceinline__ void walk(const int32_t* __restrict__ s_case, const int16_t* __restrict__ s_act,
-                                     const int64_t* __restrict__ s_ts, int64_t T0, int64_t e0, int64_t e1,
-                                     WalkState st, int32_t A, int64_t tlo, int64_t thi,
-                                     const uint64_t* __restrict__ mask, uint16_t* __restrict__ list,
+// A wave's walk over [r0, r1) of the staged tile (positions in it, the same in
+// every lane, as all of the walk's bounds are: they live in scalar registers),
+// in rounds of kSub events; pca, pt: the last kept event before r0 in the case
+// at r0.  Pass 1 tests the view's predicate on the round's events and appends
+// the kept positions to the wave's list; pass 2 takes the listed kept events
+// 64 at a time (a partial group waits for the next round, except in the last
+// one): lane l's previous kept event of the slice is lane l - 1's (a DPP
+// shift; lane 0 takes the carry, the last kept event before the group), and
+// the event starts its case's kept events iff that previous one lies in
+// another case or does not exist (cases are contiguous).  Every kept event
+// yields one record: WRITE=false counts per bucket in cursor[], WRITE=true
+// takes record places from cursor[] (each bucket's cursor starts at its run)
+// and writes the records.  With one bucket (ONE: logs of up to 63 activities)
+// a group's records take consecutive places and nothing but the kept events'
+// number is counted: every lane's atomic would meet in one word.
+template <bool WRITE, bool ONE>
+__device__ __forceinline__ void walk(const uint32_t* __restrict__ s_ca, const int64_t* __restrict__ s_ts, int r0,
+                                     int r1, uint32_t pca, int64_t pt, uint32_t A, int64_t tlo, int64_t thi,
+                                     const uint8_t* __restrict__ mask, uint16_t* __restrict__ list,
                                      uint32_t* __restrict__ cursor, uint16_t* __restrict__ rec_cell,
                                      uint64_t* __restrict__ rec_gap, bool wide) {
-    const int32_t AA = A * A;
-    const uint32_t* mask32 = reinterpret_cast<const uint32_t*>(mask);
-    // carry: the last kept event of the slice before the current group
-    bool pv = st.cr_valid;
-    int32_t pc = st.cur, pa = st.cr_a;
-    int64_t pt = st.cr_t;
-    int n = 0;   // listed kept positions (wave-uniform)
-    const int b1 = (int)(e1 - T0);
-    for (int r0 = (int)(e0 - T0); r0 < b1; r0 += kSub) {
-        const int r1 = r0 + kSub < b1 ? r0 + kSub : b1;
-        if (r1 - r0 == kSub) n = list_kept<true>(s_act, s_ts, r0, r1, tlo, thi, mask32, list, n);
-        else n = list_kept<false>(s_act, s_ts, r0, r1, tlo, thi, mask32, list, n);
+    const uint32_t AA = A * A;
+    int n = 0;   // listed kept positions
+    for (int q0 = r0; q0 < r1; q0 += kSub) {
+        const int q1 = q0 + kSub < r1 ? q0 + kSub : r1;
+        constexpr bool kListed = WRITE || !ONE;
+        if (q1 - q0 == kSub) n = list_kept<true, kListed>(s_ca, s_ts, q0, q1, tlo, thi, mask, list, n);
+        else n = list_kept<false, kListed>(s_ca, s_ts, q0, q1, tlo, thi, mask, list, n);
+        if (!kListed) continue;
         __builtin_amdgcn_wave_barrier();
-        const bool last = r1 >= b1;
+        const bool last = q1 >= r1;
         int c0 = 0;
         for (; c0 + kWave <= n || (last && c0 < n); c0 += kWave) {
             const bool in = c0 + lane() < n;
-            const KeptEv e = kept_event(s_case, s_act, s_ts, list, c0 + lane(), n);
+            uint32_t ca = 0;
+            int64_t t = 0;
+            if (in) {
+                const int q = list[c0 + lane()];
+                ca = s_ca[q];
+                if (WRITE) t = s_ts[q];
+            }
             // lane l - 1's event: a DPP wave shift right by one, whose lane 0
             // (no source lane) keeps the first operand, the carry
-            const int32_t cq = __builtin_amdgcn_update_dpp(pc, e.c, 0x138, 0xF, 0xF, false);
-            const int32_t aq = __builtin_amdgcn_update_dpp(pa, e.a, 0x138, 0xF, 0xF, false);
-            const uint32_t tql = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)pt, (int)(uint32_t)e.t,
-                                                                       0x138, 0xF, 0xF, false);
-            const uint32_t tqh = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)((uint64_t)pt >> 32),
-                                                                       (int)(uint32_t)((uint64_t)e.t >> 32),
-                                                                       0x138, 0xF, 0xF, false);
-            const uint64_t tq = ((uint64_t)tqh << 32) | tql;
-            const bool starts = (lane() == 0 && !pv) || e.c != cq;
+            const uint32_t cq = (uint32_t)__builtin_amdgcn_update_dpp((int)pca, (int)ca, 0x138, 0xF, 0xF, false);
+            uint64_t tq = 0;
+            if (WRITE) {
+                const uint32_t tql = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)pt, (int)(uint32_t)t,
+                                                                           0x138, 0xF, 0xF, false);
+                const uint32_t tqh = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)((uint64_t)pt >> 32),
+                                                                           (int)(uint32_t)((uint64_t)t >> 32),
+                                                                           0x138, 0xF, 0xF, false);
+                tq = ((uint64_t)tqh << 32) | tql;
+            }
+            const bool starts = ((ca ^ cq) >> 16) != 0;
+            const int m = n - c0 < kWave ? n - c0 : kWave;
+            uint32_t first = 0;
+            if (ONE && lane() == 0) first = atomicAdd(&cursor[0], (uint32_t)m);
+            if (ONE) first = wave_lane(first, 0) + lane();
             if (in) {
-                const int32_t cell = starts ? AA + e.a : aq * A + e.a;
-                const uint64_t gap = starts ? 0ull : (uint64_t)e.t - tq;
-                const uint32_t slot = atomicAdd(&cursor[(uint32_t)cell >> 12], 1u);
+                const uint32_t a = ca & 0xFFFFu;
+                const uint32_t cell = (starts ? AA : (cq & 0xFFFFu) * A) + a;
+                const uint32_t slot = ONE ? first : atomicAdd(&cursor[cell >> 12], 1u);
                 if (WRITE) {   // slot: the record's place (the cursor starts at its run)
-                    const uint64_t qc = (uint64_t)(cell & (kCellsPerTable - 1));
+                    const uint64_t gap = starts ? 0ull : (uint64_t)t - tq;
+                    const uint64_t qc = (uint64_t)(cell & (uint32_t)(kCellsPerTable - 1));
                     if (wide) {
                         rec_cell[slot] = (uint16_t)qc;
                         rec_gap[slot] = gap;
@@ -451,11 +497,8 @@ __device__ __forceinline__ void walk(const int32_t* __restrict__ s_case, const i
                     }
                 }
             }
-            const int ll = (n - c0 < kWave ? n - c0 : kWave) - 1;
-            pv = true;
-            pc = lane_i32(e.c, ll);
-            pa = lane_i32(e.a, ll);
-            pt = lane_i64(e.t, ll);
+            pca = wave_lane(ca, m - 1);
+            if (WRITE) pt = wave_lane(t, m - 1);
         }
         // the rest (fewer than 64) moves to the front of the list
         if (c0 > 0 && c0 < n) {
@@ -468,19 +511,83 @@ __device__ __forceinline__ void walk(const int32_t* __restrict__ s_case, const i
         n = c0 < n ? n - c0 : 0;
         __builtin_amdgcn_wave_barrier();
     }
+    if (!WRITE && ONE && lane() == 0) atomicAdd(&cursor[0], (uint32_t)n);
 }
 
-// LDS of a walk block (NW waves over a TILE-event tile).
-template <int TILE, int NW>
-struct WalkSmem {
-    int32_t s_case[TILE];
-    int16_t s_act[TILE];
-    int64_t s_ts[TILE];
-    uint64_t s_mask[NW][kMaskWords];
-    uint32_t s_cur[NW][kMaxBuckets];
-    uint16_t s_list[NW][kListAlloc];
-    uint32_t s_next;
-};
+// Stages tile [T0, T1): the case ordinals count the boundaries from the tile's
+// start (ballots, and one scan of the counts of each 64 events).  An activity
+// outside the log's range takes the mask's last byte, which no view keeps.
+template <int TILE, int NW, int ACTS>
+__device__ __forceinline__ void stage_tile(const int32_t* __restrict__ case_s, const int32_t* __restrict__ act_s,
+                                           const int64_t* __restrict__ ts_s, int64_t T0, int64_t T1, int32_t A,
+                                           WalkSmem<TILE, NW, ACTS>& S) {
+    constexpr int kPer = TILE / (NW * kWave);
+    static_assert(TILE / kWave <= kWave && kPer * NW * kWave == TILE, "one wave scans the counts");
+    const int n = (int)(T1 - T0);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    if (threadIdx.x == 0) S.s_next = NW;
+    uint32_t ca[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = u * NW * kWave + (int)threadIdx.x;
+        bool bnd = false;
+        uint32_t a = 0;
+        if (i < n) {
+            const int32_t c = case_s[T0 + i];
+            bnd = i > 0 && case_s[T0 + i - 1] != c;
+            a = (uint32_t)act_s[T0 + i];
+            if (a >= (uint32_t)A) a = S.kMaskBytes - 1;
+            S.s_ts[i] = ts_s[T0 + i];
+        }
+        const uint64_t B = __ballot(bnd);
+        if (lane() == 0) S.s_bnd[u * NW + wv] = (uint32_t)__popcll(B);
+        ca[u] = ((uint32_t)(__popcll(B & lanes_below()) + bnd) << 16) | a;
+    }
+    __syncthreads();
+    const uint32_t b = lane() < TILE / kWave ? S.s_bnd[lane()] : 0u;
+    const uint32_t before = wave_incl_sum(b) - b;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = u * NW * kWave + (int)threadIdx.x;
+        const uint32_t ord = wave_lane(before, u * NW + wv);
+        if (i < n) S.s_ca[i] = ca[u] + (ord << 16);
+    }
+}
+
+// The view's activities as bytes (byte a: kept), by a wave.
+template <int BYTES>
+__device__ __forceinline__ void stage_mask(const uint64_t* __restrict__ words, int MW, uint8_t (&mask)[BYTES]) {
+    for (int q = 0; q < MW; ++q) mask[q * kWave + lane()] = (uint8_t)((words[q] >> lane()) & 1ull);
+    if (lane() == 0) mask[BYTES - 1] = 0;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The first `pairs` slots, walked by teams of waves.
+template <bool WRITE, int SLICE, int TILE, int NW, int ACTS>
+__device__ __forceinline__ void walk_slots(uint32_t A, const ViewWs& w, int pairs, bool wide,
+                                           WalkSmem<TILE, NW, ACTS>& S) {
+    constexpr int kTeam = TILE / SLICE;
+    static_assert(NW % kTeam == 0, "whole teams");
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int s0 = (wv % kTeam) * SLICE, s1 = s0 + SLICE;
+    for (int k = wv / kTeam; k < pairs; k += NW / kTeam) {
+        const PairSlot& P = S.s_pair[k];
+        const int e0 = wave_lane(P.e0, 0), e1 = wave_lane(P.e1, 0);
+        const int r0 = s0 > e0 ? s0 : e0, r1 = s1 < e1 ? s1 : e1;
+        if (r0 >= r1) continue;
+        const int64_t tlo = wave_lane(P.tlo, 0), thi = wave_lane(P.thi, 0);
+        uint32_t pca = wave_lane(P.cr_ca, 0);
+        int64_t pt = wave_lane(P.cr_t, 0);
+        if (r0 > e0 && (WRITE || w.n_buckets > 1))
+            slice_carry(S.s_ca, S.s_ts, r0, e0, tlo, thi, S.s_mask[k], pca, pt);
+        if (w.n_buckets == 1)
+            walk<WRITE, true>(S.s_ca, S.s_ts, r0, r1, pca, pt, A, tlo, thi, S.s_mask[k], S.s_list[wv], S.s_cur[k],
+                              w.rec_cell, w.rec_gap, wide);
+        else
+            walk<WRITE, false>(S.s_ca, S.s_ts, r0, r1, pca, pt, A, tlo, thi, S.s_mask[k], S.s_list[wv], S.s_cur[k],
+                               w.rec_cell, w.rec_gap, wide);
+    }
+}
 
 // Tile order of the walks: chunks of kXcdChunk consecutive tiles are dealt
 // round-robin to the 8 XCDs (block b runs on XCD b % 8) and an XCD's blocks
@@ -501,61 +608,88 @@ __device__ __forceinline__ int64_t walk_tile(Grid gd, int64_t i, int64_t n_tiles
     return t < n_tiles ? t : -1;
 }
 
-// The tile's (view) pairs are taken in turn by the block's waves: the first
-// kVW by wave index, the others from an LDS counter as waves finish theirs.
+// The tile's views beyond the first NW, taken in turn by the block's waves.
 __device__ __forceinline__ uint32_t next_pair(uint32_t* s_next) {
     uint32_t j = 0;
     if (lane() == 0) j = atomicAdd(s_next, 1u);
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)j);
 }
 
+// Views per wave from which a block counts one view per wave (below it, waves
+// left without a view cost more than the shared walk's barriers: 48 views of a
+// 3M-event log, 6 views a tile, 52 us by views and 36 us shared; with 82 views a
+// tile 5.8 ms by views, 9.1 ms shared).
+constexpr uint32_t kManyViews = 2;
+
 // Count walk.  After a view's walk, each non-empty bucket's run takes its
 // place in the (view, bucket) segment with one atomic on the segment's
 // counter; the walk's initial carry and whether the pair keeps an event are
-// kept for the write walk (pair_carry: ts, case, act | valid << 30 | kept << 31).
-template <int TILE, int NW>
+// kept for the write walk (pair_carry: ts, 0, act | valid << 30 | kept << 31).
+template <int TILE, int NW, int ACTS>
 __device__ __forceinline__ void ph_count(Grid gd, const int32_t* __restrict__ case_s,
                                         const int32_t* __restrict__ act_s,
                                         const int64_t* __restrict__ ts_s, int64_t n, int32_t A,
                                         const pm4g_view* __restrict__ views,
                                         const uint64_t* __restrict__ masks, ViewWs w,
-                                        WalkSmem<TILE, NW>& S) {
-    int32_t* s_case = S.s_case;
-    int16_t* s_act = S.s_act;
-    int64_t* s_ts = S.s_ts;
-    constexpr int kVB = NW * kWave;
+                                        WalkSmem<TILE, NW, ACTS>& S) {
 
-    const int wv = threadIdx.x / kWave;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int NB = w.n_buckets;
     const int MW = (A + 63) / 64;
-    uint64_t* mask = S.s_mask[wv];
+    auto& mask = S.s_mask[wv];
     uint32_t* cur = S.s_cur[wv];
     if (w.scal[7] > w.pair_cap) return;   // the tile lists are incomplete: the gate stops the call
     for (int64_t it = 0, tile; (tile = walk_tile(gd, it, w.n_tiles)) >= 0; ++it) {
         if (w.tcount[tile] == 0) continue;   // no view overlaps the tile (block-uniform)
         const int64_t T0 = tile * TILE;
         const int64_t T1 = (T0 + TILE) < n ? (T0 + TILE) : n;
-        for (int64_t i = T0 + threadIdx.x; i < T1; i += kVB) {
-            s_case[i - T0] = case_s[i];
-            s_act[i - T0] = (int16_t)act_s[i];
-            s_ts[i - T0] = ts_s[i];
-        }
-        if (threadIdx.x == 0) S.s_next = NW;
+        stage_tile(case_s, act_s, ts_s, T0, T1, A, S);
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
+        const int64_t off = wave_lane((int64_t)w.toff[tile], 0);
         __syncthreads();
-        const uint32_t cnt = w.tcount[tile];
-        const int64_t off = w.toff[tile];
-        for (uint32_t j = wv; j < cnt; j = next_pair(&S.s_next)) {
-            const uint32_t v = w.list[off + j];
-            const pm4g_view vw = views[v];
-            const int64_t p0 = w.p0[v], p1 = w.p1[v];
-            for (int q = lane(); q < MW; q += kWave) mask[q] = masks[(size_t)v * MW + q];
-            const int64_t e0 = T0 > p0 ? T0 : p0;
-            const int64_t e1 = T1 < p1 ? T1 : p1;
-            const WalkState st = walk_init(case_s, act_s, ts_s, e0, p0, vw.t_lo, vw.t_hi, mask);
-            for (int q = lane(); q < NB; q += kWave) cur[q] = 0;
-            walk<false>(s_case, s_act, s_ts, T0, e0, e1, st, A, vw.t_lo, vw.t_hi, mask, S.s_list[wv], cur,
-                        w.rec_cell, w.rec_gap, false);
-            uint32_t* rel = w.pair_rel + (size_t)(off + j) * (size_t)NB;
+        // many views: one per wave, taken in turn (no barriers); few: shared,
+        // NW at a time (block-uniform)
+        const bool many = cnt >= kManyViews * NW;
+        for (uint32_t j = wv, j0 = 0; many ? j < cnt : j0 < cnt;) {
+            const int pairs = (int)(cnt - j0 < NW ? cnt - j0 : NW);
+            WalkState st{false, 0, 0};
+            uint32_t v = 0;
+            int64_t tlo = 0, thi = 0;
+            int r0 = 0, r1 = 0;
+            uint32_t cr_ca = kNoCase;
+            if (j < cnt) {
+                v = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.list[off + j]);
+                const pm4g_view vw = views[v];
+                tlo = wave_lane(vw.t_lo, 0);
+                thi = wave_lane(vw.t_hi, 0);
+                const int64_t p0 = wave_lane(w.p0[v], 0), p1 = wave_lane(w.p1[v], 0);
+                stage_mask(masks + (size_t)v * MW, MW, mask);
+                const int64_t e0 = T0 > p0 ? T0 : p0;
+                r0 = (int)(e0 - T0);
+                r1 = (int)((T1 < p1 ? T1 : p1) - T0);
+                st = walk_init(case_s, act_s, ts_s, e0, p0, tlo, thi, A, mask);
+                cr_ca = st.cr_valid ? (uint32_t)st.cr_a : kNoCase;
+                for (int q = lane(); q < NB; q += kWave) cur[q] = 0;
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (many) {
+                if (NB == 1)
+                    walk<false, true>(S.s_ca, S.s_ts, r0, r1, cr_ca, st.cr_t, (uint32_t)A, tlo, thi, mask, S.s_list[wv],
+                                      cur, w.rec_cell, w.rec_gap, false);
+                else
+                    walk<false, false>(S.s_ca, S.s_ts, r0, r1, cr_ca, st.cr_t, (uint32_t)A, tlo, thi, mask,
+                                       S.s_list[wv], cur, w.rec_cell, w.rec_gap, false);
+            } else {
+                if (j < cnt && lane() == 0) S.s_pair[wv] = PairSlot{tlo, thi, st.cr_t, r0, r1, cr_ca, 0};
+                __syncthreads();
+                walk_slots<false, kSub>((uint32_t)A, w, pairs, false, S);
+                __syncthreads();
+            }
+            const uint32_t jt = j;
+            j0 += NW;
+            j = many ? next_pair(&S.s_next) : j0 + wv;
+            if (jt >= cnt) continue;
+            uint32_t* rel = w.pair_rel + (size_t)(off + jt) * (size_t)NB;
             uint64_t any = 0;
             for (int q0 = 0; q0 < NB; q0 += kWave) {
                 const int q = q0 + lane();
@@ -566,105 +700,96 @@ __device__ __forceinline__ void ph_count(Grid gd, const int32_t* __restrict__ ca
             if (lane() == 0) {
                 const uint32_t aw = (uint32_t)(st.cr_valid ? st.cr_a : 0) | (st.cr_valid ? 1u << 30 : 0u) |
                                     (any != 0 ? 1u << 31 : 0u);
-                w.pair_carry[off + j] = make_uint4((uint32_t)(uint64_t)st.cr_t, (uint32_t)((uint64_t)st.cr_t >> 32),
-                                                   (uint32_t)st.cur, aw);
+                w.pair_carry[off + jt] = make_uint4((uint32_t)(uint64_t)st.cr_t, (uint32_t)((uint64_t)st.cr_t >> 32), 0u,
+                                                   aw);
             }
         }
         __syncthreads();
     }
 }
 
-template <int TILE>
-__global__ __launch_bounds__(kVB) void k_view_count(const int32_t* __restrict__ case_s,
+template <int TILE, int NW, int ACTS>
+__global__ __launch_bounds__(NW* kWave, NW == 16 ? 8 : 4) void k_view_count(const int32_t* __restrict__ case_s,
                                         const int32_t* __restrict__ act_s,
                                         const int64_t* __restrict__ ts_s, int64_t n, int32_t A,
                                         const pm4g_view* __restrict__ views,
                                         const uint64_t* __restrict__ masks, ViewWs w) {
-    __shared__ WalkSmem<TILE, kVW> S;
-    ph_count<TILE, kVW>(hw_grid(), case_s, act_s, ts_s, n, A, views, masks, w, S);
+    __shared__ WalkSmem<TILE, NW, ACTS> S;
+    ph_count<TILE, NW, ACTS>(hw_grid(), case_s, act_s, ts_s, n, A, views, masks, w, S);
 }
 
 // Write walk: each (tile, view) pair's buckets start at their runs' places in
 // the segment-contiguous record layout; the walk starts from the carry the
 // count walk found.
-template <int TILE, int NW>
+template <int TILE, int NW, int ACTS>
 __device__ __forceinline__ void ph_write(Grid gd, const int32_t* __restrict__ case_s,
                                         const int32_t* __restrict__ act_s,
                                         const int64_t* __restrict__ ts_s, int64_t n, int32_t A,
                                         const pm4g_view* __restrict__ views,
                                         const uint64_t* __restrict__ masks, ViewWs w,
-                                        WalkSmem<TILE, NW>& S) {
-    int32_t* s_case = S.s_case;
-    int16_t* s_act = S.s_act;
-    int64_t* s_ts = S.s_ts;
-    constexpr int kVB = NW * kWave;
-    constexpr int kQ = (kMaxBuckets + kWave - 1) / kWave;   // buckets per lane
+                                        WalkSmem<TILE, NW, ACTS>& S) {
+    constexpr int kQ = (WalkSmem<TILE, NW, ACTS>::kBuckets + kWave - 1) / kWave;   // buckets per lane
 
-    const int wv = threadIdx.x / kWave;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int NB = w.n_buckets;
     const int MW = (A + 63) / 64;
     const bool wide = w.scal[10] != 0;
-    uint64_t* mask = S.s_mask[wv];
+    auto& mask = S.s_mask[wv];
     uint32_t* cur = S.s_cur[wv];
     if (w.scal[12] != 0) return;   // a capacity is short: no record is written
     for (int64_t it = 0, tile; (tile = walk_tile(gd, it, w.n_tiles)) >= 0; ++it) {
         if (w.tcount[tile] == 0) continue;   // no view overlaps the tile (block-uniform)
         const int64_t T0 = tile * TILE;
         const int64_t T1 = (T0 + TILE) < n ? (T0 + TILE) : n;
-        for (int64_t i = T0 + threadIdx.x; i < T1; i += kVB) {
-            s_case[i - T0] = case_s[i];
-            s_act[i - T0] = (int16_t)act_s[i];
-            s_ts[i - T0] = ts_s[i];
-        }
-        if (threadIdx.x == 0) S.s_next = NW;
-        __syncthreads();
-        const uint32_t cnt = w.tcount[tile];
-        const int64_t off = w.toff[tile];
-        for (uint32_t j = wv; j < cnt; j = next_pair(&S.s_next)) {
-            const uint4 cy = w.pair_carry[off + j];
-            if (!(cy.w >> 31)) continue;   // no kept event
-            const uint32_t v = w.list[off + j];
-            // the runs' first records (buckets without a run get no record),
-            // loaded before anything waits
-            const uint32_t* rel = w.pair_rel + (size_t)(off + j) * (size_t)NB;
-            const int64_t* vbb = w.vb_base + (size_t)v * NB;
-            uint32_t qv[kQ];
+        stage_tile(case_s, act_s, ts_s, T0, T1, A, S);
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
+        const int64_t off = wave_lane((int64_t)w.toff[tile], 0);
+        for (uint32_t j0 = 0; j0 < cnt; j0 += NW) {   // block-uniform
+            const uint32_t j = j0 + wv;
+            const int pairs = (int)(cnt - j0 < NW ? cnt - j0 : NW);
+            if (j < cnt) {
+                const uint4 cy = w.pair_carry[off + j];
+                const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.list[off + j]);
+                // the runs' first records (buckets without a run get no record),
+                // loaded before anything waits
+                const uint32_t* rel = w.pair_rel + (size_t)(off + j) * (size_t)NB;
+                const int64_t* vbb = w.vb_base + (size_t)v * NB;
+                uint32_t qv[kQ];
 #pragma unroll
-            for (int u = 0; u < kQ; ++u) {
-                const int q = u * kWave + lane();
-                qv[u] = q < NB ? (uint32_t)vbb[q] + rel[q] : 0u;
-            }
-            const pm4g_view vw = views[v];
-            const int64_t p0 = w.p0[v], p1 = w.p1[v];
-            for (int q = lane(); q < MW; q += kWave) mask[q] = masks[(size_t)v * MW + q];
+                for (int u = 0; u < kQ; ++u) {
+                    const int q = u * kWave + lane();
+                    qv[u] = q < NB ? (uint32_t)vbb[q] + rel[q] : 0u;
+                }
+                const pm4g_view vw = views[v];
+                const int64_t p0 = wave_lane(w.p0[v], 0), p1 = wave_lane(w.p1[v], 0);
+                stage_mask(masks + (size_t)v * MW, MW, mask);
 #pragma unroll
-            for (int u = 0; u < kQ; ++u) {
-                const int q = u * kWave + lane();
-                if (q < NB) cur[q] = qv[u];
+                for (int u = 0; u < kQ; ++u) {
+                    const int q = u * kWave + lane();
+                    if (q < NB) cur[q] = qv[u];
+                }
+                const int64_t e0 = T0 > p0 ? T0 : p0;
+                const int64_t e1 = cy.w >> 31 ? (T1 < p1 ? T1 : p1) : e0;   // (no kept event: nothing to walk)
+                if (lane() == 0)
+                    S.s_pair[wv] = PairSlot{vw.t_lo, vw.t_hi, (int64_t)(((uint64_t)cy.y << 32) | cy.x), (int)(e0 - T0),
+                                            (int)(e1 - T0), (cy.w >> 30) & 1u ? cy.w & 0x3FFFFFFFu : kNoCase, 0};
             }
-            const int64_t e0 = T0 > p0 ? T0 : p0;
-            const int64_t e1 = T1 < p1 ? T1 : p1;
-            WalkState st;
-            st.have_cur = true;
-            st.cur = (int32_t)cy.z;
-            st.cr_valid = (cy.w >> 30) & 1u;
-            st.cr_a = (int32_t)(cy.w & 0x3FFFFFFFu);
-            st.cr_t = (int64_t)(((uint64_t)cy.y << 32) | cy.x);
-            walk<true>(s_case, s_act, s_ts, T0, e0, e1, st, A, vw.t_lo, vw.t_hi, mask, S.s_list[wv], cur,
-                       w.rec_cell, w.rec_gap, wide);
+            __syncthreads();
+            walk_slots<true, kSlice>((uint32_t)A, w, pairs, wide, S);
+            __syncthreads();
         }
         __syncthreads();
     }
 }
 
-template <int TILE>
-__global__ __launch_bounds__(kVB) void k_view_write(const int32_t* __restrict__ case_s,
+template <int TILE, int NW, int ACTS>
+__global__ __launch_bounds__(NW* kWave, NW == 16 ? 8 : 4) void k_view_write(const int32_t* __restrict__ case_s,
                                         const int32_t* __restrict__ act_s,
                                         const int64_t* __restrict__ ts_s, int64_t n, int32_t A,
                                         const pm4g_view* __restrict__ views,
                                         const uint64_t* __restrict__ masks, ViewWs w) {
-    __shared__ WalkSmem<TILE, kVW> S;
-    ph_write<TILE, kVW>(hw_grid(), case_s, act_s, ts_s, n, A, views, masks, w, S);
+    __shared__ WalkSmem<TILE, NW, ACTS> S;
+    ph_write<TILE, NW, ACTS>(hw_grid(), case_s, act_s, ts_s, n, A, views, masks, w, S);
 }
 
 // Blocks that share a segment's records.  One block takes a segment unless
@@ -1388,7 +1513,7 @@ struct FusedArgs {
 
 template <int TILE>
 union FusedSmem {
-    WalkSmem<TILE, kFT / kWave> walk;
+    WalkSmem<TILE, kFT / kWave, PM4G_BATCHED_MAX_ACTIVITIES> walk;
     AggSmem agg;
     ActsSmem<kFT> acts;
     PlaceSmem<kFT> place;
@@ -1431,7 +1556,7 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
     grid_barrier(gd, bar, ++k, st);
     {
         const FusedArgs a = PA;
-        ph_count<TILE, kFT / kWave>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
+        ph_count<TILE, kFT / kWave, PM4G_BATCHED_MAX_ACTIVITIES>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
     }
     grid_barrier(gd, bar, ++k, st);
     ph_place_sum<kFT>(gd, PA.w, sm.place);
@@ -1440,7 +1565,7 @@ __global__ __launch_bounds__(kFT) void k_view_fused(FusedArgs args) {
     grid_barrier(gd, bar, ++k, st);
     {
         const FusedArgs a = PA;
-        ph_write<TILE, kFT / kWave>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
+        ph_write<TILE, kFT / kWave, PM4G_BATCHED_MAX_ACTIVITIES>(gd, a.case_s, a.act_s, a.ts_s, a.n, a.A, a.views, a.masks, a.w, sm.walk);
     }
     grid_barrier(gd, bar, ++k, st);
     ph_agg(PA.A, PA.w, PA.out, sm.agg);
@@ -1518,10 +1643,16 @@ hipError_t launch_views_count(const pm4g_prepared* p, const pm4g_view* views, co
     const int64_t n = p->n_events;
     if (w.n_tiles > 0) {
         const unsigned g = (unsigned)(w.n_tiles < grid ? w.n_tiles : grid);
-        if (w.tile == 2048)
-            k_view_count<2048><<<g, kVB, 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views, masks, w);
-        else
-            k_view_count<4096><<<g, kVB, 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views, masks, w);
+        auto go = [&](auto kernel, int waves) {
+            kernel<<<g, (unsigned)(waves * kWave), 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views,
+                                                           masks, w);
+        };
+        constexpr int kMost = PM4G_BATCHED_MAX_ACTIVITIES;
+        const bool few = p->n_activities <= kFewActs;
+        if (w.tile == 2048 && few) go(k_view_count<2048, kWalkFew, kFewActs>, kWalkFew);
+        else if (w.tile == 2048) go(k_view_count<2048, kWalkMany, kMost>, kWalkMany);
+        else if (few) go(k_view_count<4096, kWalkFew, kFewActs>, kWalkFew);
+        else go(k_view_count<4096, kWalkMany, kMost>, kWalkMany);
     }
     return hipGetLastError();
 }
@@ -1532,10 +1663,16 @@ hipError_t launch_views_write(const pm4g_prepared* p, const pm4g_view* views, co
     const int64_t n = p->n_events;
     if (w.n_tiles > 0) {
         const unsigned g = (unsigned)(w.n_tiles < grid ? w.n_tiles : grid);
-        if (w.tile == 2048)
-            k_view_write<2048><<<g, kVB, 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views, masks, w);
-        else
-            k_view_write<4096><<<g, kVB, 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views, masks, w);
+        auto go = [&](auto kernel, int waves) {
+            kernel<<<g, (unsigned)(waves * kWave), 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views,
+                                                           masks, w);
+        };
+        constexpr int kMost = PM4G_BATCHED_MAX_ACTIVITIES;
+        const bool few = p->n_activities <= kFewActs;
+        if (w.tile == 2048 && few) go(k_view_write<2048, kWalkFew, kFewActs>, kWalkFew);
+        else if (w.tile == 2048) go(k_view_write<2048, kWalkMany, kMost>, kWalkMany);
+        else if (few) go(k_view_write<4096, kWalkFew, kFewActs>, kWalkFew);
+        else go(k_view_write<4096, kWalkMany, kMost>, kWalkMany);
     }
     return hipGetLastError();
 }
