@@ -105,9 +105,9 @@ PrepWs pm4g::prep_ws_layout(Bump& bp, int64_t n, bool with_rows) {
     w.b.act = bp.take<uint32_t>(m);
     w.a.row = with_rows ? bp.take<uint32_t>(m) : nullptr;
     w.b.row = with_rows ? bp.take<uint32_t>(m) : nullptr;
-    w.hist = bp.take<uint32_t>(256 * (size_t)(radix_blocks(n) + 1));
+    w.hist = bp.take<uint32_t>(radix_digits(n) * (size_t)(radix_blocks(n) + 1));
     w.hist_raw = bp.take<uint32_t>(256 * (size_t)(radix_blocks(n) + 1));
-    w.rowsum = bp.take<uint32_t>(256);
+    w.rowsum = bp.take<uint32_t>(size_t(1) << kRadixMaxBits);
     w.caseblk = bp.take<uint32_t>((size_t)case_blocks(n) + 1);
     w.wincnt = bp.take<uint32_t>((size_t)segsort_blocks(n) + 1);
     return w;
@@ -224,13 +224,13 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     const int act_bits = bits_of((uint64_t)(A - 1));
     // packed keys (activity above the case bits) when both fit in 32 bits
     const int act_shift = (case_bits > 0 && case_bits < 32 && case_bits + act_bits <= 32) ? case_bits : 0;
-    int passes = (case_bits + 7) / 8;
-    if (passes == 0) passes = 1;   // a single case: one pass still biases the keys
+    int width[4];
+    const int passes = radix_plan(case_bits, n, width);
     SortBufs bufs[2] = {w.a, w.b};
     SortBufs in = raw;
     int cur = 0;
-    for (int p = 0; p < passes; ++p) {
-        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, p == 0, w.info, w.hist, w.rowsum, act_shift,
+    for (int p = 0, shift = 0; p < passes; shift += width[p++]) {
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, shift, width[p], p == 0, w.info, w.hist, w.rowsum, act_shift,
                                    p == 0 ? w.hist_raw : nullptr, s));
         in = bufs[cur];
         cur ^= 1;
@@ -261,12 +261,13 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     cur = 0;
     bool first = true;
     for (int p = 0; p < ts_passes; ++p, first = false) {
-        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 1, 8 * p, first, w.info, w.hist, w.rowsum, act_shift, nullptr, s));
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 1, 8 * p, 8, first, w.info, w.hist, w.rowsum, act_shift, nullptr,
+                                   s));
         in = bufs[cur];
         cur ^= 1;
     }
-    for (int p = 0; p < passes; ++p, first = false) {
-        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, 8 * p, first, w.info, w.hist, w.rowsum, act_shift, nullptr, s));
+    for (int p = 0, shift = 0; p < passes; shift += width[p++], first = false) {
+        PM4G_HIP(launch_radix_pass(in, bufs[cur], n, 0, shift, width[p], first, w.info, w.hist, w.rowsum, act_shift, nullptr, s));
         in = bufs[cur];
         cur ^= 1;
     }

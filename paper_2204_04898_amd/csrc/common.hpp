@@ -34,14 +34,15 @@ __device__ __forceinline__ uint64_t lanes_below() {
     return (uint64_t(1) << lane()) - uint64_t(1);
 }
 
-// Lanes of this wave whose 8-bit digit equals this lane's, among `active`.
+// Lanes of this wave whose BITS-bit digit equals this lane's, among `active`.
 // Per bit: the lanes agreeing with this lane are ~(ballot ^ s), s this lane's
 // bit spread over the word (0 or all ones), which gfx950 folds with the and
 // into one three-input bit operation per 32-bit half.
-__device__ __forceinline__ uint64_t match_digit8(uint32_t d, uint64_t active) {
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t active) {
     uint32_t lo = (uint32_t)active, hi = (uint32_t)(active >> 32);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
         const uint32_t s = 0u - ((d >> b) & 1u);
         const uint64_t m = __ballot(s != 0u);
         lo &= ~((uint32_t)m ^ s);
@@ -56,7 +57,7 @@ __device__ __forceinline__ uint64_t match_digit8(uint32_t d, uint64_t active) {
 __device__ __forceinline__ uint64_t match_bits(uint32_t v, int bits, uint64_t active) {
     uint32_t lo = (uint32_t)active, hi = (uint32_t)(active >> 32);
     for (int b = 0; b < bits; ++b) {
-        const uint32_t s = 0u - ((v >> b) & 1u);   // as in match_digit8
+        const uint32_t s = 0u - ((v >> b) & 1u);   // as in match_digit
         const uint64_t m = __ballot(s != 0u);
         lo &= ~((uint32_t)m ^ s);
         hi &= ~((uint32_t)(m >> 32) ^ s);

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kB) void k_scatter(const K* __restrict__ kin, const
             const int64_t i = wbase + k * kWave + lane();
             const bool valid = i < n;
             const uint64_t active = __ballot(valid);
-            const uint64_t peers = match_digit8(dg[k], active);
+            const uint64_t peers = match_digit<8>(dg[k], active);
             const uint32_t below = __popcll(peers & lanes_below());
             uint32_t c = 0;
             if (valid) c = cnt[w * 256 + dg[k]];

@@ -86,15 +86,22 @@ PrepWs prep_ws_layout(Bump& bp, int64_t n, bool with_rows);
 
 constexpr int kRadixTile = 4096;
 inline int64_t radix_blocks(int64_t n) { return (n + kRadixTile - 1) / kRadixTile; }
-// One stable pass on an 8-bit digit.  digit_src 0: ((key & case bits) >> shift) & 255;
-// digit_src 1: ((ts - ts_min) >> shift) & 255.  With `first`, the input is
+// One stable pass on a digit of `width` bits (8 for timestamps).  digit_src 0:
+// ((key & case bits) >> shift); digit_src 1: ((ts - ts_min) >> shift); low bits.  With `first`, the input is
 // the raw log (in.key is the int32 case id, biased by case_min on the fly).
 // act_shift > 0 selects the packed layout: key = case | act << act_shift and
 // no activity column (act_shift = number of case bits, case bits + activity
 // bits <= 32); act_shift = 0: separate activity column.
 // hist_raw (may be NULL; first case pass only): the range scan's raw-byte
 // histograms, used instead of a histogram kernel.
-hipError_t launch_radix_pass(SortBufs in, SortBufs out, int64_t n, int digit_src, int shift,
+constexpr int kRadixMaxBits = 10;      // widest digit among few tiles,
+constexpr int kRadixManyBits = 9;      // and among many
+constexpr int64_t kRadixFewTiles = 64;
+inline size_t radix_digits(int64_t n) {
+    return size_t(1) << (radix_blocks(n) <= kRadixFewTiles ? kRadixMaxBits : kRadixManyBits);
+}
+int radix_plan(int bits, int64_t n, int width[4]);   // passes over `bits` bits, their widths
+hipError_t launch_radix_pass(SortBufs in, SortBufs out, int64_t n, int digit_src, int shift, int width,
                              bool first, const RangeInfo* info, uint32_t* hist, uint32_t* rowsum,
                              int act_shift, const uint32_t* hist_raw, hipStream_t s);
 

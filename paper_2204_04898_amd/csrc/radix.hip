@@ -1,7 +1,9 @@
-// Stable LSD radix passes over (key u32, ts i64, act u32) elements, 8-bit
-// digits, reduce-then-scan:
-//   k_radix_hist     per-tile digit histograms, digit-major [256][tiles]
-//   k_radix_scan     exclusive scan of each digit row, row totals
+// Stable LSD radix passes over (key u32, ts i64, act u32) elements, digits of 8
+// bits (9 or 10 where that saves a pass), reduce-then-scan:
+//   k_radix_hist     per-tile digit histograms, digit-major [digits][tiles]
+//   k_radix_scan     exclusive scan of each digit row, row totals (up to
+//                    kRadixFewTiles tiles: by each scatter block itself; a
+//                    single tile needs neither histogram nor scan)
 //   k_radix_scatter  wave64 ballot ranking (stable: wave, item, lane order),
 //                    LDS staging in digit order, coalesced-run writes; tiles
 //                    laid out XCD-contiguously over the grid
@@ -28,11 +30,12 @@ constexpr int kRB = 512;               // threads per block
 constexpr int kRI = kRadixTile / kRB;  // items per thread (8)
 constexpr int kRW = kRB / kWave;       // waves per block (8)
 
-template <int SRC>
+template <int SRC, int BITS>
 __device__ __forceinline__ uint32_t digit_of(uint32_t key, int64_t ts, int shift, int64_t ts_min,
                                              uint32_t key_mask) {
-    if (SRC == 0) return ((key & key_mask) >> shift) & 255u;
-    return (uint32_t)(((uint64_t)ts - (uint64_t)ts_min) >> shift) & 255u;
+    constexpr uint32_t kMask = (1u << BITS) - 1u;
+    if (SRC == 0) return ((key & key_mask) >> shift) & kMask;
+    return (uint32_t)(((uint64_t)ts - (uint64_t)ts_min) >> shift) & kMask;
 }
 
 // The first pass reads the raw columns: key = case - case_min (| act << act_shift when packed).
@@ -46,12 +49,13 @@ __device__ __forceinline__ uint32_t load_key(const SortBufs& in, int64_t i, int3
     return in.key[i];
 }
 
-template <int SRC, bool FIRST>
+template <int SRC, bool FIRST, int BITS>
 __global__ __launch_bounds__(kRB) void k_radix_hist(SortBufs in, int64_t n, int shift,
                                                     const RangeInfo* info, uint32_t* hist,
                                                     int64_t nb, uint32_t key_mask) {
-    __shared__ uint32_t h[256];
-    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    constexpr int D = 1 << BITS;
+    __shared__ uint32_t h[D];
+    for (int k = threadIdx.x; k < D; k += kRB) h[k] = 0;
     __syncthreads();
     const int32_t case_min = info->case_min;
     const int64_t ts_min = info->ts_min;
@@ -64,10 +68,10 @@ __global__ __launch_bounds__(kRB) void k_radix_hist(SortBufs in, int64_t n, int 
         for (int q = 0; q < kRI / 4; ++q) {
             const uint4 v = k4[q * kRB + threadIdx.x];
             const uint32_t bias = FIRST ? (uint32_t)case_min : 0u;
-            atomicAdd(&h[digit_of<0>(v.x - bias, 0, shift, 0, key_mask)], 1u);
-            atomicAdd(&h[digit_of<0>(v.y - bias, 0, shift, 0, key_mask)], 1u);
-            atomicAdd(&h[digit_of<0>(v.z - bias, 0, shift, 0, key_mask)], 1u);
-            atomicAdd(&h[digit_of<0>(v.w - bias, 0, shift, 0, key_mask)], 1u);
+            atomicAdd(&h[digit_of<0, BITS>(v.x - bias, 0, shift, 0, key_mask)], 1u);
+            atomicAdd(&h[digit_of<0, BITS>(v.y - bias, 0, shift, 0, key_mask)], 1u);
+            atomicAdd(&h[digit_of<0, BITS>(v.z - bias, 0, shift, 0, key_mask)], 1u);
+            atomicAdd(&h[digit_of<0, BITS>(v.w - bias, 0, shift, 0, key_mask)], 1u);
         }
     } else {
 #pragma unroll
@@ -75,14 +79,14 @@ __global__ __launch_bounds__(kRB) void k_radix_hist(SortBufs in, int64_t n, int 
             const int64_t i = base + k * kRB + threadIdx.x;
             if (i < n) {
                 uint32_t d;
-                if (SRC == 0) d = digit_of<0>(load_key<FIRST, false>(in, i, case_min, 0), 0, shift, 0, key_mask);
-                else d = digit_of<1>(0, in.ts[i], shift, ts_min, key_mask);
+                if (SRC == 0) d = digit_of<0, BITS>(load_key<FIRST, false>(in, i, case_min, 0), 0, shift, 0, key_mask);
+                else d = digit_of<1, BITS>(0, in.ts[i], shift, ts_min, key_mask);
                 atomicAdd(&h[d], 1u);
             }
         }
     }
     __syncthreads();
-    if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+    for (int k = threadIdx.x; k < D; k += kRB) hist[(int64_t)k * nb + blockIdx.x] = h[k];
 }
 
 // One block per digit: exclusive scan of hist[d][0..nb) in place, row total.
@@ -145,14 +149,31 @@ __global__ __launch_bounds__(256) void k_radix_scan_rot(const uint32_t* hist_raw
     if (threadIdx.x == 0) rowsum[blockIdx.x] = run;
 }
 
-template <int SRC, bool FIRST, bool PACKED, bool ROW>
+// Where a scatter block finds its tile's place in each digit: in the scanned
+// rows and the row totals; in the rows as counted (few tiles: each block adds
+// up the entries before its own and all, 64 words of a digit from the L2
+// against a launch of 4.5 us), turned by the case minimum when they are the
+// range scan's raw rows; or nowhere (the only tile starts every digit).
+enum RadixRows { ROWS_SCANNED, ROWS_COUNTED, ROWS_RAW, ROWS_NONE };
+
+// What bounds a pass: the loads and the scattered stores (12 bytes read and
+// written per packed element; at 8 bits a tile's runs average 16 elements).
+// Wider digits make more and shorter runs and take more ranking steps, so
+// they pay where they save a pass, 10 bits only among few tiles: two passes of
+// 10 bits over 10M events took 231 us where three of 8 take 215 (histograms of
+// 1024 rows, 30 us each).  Formatting 1.2M events of 17 bits went from 132 to 105
+// us, 25M of 18 bits from 950 to 868, and without histograms or scans 4000 events
+// of 9 bits from 73 to 54 us, 200,000 of 15 bits from 80 to 73.
+template <int SRC, bool FIRST, bool PACKED, bool ROW, int BITS>
 __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out, int64_t n, int shift,
                                                        const RangeInfo* info, const uint32_t* hist,
                                                        const uint32_t* rowsum, int64_t nb,
-                                                       uint32_t key_mask, int act_shift) {
-    __shared__ uint32_t cnt[kRW * 256];       // per-wave running digit counts
-    __shared__ uint32_t tstart[256];          // tile-local start of each digit
-    __shared__ int64_t gshift[256];           // global position - tile position
+                                                       uint32_t key_mask, int act_shift, RadixRows rows) {
+    constexpr int D = 1 << BITS;
+    constexpr int kDPer = (D + kRB - 1) / kRB;   // digits per thread
+    __shared__ alignas(4) uint16_t cnt[kRW * D];   // per-wave running digit counts (a tile has 4096 elements)
+    __shared__ uint32_t tstart[D];            // tile-local start of each digit
+    __shared__ int64_t gshift[D];             // global position - tile position
     __shared__ uint32_t skey[kRadixTile];
     __shared__ int64_t sts[kRadixTile];
     __shared__ uint32_t sact[PACKED ? 1 : kRadixTile];
@@ -168,7 +189,7 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
     const int64_t tile0 = tile * kRadixTile;
     const int64_t wbase = tile0 + (int64_t)w * (kWave * kRI);
 
-    for (int i = threadIdx.x; i < kRW * 256; i += kRB) cnt[i] = 0;
+    for (int i = threadIdx.x; i < kRW * D / 2; i += kRB) reinterpret_cast<uint32_t*>(cnt)[i] = 0;
 
     uint32_t key[kRI], act[kRI], dg[kRI], rk[kRI], rw[kRI];
     int64_t tv[kRI];
@@ -197,7 +218,7 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
             key[k] = rc[k] - (uint32_t)case_min;   // 0 past the end
             if (PACKED) key[k] |= ra[k] << act_shift;
             act[k] = PACKED ? 0u : ra[k];
-            dg[k] = digit_of<SRC>(key[k], tv[k], shift, ts_min, key_mask);
+            dg[k] = digit_of<SRC, BITS>(key[k], tv[k], shift, ts_min, key_mask);
         }
     } else {
 #pragma unroll
@@ -214,7 +235,7 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
                 act[k] = 0;
                 rw[k] = 0;
             }
-            dg[k] = digit_of<SRC>(key[k], tv[k], shift, ts_min, key_mask);
+            dg[k] = digit_of<SRC, BITS>(key[k], tv[k], shift, ts_min, key_mask);
         }
     }
     __syncthreads();
@@ -225,35 +246,62 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
         const int64_t i = wbase + k * kWave + lane();
         const bool valid = i < n;
         const uint64_t active = __ballot(valid);
-        const uint64_t peers = match_digit8(dg[k], active);
+        const uint64_t peers = match_digit<BITS>(dg[k], active);
         const uint32_t below = __popcll(peers & lanes_below());
         uint32_t c = 0;
-        if (valid) c = cnt[w * 256 + dg[k]];
+        if (valid) c = cnt[w * D + dg[k]];
         rk[k] = c + below;
-        if (valid && below == 0) cnt[w * 256 + dg[k]] = c + __popcll(peers);
+        if (valid && below == 0) cnt[w * D + dg[k]] = (uint16_t)(c + __popcll(peers));
     }
     __syncthreads();
 
     // Per digit: exclusive offsets of the waves, the tile's digit totals.
-    uint32_t tot = 0;
-    if (threadIdx.x < 256) {
-        const int d = threadIdx.x;
-        uint32_t run = 0;
-        for (int ww = 0; ww < kRW; ++ww) {
-            const uint32_t x = cnt[ww * 256 + d];
-            cnt[ww * 256 + d] = run;
-            run += x;
+    uint32_t tot[kDPer], own[kDPer], rs[kDPer];   // tile's elements, elements of tiles before, of all tiles
+    uint32_t tsum = 0, rsum = 0;
+#pragma unroll
+    for (int q = 0; q < kDPer; ++q) {
+        const int d = (int)threadIdx.x * kDPer + q;
+        tot[q] = own[q] = rs[q] = 0;
+        if (d < D) {
+            uint32_t run = 0;
+            for (int ww = 0; ww < kRW; ++ww) {
+                const uint32_t x = cnt[ww * D + d];
+                cnt[ww * D + d] = (uint16_t)run;
+                run += x;
+            }
+            tot[q] = rs[q] = run;
+            if (rows == ROWS_SCANNED) {
+                own[q] = hist[(int64_t)d * nb + tile];
+                rs[q] = rowsum[d];
+            } else if (rows != ROWS_NONE) {
+                const uint32_t u = rows == ROWS_RAW ? ((uint32_t)d + (uint32_t)case_min) & 255u : (uint32_t)d;
+                const uint32_t* row = hist + (int64_t)u * nb;
+                uint32_t before = 0, all = 0;
+#pragma unroll 8
+                for (int64_t k = 0; k < nb; ++k) {
+                    const uint32_t x = row[k];
+                    all += x;
+                    before += k < tile ? x : 0u;
+                }
+                own[q] = before;
+                rs[q] = all;
+            }
         }
-        tot = run;
+        tsum += tot[q];
+        rsum += rs[q];
     }
     uint32_t all;
-    const uint32_t ts_excl = block_excl_sum<kRB>(tot, tmp, &all);
-    const uint32_t rs = threadIdx.x < 256 ? rowsum[threadIdx.x] : 0u;
-    const uint32_t digit_base = block_excl_sum<kRB>(rs, tmp, &all);
-    if (threadIdx.x < 256) {
-        const int d = threadIdx.x;
-        tstart[d] = ts_excl;
-        gshift[d] = (int64_t)digit_base + (int64_t)hist[(int64_t)d * nb + tile] - (int64_t)ts_excl;
+    uint32_t ts_excl = block_excl_sum<kRB>(tsum, tmp, &all);
+    uint32_t digit_base = block_excl_sum<kRB>(rsum, tmp, &all);
+#pragma unroll
+    for (int q = 0; q < kDPer; ++q) {
+        const int d = (int)threadIdx.x * kDPer + q;
+        if (d < D) {
+            tstart[d] = ts_excl;
+            gshift[d] = (int64_t)digit_base + (int64_t)own[q] - (int64_t)ts_excl;
+        }
+        ts_excl += tot[q];
+        digit_base += rs[q];
     }
     __syncthreads();
 
@@ -261,7 +309,7 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
     for (int k = 0; k < kRI; ++k) {
         const int64_t i = wbase + k * kWave + lane();
         if (i < n) {
-            const uint32_t pos = tstart[dg[k]] + cnt[w * 256 + dg[k]] + rk[k];
+            const uint32_t pos = tstart[dg[k]] + cnt[w * D + dg[k]] + rk[k];
             skey[pos] = key[k];
             sts[pos] = tv[k];
             if (!PACKED) sact[pos] = act[k];
@@ -274,7 +322,7 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
     for (int i = threadIdx.x; i < valid_count; i += kRB) {
         const uint32_t k = skey[i];
         const int64_t t = sts[i];
-        const uint32_t d = digit_of<SRC>(k, t, shift, ts_min, key_mask);
+        const uint32_t d = digit_of<SRC, BITS>(k, t, shift, ts_min, key_mask);
         const int64_t g = gshift[d] + i;
         out.key[g] = k;
         out.ts[g] = t;
@@ -283,52 +331,79 @@ __global__ __launch_bounds__(kRB) void k_radix_scatter(SortBufs in, SortBufs out
     }
 }
 
-template <int SRC, bool FIRST, bool PACKED, bool ROW>
+template <int SRC, bool FIRST, bool PACKED, bool ROW, int BITS>
 static void run_pass(SortBufs in, SortBufs out, int64_t n, int shift, const RangeInfo* info,
                      uint32_t* hist, uint32_t* rowsum, uint32_t key_mask, int act_shift,
                      const uint32_t* hist_raw, hipStream_t s) {
     const int64_t nb = radix_blocks(n);
-    if (hist_raw) {
+    RadixRows rows = nb == 1 ? ROWS_NONE : nb > kRadixFewTiles ? ROWS_SCANNED : hist_raw ? ROWS_RAW : ROWS_COUNTED;
+    if (rows == ROWS_SCANNED && hist_raw) {
         ProfScope p(P_RADIX_SCAN, s);
         k_radix_scan_rot<<<256, 256, 0, s>>>(hist_raw, hist, nb, rowsum, info);
-    } else {
+    } else if (rows == ROWS_SCANNED || rows == ROWS_COUNTED) {
         {
             ProfScope p(P_RADIX_HIST, s);
-            k_radix_hist<SRC, FIRST><<<(unsigned)nb, kRB, 0, s>>>(in, n, shift, info, hist, nb, key_mask);
+            k_radix_hist<SRC, FIRST, BITS><<<(unsigned)nb, kRB, 0, s>>>(in, n, shift, info, hist, nb, key_mask);
         }
-        ProfScope p(P_RADIX_SCAN, s);
-        k_radix_scan<<<256, 256, 0, s>>>(hist, nb, rowsum);
+        if (rows == ROWS_SCANNED) {
+            ProfScope p(P_RADIX_SCAN, s);
+            k_radix_scan<<<1 << BITS, 256, 0, s>>>(hist, nb, rowsum);
+        }
     }
     ProfScope p(P_RADIX_SCATTER, s);
-    k_radix_scatter<SRC, FIRST, PACKED, ROW><<<(unsigned)nb, kRB, 0, s>>>(in, out, n, shift, info, hist, rowsum,
-                                                                      nb, key_mask, act_shift);
+    k_radix_scatter<SRC, FIRST, PACKED, ROW, BITS>
+        <<<(unsigned)nb, kRB, 0, s>>>(in, out, n, shift, info, rows == ROWS_RAW ? hist_raw : hist, rowsum, nb, key_mask,
+                                      act_shift, rows);
 }
 
-hipError_t launch_radix_pass(SortBufs in, SortBufs out, int64_t n, int digit_src, int shift,
+// Passes over `bits` case bits: as few as the widest digits need where that is
+// fewer than 8-bit ones need, the first as narrow as the others allow (8 bits
+// take the range scan's histograms); 8-bit digits otherwise.
+int radix_plan(int bits, int64_t n, int width[4]) {
+    const int widest = radix_blocks(n) <= kRadixFewTiles ? kRadixMaxBits : kRadixManyBits;
+    int left = bits > 0 ? bits : 1;   // a single case: one pass still biases the keys
+    const int p8 = (left + 7) / 8, pw = (left + widest - 1) / widest;
+    const int passes = pw < p8 ? pw : p8;
+    for (int p = 0; p < passes; ++p) {
+        const int rest = left - widest * (passes - 1 - p);
+        width[p] = pw < p8 && rest > 8 ? rest : 8;
+        left -= width[p];
+    }
+    return passes;
+}
+
+hipError_t launch_radix_pass(SortBufs in, SortBufs out, int64_t n, int digit_src, int shift, int width,
                              bool first, const RangeInfo* info, uint32_t* hist, uint32_t* rowsum,
                              int act_shift, const uint32_t* hist_raw, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const bool packed = act_shift > 0;
     const uint32_t key_mask = packed ? ((act_shift >= 32) ? 0xFFFFFFFFu : ((1u << act_shift) - 1u)) : 0xFFFFFFFFu;
     // the raw-byte histograms describe the first case pass only
-    if (!(digit_src == 0 && first && shift == 0)) hist_raw = nullptr;
+    if (!(digit_src == 0 && first && shift == 0 && width == 8)) hist_raw = nullptr;
     // the row order is carried iff the output has a row array
-#define PM4G_PASS(SRC, FIRST, PACKED)                                                                        \
+#define PM4G_PASS(SRC, FIRST, PACKED, BITS)                                                                  \
     do {                                                                                                    \
         if (out.row)                                                                                        \
-            run_pass<SRC, FIRST, PACKED, true>(in, out, n, shift, info, hist, rowsum, key_mask, act_shift, \
-                                               hist_raw, s);                                                \
+            run_pass<SRC, FIRST, PACKED, true, BITS>(in, out, n, shift, info, hist, rowsum, key_mask,       \
+                                                     act_shift, hist_raw, s);                               \
         else                                                                                                \
-            run_pass<SRC, FIRST, PACKED, false>(in, out, n, shift, info, hist, rowsum, key_mask, act_shift, \
-                                                hist_raw, s);                                               \
+            run_pass<SRC, FIRST, PACKED, false, BITS>(in, out, n, shift, info, hist, rowsum, key_mask,      \
+                                                      act_shift, hist_raw, s);                              \
+    } while (0)
+#define PM4G_CASE_PASS(BITS)                                                                                 \
+    do {                                                                                                    \
+        if (first) { if (packed) PM4G_PASS(0, true, true, BITS); else PM4G_PASS(0, true, false, BITS); }    \
+        else { if (packed) PM4G_PASS(0, false, true, BITS); else PM4G_PASS(0, false, false, BITS); }        \
     } while (0)
     if (digit_src == 0) {
-        if (first) { if (packed) PM4G_PASS(0, true, true); else PM4G_PASS(0, true, false); }
-        else { if (packed) PM4G_PASS(0, false, true); else PM4G_PASS(0, false, false); }
+        if (width == 8) PM4G_CASE_PASS(8);
+        else if (width == 9) PM4G_CASE_PASS(9);
+        else PM4G_CASE_PASS(10);
     } else {
-        if (first) { if (packed) PM4G_PASS(1, true, true); else PM4G_PASS(1, true, false); }
-        else { if (packed) PM4G_PASS(1, false, true); else PM4G_PASS(1, false, false); }
+        if (first) { if (packed) PM4G_PASS(1, true, true, 8); else PM4G_PASS(1, true, false, 8); }
+        else { if (packed) PM4G_PASS(1, false, true, 8); else PM4G_PASS(1, false, false, 8); }
     }
+#undef PM4G_CASE_PASS
 #undef PM4G_PASS
     return hipGetLastError();
 }

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(dev::kB) void k_var_order(VarWs w, int64_t nb) {
         for (int k = 0; k < kI; ++k) {
             const bool valid = key[k] != 0u;
             const uint32_t d = count_digit(key[k]);
-            const uint64_t peers = match_digit8(d, __ballot(valid));
+            const uint64_t peers = match_digit<8>(d, __ballot(valid));
             const uint32_t below = __popcll(peers & lanes_below());
             uint32_t c = 0;
             if (valid) c = cnt[wv * 256 + d];
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kTopThreads) void k_var_top(VarWs w) {
             const bool valid = i < M;
             const uint32_t c = valid ? ck[i] : 0u, k = valid ? cv[i] : 0u;
             const uint32_t d = (~k >> shift) & 255u;
-            const uint64_t peers = match_digit8(d, __ballot(valid));
+            const uint64_t peers = match_digit<8>(d, __ballot(valid));
             const uint32_t below = __popcll(peers & lanes_below());
             if (valid && below == 0) cnt[wv * 256 + d] = __popcll(peers);
             __syncthreads();
