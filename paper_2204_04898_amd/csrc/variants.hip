@@ -121,12 +121,12 @@ __device__ __forceinline__ int seg_of(int64_t vstart, int64_t p) {
 }
 
 // The same search over 32-bit starts (one lane exchange per step instead of two).
-__device__ __forceinline__ int seg_of32(int32_t vstart, int64_t p) {
+__device__ __forceinline__ int seg_of32(uint32_t vstart, uint32_t p) {
     int lo = 0;
 #pragma unroll
     for (int step = 32; step > 0; step >>= 1) {
         const int cand = lo + step;
-        if ((int64_t)__shfl(vstart, cand) <= p) lo = cand;
+        if (__shfl(vstart, cand) <= p) lo = cand;
     }
     return lo;
 }
@@ -166,12 +166,14 @@ __device__ __forceinline__ uint32_t enter(uint64_t* claim, int64_t slots, uint64
 // variant are counted in a block-wide LDS cache by claiming case, written out
 // at the end: a variant that holds a third of the cases costs a global atomic
 // per block, not one per case (they queue on one address at about 8 ns each).
-// Bound by the latency of the scattered claims beside the hash's arithmetic:
-// 0.45 ms on 5M cases of 99M events (the hash alone 0.21 ms; sorting by hash
-// and regrouping took 0.80 ms after it).
+// Bound by the latency of the scattered claims (a hash of a seventh of the
+// multiplies made no difference): 0.39 ms on 5M cases of 99M events (0.45 with
+// a part-filled last wave of blocks; sorting by hash and regrouping took 0.80
+// ms after the hash).
 constexpr int kHashWin = 1024;
 constexpr int kMeet = 2 * kWave;   // LDS slots for a wave's hashes
 constexpr int kMore = 512;         // cached member counts per block
+constexpr int kGroupGrid = 1280;   // five blocks per CU, what its LDS holds: with 2048 the last 768 ran alone
 __global__ __launch_bounds__(kBlk) void k_var_group(const int32_t* __restrict__ act_s,
                                                     const int64_t* __restrict__ case_off, VarWs w,
                                                     uint64_t mask, int64_t n) {
@@ -543,11 +545,16 @@ __global__ __launch_bounds__(kEmitBlk) void k_var_ids(VarWs w, const int64_t* __
 // Sequences in final order: a block takes its range in steps of 512 variants
 // (offsets from the ranges' totals and a block scan), a wave 64 consecutive
 // variants of a step, copying their representatives' activities, writes
-// coalesced over the output range.
+// coalesced over the output range.  Bound by the vector instructions that find
+// each position's variant: with one search per four positions 0.255 ms for the
+// 99M activities of 5M cases, 0.306 with one per position.
 __global__ __launch_bounds__(kEmitBlk) void k_var_emit(const int32_t* __restrict__ act_s,
                                                        const int64_t* __restrict__ case_off, VarWs w,
                                                        const int32_t* status_in, VarOutDev out) {
     __shared__ int64_t tmp[kEmitBlk / kWave + 1];
+    __shared__ uint32_t sdst[kEmitBlk / kWave][kWave + 1];  // a wave's variants: output start after the wave's,
+    __shared__ int32_t ssrc[kEmitBlk / kWave][kWave];       // source position minus output position
+    const int wl = threadIdx.x / kWave;
     const int64_t C = w.scal[0];
     const int64_t V = w.scal[1], chunk = emit_chunk(V);
     const int64_t b0 = blockIdx.x * chunk, b1 = b0 + chunk < V ? b0 + chunk : V;
@@ -579,29 +586,43 @@ __global__ __launch_bounds__(kEmitBlk) void k_var_emit(const int32_t* __restrict
         const int last = (b1 - 1 - k0) < (kWave - 1) ? (int)(b1 - 1 - k0) : (kWave - 1);
         const int64_t base = __shfl(dst, 0);
         const int64_t end = __shfl(dst + len, last);
-        // event positions are below 2^31 (the log's size limit), so output
-        // starts and the source-minus-output shift fit 32 bits: the search and
-        // the shift take one lane exchange each instead of two
-        const int32_t dst32 = has ? (int32_t)dst : INT32_MAX;
-        const int32_t shift = (int32_t)(src - (has ? dst : 0));
-        // wave-uniform trip count: every lane takes part in the shuffles;
-        // four 64-element steps per trip, their loads issued first
-        constexpr int kU = 4;
-        for (int64_t p0 = base; p0 < end; p0 += kU * kWave) {
-            int32_t av[kU];
+        // four consecutive output positions per lane, from an aligned one on: one
+        // search per four, the variant's end tells when to step on.  Offsets from
+        // that position fit 32 bits (a log has fewer than 2^31 events).
+        const uint32_t skip = (uint32_t)((reinterpret_cast<uintptr_t>(out.var_acts + base) / 4) & 3);
+        int32_t* to = out.var_acts + base - skip;
+        const int32_t* from = act_s + base - skip;
+        const uint32_t top = (uint32_t)(end - base) + skip;
+        const uint32_t first = has ? (uint32_t)(dst - base) + skip : UINT32_MAX;
+        sdst[wl][lane()] = first;
+        ssrc[wl][lane()] = has ? (int32_t)(src - dst) : 0;
+        if (lane() == 0) sdst[wl][kWave] = UINT32_MAX;
+        wave_sync();
+        for (uint32_t q0 = 0; q0 < top; q0 += 4 * kWave) {   // wave-uniform
+            const uint32_t q = q0 + 4 * lane();
+            int m = seg_of32(first, q < skip ? skip : q);
+            uint32_t nxt = sdst[wl][m + 1];
+            int32_t sh = ssrc[wl][m];
+            int32_t av[4];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t p = p0 + u * kWave + lane();
-                const int m = seg_of32(dst32, p);
-                const int32_t sh = __shfl(shift, m);
-                av[u] = p < end ? act_s[p + sh] : 0;
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t p = q + j;
+                if (p >= nxt) {   // variants are non-empty: one step at a time
+                    ++m;
+                    nxt = sdst[wl][m + 1];
+                    sh = ssrc[wl][m];
+                }
+                av[j] = p >= skip && p < top ? from[(int64_t)p + sh] : 0;
             }
+            if (q >= skip && q + 3 < top) {
+                *reinterpret_cast<int4*>(to + q) = make_int4(av[0], av[1], av[2], av[3]);
+            } else {
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t p = p0 + u * kWave + lane();
-                if (p < end) out.var_acts[p] = av[u];
+                for (int j = 0; j < 4; ++j)
+                    if (q + j >= skip && q + j < top) to[q + j] = av[j];
             }
         }
+        wave_sync();
     }
     if (out.case_variant) {
         for (int64_t c = (int64_t)blockIdx.x * kEmitBlk + threadIdx.x; c < C; c += (int64_t)gridDim.x * kEmitBlk)
@@ -623,7 +644,7 @@ hipError_t launch_variants(const int32_t* act_s, const int64_t* case_off, const 
     {
         ProfScope p(P_VAR_HASH, s);
         k_var_clear<<<grid((n + kBlk - 1) / kBlk, kGrid), kBlk, 0, s>>>(w, n_cases);
-        k_var_group<<<grid((n + kBlk - 1) / kBlk, kGrid), kBlk, 0, s>>>(act_s, case_off, w, mask, n);
+        k_var_group<<<grid((n + kBlk - 1) / kBlk, kGroupGrid), kBlk, 0, s>>>(act_s, case_off, w, mask, n);
     }
     {
         ProfScope p(P_VAR_ORDER, s);
