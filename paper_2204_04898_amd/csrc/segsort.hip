@@ -41,11 +41,12 @@ namespace pm4g {
 constexpr int kSB = 512;
 constexpr int kSW = kSB / kWave;     // waves per block
 constexpr int kSI = kSegCap / kSB;   // items per thread = chunks per wave
-constexpr int kPre = 3;              // window + lookahead read in the first load round
-static_assert(kSI < 8, "a thread's case starts are counted in three bits");
+constexpr int kRounds = kSegWindow / kSB;   // rounds of the block over the window
+constexpr int kLook = 4;             // waves that read the lookahead after it
 static_assert(kSegCap % kSB == 0, "staging capacity must be a multiple of the block");
 static_assert(kSegCap <= 4096, "cross keys hold the staging position in 12 bits");
-static_assert(kPre * kSB >= kSegWindow, "the first load round covers the window");
+static_assert(kRounds * kSB == kSegWindow && kLook <= kSW, "the rounds cover the window");
+static_assert((kRounds + 1) * kSW <= kWave, "one wave looks through the rows' starts");
 
 __device__ __forceinline__ int64_t block_min_i64(int64_t v, int64_t* red) {
     v = wave_min(v);
@@ -136,6 +137,10 @@ constexpr uint64_t kOffBias = 1ull << 51;
 constexpr uint64_t kOffMask = (1ull << 52) - 1;
 
 // act_shift > 0: packed keys (case bits below act_shift, activity above).
+// Bound by vector instructions (28 bytes per event take 0.6 ms at copy rate
+// for 99M events): 1.33 ms, where a lookahead read by every wave, 64-bit
+// positions, a second pass over LDS for the case starts and the case ids read
+// again for the output took 1.45.
 template <bool ROW>
 __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeInfo* info,
                                                  int32_t* __restrict__ case_s,
@@ -149,9 +154,9 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
     __shared__ uint16_t lcs[kSegCap];    // case start of position i
     __shared__ uint16_t lce[kSegCap];    // case end, stored at the case start
     __shared__ int64_t red[2 * kSW];
-    __shared__ int32_t wred[kSW];
     __shared__ int32_t wst[kSW];
     __shared__ uint32_t wfirst[2][kSW];
+    __shared__ int32_t rlast[(kRounds + 1) * kSW];   // last case start of each row of 64, or -1
 
     const uint32_t* __restrict__ key = in.key;
     const uint32_t kmask = act_shift > 0 ? ((1u << act_shift) - 1u) : 0xFFFFFFFFu;
@@ -159,47 +164,65 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
     // window's start, read by the same XCD at about the same time (its L2)
     const int64_t win = xcd_split(gridDim.x).first;
     const int64_t w0 = win * kSegWindow;
-    const int64_t w1 = (w0 + kSegWindow) < n ? (w0 + kSegWindow) : n;
 
-    // 1. one load round: the window and a lookahead are read into registers; the
-    //    first case start inside the window (s) and the first at or after its end
-    //    (e; n counts) come from them.  Item q of thread t is position
-    //    w0 + q*kSB + t, so within a wave positions grow with q, then with the
-    //    lane: the first q whose ballot is not empty holds the wave's first
-    //    start (wave-uniform, scalar work); the block takes the smallest over
-    //    its waves.  Offsets from w0 fit in 32 bits.
-    // The loads take clamped (in-bounds) positions with no branch around them
-    // and all are issued before any is used; values past n are never used.
-    uint32_t pk[kPre], pa[kPre], pkm1[kPre];
-    int64_t pt[kPre];
-    bool pst[kPre];
-    const int wv0 = threadIdx.x / kWave;
-    uint32_t s_off = UINT32_MAX, e_off = UINT32_MAX;
+    // 1. one load round: the window and a lookahead (by the first waves: most
+    //    windows' last case ends in it) are read into registers; the first case
+    //    start inside the window (s) and the first at or after its end (e; n
+    //    counts) come from them.  Item q of thread t is position w0 + q*kSB + t:
+    //    rows of 64 positions, a wave's in one item.  A row's starts are a ballot
+    //    (the key before a lane's is the lane below's; lane 0's is one scalar
+    //    load), its last start is published, and the block takes the smallest s
+    //    and e over its waves.  Offsets from w0 fit in 32 bits.
+    // The loads take clamped (in-bounds) positions and all are issued before any
+    // is used; values past n are never used.
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int left = (int)(n - w0);   // n < 2^31
+    const int wlen = left < kSegWindow ? left : kSegWindow;
+    const uint32_t* __restrict__ kw = key + w0;
+    const int64_t* __restrict__ tw = in.ts + w0;
+    const uint32_t bias = (uint32_t)info->case_min;
+    constexpr int kItems = kRounds + 1;
+    uint32_t pk[kItems], pa[kItems], pb[kItems];
+    int64_t pt[kItems];
 #pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const int64_t P = w0 + threadIdx.x + q * kSB;
-        const int64_t Pc = P < n ? P : n - 1;
-        pk[q] = key[Pc];
-        pkm1[q] = key[Pc > 0 ? Pc - 1 : 0];
-        pt[q] = in.ts[Pc];
-        pa[q] = 0;
-        if (act_shift <= 0) pa[q] = in.act[Pc];   // block-uniform: no activity column when packed
+    for (int q = 0; q < kItems; ++q) {
+        pk[q] = pa[q] = pb[q] = 0;
+        pt[q] = 0;
+        if (q == kRounds && wv >= kLook) continue;   // wave-uniform
+        const int i = q * kSB + (int)threadIdx.x;
+        const int ic = i < left ? i : left - 1;
+        pk[q] = kw[ic];
+        pt[q] = tw[ic];
+        if (act_shift <= 0) pa[q] = in.act[w0 + ic];   // block-uniform: no activity column when packed
+        const int ib = q * kSB + wv * kWave - 1;       // wave-uniform
+        if (w0 + ib >= 0 && ib < left) pb[q] = kw[ib];
     }
     __builtin_amdgcn_sched_barrier(0);
+    uint32_t s_off = UINT32_MAX, e_off = UINT32_MAX;
+    uint64_t starts[kItems];   // the row's case starts inside the window
+    int nst = 0;
 #pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const int64_t P = w0 + threadIdx.x + q * kSB;
-        if (act_shift > 0) pa[q] = pk[q] >> act_shift;
-        pst[q] = P < n && (P == 0 || ((pk[q] ^ pkm1[q]) & kmask) != 0);
-        const uint64_t bs = __ballot(pst[q] && P < w1);
-        const uint64_t be = __ballot((pst[q] && P >= w1) || P == n);
-        const uint32_t base = (uint32_t)(q * kSB + wv0 * kWave);
-        if (s_off == UINT32_MAX && bs) s_off = base + (uint32_t)__ffsll((unsigned long long)bs) - 1u;
-        if (e_off == UINT32_MAX && be) e_off = base + (uint32_t)__ffsll((unsigned long long)be) - 1u;
+    for (int q = 0; q < kItems; ++q) {
+        const int base = q * kSB + wv * kWave;
+        const int i = base + lane();
+        starts[q] = 0;
+        if (!(q == kRounds && wv >= kLook)) {
+            if (act_shift > 0) pa[q] = pk[q] >> act_shift;
+            // lane l - 1's key: a DPP wave shift right by one, whose lane 0 keeps pb
+            const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)pb[q], (int)pk[q], 0x138, 0xF, 0xF, false);
+            const bool st = i < left && (w0 + i == 0 || ((pk[q] ^ before) & kmask) != 0);
+            starts[q] = __ballot(st && i < wlen);
+            const uint64_t be = __ballot((st && i >= wlen) || i == left);
+            if (s_off == UINT32_MAX && starts[q]) s_off = (uint32_t)(base + __ffsll((unsigned long long)starts[q]) - 1);
+            if (e_off == UINT32_MAX && be) e_off = (uint32_t)(base + __ffsll((unsigned long long)be) - 1);
+            nst += __popcll(starts[q]);
+        }
+        if (lane() == 0) rlast[q * kSW + wv] = starts[q] ? base + 63 - __clzll((long long)starts[q]) : -1;
     }
     if (lane() == 0) {
-        wfirst[0][wv0] = s_off;
-        wfirst[1][wv0] = e_off;
+        wfirst[0][wv] = s_off;
+        wfirst[1][wv] = e_off;
+        wst[wv] = nst;
     }
     __syncthreads();
 #pragma unroll
@@ -207,13 +230,16 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
         s_off = wfirst[0][k] < s_off ? wfirst[0][k] : s_off;
         e_off = wfirst[1][k] < e_off ? wfirst[1][k] : e_off;
     }
+    if (threadIdx.x == 0) {   // the region's cases are the cases starting in the window
+        int32_t t = 0;
+        for (int k = 0; k < kSW; ++k) t += wst[k];
+        wincnt[win] = (uint32_t)t;
+    }
     int64_t s = s_off == UINT32_MAX ? INT64_MAX : w0 + (int64_t)s_off;
     int64_t e = e_off == UINT32_MAX ? INT64_MAX : w0 + (int64_t)e_off;
-    if (s == INT64_MAX) {   // a long case covers the whole window (block-uniform): no case starts here
-        if (threadIdx.x == 0) wincnt[win] = 0;
-        return;
-    }
-    for (int64_t base = w0 + kPre * kSB; e == INT64_MAX && base <= n && base - s <= kSegCap; base += kSB) {
+    if (s == INT64_MAX) return;   // a long case covers the whole window (block-uniform): no case starts here
+    constexpr int kRead = kRounds * kSB + kLook * kWave;
+    for (int64_t base = w0 + kRead; e == INT64_MAX && base <= n && base - s <= kSegCap; base += kSB) {
         const int64_t p = base + threadIdx.x;
         int64_t c = INT64_MAX;
         if (p == n) c = n;
@@ -226,77 +252,41 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
     }
     const int R = (int)(e - s);
 
-    // 2. stage the region [s, e): prefetched events, then any beyond the lookahead
+    // 2. stage the region [s, e): the events read, then any beyond the lookahead,
+    //    with their case starts: a row's own last start at or before the lane,
+    //    else the last one of the rows before it.  The region's events past the
+    //    window belong to the window's last case.  Sorting moves events within
+    //    their case, so the case column is written from here.
+    const int32_t lastst = lane() < kItems * kSW ? rlast[lane()] : -1;
+    const uint64_t rows = __ballot(lastst >= 0);   // rows with a start
+    const int lastcs = wave_lane(lastst, 63 - __clzll((long long)rows));   // (s exists: some row has a start)
+    const int e0 = (int)(e - w0), s0 = (int)s_off;
 #pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const int64_t P = w0 + threadIdx.x + q * kSB;
-        if (P >= s && P < e) {
-            const int i = (int)(P - s);
-            lts[i] = pt[q];
-            lact[i] = (uint16_t)pa[q];
-            lcs[i] = (uint16_t)(pst[q] ? i : 0);
+    for (int q = 0; q < kItems; ++q) {
+        if (q == kRounds && wv >= kLook) continue;
+        const int base = q * kSB + wv * kWave;
+        if (base >= e0) continue;   // wave-uniform
+        const int i = base + lane();
+        const uint64_t before = rows & ((uint64_t(1) << (q * kSW + wv)) - 1);
+        const int carry = before ? wave_lane(lastst, 63 - __clzll((long long)before)) : 0;
+        const uint64_t own = starts[q] & (lanes_below() | (uint64_t(1) << lane()));
+        const int cs = own ? base + 63 - __clzll((long long)own) : carry;
+        if (i >= s0 && i < e0) {
+            lts[i - s0] = pt[q];
+            lact[i - s0] = (uint16_t)pa[q];
+            lcs[i - s0] = (uint16_t)(cs - s0);
+            case_s[w0 + i] = (int32_t)((pk[q] & kmask) + bias);
         }
     }
-    for (int64_t P = w0 + kPre * kSB + threadIdx.x; P < e; P += kSB) {
-        const int i = (int)(P - s);
-        const uint32_t kr = key[P];
-        lts[i] = in.ts[P];
-        lact[i] = (uint16_t)(act_shift > 0 ? (kr >> act_shift) : in.act[P]);
-        lcs[i] = (uint16_t)((((kr ^ key[P - 1]) & kmask) != 0) ? i : 0);
-    }
-    // case ids of the output positions (striped), in flight during the sort:
-    // position i keeps the case of staging position i
-    uint32_t ck[kSI];
-#pragma unroll
-    for (int q = 0; q < kSI; ++q) {
-        const int i = threadIdx.x + q * kSB;
-        ck[q] = key[s + (i < R ? i : R - 1)];   // in bounds, no branch; masked at the write
-    }
-    __syncthreads();
-
-    // 3. case start of every event: inclusive max-scan of the start positions
-    //    (blocked layout: thread t owns items kSI*t .. kSI*t + kSI - 1)
-    {
-        int32_t loc[kSI];
-        int32_t m = 0, nst = 0;
-#pragma unroll
-        for (int q = 0; q < kSI; ++q) {
-            const int i = threadIdx.x * kSI + q;
-            if (i < R) {
-                m = (int32_t)lcs[i] > m ? (int32_t)lcs[i] : m;
-                nst += (int32_t)lcs[i] == i;   // a case starts at i
-            }
-            loc[q] = m;
-        }
-        const int w = threadIdx.x / kWave;
-        // inclusive max over the lanes: where m is not zero it is the last start
-        // among the lane's items, so it grows with the lane; the max is the m of
-        // the highest lane at or below this one with m > 0
-        const uint64_t nz = __ballot(m > 0) & (lanes_below() | (uint64_t(1) << lane()));
-        const int32_t inc = nz ? __shfl(m, 63 - __clzll((long long)nz)) : 0;
-        // the wave's starts: nst < 8, so three ballots of its bits
-        const int32_t wn = __popcll(__ballot(nst & 1)) + 2 * __popcll(__ballot(nst & 2)) +
-                           4 * __popcll(__ballot(nst & 4));
-        if (lane() == kWave - 1) wred[w] = inc;
-        if (lane() == 0) wst[w] = wn;
-        __syncthreads();
-        if (threadIdx.x == 0) {   // the region's cases are the cases starting in the window
-            int32_t t = 0;
-            for (int k = 0; k < kSW; ++k) t += wst[k];
-            wincnt[win] = (uint32_t)t;
-        }
-        int32_t before = 0;
-        for (int i = 0; i < w; ++i) before = wred[i] > before ? wred[i] : before;
-        // lane l - 1's inclusive max (DPP wave shift right by one; lane 0 reads 0)
-        int32_t excl = __builtin_amdgcn_update_dpp(0, inc, 0x138, 0xF, 0xF, false);
-        excl = excl > before ? excl : before;
-#pragma unroll
-        for (int q = 0; q < kSI; ++q) {
-            const int i = threadIdx.x * kSI + q;
-            if (i < R) lcs[i] = (uint16_t)(loc[q] > excl ? loc[q] : excl);
-        }
+    for (int i = kRead + (int)threadIdx.x; i < e0; i += kSB) {
+        const uint32_t kr = kw[i];
+        lts[i - s0] = tw[i];
+        lact[i - s0] = (uint16_t)(act_shift > 0 ? (kr >> act_shift) : in.act[w0 + i]);
+        lcs[i - s0] = (uint16_t)(lastcs - s0);
+        case_s[w0 + i] = (int32_t)((kr & kmask) + bias);
     }
     __syncthreads();
+    // 3. the cases' ends
     // case end, stored at the case start: the last event of each case writes it
     for (int i = threadIdx.x; i < R; i += kSB) {
         if (i == R - 1 || lcs[i + 1] == i + 1) lce[lcs[i]] = (uint16_t)(i + 1);
@@ -304,7 +294,7 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
 
     // 4. sort every 64-event chunk in registers (wave w: chunks w, w + kSW, ...;
     //    chunk w + q*kSW, lane l is position threadIdx.x + q*kSB, as in step 5)
-    const int w = threadIdx.x / kWave;
+    const int w = wv;
     const int l = lane();
     uint64_t sk[kSI];
     int64_t sb[kSI];
@@ -444,12 +434,10 @@ __global__ __launch_bounds__(kSB) void k_segsort(SortBufs in, int64_t n, RangeIn
     __syncthreads();
 
     // 6. write the prepared columns
-    const uint32_t bias = (uint32_t)info->case_min;
 #pragma unroll
     for (int q = 0; q < kSI; ++q) {
         const int i = threadIdx.x + q * kSB;
         if (i < R) {
-            case_s[s + i] = (int32_t)((ck[q] & kmask) + bias);
             act_s[s + i] = (int32_t)lact[i];
             ts_s[s + i] = lts[i];
             if (ROW) row_s[s + i] = (int32_t)in.row[s + lidx[i]];
