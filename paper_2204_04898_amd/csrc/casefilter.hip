@@ -102,62 +102,93 @@ __global__ __launch_bounds__(kCB) void k_cases_df(const int64_t* __restrict__ ca
 __device__ __forceinline__ bool bit_of(const uint64_t* m, int64_t b) { return (m[b >> 6] >> (b & 63)) & 1ull; }
 
 // flags[c]: bit 0 = the case has an activity of act_mask, bit 1 = it has a
-// directly-follows pair of path_mask.
+// directly-follows pair of path_mask.  A wave takes 64 cases, a lane four
+// consecutive events from an aligned one on: one 16-byte load, one search for
+// the first one's case, which the following ones leave at its end; the event
+// before the lane's first is the lane below's last.  The path bits lie in LDS
+// where they fit (LDS): a look-up of 64 scattered words took longer than all
+// the rest from the caches.  20M events, 512 activities: 71 us with a search
+// and a look-up in memory per event, 38 us (the activities alone: 17
+// us at copy rate).
+constexpr size_t kPathLds = 40 * 1024;   // bytes of path bits held in LDS: three blocks per CU at least
+template <bool LDS>
 __global__ __launch_bounds__(kCB) void k_cf_contains(const int32_t* __restrict__ act_s,
                                                      const int64_t* __restrict__ case_off, const int64_t* n_cases,
                                                      int32_t A, const uint64_t* __restrict__ act_mask,
                                                      const uint64_t* __restrict__ path_mask,
                                                      uint32_t* __restrict__ flags) {
+    extern __shared__ uint32_t pbits[];
     __shared__ uint32_t lflag[kCB / kWave][kWave];
+    __shared__ uint32_t lst[kCB / kWave][kWave + 1];   // the cases' starts, after the wave's first position
     const int64_t C = *n_cases;
     const int wl = threadIdx.x / kWave;
     const int64_t wv = ((int64_t)blockIdx.x * kCB + threadIdx.x) / kWave;
     const int64_t nw = (int64_t)gridDim.x * kCB / kWave;
+    if (LDS) {
+        stage_bits<kCB>(path_mask, (int64_t)A * A, pbits);
+        __syncthreads();
+    }
     for (int64_t c0 = wv * kWave; c0 < C; c0 += nw * kWave) {
         const int64_t c = c0 + lane();
         const bool has = c < C;
         const int64_t st = has ? case_off[c] : INT64_MAX;
         const int64_t en = has ? case_off[c + 1] : 0;
-        lflag[wl][lane()] = 0;
         const int last = (C - 1 - c0) < (kWave - 1) ? (int)(C - 1 - c0) : (kWave - 1);
-        const int64_t base = __shfl(st, 0);
-        const int64_t end = __shfl(en, last);
-        const int32_t st32 = has ? (int32_t)st : INT32_MAX;
-        // wave-uniform trip count; four 64-event steps per trip: their activities,
-        // then their bit-set words, each group loaded before it is used
-        constexpr int kU = 4;
-        for (int64_t p0 = base; p0 < end; p0 += kU * kWave) {
-            int32_t a[kU], ap[kU];
+        const int64_t base = wave_lane(st, 0);
+        const int64_t end = wave_lane(en, last);
+        // offsets from an aligned position fit 32 bits (a log has fewer than 2^31 events)
+        const uint32_t skip = (uint32_t)((reinterpret_cast<uintptr_t>(act_s + base) / 4) & 3);
+        const int32_t* from = act_s + base - skip;
+        const uint32_t top = (uint32_t)(end - base) + skip;
+        const uint32_t first = has ? (uint32_t)(st - base) + skip : UINT32_MAX;
+        lflag[wl][lane()] = 0;
+        lst[wl][lane()] = first;
+        if (lane() == 0) lst[wl][kWave] = UINT32_MAX;
+        wave_sync();
+        int32_t carry = 0;   // the event before the step's first: none before the first case
+        for (uint32_t q0 = 0; q0 < top; q0 += 4 * kWave) {   // wave-uniform
+            const uint32_t q = q0 + 4 * lane();
+            int32_t a[4];
+            if (q >= skip && q + 3 < top) {
+                const int4 x = *reinterpret_cast<const int4*>(from + q);
+                a[0] = x.x;
+                a[1] = x.y;
+                a[2] = x.z;
+                a[3] = x.w;
+            } else {
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t p = p0 + u * kWave + lane();
-                const int64_t pc = p < end ? p : end - 1;
-                a[u] = act_s[pc];
-                ap[u] = act_s[pc > 0 ? pc - 1 : 0];
+                for (int j = 0; j < 4; ++j) a[j] = q + j >= skip && q + j < top ? from[q + j] : 0;
             }
-            int m[kU];
-            bool pair[kU];
+            int m = seg_of32(first, q < skip ? skip : q);
+            uint32_t start = lst[wl][m], nxt = lst[wl][m + 1], bits = 0;
+            int32_t before = __builtin_amdgcn_update_dpp(carry, a[3], 0x138, 0xF, 0xF, false);   // lane l - 1's last
+            carry = wave_lane(a[3], kWave - 1);
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t p = p0 + u * kWave + lane();
-                m[u] = seg_at32(st32, p);
-                pair[u] = p > (int64_t)__shfl(st32, m[u]);
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t p = q + j;
+                if (p >= nxt) {   // cases are non-empty: one step at a time
+                    if (bits) atomicOr(&lflag[wl][m], bits);
+                    bits = 0;
+                    ++m;
+                    start = nxt;
+                    nxt = lst[wl][m + 1];
+                }
+                if (p >= skip && p < top) {
+                    if (act_mask) bits |= (uint32_t)(act_mask[a[j] >> 6] >> (a[j] & 63)) & 1u;
+                    if (path_mask && p > start) {
+                        const uint32_t cell = (uint32_t)before * (uint32_t)A + (uint32_t)a[j];   // below 2^24
+                        const uint32_t hit = LDS ? pbits[cell >> 5] >> (cell & 31)
+                                                 : (uint32_t)(path_mask[cell >> 6] >> (cell & 63));
+                        bits |= (hit & 1u) << 1;
+                    }
+                }
+                before = a[j];
             }
-            uint64_t wa[kU], wp[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                wa[u] = act_mask ? act_mask[a[u] >> 6] : 0ull;
-                wp[u] = path_mask ? path_mask[(pair[u] ? (int64_t)ap[u] * A + a[u] : 0) >> 6] : 0ull;
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (p0 + u * kWave + lane() >= end) continue;
-                const uint32_t bits = (uint32_t)((wa[u] >> (a[u] & 63)) & 1u) |
-                                      (pair[u] ? (uint32_t)((wp[u] >> (((int64_t)ap[u] * A + a[u]) & 63)) & 1u) << 1 : 0u);
-                if (bits) atomicOr(&lflag[wl][m[u]], bits);
-            }
+            if (bits) atomicOr(&lflag[wl][m], bits);
         }
+        wave_sync();
         if (has) flags[c] = lflag[wl][lane()];
+        wave_sync();
     }
 }
 
@@ -358,6 +389,12 @@ unsigned range_grid(int64_t n) {
     return (unsigned)(g < 1 ? 1 : (g < dev::kScanGrid ? g : dev::kScanGrid));
 }
 
+// Blocks of the containment kernel: n bounds the cases.
+unsigned contains_grid(int64_t n) {
+    const int64_t g = (n + kCB - 1) / kCB;
+    return (unsigned)(g < 1 ? 1 : (g < kCGrid ? g : kCGrid));
+}
+
 // The kept cases (w.cnt and the ranges' totals) copied into out.
 void materialise_cases(const pm4g_prepared* p, const pm4g_prepared* out, CaseFilterWs w, hipStream_t s) {
     k_cf_emit<<<range_grid(p->n_events), kCB, 0, s>>>(p->case_s, p->act_s, p->ts_s, p->case_off, p->case_code,
@@ -372,9 +409,17 @@ hipError_t launch_filter_cases(const pm4g_prepared* p, const pm4g_case_filter* f
                                CaseFilterWs w, hipStream_t s) {
     ProfScope ps(P_CASE_FILTER, s);
     const pm4g_case_filter fv = *f;
-    if (fv.act_mask || fv.path_mask)
-        k_cf_contains<<<kCGrid, kCB, 0, s>>>(p->act_s, p->case_off, p->n_cases, p->n_activities, fv.act_mask,
-                                             fv.path_mask, w.flags);
+    if (fv.act_mask || fv.path_mask) {
+        const size_t bytes = bits_bytes((int64_t)p->n_activities * p->n_activities);
+        if (fv.path_mask && bytes <= kPathLds)
+            k_cf_contains<true><<<contains_grid(p->n_events), kCB, bytes, s>>>(p->act_s, p->case_off, p->n_cases,
+                                                                               p->n_activities, fv.act_mask,
+                                                                               fv.path_mask, w.flags);
+        else
+            k_cf_contains<false><<<contains_grid(p->n_events), kCB, 0, s>>>(p->act_s, p->case_off, p->n_cases,
+                                                                            p->n_activities, fv.act_mask, fv.path_mask,
+                                                                            w.flags);
+    }
     k_cf_decide<<<range_grid(p->n_events), kCB, 0, s>>>(p->act_s, p->case_off, p->ts_s, p->n_cases, fv, w);
     materialise_cases(p, out, w, s);
     return hipGetLastError();

@@ -102,6 +102,13 @@ __device__ __forceinline__ int seg_at(int64_t vstart, int64_t p) {
     return lo;
 }
 
+// Orders this wave's LDS accesses before it and after it (the lanes run
+// together; only the compiler has to keep the order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Sums over a wave run on DPP moves: six steps of a few cycles each, where a
 // shuffle goes through LDS (a dependent step of 60 cycles and more).  Every
 // lane of the wave must execute them.  wave_add_dpp: v plus the value that the
@@ -148,6 +155,28 @@ __device__ __forceinline__ T wave_incl_sum(T v) {
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
     return wave_lane(wave_incl_sum(v), kWave - 1);
+}
+
+// A bit set of `bits` bits (64-bit words in memory) as 32-bit words in LDS, by a
+// block; bits_bytes: their room.
+inline size_t bits_bytes(int64_t bits) { return (size_t)((bits + 63) / 64) * 8; }
+template <int BLOCK>
+__device__ __forceinline__ void stage_bits(const uint64_t* __restrict__ words, int64_t bits, uint32_t* lds) {
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(words);
+    const int n = 2 * (int)((bits + 63) / 64);
+    for (int i = threadIdx.x; i < n; i += BLOCK) lds[i] = w[i];
+}
+
+// The same search over 32-bit starts (one lane exchange per step instead of
+// two; UINT32_MAX if absent).
+__device__ __forceinline__ int seg_of32(uint32_t vstart, uint32_t p) {
+    int lo = 0;
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) {
+        const int cand = lo + step;
+        if (__shfl(vstart, cand) <= p) lo = cand;
+    }
+    return lo;
 }
 
 // First position of the ascending a[0, n) not below x; a wave together, 64

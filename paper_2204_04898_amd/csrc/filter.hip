@@ -46,6 +46,7 @@ namespace {
 
 constexpr int kFB = 256;
 constexpr int kFI = kFilterTile / kFB;   // 16 events per thread
+constexpr size_t kPairLds = 40 * 1024;   // bytes of a pair set held in LDS: four blocks per CU
 
 // scal: [0] p0, [1] p1, [3] kept total, [7] slice size or kept total when it
 // exceeded the output capacity.  One wave.
@@ -125,7 +126,7 @@ __device__ __forceinline__ void decide_all(const Ready& keep, Row (&x)[kN], int6
     }
     uint64_t wd[kN];
 #pragma unroll
-    for (int q = 0; q < kN; ++q) wd[q] = Pred::kBits ? keep.bits()[ix[q]] : 0ull;
+    for (int q = 0; q < kN; ++q) wd[q] = Pred::kBits ? keep.word(ix[q]) : 0ull;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < kN; ++q) {
@@ -142,7 +143,7 @@ struct ViewPred {
         pm4g_view v;
         const uint64_t* mask;
         __device__ __forceinline__ int64_t partner(int64_t) const { return 0; }
-        __device__ __forceinline__ const uint64_t* bits() const { return mask; }
+        __device__ __forceinline__ uint64_t word(int64_t ix) const { return mask[ix]; }
         __device__ __forceinline__ int64_t prep(Row& x, int64_t, bool in) const {
             x.bit = x.a & 63;
             return in ? (x.a >> 6) : 0;
@@ -151,15 +152,18 @@ struct ViewPred {
             return in && x.t >= v.t_lo && x.t <= v.t_hi && ((word >> x.bit) & 1ull);
         }
     };
-    __device__ __forceinline__ Ready ready() const { return Ready{*view, mask}; }
+    __device__ __forceinline__ Ready ready(uint32_t*) const { return Ready{*view, mask}; }
 };
 
 // Directly-follows level: the pair an event forms with the previous (side 0)
 // or next (side 1) event of its case, looked up in a bit set over src*A+dst.
 // Its slice is the whole log (positions 0..n-1), so the partner of an event,
 // when it exists, sits in the neighbouring lane, except at the wave's edge,
-// whose lane takes the partner's loaded values (every lane loads them, at a
-// clamped position, so that no load waits behind a branch).
+// whose lane takes the partner loaded beside (the wave's one position after or
+// before, the same address in every lane).  The bit set lies in LDS where it
+// fits (LDS): 20M events, 512 activities: count 77 and copy 155 us with 64
+// scattered words read from the caches per look-up, 63 and 148 from LDS.
+template <bool LDS>
 struct PairPred {
     static constexpr bool kC = true, kA = true, kT = false, kPartner = true, kBits = true;
     const uint64_t* pairs;
@@ -167,35 +171,51 @@ struct PairPred {
     int32_t A;
     int32_t side;
     int32_t keep;
-    __device__ __forceinline__ PairPred ready() const { return *this; }
-    __device__ __forceinline__ int64_t partner(int64_t i) const {
-        const int64_t j = side ? i + 1 : i - 1;
-        return j < 0 ? 0 : (j >= n ? n - 1 : j);
-    }
-    __device__ __forceinline__ const uint64_t* bits() const { return pairs; }
-    __device__ __forceinline__ int64_t prep(Row& x, int64_t i, bool in) const {
-        const int32_t c = in ? x.c : 0;
-        const int32_t a = in ? x.a : 0;
-        const int64_t j = side ? i + 1 : i - 1;   // partner position
-        int32_t cj = side ? __shfl_down(c, 1) : __shfl_up(c, 1);
-        int32_t aj = side ? __shfl_down(a, 1) : __shfl_up(a, 1);
-        const bool has = in && j >= 0 && j < n;
-        const bool edge = side ? lane() == kWave - 1 : lane() == 0;
-        if (edge && has) {
-            cj = x.cj;
-            aj = x.aj;
+    struct Ready {
+        const uint64_t* pairs;
+        const uint32_t* lds;
+        int64_t n;
+        int32_t A;
+        int32_t side;
+        int32_t keep;
+        __device__ __forceinline__ int64_t partner(int64_t i) const {
+            const int64_t w0 = i - lane();   // the wave's first position (or, past the log, any in bounds)
+            const int64_t j = side ? w0 + kWave : w0 - 1;
+            return j < 0 ? 0 : (j >= n ? n - 1 : j);
         }
-        x.bit = -1;
-        if (!(has && cj == c)) return 0;
-        const int64_t src = side ? a : aj;
-        const int64_t dst = side ? aj : a;
-        const int64_t cell = src * A + dst;
-        x.bit = (int32_t)(cell & 63);
-        return cell >> 6;
-    }
-    __device__ __forceinline__ bool decide(const Row& x, uint64_t word, int64_t, bool in) const {
-        const bool match = x.bit >= 0 && ((word >> x.bit) & 1ull);
-        return in && (keep ? match : !match);
+        __device__ __forceinline__ uint64_t word(int64_t ix) const { return LDS ? (uint64_t)lds[ix] : pairs[ix]; }
+        __device__ __forceinline__ int64_t prep(Row& x, int64_t i, bool in) const {
+            const int32_t c = in ? x.c : 0;
+            const int32_t a = in ? x.a : 0;
+            const int64_t j = side ? i + 1 : i - 1;   // partner position
+            int32_t cj, aj;   // the neighbouring lane's, at the edge the loaded one
+            if (side) {
+                cj = __builtin_amdgcn_update_dpp(x.cj, c, 0x130, 0xF, 0xF, false);   // wave shift left by one
+                aj = __builtin_amdgcn_update_dpp(x.aj, a, 0x130, 0xF, 0xF, false);
+            } else {
+                cj = __builtin_amdgcn_update_dpp(x.cj, c, 0x138, 0xF, 0xF, false);   // wave shift right by one
+                aj = __builtin_amdgcn_update_dpp(x.aj, a, 0x138, 0xF, 0xF, false);
+            }
+            const bool has = in && j >= 0 && j < n;
+            x.bit = -1;
+            if (!(has && cj == c)) return 0;
+            const int64_t src = side ? a : aj;
+            const int64_t dst = side ? aj : a;
+            const int64_t cell = src * A + dst;
+            x.bit = (int32_t)(cell & (LDS ? 31 : 63));
+            return cell >> (LDS ? 5 : 6);
+        }
+        __device__ __forceinline__ bool decide(const Row& x, uint64_t word, int64_t, bool in) const {
+            const bool match = x.bit >= 0 && ((word >> x.bit) & 1ull);
+            return in && (keep ? match : !match);
+        }
+    };
+    __device__ __forceinline__ Ready ready(uint32_t* lds) const {
+        if (LDS) {
+            stage_bits<kFB>(pairs, (int64_t)A * A, lds);
+            __syncthreads();
+        }
+        return Ready{pairs, lds, n, A, side, keep};
     }
 };
 
@@ -209,13 +229,13 @@ struct SamplePred {
         uint64_t seed, T;
         int32_t none, all;
         __device__ __forceinline__ int64_t partner(int64_t) const { return 0; }
-        __device__ __forceinline__ const uint64_t* bits() const { return nullptr; }
+        __device__ __forceinline__ uint64_t word(int64_t) const { return 0; }
         __device__ __forceinline__ int64_t prep(Row&, int64_t, bool) const { return 0; }
         __device__ __forceinline__ bool decide(const Row&, uint64_t, int64_t i, bool in) const {
             return in && !none && (all || splitmix64(seed, (uint64_t)i) <= T);
         }
     };
-    __device__ __forceinline__ Ready ready() const { return Ready{seed, sel->T, sel->none, sel->all}; }
+    __device__ __forceinline__ Ready ready(uint32_t*) const { return Ready{seed, sel->T, sel->none, sel->all}; }
 };
 
 // The columns a predicate (or the copy, ALL) needs at position i, or at the
@@ -243,7 +263,8 @@ __global__ __launch_bounds__(kFB) void k_filter_count(Pred pred, const int32_t* 
                                                       const int32_t* __restrict__ act_s,
                                                       const int64_t* __restrict__ ts_s, FilterWs w, int64_t whole) {
     __shared__ uint32_t tmp[kFB / kWave + 1];
-    const auto keep = pred.ready();
+    extern __shared__ uint32_t lds_bits[];
+    const auto keep = pred.ready(lds_bits);
     const int64_t p0 = whole >= 0 ? 0 : w.scal[0], p1 = whole >= 0 ? whole : w.scal[1];
     const int64_t safe = p1 > p0 ? p1 - 1 : 0;
     uint32_t c = 0;
@@ -311,7 +332,8 @@ __global__ __launch_bounds__(kFB) void k_filter_emit(const int32_t* __restrict__
     constexpr int kHalf = kFI / 2;   // stripes per half tile: all loads of a half are issued together
     __shared__ uint32_t wcnt[kHalf][kFB / kWave];
     __shared__ int64_t tmp[kFB / kWave + 1];
-    const auto keep = pred.ready();
+    extern __shared__ uint32_t lds_bits[];
+    const auto keep = pred.ready(lds_bits);
     const int64_t p0 = whole >= 0 ? 0 : w.scal[0], p1 = whole >= 0 ? whole : w.scal[1];
     const int64_t safe = p1 > p0 ? p1 - 1 : 0;
     int64_t kept;
@@ -443,9 +465,9 @@ __global__ __launch_bounds__(256) void k_filter_case_emit(const int32_t* __restr
 // events) -> out (events, then their case table).
 template <class Pred>
 void filter_compact(const pm4g_prepared* p, Pred pred, const pm4g_prepared* out, FilterWs w, int64_t whole,
-                    unsigned grid, hipStream_t s) {
-    k_filter_count<<<grid, kFB, 0, s>>>(pred, p->case_s, p->act_s, p->ts_s, w, whole);
-    k_filter_emit<<<grid, kFB, 0, s>>>(p->case_s, p->act_s, p->ts_s, pred, w, out->case_s, out->act_s, out->ts_s,
+                    unsigned grid, size_t lds, hipStream_t s) {
+    k_filter_count<<<grid, kFB, lds, s>>>(pred, p->case_s, p->act_s, p->ts_s, w, whole);
+    k_filter_emit<<<grid, kFB, lds, s>>>(p->case_s, p->act_s, p->ts_s, pred, w, out->case_s, out->act_s, out->ts_s,
                                        out->n_events, whole);
     static_assert(kCaseTile == kFilterTile, "the counts of either grid fit tile_cnt and caseblk");
     k_filter_case_count<<<grid, 256, 0, s>>>(out->case_s, w);
@@ -464,21 +486,26 @@ hipError_t launch_filter_view(const pm4g_prepared* p, const pm4g_view* view, con
                               const pm4g_prepared* out, FilterWs w, hipStream_t s) {
     ProfScope ps(P_VIEW_FILTER, s);
     k_filter_slice<<<1, kWave, 0, s>>>(view, p->case_off, p->case_code, p->n_cases, out->n_events, w);
-    filter_compact(p, ViewPred{view, mask}, out, w, -1, filter_grid(p->n_events), s);
+    filter_compact(p, ViewPred{view, mask}, out, w, -1, filter_grid(p->n_events), 0, s);
     return hipGetLastError();
 }
 
 hipError_t launch_sample_events(const pm4g_prepared* p, uint64_t seed, const SelState* sel,
                                 const pm4g_prepared* out, FilterWs w, hipStream_t s) {
-    filter_compact(p, SamplePred{seed, sel}, out, w, p->n_events, filter_grid(p->n_events), s);
+    filter_compact(p, SamplePred{seed, sel}, out, w, p->n_events, filter_grid(p->n_events), 0, s);
     return hipGetLastError();
 }
 
 hipError_t launch_filter_df_events(const pm4g_prepared* p, const uint64_t* pairs, int32_t side, int32_t keep,
                                    const pm4g_prepared* out, FilterWs w, hipStream_t s) {
     ProfScope ps(P_DF_FILTER, s);
-    filter_compact(p, PairPred{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
-                   filter_grid(p->n_events), s);
+    const size_t bytes = bits_bytes((int64_t)p->n_activities * p->n_activities);
+    if (bytes <= kPairLds)
+        filter_compact(p, PairPred<true>{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
+                       filter_grid(p->n_events), bytes, s);
+    else
+        filter_compact(p, PairPred<false>{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
+                       filter_grid(p->n_events), 0, s);
     return hipGetLastError();
 }
 

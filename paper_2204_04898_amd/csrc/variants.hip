@@ -98,30 +98,12 @@ __global__ __launch_bounds__(kBlk) void k_var_clear(VarWs w, const int64_t* n_ca
     if (blockIdx.x == 0 && threadIdx.x == 0) w.scal[0] = C;
 }
 
-// Orders this wave's LDS accesses before it and after it (the lanes run
-// together; only the compiler has to keep the order).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Wave-cooperative walk over 64 consecutive segments: lane m holds the
 // virtual start of segment m (INT64_MAX if absent); returns the segment that
 // contains virtual position p (the last m with start_m <= p).  Starts are
 // strictly increasing (segments are non-empty) and p >= start_0.  Must be
 // called with all 64 lanes active (the shuffles read every lane).
 __device__ __forceinline__ int seg_of(int64_t vstart, int64_t p) {
-    int lo = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1) {
-        const int cand = lo + step;
-        if (__shfl(vstart, cand) <= p) lo = cand;
-    }
-    return lo;
-}
-
-// The same search over 32-bit starts (one lane exchange per step instead of two).
-__device__ __forceinline__ int seg_of32(uint32_t vstart, uint32_t p) {
     int lo = 0;
 #pragma unroll
     for (int step = 32; step > 0; step >>= 1) {
