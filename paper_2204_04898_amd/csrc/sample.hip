@@ -7,9 +7,10 @@
 // (no memory traffic for events; 4 B per case code), each a histogram of the
 // next 8 bits of the keys that match the prefix found so far; every block finds
 // the prefix itself from the histograms before.  The candidates left (keys are
-// a bijection's images: about one in 2^24 units) are listed, and one block ranks
-// them.  More candidates than the list holds (only case ids chosen for it) are
-// selected by that block alone, 8 bits a pass over all units.
+// a bijection's images: about one in 2^24 units, a few hundred of all 2^32 case
+// ids) are listed, and one block ranks them.  More candidates than the list
+// holds are not expected of any ids; should they come, that block selects among
+// all units, 8 bits a pass, so the answer never depends on it.
 // Six launches; eight passes with a picking launch each were 17.
 #include "common.hpp"
 #include "internal.hpp"

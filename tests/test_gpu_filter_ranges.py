@@ -1,7 +1,7 @@
 """Event and case filters and sampling around their block ranges (4096-event
 tiles, 512-case steps), capacities of exactly the kept events and one less,
 views at the ends of the case range, and case ids whose sampling keys share
-their leading bits (more candidates than the selection lists)."""
+their leading bits."""
 import numpy as np
 import pytest
 import torch
@@ -118,9 +118,9 @@ def _unmix(key, seed):
 
 
 def test_sampling_keys_with_equal_leading_bits():
-    """Case ids are 32-bit: choose the seed so that one key is a given value,
-    and take ids around it; then a log whose 24-bit prefixes collide is built
-    from the ids that share the most frequent prefix (found by search)."""
+    """The cases with the smallest keys of 2^24 ids: their leading bytes are equal,
+    so the digit passes narrow nothing down before the last, and the candidates
+    listed decide; the key's steps are inverted on the host as a check."""
     seed, want = 12345, 0x0123456789ABCDEF
     x = _unmix(want, seed)
     z = (seed + (x + 1) * 0x9E3779B97F4A7C15) & M64
