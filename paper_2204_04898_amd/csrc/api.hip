@@ -188,9 +188,9 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     RangeInfo h{};
     PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, presorted, w.info, w.rpart,
                                w.hist_raw, out->status, back.dst(), s));
-    const auto table = [&](const uint32_t* wincnt) {
+    const auto table = [&](const uint32_t* wincnt, BackDst dst = BackDst{nullptr, nullptr, 0}) {
         return case_table ? launch_case_table(out->case_s, n, w.caseblk, out->case_off, out->case_code, out->n_cases,
-                                              wincnt, w.info, s)
+                                              wincnt, w.info, dst, s)
                           : hipSuccess;
     };
     const auto status = [&]() -> int {   // out->status holds it too
@@ -237,8 +237,9 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     }
     PM4G_HIP(launch_segsort(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, w.wincnt, row_s, s));
     const bool may_be_long = n > kSegCap;   // a log that fits one window has no longer case
-    if (may_be_long) PM4G_HIP(launch_publish(w.info, back.dst(), s));
-    PM4G_HIP(table(w.wincnt));
+    // the header goes to the host from the case table's first kernel, if there is one
+    if (may_be_long && !case_table) PM4G_HIP(launch_publish(w.info, back.dst(), s));
+    PM4G_HIP(may_be_long && case_table ? table(w.wincnt, back.dst()) : table(w.wincnt));
     if (may_be_long && !back.live()) PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
     if (!h.long_case) {
         if (int rc = after()) return rc;

@@ -59,9 +59,15 @@ __device__ __forceinline__ uint32_t tile_count(const uint32_t* cnt, int64_t nc, 
     return c;
 }
 
+// The formatting step's header to the host (one thread), where the call waits for it.
+__device__ __forceinline__ void publish_info(const BackDst& back, const RangeInfo* info) {
+    if (info) publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
+}
+
 __global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t nc, int per_tile, uint32_t* blockoff,
                                                     int64_t nb, int64_t n, int64_t* case_off, int64_t* n_cases,
-                                                    const RangeInfo* info) {
+                                                    const RangeInfo* info, BackDst back) {
+    if (threadIdx.x == 0) publish_info(back, info);
     if (info && info->long_case) {   // uncounted windows
         if (threadIdx.x == 0) *n_cases = case_off[0] = 0;
         return;
@@ -95,7 +101,8 @@ __global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t
 __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ case_s, int64_t n,
                                                    const uint32_t* blockoff, const uint32_t* cnt, int64_t nc,
                                                    int per_tile, int64_t* case_off, int32_t* case_code,
-                                                   int64_t* n_cases, const RangeInfo* info) {
+                                                   int64_t* n_cases, const RangeInfo* info, BackDst back) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish_info(back, info);
     if (info && info->long_case) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *n_cases = case_off[0] = 0;
         return;
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(kCB) void k_case_emit(const int32_t* __restrict__ c
 
 hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcnt, int64_t* case_off,
                              int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, const RangeInfo* info,
-                             hipStream_t s) {
+                             BackDst back, hipStream_t s) {
     ProfScope p(P_CASE_TABLE, s);
     const int64_t nb = case_blocks(n);
     // nb partial sums of the tiles before: nb^2 / 2 cached loads against a launch
@@ -173,10 +180,13 @@ hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcn
         per_tile = 1;
     }
     const bool scan = nb == 0 || nb > kCaseDirect;
-    if (scan) k_case_scan<<<1, 1024, 0, s>>>(cnt, nc, per_tile, blockcnt, nb, n, case_off, n_cases, info);
+    if (scan) {
+        k_case_scan<<<1, 1024, 0, s>>>(cnt, nc, per_tile, blockcnt, nb, n, case_off, n_cases, info, back);
+        back.words = nullptr;   // the first kernel writes the header
+    }
     if (nb > 0)
         k_case_emit<<<(unsigned)nb, kCB, 0, s>>>(case_s, n, scan ? blockcnt : nullptr, cnt, nc, per_tile, case_off,
-                                                 case_code, n_cases, info);
+                                                 case_code, n_cases, info, back);
     return hipGetLastError();
 }
 

@@ -128,7 +128,7 @@ inline int64_t case_blocks(int64_t n) { return (n + kCaseTile - 1) / kCaseTile; 
 // counted: the table is left empty (no cases).
 hipError_t launch_case_table(const int32_t* case_s, int64_t n, uint32_t* blockcnt, int64_t* case_off,
                              int32_t* case_code, int64_t* n_cases, const uint32_t* wincnt, const RangeInfo* info,
-                             hipStream_t s);
+                             BackDst back, hipStream_t s);
 
 // ---- DFG aggregation (dfg.hip) ----
 constexpr int kCellsPerTable = 4096;     // one LDS table of cells

@@ -56,75 +56,11 @@ __global__ __launch_bounds__(256) void k_range_scan(const int32_t* __restrict__ 
         part[blockIdx.x] = RangePart{INT32_MAX, INT32_MIN, any_bad ? 1 : 0, any_unsorted ? 1 : 0, INT64_MAX, INT64_MIN};
 }
 
-// The formatting step's range scan over radix tiles (kRadixTile events per
-// block, no timestamps): besides the partials, each tile's histogram of the
-// low 8 bits of the raw case id.  The first radix pass digit is the low byte
-// of case - case_min, a rotation of that byte by case_min, so this histogram
-// replaces the first pass's histogram kernel (k_radix_scan_rot rotates it).
-__global__ __launch_bounds__(kRangeTileThreads) void k_range_tiles(const int32_t* __restrict__ case_id,
-                                                                   const int32_t* __restrict__ act, int64_t n,
-                                                                   int32_t A, RangePart* part,
-                                                                   uint32_t* hist_raw, int64_t nb) {
-    __shared__ uint32_t h[256];
-    __shared__ RangePart red[kRangeTileThreads / kWave];
-    constexpr int kT = kRangeTileThreads;
-    if (threadIdx.x < 256) h[threadIdx.x] = 0;
-    __syncthreads();
-    int32_t cmin = INT32_MAX, cmax = INT32_MIN;
-    bool bad = false;
-    auto visit = [&](int32_t c, int32_t a) {
-        bad |= (uint32_t)a >= (uint32_t)A;
-        cmin = c < cmin ? c : cmin;
-        cmax = c > cmax ? c : cmax;
-        atomicAdd(&h[(uint32_t)c & 255u], 1u);
-    };
-    const int64_t base = (int64_t)blockIdx.x * kRadixTile;
-    const bool vec = base + kRadixTile <= n &&
-                     ((reinterpret_cast<uintptr_t>(case_id) | reinterpret_cast<uintptr_t>(act)) & 15) == 0;
-    if (vec) {
-        const int4* c4 = reinterpret_cast<const int4*>(case_id + base);
-        const int4* a4 = reinterpret_cast<const int4*>(act + base);
-#pragma unroll
-        for (int q = 0; q < kRadixTile / (4 * kT); ++q) {
-            const int4 c = c4[q * kT + threadIdx.x];
-            const int4 a = a4[q * kT + threadIdx.x];
-            visit(c.x, a.x);
-            visit(c.y, a.y);
-            visit(c.z, a.z);
-            visit(c.w, a.w);
-        }
-    } else {
-        for (int64_t i = base + threadIdx.x; i < n && i < base + kRadixTile; i += kT) visit(case_id[i], act[i]);
-    }
-    RangePart r{wave_min(cmin), wave_max(cmax), __ballot(bad) != 0, 0, INT64_MAX, INT64_MIN};
-    if (lane() == 0) red[threadIdx.x / kWave] = r;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < kT / kWave; ++k) {
-            r.cmin = red[k].cmin < r.cmin ? red[k].cmin : r.cmin;
-            r.cmax = red[k].cmax > r.cmax ? red[k].cmax : r.cmax;
-            r.bad |= red[k].bad;
-        }
-        part[blockIdx.x] = r;
-    }
-    if (threadIdx.x < 256) hist_raw[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
-}
-
-// One block folds the per-block partials into the RangeInfo (no partials: an
-// empty log) and starts the call's status word.
-__global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int nparts, RangeInfo* info,
-                                                      int32_t* status, BackDst back) {
-    __shared__ RangePart red[1024 / kWave];
-    RangePart r{INT32_MAX, INT32_MIN, 0, 0, INT64_MAX, INT64_MIN};
-    for (int k = threadIdx.x; k < nparts; k += 1024) {
-        const RangePart o = part[k];
-        r.cmin = o.cmin < r.cmin ? o.cmin : r.cmin;
-        r.cmax = o.cmax > r.cmax ? o.cmax : r.cmax;
-        r.tmin = o.tmin < r.tmin ? o.tmin : r.tmin;
-        r.tmax = o.tmax > r.tmax ? o.tmax : r.tmax;
-        r.bad |= o.bad;
-        r.unsorted |= o.unsorted;
-    }
+// Folds a block's partials (one per thread) into the RangeInfo and starts the
+// call's status word.
+template <int THREADS>
+__device__ __forceinline__ void store_range(RangePart r, RangePart* red, RangeInfo* info, int32_t* status,
+                                            const BackDst& back) {
     r.cmin = wave_min(r.cmin);
     r.cmax = wave_max(r.cmax);
     r.tmin = wave_min(r.tmin);
@@ -134,7 +70,7 @@ __global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int
     if (lane() == 0) red[threadIdx.x / kWave] = r;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < 1024 / kWave; ++k) {
+        for (int k = 1; k < THREADS / kWave; ++k) {
             const RangePart& o = red[k];
             r.cmin = o.cmin < r.cmin ? o.cmin : r.cmin;
             r.cmax = o.cmax > r.cmax ? o.cmax : r.cmax;
@@ -152,6 +88,92 @@ __global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int
         *status = info->status;
         publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
     }
+}
+
+// The formatting step's range scan over radix tiles (kRadixTile events per
+// block, no timestamps): besides the partials, each tile's histogram of the
+// low 8 bits of the raw case id.  The first radix pass digit is the low byte
+// of case - case_min, a rotation of that byte by case_min, so this histogram
+// replaces the first pass's histogram kernel (k_radix_scan_rot rotates it).
+// WHOLE: one block takes all tiles and stores the result itself; with few
+// tiles they take less than the folding launch (kRangeWhole).
+constexpr int64_t kRangeWhole = 4;
+template <bool WHOLE>
+__global__ __launch_bounds__(kRangeTileThreads) void k_range_tiles(const int32_t* __restrict__ case_id,
+                                                                   const int32_t* __restrict__ act, int64_t n,
+                                                                   int32_t A, RangePart* part,
+                                                                   uint32_t* hist_raw, int64_t nb, RangeInfo* info,
+                                                                   int32_t* status, BackDst back) {
+    __shared__ uint32_t h[256];
+    __shared__ RangePart red[kRangeTileThreads / kWave];
+    constexpr int kT = kRangeTileThreads;
+    int32_t cmin = INT32_MAX, cmax = INT32_MIN;
+    bool bad = false;
+    auto visit = [&](int32_t c, int32_t a) {
+        bad |= (uint32_t)a >= (uint32_t)A;
+        cmin = c < cmin ? c : cmin;
+        cmax = c > cmax ? c : cmax;
+        atomicAdd(&h[(uint32_t)c & 255u], 1u);
+    };
+    for (int64_t t = WHOLE ? 0 : blockIdx.x; t < (WHOLE ? nb : (int64_t)blockIdx.x + 1); ++t) {
+        if (threadIdx.x < 256) h[threadIdx.x] = 0;
+        __syncthreads();
+        const int64_t base = t * kRadixTile;
+        const bool vec = base + kRadixTile <= n &&
+                         ((reinterpret_cast<uintptr_t>(case_id) | reinterpret_cast<uintptr_t>(act)) & 15) == 0;
+        if (vec) {
+            const int4* c4 = reinterpret_cast<const int4*>(case_id + base);
+            const int4* a4 = reinterpret_cast<const int4*>(act + base);
+#pragma unroll
+            for (int q = 0; q < kRadixTile / (4 * kT); ++q) {
+                const int4 c = c4[q * kT + threadIdx.x];
+                const int4 a = a4[q * kT + threadIdx.x];
+                visit(c.x, a.x);
+                visit(c.y, a.y);
+                visit(c.z, a.z);
+                visit(c.w, a.w);
+            }
+        } else {
+            for (int64_t i = base + threadIdx.x; i < n && i < base + kRadixTile; i += kT) visit(case_id[i], act[i]);
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) hist_raw[(int64_t)threadIdx.x * nb + t] = h[threadIdx.x];
+    }
+    RangePart r{cmin, cmax, bad, 0, INT64_MAX, INT64_MIN};
+    if (WHOLE) {
+        store_range<kT>(r, red, info, status, back);
+        return;
+    }
+    r.cmin = wave_min(cmin);
+    r.cmax = wave_max(cmax);
+    r.bad = __ballot(bad) != 0;
+    if (lane() == 0) red[threadIdx.x / kWave] = r;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kT / kWave; ++k) {
+            r.cmin = red[k].cmin < r.cmin ? red[k].cmin : r.cmin;
+            r.cmax = red[k].cmax > r.cmax ? red[k].cmax : r.cmax;
+            r.bad |= red[k].bad;
+        }
+        part[blockIdx.x] = r;
+    }
+}
+
+// One block folds the per-block partials (none: an empty log).
+__global__ __launch_bounds__(1024) void k_range_final(const RangePart* part, int nparts, RangeInfo* info,
+                                                      int32_t* status, BackDst back) {
+    __shared__ RangePart red[1024 / kWave];
+    RangePart r{INT32_MAX, INT32_MIN, 0, 0, INT64_MAX, INT64_MIN};
+    for (int k = threadIdx.x; k < nparts; k += 1024) {
+        const RangePart o = part[k];
+        r.cmin = o.cmin < r.cmin ? o.cmin : r.cmin;
+        r.cmax = o.cmax > r.cmax ? o.cmax : r.cmax;
+        r.tmin = o.tmin < r.tmin ? o.tmin : r.tmin;
+        r.tmax = o.tmax > r.tmax ? o.tmax : r.tmax;
+        r.bad |= o.bad;
+        r.unsorted |= o.unsorted;
+    }
+    store_range<1024>(r, red, info, status, back);
 }
 
 __global__ __launch_bounds__(256) void k_ts_range(const int64_t* __restrict__ ts, int64_t n,
@@ -196,7 +218,13 @@ hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const i
         k_range_scan<<<parts, 256, 0, s>>>(case_id, act, ts, n, A, part);
     } else if (n > 0) {
         parts = (int)radix_blocks(n);
-        k_range_tiles<<<parts, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, parts);
+        if (parts <= kRangeWhole) {
+            k_range_tiles<true><<<1, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, parts, info, status,
+                                                                back);
+            return hipGetLastError();
+        }
+        k_range_tiles<false><<<parts, kRangeTileThreads, 0, s>>>(case_id, act, n, A, part, hist_raw, parts, info, status,
+                                                                 back);
     }
     k_range_final<<<1, 1024, 0, s>>>(part, parts, info, status, back);
     return hipGetLastError();

@@ -16,7 +16,7 @@
 //                  the table: claiming case, further members, smallest member
 //   k_var_reps     representatives and their counts, in case order; histogram
 //                  of the count digit (255 - min(count, 255)) per tile
-//   scan           of the digit rows
+//   scan           of the digit rows (more than 64 tiles)
 //   k_var_order    representatives to their place by (digit, case): the final
 //                  order, except among the variants of 255 cases or more
 //   k_var_top      those by descending count
@@ -322,6 +322,9 @@ __global__ __launch_bounds__(dev::kB) void k_var_reps(VarWs w, int64_t nb) {
 // Representatives (count, case) to their place by (digit, case), in vcr: one
 // stable digit pass over the cases, as dev::k_scatter, where only the
 // representatives take part.
+// Up to kFewTiles tiles the rows are not scanned: each block adds them up
+// itself (64 words of a digit at most, against a launch of 4.5 us).
+constexpr int64_t kFewTiles = 64;
 __global__ __launch_bounds__(dev::kB) void k_var_order(VarWs w, int64_t nb) {
     using namespace dev;
     __shared__ uint32_t cnt[kW * 256];
@@ -334,7 +337,15 @@ __global__ __launch_bounds__(dev::kB) void k_var_order(VarWs w, int64_t nb) {
     const int64_t C = w.scal[0], tiles_n = (C + kTile - 1) / kTile;
     const int wv = threadIdx.x / kWave;
     uint32_t all;
-    const uint32_t rs = threadIdx.x < 256 ? w.rowsum[threadIdx.x] : 0u;
+    const bool scanned = nb > kFewTiles;
+    // elements of this thread's digit in the tiles before `tile`
+    auto before = [&](int64_t tile) {
+        uint32_t x = 0;
+#pragma unroll 8
+        for (int64_t t = 0; t < tile; ++t) x += w.hist[(int64_t)threadIdx.x * nb + t];
+        return x;
+    };
+    const uint32_t rs = threadIdx.x >= 256 ? 0u : scanned ? w.rowsum[threadIdx.x] : before(tiles_n);
     const uint32_t digit_base = block_excl_sum<kB>(rs, tmp, &all);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         w.scal[1] = all;   // V
@@ -377,7 +388,8 @@ __global__ __launch_bounds__(dev::kB) void k_var_order(VarWs w, int64_t nb) {
         const uint32_t ex = block_excl_sum<kB>(tot, tmp, &reps);
         if (threadIdx.x < 256) {
             tstart[threadIdx.x] = ex;
-            gshift[threadIdx.x] = (int64_t)digit_base + (int64_t)w.hist[(int64_t)threadIdx.x * nb + tile] - (int64_t)ex;
+            const uint32_t at = scanned ? w.hist[(int64_t)threadIdx.x * nb + tile] : before(tile);
+            gshift[threadIdx.x] = (int64_t)digit_base + (int64_t)at - (int64_t)ex;
         }
         __syncthreads();
 #pragma unroll
@@ -631,7 +643,7 @@ hipError_t launch_variants(const int32_t* act_s, const int64_t* case_off, const 
     {
         ProfScope p(P_VAR_ORDER, s);
         k_var_reps<<<dev::grid_for(nb), dev::kB, 0, s>>>(w, nb);
-        dev::k_hist_scan<<<256, 256, 0, s>>>(w.hist, &w.scal[0], nb, w.rowsum);
+        if (nb > kFewTiles) dev::k_hist_scan<<<256, 256, 0, s>>>(w.hist, &w.scal[0], nb, w.rowsum);
         k_var_order<<<dev::grid_for(nb), dev::kB, 0, s>>>(w, nb);
         // at most n / 255 variants have 255 cases
         k_var_top<<<grid((n / 255 + kWave - 1) / kWave, kTopPairs / kWave), kTopThreads, 0, s>>>(w);

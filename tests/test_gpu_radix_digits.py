@@ -18,7 +18,7 @@ TILE, FEW = 4096, 64
     (1, 1), (TILE, 1), (TILE, 256), (TILE, 257), (TILE - 3, 1 << 10), (TILE, (1 << 10) + 1),
     (TILE + 1, 256), (TILE + 1, 512), (3 * TILE, 1 << 10), (FEW * TILE, 1 << 16), (FEW * TILE, (1 << 20) - 7),
     (FEW * TILE + 1, 1 << 16), (FEW * TILE + 1, 1 << 17), (300_000, 1 << 18), (300_000, (1 << 18) + 1),
-    (300_000, 1 << 25), (TILE, 1 << 21), (100_000, 1 << 21),
+    (300_000, 1 << 25), (TILE, 1 << 21), (100_000, 1 << 21), (4 * TILE, 700), (4 * TILE + 1, 700),
 ])
 def test_case_digits(n, span, A, rows):
     rng = np.random.default_rng(n + span + A)
