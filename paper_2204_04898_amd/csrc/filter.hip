@@ -46,7 +46,8 @@ namespace {
 
 constexpr int kFB = 256;
 constexpr int kFI = kFilterTile / kFB;   // 16 events per thread
-constexpr size_t kPairLds = 40 * 1024;   // bytes of a pair set held in LDS: four blocks per CU
+constexpr size_t kPairLds = 40 * 1024;   // bytes of a pair set held in LDS: four blocks per CU,
+constexpr int64_t kPairGrid = 1024;      // all of them resident: each block reads the set once
 
 // scal: [0] p0, [1] p1, [3] kept total, [7] slice size or kept total when it
 // exceeded the output capacity.  One wave.
@@ -162,7 +163,7 @@ struct ViewPred {
 // whose lane takes the partner loaded beside (the wave's one position after or
 // before, the same address in every lane).  The bit set lies in LDS where it
 // fits (LDS): 20M events, 512 activities: count 77 and copy 155 us with 64
-// scattered words read from the caches per look-up, 63 and 148 from LDS.
+// scattered words read from the caches per look-up, 55 and 137 from LDS.
 template <bool LDS>
 struct PairPred {
     static constexpr bool kC = true, kA = true, kT = false, kPartner = true, kBits = true;
@@ -475,9 +476,9 @@ void filter_compact(const pm4g_prepared* p, Pred pred, const pm4g_prepared* out,
                                             p->status);
 }
 
-unsigned filter_grid(int64_t n) {
+unsigned filter_grid(int64_t n, int64_t most = 2048) {
     const int64_t ntiles = (n + kFilterTile - 1) / kFilterTile;
-    return (unsigned)(ntiles < 2048 ? (ntiles < 1 ? 1 : ntiles) : 2048);
+    return (unsigned)(ntiles < most ? (ntiles < 1 ? 1 : ntiles) : most);
 }
 
 }  // namespace
@@ -502,7 +503,7 @@ hipError_t launch_filter_df_events(const pm4g_prepared* p, const uint64_t* pairs
     const size_t bytes = bits_bytes((int64_t)p->n_activities * p->n_activities);
     if (bytes <= kPairLds)
         filter_compact(p, PairPred<true>{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
-                       filter_grid(p->n_events), bytes, s);
+                       filter_grid(p->n_events, kPairGrid), bytes, s);
     else
         filter_compact(p, PairPred<false>{pairs, p->n_events, p->n_activities, side, keep}, out, w, p->n_events,
                        filter_grid(p->n_events), 0, s);
