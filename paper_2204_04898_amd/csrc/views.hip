@@ -1133,9 +1133,14 @@ __device__ __forceinline__ void agg_segments(int32_t A, const ViewWs& w, const B
 #pragma unroll
             for (int q = 0; q < kPer; ++q)
                 tab[3 * kAB2 + q * kAB2 + threadIdx.x] = *reinterpret_cast<const uint4*>(&smm[2 * (c0 + q)]);
+            // every wave's part has reached the L2 before one thread writes the L2
+            // back, announces the table and, as the last, drops stale lines
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (threadIdx.x == 0) {
                 __threadfence();
+                __builtin_amdgcn_s_waitcnt(0);   // the write-back too
                 L.s_last = atomicAdd(&w.agg_done[k.it.w], 1u) == k.it.z - 1;
                 __threadfence();
             }
