@@ -794,7 +794,7 @@ def summarize_counters(a) -> None:
     if a.stage == "step":
         fetch = _counter_rows(a.fetch_csv, "pm4g::", "FETCH_SIZE")
         write = _counter_rows(a.write_csv, "pm4g::", "WRITE_SIZE")
-        steps = len(_counter_rows(a.fetch_csv, "k_range_init", "FETCH_SIZE"))
+        steps = len(_counter_rows(a.fetch_csv, "k_range_tiles", "FETCH_SIZE"))
         if not (fetch and write and steps):
             raise SystemExit("counter rows missing for the step's kernels")
         fb = sum(fetch) * 1024.0 * f_scale / steps
