@@ -231,6 +231,7 @@ constexpr int kViewMaxBlocks = 1024;   // blocks of the persistent launch, at mo
 struct ViewWs {
     int32_t tile;
     int32_t n_buckets;
+    int32_t parts;          // blocks that may share a tile's views
     int64_t n_tiles;
     int64_t pair_cap, rec_cap, cell_cap;
     int64_t* p0;            // [V] event slice of each view

@@ -72,6 +72,17 @@ int64_t view_buckets(int32_t A) {
     return ((int64_t)A * (A + 1) + kCellsPerTable - 1) / kCellsPerTable;
 }
 
+// Blocks that may share a tile's views in the walks: a log of few tiles would
+// otherwise leave most of the chip idle (512 blocks fill it; 4096 views of 50k
+// events, 13 tiles: a call of 797 us whole, 430 shared; 300 views of 200k
+// events, 49 tiles: 248 and 175).  Above 256 tiles, or with few views, it would
+// only add empty blocks (200 views of 2M events, 489 tiles: 195 and 215 us).
+static int32_t walk_parts(int64_t n_tiles, int32_t V) {
+    if (n_tiles < 1 || n_tiles > 256 || V < 32) return 1;
+    const int64_t fill = (511 + n_tiles) / n_tiles, most = V / 16 < 16 ? V / 16 : 16;
+    return (int32_t)(fill < most ? fill : most);
+}
+
 ViewWs view_ws_layout(Bump& b, int64_t n, int32_t A, int32_t V, int32_t tile, int64_t pair_cap,
                       int64_t rec_cap, int64_t cell_cap) {
     ViewWs w{};
@@ -83,6 +94,7 @@ ViewWs view_ws_layout(Bump& b, int64_t n, int32_t A, int32_t V, int32_t tile, in
     w.tile = tile;
     w.n_tiles = tiles;
     w.n_buckets = (int32_t)view_buckets(A);
+    w.parts = walk_parts(tiles, V);
     w.pair_cap = pair_cap;
     w.rec_cap = rec_cap;
     w.p0 = b.take<int64_t>(vm);
@@ -621,6 +633,14 @@ __device__ __forceinline__ uint32_t next_pair(uint32_t* s_next) {
 // tile 5.8 ms by views, 9.1 ms shared).
 constexpr uint32_t kManyViews = 2;
 
+// Views of a tile per block that shares it (w.parts blocks at most): sixteen or
+// more, one per wave; with fewer a block would stage the tile for less work than
+// the staging.
+__device__ __forceinline__ uint32_t walk_share(uint32_t views, uint32_t parts) {
+    const uint32_t even = (views + parts - 1) / parts;
+    return even < 16 ? 16 : even;
+}
+
 // Count walk.  After a view's walk, each non-empty bucket's run takes its
 // place in the (view, bucket) segment with one atomic on the segment's
 // counter; the walk's initial carry and whether the pair keeps an event are
@@ -639,13 +659,19 @@ __device__ __forceinline__ void ph_count(Grid gd, const int32_t* __restrict__ ca
     auto& mask = S.s_mask[wv];
     uint32_t* cur = S.s_cur[wv];
     if (w.scal[7] > w.pair_cap) return;   // the tile lists are incomplete: the gate stops the call
-    for (int64_t it = 0, tile; (tile = walk_tile(gd, it, w.n_tiles)) >= 0; ++it) {
-        if (w.tcount[tile] == 0) continue;   // no view overlaps the tile (block-uniform)
+    const uint32_t parts = (uint32_t)w.parts;
+    for (int64_t it = 0, at; (at = walk_tile(gd, it, w.n_tiles * parts)) >= 0; ++it) {
+        const int64_t tile = (uint32_t)at / parts;
+        const uint32_t part = (uint32_t)at % parts;
+        const uint32_t views_n = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
+        const uint32_t share = walk_share(views_n, parts);
+        const uint32_t j_lo = share * part < views_n ? share * part : views_n;
+        const uint32_t cnt = views_n - j_lo < share ? views_n - j_lo : share;
+        if (cnt == 0) continue;   // no view of the tile is this block's (block-uniform)
         const int64_t T0 = tile * TILE;
         const int64_t T1 = (T0 + TILE) < n ? (T0 + TILE) : n;
         stage_tile(case_s, act_s, ts_s, T0, T1, A, S);
-        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
-        const int64_t off = wave_lane((int64_t)w.toff[tile], 0);
+        const int64_t off = wave_lane((int64_t)w.toff[tile] + j_lo, 0);
         __syncthreads();
         // many views: one per wave, taken in turn (no barriers); few: shared,
         // NW at a time (block-uniform)
@@ -737,13 +763,19 @@ __device__ __forceinline__ void ph_write(Grid gd, const int32_t* __restrict__ ca
     auto& mask = S.s_mask[wv];
     uint32_t* cur = S.s_cur[wv];
     if (w.scal[12] != 0) return;   // a capacity is short: no record is written
-    for (int64_t it = 0, tile; (tile = walk_tile(gd, it, w.n_tiles)) >= 0; ++it) {
-        if (w.tcount[tile] == 0) continue;   // no view overlaps the tile (block-uniform)
+    const uint32_t parts = (uint32_t)w.parts;
+    for (int64_t it = 0, at; (at = walk_tile(gd, it, w.n_tiles * parts)) >= 0; ++it) {
+        const int64_t tile = (uint32_t)at / parts;
+        const uint32_t part = (uint32_t)at % parts;
+        const uint32_t views_n = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
+        const uint32_t share = walk_share(views_n, parts);
+        const uint32_t j_lo = share * part < views_n ? share * part : views_n;
+        const uint32_t cnt = views_n - j_lo < share ? views_n - j_lo : share;
+        if (cnt == 0) continue;   // no view of the tile is this block's (block-uniform)
         const int64_t T0 = tile * TILE;
         const int64_t T1 = (T0 + TILE) < n ? (T0 + TILE) : n;
         stage_tile(case_s, act_s, ts_s, T0, T1, A, S);
-        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.tcount[tile]);
-        const int64_t off = wave_lane((int64_t)w.toff[tile], 0);
+        const int64_t off = wave_lane((int64_t)w.toff[tile] + j_lo, 0);
         for (uint32_t j0 = 0; j0 < cnt; j0 += NW) {   // block-uniform
             const uint32_t j = j0 + wv;
             const int pairs = (int)(cnt - j0 < NW ? cnt - j0 : NW);
@@ -1647,7 +1679,8 @@ hipError_t launch_views_count(const pm4g_prepared* p, const pm4g_view* views, co
     ProfScope ps(P_VIEW_EMIT, s);
     const int64_t n = p->n_events;
     if (w.n_tiles > 0) {
-        const unsigned g = (unsigned)(w.n_tiles < grid ? w.n_tiles : grid);
+        const int64_t work = w.n_tiles * w.parts;
+        const unsigned g = (unsigned)(work < grid ? work : grid);
         auto go = [&](auto kernel, int waves) {
             kernel<<<g, (unsigned)(waves * kWave), 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views,
                                                            masks, w);
@@ -1667,7 +1700,8 @@ hipError_t launch_views_write(const pm4g_prepared* p, const pm4g_view* views, co
     ProfScope ps(P_VIEW_WRITE, s);
     const int64_t n = p->n_events;
     if (w.n_tiles > 0) {
-        const unsigned g = (unsigned)(w.n_tiles < grid ? w.n_tiles : grid);
+        const int64_t work = w.n_tiles * w.parts;
+        const unsigned g = (unsigned)(work < grid ? work : grid);
         auto go = [&](auto kernel, int waves) {
             kernel<<<g, (unsigned)(waves * kWave), 0, s>>>(p->case_s, p->act_s, p->ts_s, n, p->n_activities, views,
                                                            masks, w);

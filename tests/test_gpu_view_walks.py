@@ -38,3 +38,27 @@ def test_walks(A, V, tile, launch):
     note(f"view walks: A={A} V={V} tile={tile} launch={launch}")
     res = check_views(log, views, tuning=pm4g.BatchedTuning(tile_events=tile, launch=launch))
     assert res[0]["n_events"] == n
+
+
+@pytest.mark.parametrize("launch", [0, 1])
+@pytest.mark.parametrize("n,V", [(5000, 31), (5000, 32), (5000, 700), (200_000, 300), (1_050_000, 40)])
+def test_tiles_shared_by_blocks(n, V, launch):
+    """Few tiles under many views: several blocks per tile (2 to 257 tiles, below
+    and at the limits, a share cut short)."""
+    rng = np.random.default_rng(n + V)
+    A = 30
+    case = np.sort(rng.integers(0, n // 9 + 1, n)).astype(np.int32)
+    act = rng.integers(0, A, n).astype(np.int32)
+    ts = rng.integers(0, 10**6, n, dtype=np.int64)
+    log = synth.Log(case=case, act=act, ts=ts, n_activities=A, presorted=False,
+                    lengths_by_code=np.bincount(case))
+    top = int(case.max()) + 1
+    lo = rng.integers(0, max(1, top // 2), V).astype(np.int32)
+    hi = (lo + rng.integers(1, top, V)).astype(np.int32)
+    tl = rng.integers(0, 9 * 10**5, V)
+    th = tl + rng.integers(10**3, 10**5, V)
+    masks = rng.integers(0, 1 << 30, (V, 1)).astype(np.uint64)
+    views = synth.Views(case_lo=lo, case_hi=hi, t_lo=tl, t_hi=th, masks=masks)
+    note(f"shared tiles: N={n} V={V} launch={launch}")
+    sample = sorted({0, V - 1, *rng.integers(0, V, 25).tolist()})
+    check_views(log, views, tuning=pm4g.BatchedTuning(launch=launch), sample=sample)
