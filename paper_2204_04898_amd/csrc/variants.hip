@@ -73,12 +73,63 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     return z ^ (z >> 31);
 }
 
+// Equal sequences?  By one lane; a step's loads are in flight together (at the
+// end clamped to the last event).
 __device__ bool same_seq(const int32_t* act_s, const int64_t* case_off, uint32_t a, uint32_t b) {
-    const int64_t a0 = case_off[a], a1 = case_off[a + 1];
-    const int64_t b0 = case_off[b], b1 = case_off[b + 1];
-    if (a1 - a0 != b1 - b0) return false;
-    for (int64_t k = 0; k < a1 - a0; ++k)
-        if (act_s[a0 + k] != act_s[b0 + k]) return false;
+    const int64_t a0 = case_off[a], n = case_off[a + 1] - a0;
+    const int64_t b0 = case_off[b];
+    if (n != case_off[b + 1] - b0) return false;
+    const int32_t *pa = act_s + a0, *pb = act_s + b0;
+    constexpr int kU = 6, kT = 4;
+    int64_t k = 0;
+    for (; k + kU <= n; k += kU) {
+        int32_t x[kU], y[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            x[u] = pa[k + u];
+            y[u] = pb[k + u];
+        }
+        int32_t diff = 0;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) diff |= x[u] ^ y[u];
+        if (diff) return false;
+    }
+    for (; k < n; k += kT) {
+        int32_t x[kT], y[kT], diff = 0;
+#pragma unroll
+        for (int u = 0; u < kT; ++u) {
+            const int64_t i = k + u < n ? k + u : n - 1;
+            x[u] = pa[i];
+            y[u] = pb[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kT; ++u) diff |= x[u] ^ y[u];
+        if (diff) return false;
+    }
+    return true;
+}
+
+// By a wave (a and b the same in every lane), for sequences of kLongSeq events
+// or more: one lane's steps would follow each other.
+constexpr int64_t kLongSeq = 128;
+__device__ bool same_long_seq(const int32_t* act_s, const int64_t* case_off, uint32_t a, uint32_t b) {
+    const int64_t a0 = case_off[a], n = case_off[a + 1] - a0;
+    const int64_t b0 = case_off[b];
+    if (n != case_off[b + 1] - b0) return false;
+    constexpr int kU = 4;
+    for (int64_t k = 0; k < n; k += kU * kWave) {
+        int32_t x[kU], y[kU], diff = 0;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = k + u * kWave + lane();
+            const int64_t ic = i < n ? i : n - 1;
+            x[u] = act_s[a0 + ic];
+            y[u] = act_s[b0 + ic];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) diff |= x[u] ^ y[u];
+        if (__ballot(diff != 0) != 0) return false;
+    }
     return true;
 }
 
@@ -113,27 +164,46 @@ __device__ __forceinline__ int seg_of(int64_t vstart, int64_t p) {
     return lo;
 }
 
-// The table slot of case c's sequence (hash h): the case that claimed it, c
-// itself if it is the first.  A slot is read without a device-scope access
-// first: a claim never changes, so a stale read can only show it empty, and
-// the compare-and-swap then tells.
-__device__ __forceinline__ uint32_t enter(uint64_t* claim, int64_t slots, uint64_t h, uint32_t c,
+// The table slot of each entering lane's case c (hash h, len events): the case
+// that claimed it, c itself if it is the first.  A slot is read without a
+// device-scope access first: a claim never changes, so a stale read can only
+// show it empty, and the compare-and-swap then tells.  Every lane of the wave
+// must execute it.
+__device__ __forceinline__ uint32_t enter(bool open, uint64_t* claim, int64_t slots, uint64_t h, uint32_t c, int64_t len,
                                           const int32_t* act_s, const int64_t* case_off) {
     const uint64_t mine = (h << 32) | (uint64_t)(c + 1u);
     uint64_t p = __umul64hi(h, (uint64_t)slots);
-    for (;;) {   // ends: the table has twice as many slots as cases
-        uint64_t cur = __hip_atomic_load(&claim[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        if (cur == 0) {
-            uint64_t want = 0;
-            if (__hip_atomic_compare_exchange_strong(&claim[p], &want, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT))
-                return c;
-            cur = want;
+    uint32_t lead = c;
+    while (__ballot(open) != 0) {   // ends: the table has twice as many slots as cases
+        bool meets = false, same = false;
+        if (open) {
+            uint64_t cur = __hip_atomic_load(&claim[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            if (cur == 0) {
+                uint64_t want = 0;
+                if (__hip_atomic_compare_exchange_strong(&claim[p], &want, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT))
+                    open = false;   // lead is c
+                else
+                    cur = want;
+            }
+            if (open) {
+                lead = (uint32_t)cur - 1u;
+                meets = (uint32_t)(cur >> 32) == (uint32_t)h;
+            }
         }
-        const uint32_t lead = (uint32_t)cur - 1u;
-        if ((uint32_t)(cur >> 32) == (uint32_t)h && same_seq(act_s, case_off, c, lead)) return lead;
-        p = p + 1 == (uint64_t)slots ? 0 : p + 1;
+        for (uint64_t m = __ballot(meets && len >= kLongSeq); m != 0; m &= m - 1) {   // wave-uniform
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const bool eq = same_long_seq(act_s, case_off, wave_lane(c, l), wave_lane(lead, l));
+            if (lane() == l) same = eq;
+        }
+        if (meets && len < kLongSeq) same = same_seq(act_s, case_off, c, lead);
+        if (same) open = false;
+        if (open) {
+            lead = c;
+            p = p + 1 == (uint64_t)slots ? 0 : p + 1;
+        }
     }
+    return lead;
 }
 
 // Sequence hash of every case, and its variant's slot.  The hash is a sum over
@@ -145,24 +215,26 @@ __device__ __forceinline__ uint32_t enter(uint64_t* claim, int64_t slots, uint64
 // additions, not one per event).
 // Then the wave's equal hashes meet in a 128-slot LDS table, one lane of each
 // enters the global table for all of them, and the further members of a
-// variant are counted in a block-wide LDS cache by claiming case, written out
-// at the end: a variant that holds a third of the cases costs a global atomic
-// per block, not one per case (they queue on one address at about 8 ns each).
+// variant and its smallest one are kept in a block-wide LDS cache by claiming
+// case, written out at the end: a variant that holds a third of the cases costs
+// two global atomics per block, not per case (they queue on one address at
+// about 8 ns each: with an atomic for every case below its claiming one, a call
+// on 200,000 equal cases of 50 events took 520 to 790 us, so 95).
 // Bound by the latency of the scattered claims (a hash of a seventh of the
 // multiplies made no difference): 0.39 ms on 5M cases of 99M events (0.45 with
 // a part-filled last wave of blocks; sorting by hash and regrouping took 0.80
 // ms after the hash).
 constexpr int kHashWin = 1024;
 constexpr int kMeet = 2 * kWave;   // LDS slots for a wave's hashes
-constexpr int kMore = 512;         // cached member counts per block
+constexpr int kMore = 512;         // claiming cases cached per block
 constexpr int kGroupGrid = 1280;   // five blocks per CU, what its LDS holds: with 2048 the last 768 ran alone
 __global__ __launch_bounds__(kBlk) void k_var_group(const int32_t* __restrict__ act_s,
                                                     const int64_t* __restrict__ case_off, VarWs w,
                                                     uint64_t mask, int64_t n) {
     __shared__ uint32_t meet[kBlk / kWave][kMeet];       // lane + 1 of a hash's first lane
-    __shared__ uint32_t members[kBlk / kWave][kWave];    // its lanes
+    __shared__ unsigned long long members[kBlk / kWave][kWave];   // its lanes, a bit each
     __shared__ uint32_t lead_of[kBlk / kWave][kWave];    // its claiming case
-    __shared__ uint32_t mtag[kMore], mcnt[kMore];        // claiming case + 1, further members
+    __shared__ uint32_t mtag[kMore], mcnt[kMore], mlow[kMore];   // claiming case + 1, further members, smallest member
     __shared__ unsigned long long hsum[kBlk / kWave][kWave];
     __shared__ int64_t sst[kBlk / kWave][kWave + 1];
     __shared__ int32_t sact[kBlk / kWave][kHashWin];
@@ -171,13 +243,21 @@ __global__ __launch_bounds__(kBlk) void k_var_group(const int32_t* __restrict__ 
     const int64_t wv = ((int64_t)blockIdx.x * kBlk + threadIdx.x) / kWave;
     const int64_t nw = (int64_t)gridDim.x * kBlk / kWave;
     const bool aligned = (reinterpret_cast<uintptr_t>(act_s) & 15) == 0;
-    for (int i = threadIdx.x; i < kMore; i += kBlk) mtag[i] = mcnt[i] = 0;
+    for (int i = threadIdx.x; i < kMore; i += kBlk) {
+        mtag[i] = mcnt[i] = 0;
+        mlow[i] = 0xFFFFFFFFu;
+    }
     __syncthreads();
-    auto more = [&](uint32_t lead, uint32_t k) {
+    auto more = [&](uint32_t lead, uint32_t k, uint32_t low) {
         const uint32_t at = (lead * 0x9E3779B1u) >> 23;   // 9 bits: kMore
         const uint32_t old = atomicCAS(&mtag[at], 0u, lead + 1u);
-        if (old == 0u || old == lead + 1u) atomicAdd(&mcnt[at], k);
-        else atomicAdd(&w.repflag[lead], k);
+        if (old == 0u || old == lead + 1u) {
+            atomicAdd(&mcnt[at], k);
+            atomicMin(&mlow[at], low);
+        } else {
+            if (k) atomicAdd(&w.repflag[lead], k);
+            if (low < lead) atomicMin(&w.rrank[lead], low);
+        }
     };
     constexpr int kPer = kHashWin / kWave;   // 16 events per lane and window
     for (int64_t c0 = wv * kWave; c0 < C; c0 += nw * kWave) {
@@ -260,25 +340,26 @@ __global__ __launch_bounds__(kBlk) void k_var_group(const int32_t* __restrict__ 
             }
             // one hash, another sequence: the lane enters the table by itself
             if (first != lane() && !same_seq(act_s, case_off, (uint32_t)c, (uint32_t)(c0 + first))) first = lane();
-            atomicAdd(&members[wl][first], 1u);
+            atomicOr(&members[wl][first], 1ull << lane());
         }
         wave_sync();
-        if (has && first == lane()) {
-            const uint32_t lead = enter(w.hash, var_slots(C), h, (uint32_t)c, act_s, case_off);
+        const bool enters = has && first == lane();
+        const uint32_t lead = enter(enters, w.hash, var_slots(C), h, (uint32_t)c, en - st, act_s, case_off);
+        if (enters) {
             lead_of[wl][lane()] = lead;
-            const uint32_t k = members[wl][lane()] - (lead == (uint32_t)c ? 1u : 0u);
-            if (k) more(lead, k);
+            const uint64_t m = members[wl][lane()];
+            const uint32_t k = (uint32_t)__popcll(m) - (lead == (uint32_t)c ? 1u : 0u);
+            const uint32_t low = (uint32_t)c0 + (uint32_t)__builtin_ctzll(m);
+            if (k || low < lead) more(lead, k, low);
         }
         wave_sync();
-        if (has) {
-            const uint32_t lead = lead_of[wl][first];
-            w.cvar[c] = lead;
-            if ((uint32_t)c < lead) atomicMin(&w.rrank[lead], (uint32_t)c);
-        }
+        if (has) w.cvar[c] = lead_of[wl][first];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kMore; i += kBlk)
+    for (int i = threadIdx.x; i < kMore; i += kBlk) {
         if (mcnt[i]) atomicAdd(&w.repflag[mtag[i] - 1u], mcnt[i]);
+        if (mtag[i] && mlow[i] < mtag[i] - 1u) atomicMin(&w.rrank[mtag[i] - 1u], mlow[i]);
+    }
 }
 
 // Representative of every case (w.idx), and the count of a representative's
