@@ -918,9 +918,15 @@ hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t
         }
         ProfScope p(P_DFG_REDUCE, s);
         // many buckets hold one slot or two each: a thread per cell; few buckets
-        // share up to 512 slots, the frequent ones half of them
+        // share up to 512 slots, the frequent ones half of them: 16 threads per
+        // cell; in between eight, so that a block has twice the cells (a call on
+        // 100,000 events of 1000 activities, 245 buckets: 117 us with 16, 85 with
+        // eight, 73 with one; on 20M events of Zipf activities 329, 296 and 356.
+        // 65 activities, 20M such events, two buckets: 296, 303 and 431)
         if (nbk > 256)
             k_dfg_reduce<256, 1><<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(A, 0, ws, status_in, out);
+        else if (nbk > 32)
+            k_dfg_reduce<32, 8><<<(unsigned)((cells + 31) / 32), 256, 0, s>>>(A, 0, ws, status_in, out);
         else
             k_dfg_reduce<16, 16><<<(unsigned)((cells + 15) / 16), 256, 0, s>>>(A, 0, ws, status_in, out);
         k_dfg_acts<<<(unsigned)((A + kActs - 1) / kActs + 1), kAT, 0, s>>>(A, (int32_t)g, (int32_t)g, ws, status_in, out);
