@@ -173,8 +173,10 @@ int bits_of(uint64_t range) {
 // second answer is almost always no, so `after` is queued before it is known
 // and the GPU goes on; if it is yes, the fallback sorts again and `after` runs
 // again on its result.  Until then the arrays may hold anything where the sort
-// left windows out: the case table is empty in that case (launch_case_table) and
-// the DFG's kernels check every activity they index with.
+// left windows out: the case table is empty in that case (launch_case_table),
+// and `after` is given a device word that is then not zero, so that the first
+// run finds nothing to do (2M events of one case, 500 activities: 616 us with a
+// DFG of what the sort left, 560 without).
 template <class After>
 int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& bp, hipStream_t s, bool ws_rows,
                 bool own, const After& after) {
@@ -212,11 +214,11 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
         }
         PM4G_HIP(table(nullptr));
         if (back.live()) {
-            if (int rc = after()) return rc;
+            if (int rc = after(nullptr)) return rc;
             return status();
         }
         if (int rc = status()) return rc;   // copied from the workspace, which `after` may use again
-        return after();
+        return after(nullptr);
     }
     if (int rc = status()) return rc;
     const SortBufs raw{(uint32_t*)log->case_id, (int64_t*)log->timestamp, (uint32_t*)log->activity, nullptr};
@@ -237,12 +239,14 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     }
     PM4G_HIP(launch_segsort(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, w.wincnt, row_s, s));
     const bool may_be_long = n > kSegCap;   // a log that fits one window has no longer case
-    // the header goes to the host from the case table's first kernel, if there is one
-    if (may_be_long && !case_table) PM4G_HIP(launch_publish(w.info, back.dst(), s));
+    // the header goes to the host from the case table's first kernel, if there is
+    // one (else out->n_cases is free: the word for `after`)
+    const int64_t* skip = may_be_long && !case_table ? out->n_cases : nullptr;
+    if (skip) PM4G_HIP(launch_publish(w.info, back.dst(), out->n_cases, s));
     PM4G_HIP(may_be_long && case_table ? table(w.wincnt, back.dst()) : table(w.wincnt));
     if (may_be_long && !back.live()) PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
     if (!h.long_case) {
-        if (int rc = after()) return rc;
+        if (int rc = after(skip)) return rc;
         if (!may_be_long || !back.live()) return PM4G_OK;
         PM4G_HIP(back.wait(w.info, reinterpret_cast<int64_t*>(&h), kInfoWords, s));
         if (!h.long_case) return PM4G_OK;
@@ -251,8 +255,7 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     // `after` may use the sort's workspace again (the raw-log entry points do):
     // it is done before the passes, in stream order, but the header has to be
     // put back.
-    PM4G_HIP(launch_range_scan(log->case_id, log->activity, log->timestamp, n, A, false, w.info, w.rpart, w.hist_raw,
-                               out->status, BackDst{nullptr, nullptr, 0}, s));
+    PM4G_HIP(launch_put_info(h, w.info, s));
     PM4G_HIP(launch_ts_range(log->timestamp, n, w.info, s));
     PM4G_HIP(hipMemcpyAsync(&h, w.info, sizeof(h), hipMemcpyDeviceToHost, s));
     PM4G_HIP(hipStreamSynchronize(s));
@@ -274,7 +277,7 @@ int run_prepare(const pm4g_log* log, pm4g_prepared* out, bool case_table, Bump& 
     }
     PM4G_HIP(launch_unbias_copy(in, n, w.info, out->case_s, out->act_s, out->ts_s, act_shift, row_s, s));
     PM4G_HIP(table(nullptr));
-    return after();
+    return after(nullptr);
 }
 
 // Library-owned workspace of pm4g_dfg_prepared_noalloc: one copy per GPU,
@@ -837,7 +840,8 @@ int pm4g_prepare(const pm4g_log* log, const pm4g_prepared* out, void* ws, size_t
     }
     Bump bp(ws);
     pm4g_prepared p = *out;
-    return run_prepare(log, &p, true, bp, (hipStream_t)stream, true, false, [] { return (int)PM4G_OK; });
+    return run_prepare(log, &p, true, bp, (hipStream_t)stream, true, false,
+                       [](const int64_t*) { return (int)PM4G_OK; });
 }
 
 int pm4g_dfg_prepared(const pm4g_prepared* log, const pm4g_dfg_out* out, void* ws, size_t ws_size,
@@ -895,10 +899,11 @@ int pm4g_dfg(const pm4g_log* log, const pm4g_dfg_out* out, void* ws, size_t ws_s
     pm4g_prepared p = prepared_in_ws(bp, log->n_events, log->n_activities);
     const size_t rest = bp.off;
     Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-    const int rc = run_prepare(log, &p, false, b2, s, false, true, [&]() -> int {
+    const int rc = run_prepare(log, &p, false, b2, s, false, true, [&](const int64_t* skip) -> int {
         Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
         DfgWs w = dfg_ws_layout(b3, log->n_events, log->n_activities);
-        PM4G_HIP(launch_dfg(p.case_s, p.act_s, p.ts_s, p.n_events, p.n_activities, p.status, w, dev_out(out), s));
+        PM4G_HIP(launch_dfg(p.case_s, p.act_s, p.ts_s, p.n_events, p.n_activities, p.status, w, dev_out(out), s,
+                            skip));
         return PM4G_OK;
     });
     return raw_status(rc, out->status, s);
@@ -937,7 +942,7 @@ int pm4g_variants(const pm4g_log* log, const pm4g_variants_out* out, void* ws, s
     pm4g_prepared p = prepared_in_ws(bp, log->n_events, log->n_activities);
     const size_t rest = bp.off;
     Bump b2(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
-    const int rc = run_prepare(log, &p, true, b2, s, false, true, [&]() -> int {
+    const int rc = run_prepare(log, &p, true, b2, s, false, true, [&](const int64_t*) -> int {   // (no cases: nothing to do)
         Bump b3(static_cast<char*>(ws) + ((rest + 255) & ~size_t(255)));
         VarWs w = var_ws_layout(b3, log->n_events);
         const VarOutDev o{out->n_variants, out->var_count, out->var_len, out->var_rep,

@@ -232,7 +232,9 @@ constexpr uint64_t kBadSpan = ~0ull;
 __global__ __launch_bounds__(kLB) void k_dfg_lds(const int32_t* __restrict__ case_s,
                                                  const int32_t* __restrict__ act_s,
                                                  const int64_t* __restrict__ ts_s, int64_t n, int32_t A, int clog,
-                                                 DfgWs ws, const int32_t* status_in, DfgOutDev out) {
+                                                 DfgWs ws, const int32_t* status_in, DfgOutDev out,
+                                                 const int64_t* skip) {
+    if (skip && *skip) n = 0;
     __shared__ uint32_t scount[kCellsPerTable];
     __shared__ uint64_t ssum[kCellsPerTable];
     __shared__ alignas(16) int64_t smm[2 * kCellsPerTable];
@@ -373,7 +375,8 @@ constexpr int kCB = 512;                  // threads of k_dfg_count / k_dfg_scat
 __global__ __launch_bounds__(kCB) void k_dfg_count(const int32_t* __restrict__ case_s,
                                                    const int32_t* __restrict__ act_s, int64_t n,
                                                    int32_t A, int64_t nbk, int64_t nch, int64_t chunk,
-                                                   DfgWs ws) {
+                                                   DfgWs ws, const int64_t* skip) {
+    if (skip && *skip) n = 0;
     extern __shared__ uint32_t dsm[];
     uint32_t* sstart = dsm;
     uint32_t* bcnt = dsm + A;
@@ -435,7 +438,9 @@ __global__ __launch_bounds__(kCB) void k_dfg_count(const int32_t* __restrict__ c
 __global__ __launch_bounds__(kCB) void k_dfg_scatter(const int32_t* __restrict__ case_s,
                                                      const int32_t* __restrict__ act_s,
                                                      const int64_t* __restrict__ ts_s, int64_t n, int32_t A,
-                                                     int64_t nbk, int64_t nch, int64_t chunk, DfgWs ws) {
+                                                     int64_t nbk, int64_t nch, int64_t chunk, DfgWs ws,
+                                                     const int64_t* skip) {
+    if (skip && *skip) n = 0;
     extern __shared__ uint32_t dsm[];
     uint32_t* cur = dsm;              // global cursor of each bucket
     uint32_t* lcnt = dsm + nbk;       // edges per bucket in this tile
@@ -858,8 +863,8 @@ __global__ __launch_bounds__(kWave) void k_dfg_direct(const int32_t* __restrict_
     }
 }
 
-hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t* ts_s, int64_t n,
-                      int32_t A, const int32_t* status_in, DfgWs ws, DfgOutDev out, hipStream_t s) {
+hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t* ts_s, int64_t n, int32_t A,
+                      const int32_t* status_in, DfgWs ws, DfgOutDev out, hipStream_t s, const int64_t* skip) {
     const int64_t cells = (int64_t)A * A;
     if (A <= kDfgLdsMaxA) {
         // one tile per block until every block has one; up to two tiles are one
@@ -874,7 +879,7 @@ hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t
         while (clog < cmax && (cells << (clog + 1)) <= kCellsPerTable) ++clog;
         {
             ProfScope p(P_DFG_MAIN, s);
-            k_dfg_lds<<<(unsigned)g, kLB, 0, s>>>(case_s, act_s, ts_s, n, A, clog, ws, status_in, out);
+            k_dfg_lds<<<(unsigned)g, kLB, 0, s>>>(case_s, act_s, ts_s, n, A, clog, ws, status_in, out, skip);
         }
         if (g > 1) {
             ProfScope p(P_DFG_REDUCE, s);
@@ -898,13 +903,14 @@ hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t
         const unsigned g = (unsigned)ws.n_act_blocks;
         {
             ProfScope p(P_DFG_COUNT, s);
-            k_dfg_count<<<g, kCB, (size_t)(A + nbk) * sizeof(uint32_t), s>>>(case_s, act_s, n, A, nbk, nch, chunk, ws);
+            k_dfg_count<<<g, kCB, (size_t)(A + nbk) * sizeof(uint32_t), s>>>(case_s, act_s, n, A, nbk, nch, chunk, ws,
+                                                                             skip);
             dev::excl_scan<uint32_t>(ws.ecnt, &ws.scal[0], ws.escan, ws.part32, ws.utotal, s);
         }
         {
             ProfScope p(P_DFG_MAIN, s);
             k_dfg_scatter<<<g, kCB, (size_t)3 * nbk * sizeof(uint32_t), s>>>(case_s, act_s, ts_s, n, A, nbk,
-                                                                           nch, chunk, ws);
+                                                                           nch, chunk, ws, skip);
         }
         {
             ProfScope p(P_DFG_PLAN, s);

@@ -57,8 +57,10 @@ static_assert(kInfoWords <= kBackWords, "the header fits a slot");
 hipError_t launch_range_scan(const int32_t* case_id, const int32_t* act, const int64_t* ts, int64_t n,
                              int32_t A, bool presorted, RangeInfo* info, RangePart* part,
                              uint32_t* hist_raw, int32_t* status, BackDst back, hipStream_t s);
-// The header to the host, once the stream gets here.
-hipError_t launch_publish(const RangeInfo* info, BackDst back, hipStream_t s);
+// The header to the host, once the stream gets here, and its long_case to *skip.
+hipError_t launch_publish(const RangeInfo* info, BackDst back, int64_t* skip, hipStream_t s);
+// The header as the host has it.
+hipError_t launch_put_info(const RangeInfo& h, RangeInfo* info, hipStream_t s);
 hipError_t launch_ts_range(const int64_t* ts, int64_t n, RangeInfo* info, hipStream_t s);
 
 // ---- LSD radix passes over (case key u32, ts i64, act u32) elements (radix.hip) ----
@@ -181,9 +183,10 @@ struct DfgOutDev {
     int32_t* status;
 };
 // n_cases is the number of case starts seen; status_in (may be NULL) is the
-// producing prepare's status word, propagated to out.status.
-hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t* ts_s, int64_t n,
-                      int32_t A, const int32_t* status_in, DfgWs ws, DfgOutDev out, hipStream_t s);
+// producing prepare's status word, propagated to out.status; skip (may be NULL):
+// a word that, if not zero, says the log holds nothing yet: no event is read.
+hipError_t launch_dfg(const int32_t* case_s, const int32_t* act_s, const int64_t* ts_s, int64_t n, int32_t A,
+                      const int32_t* status_in, DfgWs ws, DfgOutDev out, hipStream_t s, const int64_t* skip = nullptr);
 
 // ---- variants (variants.hip) ----
 struct VarWs {

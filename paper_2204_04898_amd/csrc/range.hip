@@ -193,12 +193,20 @@ __global__ __launch_bounds__(256) void k_ts_range(const int64_t* __restrict__ ts
     }
 }
 
-__global__ void k_publish(const RangeInfo* info, BackDst back) {
+__global__ void k_publish(const RangeInfo* info, BackDst back, int64_t* skip) {
+    *skip = info->long_case;
     publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
 }
 
-hipError_t launch_publish(const RangeInfo* info, BackDst back, hipStream_t s) {
-    if (back.words) k_publish<<<1, 1, 0, s>>>(info, back);
+hipError_t launch_publish(const RangeInfo* info, BackDst back, int64_t* skip, hipStream_t s) {
+    k_publish<<<1, 1, 0, s>>>(info, back, skip);
+    return hipGetLastError();
+}
+
+__global__ void k_put_info(RangeInfo h, RangeInfo* info) { *info = h; }
+
+hipError_t launch_put_info(const RangeInfo& h, RangeInfo* info, hipStream_t s) {
+    k_put_info<<<1, 1, 0, s>>>(h, info);
     return hipGetLastError();
 }
 
