@@ -67,7 +67,17 @@ class _BatchedOut(ctypes.Structure):
 
 
 class BatchedTuning(ctypes.Structure):
-    """Launch shape and capacities of pm4g_dfg_batched (zero fields: library defaults)."""
+    """Launch shape and capacities of pm4g_dfg_batched (zero fields: library
+    defaults).  `launch` 0 is a mode of its own (the persistent launch): a
+    tuning that is given a launch, 0 or 1, keeps it; one that is not leaves the
+    choice to the call."""
+
+    launch_given = False
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        if name == "launch":
+            self.__dict__["launch_given"] = True
 
     _fields_ = [("tile_events", ctypes.c_int32), ("emit_blocks", ctypes.c_int32),
                 ("agg_blocks", ctypes.c_int32), ("launch", ctypes.c_int32),
@@ -495,6 +505,25 @@ def _batched_struct(o: dict) -> _BatchedOut:
                        o["cap_edges"], _ptr(o["required"]), _ptr(o["status"]))
 
 
+def _launch_shape(tuning: BatchedTuning | None, A: int, n_views: int, n_events: int) -> BatchedTuning:
+    """A copy of the tuning with its launch shape, if it has none, from the
+    autotune cache; its capacities and a launch it was given stay."""
+    t = BatchedTuning() if tuning is None else BatchedTuning.from_buffer_copy(tuning)
+    if t.tile_events == 0 and t.emit_blocks == 0 and t.agg_blocks == 0 and t.launch == 0:
+        from . import tune
+        hit = tune.default_cache().lookup(A, n_views, n_events)
+        if hit is not None:
+            t.tile_events = int(hit["tile_events"])
+            t.emit_blocks = int(hit["emit_blocks"])
+            t.agg_blocks = int(hit["agg_blocks"])
+        if tuning is None or not tuning.launch_given:
+            # not tuned: one launch per phase, faster than the persistent launch
+            # (whose grid barriers take longer than launches): 123 us against 210
+            # with 1 view of 50k events, 252 against 368 with 200 views of 2M
+            t.launch = int(hit.get("launch", 1)) if hit is not None else 1
+    return t
+
+
 @_on_stream
 def pm4g_dfg_batched(prep: Prepared, views: torch.Tensor, masks: torch.Tensor, n_views: int,
                      tuning: BatchedTuning | None = None, cap_edges: int | None = None,
@@ -503,8 +532,8 @@ def pm4g_dfg_batched(prep: Prepared, views: torch.Tensor, masks: torch.Tensor, n
     """DFGs of n_views drill-down views in one pass (Sec. 1 drill-down, Sec. 3 filters).
 
     views: device uint8 tensor of n_views packed pm4g_view records; masks: device
-    int64 tensor [n_views, ceil(A/64)].  With no `tuning`, the launch shape
-    comes from the autotune cache (tune.py).  The library call does not wait;
+    int64 tensor [n_views, ceil(A/64)].  With no launch shape in `tuning`, it
+    comes from the autotune cache (tune.py) or is one launch per phase.  The library call does not wait;
     this wrapper synchronises the stream once to read the device status.  With
     `retry`, capacities found too small are raised to what the call reported
     and the call is repeated.  keep_workspace=False allocates the workspace for
@@ -513,21 +542,7 @@ def pm4g_dfg_batched(prep: Prepared, views: torch.Tensor, masks: torch.Tensor, n
     L = load()
     A = prep.n_activities
     dev = prep.case_s.device
-    t = BatchedTuning() if tuning is None else BatchedTuning.from_buffer_copy(tuning)
-    if t.tile_events == 0 and t.emit_blocks == 0 and t.agg_blocks == 0 and t.launch == 0:
-        # launch shape from the autotune cache (capacities: the tuning's or the library's)
-        from . import tune
-        hit = tune.default_cache().lookup(A, n_views, prep.n_events)
-        if hit is not None:
-            t.tile_events = int(hit["tile_events"])
-            t.emit_blocks = int(hit["emit_blocks"])
-            t.agg_blocks = int(hit["agg_blocks"])
-            t.launch = int(hit.get("launch", 1))
-        else:
-            # not tuned: one launch per phase, faster than the persistent launch
-            # (whose grid barriers take longer than launches): 123 us against 210
-            # with 1 view of 50k events, 252 against 368 with 200 views of 2M
-            t.launch = 1
+    t = _launch_shape(tuning, A, n_views, prep.n_events)
     # output cells: at most A*A per view and one per kept event
     cap = int(cap_edges) if cap_edges is not None else \
         max(1024, min(int(n_views) * A * A, prep.n_events, 1 << 24))
