@@ -1487,15 +1487,21 @@ __global__ __launch_bounds__(256) void k_view_out(int32_t V, int32_t A, ViewWs w
 // for that.  Tags are unique per call, so words left in the workspace by
 // earlier calls never match.  The release fence before the arrival and the
 // acquire fence after the wait make each phase's writes visible to the next
-// phase on every XCD.  A wait is bounded: past kBarrierPolls polls (seconds,
+// phase on every XCD; the waits beside them are explicit, for every wave's
+// stores before the block announces itself, and for the write-back of the L2
+// that the release fence starts (the compiler leaves that one out where the wave
+// itself has nothing outstanding).  A wait is bounded: past kBarrierPolls polls (seconds,
 // far beyond any phase) the call's status becomes PM4G_E_DEVICE and the
 // block goes on, so a broken schedule ends the call instead of hanging it.
 constexpr int64_t kBarrierPolls = int64_t(1) << 22;
 
 __device__ void grid_barrier(Grid gd, uint64_t* bar, uint64_t tag, int32_t* status) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x < kWave) {
         __threadfence();
+        __builtin_amdgcn_s_waitcnt(0);
         if (lane() == 0) __hip_atomic_store(&bar[gd.bid], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bool late = false;
         if (gd.bid == 0) {
@@ -1514,6 +1520,7 @@ __device__ void grid_barrier(Grid gd, uint64_t* bar, uint64_t tag, int32_t* stat
                 }
             }
             __threadfence();
+            __builtin_amdgcn_s_waitcnt(0);
             if (lane() == 0) __hip_atomic_store(&bar[kViewMaxBlocks], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (lane() == 0) {
             int64_t polls = 0;
@@ -1527,6 +1534,7 @@ __device__ void grid_barrier(Grid gd, uint64_t* bar, uint64_t tag, int32_t* stat
         }
         if (late && lane() == 0) set_status(status, PM4G_E_DEVICE);
         __threadfence();
+        __builtin_amdgcn_s_waitcnt(0);   // the stale lines are gone before the block's other waves read
     }
     __syncthreads();
 }
