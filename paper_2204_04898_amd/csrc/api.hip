@@ -105,7 +105,7 @@ PrepWs pm4g::prep_ws_layout(Bump& bp, int64_t n, bool with_rows) {
     w.b.act = bp.take<uint32_t>(m);
     w.a.row = with_rows ? bp.take<uint32_t>(m) : nullptr;
     w.b.row = with_rows ? bp.take<uint32_t>(m) : nullptr;
-    w.hist = bp.take<uint32_t>(radix_digits(n) * (size_t)(radix_blocks(n) + 1));
+    w.hist = bp.take<uint32_t>(radix_hist_words(n));
     w.hist_raw = bp.take<uint32_t>(256 * (size_t)(radix_blocks(n) + 1));
     w.rowsum = bp.take<uint32_t>(size_t(1) << kRadixMaxBits);
     w.caseblk = bp.take<uint32_t>((size_t)case_blocks(n) + 1);

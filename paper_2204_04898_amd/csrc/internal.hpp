@@ -99,8 +99,12 @@ inline int64_t radix_blocks(int64_t n) { return (n + kRadixTile - 1) / kRadixTil
 constexpr int kRadixMaxBits = 10;      // widest digit among few tiles,
 constexpr int kRadixManyBits = 9;      // and among many
 constexpr int64_t kRadixFewTiles = 64;
-inline size_t radix_digits(int64_t n) {
-    return size_t(1) << (radix_blocks(n) <= kRadixFewTiles ? kRadixMaxBits : kRadixManyBits);
+// Words of the digit histograms: a row of tiles (and one more) per digit, the
+// few tiles' wide rows in any case, so that a larger log never needs less.
+inline size_t radix_hist_words(int64_t n) {
+    const size_t nb = (size_t)radix_blocks(n), few = nb < (size_t)kRadixFewTiles ? nb : (size_t)kRadixFewTiles;
+    const size_t wide = (few + 1) << kRadixMaxBits, many = (nb + 1) << kRadixManyBits;
+    return wide > many ? wide : many;
 }
 int radix_plan(int bits, int64_t n, int width[4]);   // passes over `bits` bits, their widths
 hipError_t launch_radix_pass(SortBufs in, SortBufs out, int64_t n, int digit_src, int shift, int width,
