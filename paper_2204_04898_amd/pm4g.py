@@ -275,8 +275,13 @@ def _cols(case, act, ts):
         raise ValueError("case, act and ts differ in length")
 
 
-def _log(case, act, ts, A: int, presorted: bool) -> _Log:
+def _log(case, act, ts, A: int, presorted: bool, stream=None) -> _Log:
+    """The raw log's struct; its columns outlive the call's work on `stream` (the
+    kernels that read them may still run when the call returns)."""
     _cols(case, act, ts)
+    if stream is not None:
+        for t in (case, act, ts):
+            t.record_stream(stream)
     return _Log(_ptr(case), _ptr(act), _ptr(ts), case.numel(), int(A), PM4G_PRESORTED if presorted else 0)
 
 
@@ -321,7 +326,7 @@ def pm4g_prepare(case, act, ts, A: int, presorted: bool = False, out: Prepared |
                  rows: bool = False, stream=None) -> Prepared:
     """Formats a raw log on the GPU (order, per-case table; with `rows`, also
     the raw row of each position).  Synchronises the stream."""
-    log = _log(case, act, ts, A, presorted)
+    log = _log(case, act, ts, A, presorted, stream)
     if out is None:
         out = Prepared.empty(case.numel(), A, case.device, rows=rows)
     ws, need = workspace(OP_PREPARE, case.numel(), A, case.device, stream)
@@ -356,7 +361,7 @@ def _dfg_struct(o: dict) -> _DfgOut:
 def pm4g_dfg(case, act, ts, A: int, presorted: bool = False, out: dict | None = None,
              stream=None) -> dict:
     """DFG of a raw log (formats it in the workspace first).  Synchronises once or twice."""
-    log = _log(case, act, ts, A, presorted)
+    log = _log(case, act, ts, A, presorted, stream)
     o = out if out is not None else _dfg_out(A, case.device)
     ws, need = workspace(OP_DFG, case.numel(), A, case.device, stream)
     s = _dfg_struct(o)
@@ -410,7 +415,7 @@ def _var_struct(o: dict) -> _VarOut:
 def pm4g_variants(case, act, ts, A: int, presorted: bool = False, out: dict | None = None,
                   stream=None) -> dict:
     """Trace variants of a raw log.  Synchronises once or twice."""
-    log = _log(case, act, ts, A, presorted)
+    log = _log(case, act, ts, A, presorted, stream)
     o = out if out is not None else _var_out(case.numel(), case.device)
     ws, need = workspace(OP_VARIANTS, case.numel(), A, case.device, stream)
     s = _var_struct(o)
