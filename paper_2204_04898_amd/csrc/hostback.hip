@@ -19,7 +19,6 @@ constexpr int kSlots = 64;
 
 std::mutex g_mu;
 Slot* g_page = nullptr;
-bool g_failed = false;
 uint64_t g_used = 0;   // bit per slot
 uint64_t g_seq = 0;
 
@@ -27,15 +26,16 @@ uint64_t g_seq = 0;
 
 HostBack::HostBack() {
     std::lock_guard<std::mutex> l(g_mu);
-    if (!g_page && !g_failed) {
+    if (!g_page) {
         void* p = nullptr;
         if (hipHostMalloc(&p, kSlots * sizeof(Slot),
                           hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
             g_page = static_cast<Slot*>(p);
             for (int k = 0; k < kSlots; ++k) g_page[k].flag = 0;
         } else {
-            (void)hipGetLastError();   // the copying way works without it
-            g_failed = true;
+            // the copying way works without it; the next call asks again (another
+            // thread's graph capture refuses allocations while it lasts)
+            (void)hipGetLastError();
         }
     }
     if (!g_page || g_used == ~0ull) return;
