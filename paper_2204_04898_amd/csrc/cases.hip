@@ -61,7 +61,7 @@ __device__ __forceinline__ uint32_t tile_count(const uint32_t* cnt, int64_t nc, 
 
 // The formatting step's header to the host (one thread), where the call waits for it.
 __device__ __forceinline__ void publish_info(const BackDst& back, const RangeInfo* info) {
-    if (info) publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
+    if (info) publish(back, info, kInfoWords);
 }
 
 __global__ __launch_bounds__(1024) void k_case_scan(const uint32_t* cnt, int64_t nc, int per_tile, uint32_t* blockoff,

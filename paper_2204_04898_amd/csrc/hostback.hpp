@@ -19,11 +19,15 @@ struct BackDst {
     uint64_t seq;
 };
 
-// One thread writes the words, then the sequence number.
-__device__ __forceinline__ void publish(const BackDst& d, const int64_t* src, int n) {
+// One thread writes the words, then the sequence number.  The words are read as
+// bytes: `src` may be a struct of narrower fields that the thread has just stored.
+__device__ __forceinline__ void publish(const BackDst& d, const void* src, int n) {
     if (!d.words) return;
-    for (int k = 0; k < n; ++k)
-        __hip_atomic_store(&d.words[k], src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int k = 0; k < n; ++k) {
+        int64_t w;
+        __builtin_memcpy(&w, static_cast<const char*>(src) + k * sizeof(w), sizeof(w));
+        __hip_atomic_store(&d.words[k], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     __hip_atomic_store(d.flag, d.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

@@ -86,7 +86,7 @@ __device__ __forceinline__ void store_range(RangePart r, RangePart* red, RangeIn
         info->status = r.bad ? PM4G_E_RANGE : (r.unsorted ? PM4G_E_NOT_SORTED : 0);
         info->long_case = 0;
         *status = info->status;
-        publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
+        publish(back, info, kInfoWords);
     }
 }
 
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void k_ts_range(const int64_t* __restrict__ ts
 
 __global__ void k_publish(const RangeInfo* info, BackDst back, int64_t* skip) {
     *skip = info->long_case;
-    publish(back, reinterpret_cast<const int64_t*>(info), kInfoWords);
+    publish(back, info, kInfoWords);
 }
 
 hipError_t launch_publish(const RangeInfo* info, BackDst back, int64_t* skip, hipStream_t s) {
