@@ -29,6 +29,28 @@ __device__ __forceinline__ XcdSplit xcd_split(int64_t n) {
     return XcdSplit{begin + j, begin + q + (x < r ? 1 : 0), blocks};
 }
 
+// Order of the batched views' walks over tiles (or parts of tiles): the i-th of
+// n items for block b of G, or -1 past the end (increasing in i).  With no more
+// items than blocks, one each.  Otherwise chunks of kXcdChunk consecutive items
+// are dealt round-robin to the 8 XCDs (block b runs on XCD b % 8) and an XCD's
+// blocks stride over its chunks, so neighbouring tiles, whose runs of records
+// sit side by side in the record segments, are written through the same L2,
+// while the chunks keep the XCDs' loads even along the log.  (Few items dealt in
+// chunks leave XCDs without any: 48 views of a 65,536-event log, 48 items, took
+// 388 us, 142 one per block; a contiguous range of few items per XCD was no
+// faster than the round-robin and up to 20 % slower.)
+constexpr int64_t kXcdChunk = 64;
+__host__ __device__ __forceinline__ int64_t walk_item(int64_t b, int64_t G, int64_t i, int64_t n) {
+    int64_t t;
+    if (G % 8 != 0 || n <= G) {
+        t = b + i * G;
+    } else {
+        const int64_t x = b % 8, s = b / 8 + i * (G / 8);
+        t = ((s / kXcdChunk) * 8 + x) * kXcdChunk + s % kXcdChunk;
+    }
+    return t < n ? t : -1;
+}
+
 // Mask of the lanes below this one.
 __device__ __forceinline__ uint64_t lanes_below() {
     return (uint64_t(1) << lane()) - uint64_t(1);

@@ -73,10 +73,11 @@ int64_t view_buckets(int32_t A) {
 }
 
 // Blocks that may share a tile's views in the walks: a log of few tiles would
-// otherwise leave most of the chip idle (512 blocks fill it; 4096 views of 50k
-// events, 13 tiles: a call of 797 us whole, 430 shared; 300 views of 200k
-// events, 49 tiles: 248 and 175).  Above 256 tiles, or with few views, it would
-// only add empty blocks (200 views of 2M events, 489 tiles: 195 and 215 us).
+// otherwise leave most of the chip idle (512 blocks fill it).  Calls in us, a
+// block per tile and shared: 4096 views of 50k events (13 tiles) 2320, 451; 300
+// of 200k (49 tiles) 373, 192; 100 of 1.05M (256 tiles) 457, 427.  Above 256
+// tiles, or with few views, it would only stage tiles again: 16 views of 1.05M
+// events 229, 243; 48 of 2M (489 tiles) 247, 281.
 static int32_t walk_parts(int64_t n_tiles, int32_t V) {
     if (n_tiles < 1 || n_tiles > 256 || V < 32) return 1;
     const int64_t fill = (511 + n_tiles) / n_tiles, most = V / 16 < 16 ? V / 16 : 16;
@@ -601,23 +602,9 @@ __device__ __forceinline__ void walk_slots(uint32_t A, const ViewWs& w, int pair
     }
 }
 
-// Tile order of the walks: chunks of kXcdChunk consecutive tiles are dealt
-// round-robin to the 8 XCDs (block b runs on XCD b % 8) and an XCD's blocks
-// stride over its chunks' tiles, so neighbouring tiles, whose runs of records
-// sit side by side in the record segments, are written through the same L2,
-// while the chunks keep the XCDs' loads even along the log.  The block's i-th
-// tile, or -1 past the end (the order is increasing in i).
-constexpr int64_t kXcdChunk = 64;
-__device__ __forceinline__ int64_t walk_tile(Grid gd, int64_t i, int64_t n_tiles) {
-    const int64_t G = gd.nblk, b = gd.bid;
-    int64_t t;
-    if (G % 8 != 0) {
-        t = b + i * G;
-    } else {
-        const int64_t x = b % 8, s = b / 8 + i * (G / 8);
-        t = ((s / kXcdChunk) * 8 + x) * kXcdChunk + s % kXcdChunk;
-    }
-    return t < n_tiles ? t : -1;
+// The block's i-th piece of work in the walks (walk_item), or -1 past the end.
+__device__ __forceinline__ int64_t walk_tile(Grid gd, int64_t i, int64_t n_items) {
+    return walk_item(gd.bid, gd.nblk, i, n_items);
 }
 
 // The tile's views beyond the first NW, taken in turn by the block's waves.
