@@ -648,6 +648,18 @@ int64_t pm4g_debug_efg_pass_pairs(int64_t pairs);
 int pm4g_debug_csv_hash_bits(int bits);
 
 /*
+ * Test hooks for sampling: the calling thread's later pm4g_sample calls narrow
+ * the candidates down by `passes` digits of 8 bits before they list them (0:
+ * three), and list at most `entries` of them (negative: 4096); more are selected
+ * among by further digits.  Three digits leave one candidate in about 2^24 units
+ * beside the one sought; with fewer, long lists and what lies beyond them can be
+ * exercised on small logs.  Results do not depend on them.  Each returns the
+ * previous setting.
+ */
+int pm4g_debug_sample_passes(int passes);
+int pm4g_debug_sample_list(int entries);
+
+/*
  * Stage timing for measurement: while enabled (process-wide), every stage of
  * the library records a pair of HIP events on the stream it launches on.
  * pm4g_profile_read() waits for the recorded events, writes per-stage total

@@ -19,6 +19,8 @@ thread_local char g_err[512] = "";
 thread_local int g_variant_hash_bits = 0;   // test hook, 0 = full 64-bit hash
 thread_local int64_t g_efg_pass_pairs = 0;  // test hook, 0 = the EFG's full LDS pass length
 thread_local int g_csv_hash_bits = 0;       // test hook, 0 = full 64-bit value hashes
+thread_local int g_sample_passes = 0;       // test hook, 0 = all digit passes before the candidates are listed
+thread_local int g_sample_list = -1;        // test hook, -1 = the whole candidate list
 
 void set_err(const char* fmt, ...) {
     va_list ap;
@@ -399,6 +401,18 @@ int pm4g_debug_csv_hash_bits(int bits) {
     return old;
 }
 
+int pm4g_debug_sample_passes(int passes) {
+    const int old = g_sample_passes;
+    g_sample_passes = passes > 0 ? passes : 0;
+    return old;
+}
+
+int pm4g_debug_sample_list(int entries) {
+    const int old = g_sample_list;
+    g_sample_list = entries >= 0 ? entries : -1;
+    return old;
+}
+
 int64_t pm4g_debug_efg_pass_pairs(int64_t pairs) {
     const int64_t old = g_efg_pass_pairs;
     g_efg_pass_pairs = pairs > 0 ? pairs : 0;
@@ -544,7 +558,7 @@ int pm4g_sample(const pm4g_prepared* log, int64_t k, uint64_t seed, int32_t by_e
     ProfScope ps(P_SAMPLE, s);
     Bump bp(ws);
     SelState* sel = bp.take<SelState>(1);
-    PM4G_HIP(launch_sample_select(log, k, seed, by_events != 0, sel, s));
+    PM4G_HIP(launch_sample_select(log, k, seed, by_events != 0, sel, g_sample_passes, g_sample_list, s));
     if (by_events) {
         FilterWs w = filter_ws_layout(bp, log->n_events);
         PM4G_HIP(launch_sample_events(log, seed, sel, out, w, s));

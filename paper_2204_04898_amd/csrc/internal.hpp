@@ -403,8 +403,9 @@ struct SelState {
     uint32_t hist[kSelPasses][256];
     uint64_t list[kSelList];
 };
+// passes, list: kSelPasses (0) and kSelList (negative), or fewer (test hooks).
 hipError_t launch_sample_select(const pm4g_prepared* p, int64_t k, uint64_t seed, bool by_events, SelState* sel,
-                                hipStream_t s);
+                                int passes, int list, hipStream_t s);
 hipError_t launch_sample_events(const pm4g_prepared* p, uint64_t seed, const SelState* sel,
                                 const pm4g_prepared* out, FilterWs w, hipStream_t s);
 hipError_t launch_sample_cases(const pm4g_prepared* p, uint64_t seed, const SelState* sel,

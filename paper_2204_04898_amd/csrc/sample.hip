@@ -65,8 +65,9 @@ __device__ __forceinline__ uint32_t pick(const uint32_t* hist, int64_t* krem, ui
 }
 
 // Histogram of digit `pass` (most significant first) of the keys whose higher
-// digits equal the prefix; pass kSelPasses lists those keys instead.
-__global__ __launch_bounds__(kSB) void k_sel_pass(Units units, int64_t k, int pass, SelState* sel) {
+// digits equal the prefix; pass `last` lists those keys instead, `cap` at most.
+__global__ __launch_bounds__(kSB) void k_sel_pass(Units units, int64_t k, int pass, int last, uint32_t cap,
+                                                  SelState* sel) {
     __shared__ uint32_t h[256];
     __shared__ uint32_t tmp[kSB / kWave + 1];
     __shared__ int64_t found[2];
@@ -81,29 +82,29 @@ __global__ __launch_bounds__(kSB) void k_sel_pass(Units units, int64_t k, int pa
     for (int64_t u = (int64_t)blockIdx.x * kSB + threadIdx.x; u < count; u += (int64_t)gridDim.x * kSB) {
         const uint64_t key = units.key(u);
         if (pass > 0 && (key >> shift) != prefix) continue;
-        if (pass < kSelPasses) {
+        if (pass < last) {
             atomicAdd(&h[(key >> (shift - 8)) & 255u], 1u);
         } else {
             const uint32_t at = atomicAdd(&sel->n_list, 1u);
-            if (at < kSelList) sel->list[at] = key;
+            if (at < cap) sel->list[at] = key;
         }
     }
-    if (pass == kSelPasses) return;
+    if (pass == last) return;
     __syncthreads();
     if (threadIdx.x < 256 && h[threadIdx.x]) atomicAdd(&sel->hist[pass][threadIdx.x], h[threadIdx.x]);
 }
 
-// One block: the krem-th smallest of the listed keys.
-__global__ __launch_bounds__(kSB) void k_sel_final(Units units, int64_t k, SelState* sel) {
+// One block: the krem-th smallest of the keys listed after `last` passes.
+__global__ __launch_bounds__(kSB) void k_sel_final(Units units, int64_t k, int last, uint32_t cap, SelState* sel) {
     __shared__ uint32_t tmp[kSB / kWave + 1];
     __shared__ int64_t found[2];
     __shared__ uint32_t h[256];
     if (sel->none || sel->all) return;
     uint64_t prefix = 0;
     int64_t krem = k;
-    for (int p = 0; p < kSelPasses; ++p) prefix = prefix << 8 | pick<kSB>(sel->hist[p], &krem, tmp, found);
+    for (int p = 0; p < last; ++p) prefix = prefix << 8 | pick<kSB>(sel->hist[p], &krem, tmp, found);
     const uint32_t m = sel->n_list;
-    if (m <= kSelList) {
+    if (m <= cap) {
         for (uint32_t i = threadIdx.x; i < m; i += kSB) {
             const uint64_t key = sel->list[i];
             int64_t rank = 1;
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kSB) void k_sel_final(Units units, int64_t k, SelSt
         return;
     }
     const int64_t count = units.count();
-    for (int pass = kSelPasses; pass < 8; ++pass) {
+    for (int pass = last; pass < 8; ++pass) {
         if (threadIdx.x < 256) h[threadIdx.x] = 0;
         __syncthreads();
         const int shift = 64 - 8 * pass;
@@ -130,15 +131,17 @@ __global__ __launch_bounds__(kSB) void k_sel_final(Units units, int64_t k, SelSt
 }  // namespace
 
 hipError_t launch_sample_select(const pm4g_prepared* p, int64_t k, uint64_t seed, bool by_events, SelState* sel,
-                                hipStream_t s) {
+                                int passes, int list, hipStream_t s) {
+    const int last = passes > 0 && passes < kSelPasses ? passes : kSelPasses;
+    const uint32_t cap = list >= 0 && list < kSelList ? (uint32_t)list : (uint32_t)kSelList;
     // events, or an upper bound of the cases
     const Units units{by_events ? nullptr : p->case_code, by_events ? nullptr : p->n_cases, p->n_events, seed};
     const int64_t g = (p->n_events + kSB - 1) / kSB;
     // 512 blocks: each adds its 256 counts to the same words
     const unsigned grid = (unsigned)(g < 512 ? (g < 1 ? 1 : g) : 512);
     k_sel_init<<<1, 256, 0, s>>>(sel, k, units.count_dev, units.count_host);
-    for (int pass = 0; pass <= kSelPasses; ++pass) k_sel_pass<<<grid, kSB, 0, s>>>(units, k, pass, sel);
-    k_sel_final<<<1, kSB, 0, s>>>(units, k, sel);
+    for (int pass = 0; pass <= last; ++pass) k_sel_pass<<<grid, kSB, 0, s>>>(units, k, pass, last, cap, sel);
+    k_sel_final<<<1, kSB, 0, s>>>(units, k, last, cap, sel);
     return hipGetLastError();
 }
 

@@ -210,6 +210,9 @@ def load():
             L.pm4g_profile_stage_count.restype = ctypes.c_int
             L.pm4g_debug_csv_hash_bits.argtypes = [ctypes.c_int]
             L.pm4g_debug_csv_hash_bits.restype = ctypes.c_int
+            for hook in (L.pm4g_debug_sample_passes, L.pm4g_debug_sample_list):
+                hook.argtypes = [ctypes.c_int]
+                hook.restype = ctypes.c_int
             L.pm4g_debug_efg_pass_pairs.argtypes = [ctypes.c_int64]
             L.pm4g_debug_efg_pass_pairs.restype = ctypes.c_int64
             if hasattr(L, "pm4g_debug_variant_hash_bits"):
