@@ -598,7 +598,7 @@ struct ValueHash {
 };
 
 // Eight staged bytes from stage offset o: the two aligned words around them,
-// funnel-shifted (the stage keeps 16 bytes of room past its capacity).
+// funnel-shifted (the stage keeps 32 bytes of room past its capacity).
 __device__ __forceinline__ uint64_t stage_word(const uint8_t* stage, int64_t o) {
     const int64_t a = o & ~(int64_t)7;
     const uint64_t* s64 = reinterpret_cast<const uint64_t*>(stage + a);
@@ -798,7 +798,9 @@ __device__ __forceinline__ bool parse_row(Src B, int64_t r, int64_t a, int64_t e
     return true;
 }
 
-constexpr int kStage = 20448;   // bytes of text staged per block of rows: 8 blocks of 20 KB per CU
+// Bytes of text staged per block of rows.  With the table of met values a block
+// holds 24 KB of LDS, six to a CU; its 114 registers leave room for four.
+constexpr int kStage = 20448;
 
 // A block takes 256 consecutive rows; their bytes (one contiguous range) are
 // copied to LDS with coalesced 16-byte loads and walked there.  Rows of more

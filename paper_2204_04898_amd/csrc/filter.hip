@@ -81,8 +81,8 @@ __device__ __forceinline__ Range block_range(int64_t n) {
     return Range{a < n ? a : n, a + per < n ? a + per : n};
 }
 
-// Sum of the counts of the blocks before this one, and of all blocks.  `tmp`
-// holds two more entries than block_excl_sum's.
+// Sum of the counts of the blocks before this one, and of all blocks (`tmp` as
+// block_excl_sum's).
 template <int BLOCK>
 __device__ __forceinline__ int64_t counts_before(const uint32_t* cnt, int64_t* tmp, int64_t* all) {
     int64_t b = 0, t = 0;

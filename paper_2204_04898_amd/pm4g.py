@@ -328,7 +328,8 @@ class Prepared:
 def pm4g_prepare(case, act, ts, A: int, presorted: bool = False, out: Prepared | None = None,
                  rows: bool = False, stream=None) -> Prepared:
     """Formats a raw log on the GPU (order, per-case table; with `rows`, also
-    the raw row of each position).  Synchronises the stream."""
+    the raw row of each position).  Waits for words of the device once or twice;
+    its last kernels may still run on the stream when it returns."""
     log = _log(case, act, ts, A, presorted, stream)
     if out is None:
         out = Prepared.empty(case.numel(), A, case.device, rows=rows)
@@ -363,7 +364,8 @@ def _dfg_struct(o: dict) -> _DfgOut:
 @_on_stream
 def pm4g_dfg(case, act, ts, A: int, presorted: bool = False, out: dict | None = None,
              stream=None) -> dict:
-    """DFG of a raw log (formats it in the workspace first).  Synchronises once or twice."""
+    """DFG of a raw log (formats it in the workspace first).  Waits for words of the
+    device once or twice; its last kernels may still run on the stream when it returns."""
     log = _log(case, act, ts, A, presorted, stream)
     o = out if out is not None else _dfg_out(A, case.device)
     ws, need = workspace(OP_DFG, case.numel(), A, case.device, stream)
@@ -417,7 +419,8 @@ def _var_struct(o: dict) -> _VarOut:
 @_on_stream
 def pm4g_variants(case, act, ts, A: int, presorted: bool = False, out: dict | None = None,
                   stream=None) -> dict:
-    """Trace variants of a raw log.  Synchronises once or twice."""
+    """Trace variants of a raw log.  Waits for words of the device once or twice;
+    its last kernels may still run on the stream when it returns."""
     log = _log(case, act, ts, A, presorted, stream)
     o = out if out is not None else _var_out(case.numel(), case.device)
     ws, need = workspace(OP_VARIANTS, case.numel(), A, case.device, stream)
