@@ -25,8 +25,8 @@
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL is the
  *     default stream).  Functions taking a raw (unsorted) log wait once or
  *     twice for a few bytes (key ranges, a long-case flag; their later work
- *     may still be running when they return, in stream order); functions
- *     taking a prepared log do not wait.
+ *     may still be running when they return, in stream order, and may still
+ *     read the log's columns); functions taking a prepared log do not wait.
  *   - Host-detectable errors (NULL pointer, negative size, A outside
  *     [1, PM4G_MAX_ACTIVITIES], n_events >= 2^31, unknown flags, workspace too
  *     small) are returned before anything is enqueued.
@@ -329,7 +329,9 @@ int pm4g_dfg_prepared_noalloc(const pm4g_prepared *log, const pm4g_dfg_out *out,
  * are bounded, and a barrier that does not complete within seconds sets
  * out->status to PM4G_E_DEVICE (the outputs are then not valid) instead of
  * hanging; a failed cooperative launch returns PM4G_E_DEVICE.  With launch 1
- * each phase is a launch of its own.  Both give the same bytes.
+ * each phase is a launch of its own.  Both give the same bytes.  (The Python
+ * binding takes launch 1 where its caller names no mode: with one or a few
+ * hundred views a launch is cheaper than a grid barrier.)
  */
 size_t pm4g_batched_workspace_bytes(int64_t n_events, int32_t n_activities, int32_t n_views,
                                     const pm4g_batched_tuning *tuning);
